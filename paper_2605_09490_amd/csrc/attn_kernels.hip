@@ -224,6 +224,11 @@ __device__ __forceinline__ float half_of(uint32_t w, int hi) {
   return (float)__builtin_bit_cast(_Float16, (uint16_t)(hi ? (w >> 16) : (w & 0xffffu)));
 }
 
+// Scaled logits of one call: [sequence entry][query head][xs_stride], by list index
+__device__ __forceinline__ size_t xs_at(const AttnArgs& a, int seq, int hq, int col) {
+  return ((size_t)seq * a.Hq + hq) * a.xs_stride + col;
+}
+
 template <int G>
 struct GPad { static constexpr int v = (G <= 4) ? 4 : 8; };
 
@@ -696,7 +701,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
     // -- online softmax, one entry per lane; the denominator is summed per lane and reduced once at the end
     float corr[G];
     {
-      const size_t xbase = ((size_t)((b * a.n_q + jq) * a.Hq + kvh * G)) * a.xs_stride + (size_t)(xs_tile0 + tile) * 64 + lane;
+      const size_t xbase = xs_at(a, b * a.n_q + jq, kvh * G, (xs_tile0 + tile) * 64 + lane);
       float pv[GP];
 #pragma unroll
       for (int h = 0; h < GP; ++h) pv[h] = 0.f;
@@ -944,7 +949,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     live[cb] = col < ncol;
     n_seen[cb] = IS_Q ? n_list : n_list - (live[cb] ? a.cq - 1 - jq : 0);
     const int qi = live[cb] ? jq * a.Hq + kvh * G + h : kvh * G;
-    xrow[cb] = ((size_t)((b * a.n_q + jz) * a.cq * a.Hq + qi)) * a.xs_stride + (size_t)(4 * kb);
+    xrow[cb] = xs_at(a, (b * a.n_q + jz) * a.cq + (live[cb] ? jq : 0), kvh * G + (live[cb] ? h : 0), 4 * kb);
     const u32x4* qp = (const u32x4*)((const char*)a.q + (((size_t)b * a.q_bs + (size_t)jz * a.cq * a.Hq + qi) * D + 8 * kb) * 2);
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) qreg[cb][ks] = live[cb] ? qp[ks * 4] : u32x4{0u, 0u, 0u, 0u};
@@ -1396,7 +1401,10 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
   const int s = blockIdx.x, kvh = blockIdx.y;
   // several query tokens per sequence: query jq of sequence b; it is n_q - 1 - jq positions older than the last one,
   // and those positions (the tail of list F) are not its to see
-  const int b = a.n_q > 1 ? (int)blockIdx.z / a.n_q : (int)blockIdx.z, jq = a.n_q > 1 ? (int)blockIdx.z % a.n_q : 0;
+  // a whole decode step: layer li of the launch's a.nl; bl is the (layer, sequence) entry of rows, q, logits and partials
+  const int jq = a.n_q > 1 ? (int)blockIdx.z % a.n_q : 0, bl = a.n_q > 1 ? (int)blockIdx.z / a.n_q : (int)blockIdx.z;
+  const int li = a.nl > 1 ? bl / a.B : 0, b = bl - li * a.B;
+  const int* f_loc = ((a.old_mask >> li) & 1) ? a.f_loc_old : a.f_loc;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   int nF, nQ, xsb = 0;
   if (!a.second) {
@@ -1429,11 +1437,11 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
   }
   bool o_written = false;
   if (u < nwf) {
-    attn_wave<D, G, KG::MF, KT>(a, w, b, jq, kvh, lane, u, nwf, nF, a.f_loc + (size_t)b * a.Nmax, xsb, o, m_run, l_lane);
+    attn_wave<D, G, KG::MF, KT>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb, o, m_run, l_lane);
   } else {
     if constexpr (EV == 8) {
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, b, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT>(a, w, b, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o, m_run, l_lane);
     } else {
       // binary32 rows use 4 elements per lane, code rows 8: separate accumulators, parked directly
       float o8[G][8];
@@ -1441,8 +1449,8 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
       for (int h = 0; h < G; ++h)
 #pragma unroll
         for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, b, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o8, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT>(a, w, b, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o8, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o8, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o8, m_run, l_lane);
       constexpr int L8 = D / 8;
 #pragma unroll
       for (int st = L8; st < 64; st <<= 1)
@@ -1483,7 +1491,7 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
     if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
   }
   __syncthreads();
-  const int bq = b * a.n_q + jq;
+  const int bq = bl * a.n_q + jq;
   float* po = a.part_o + ((size_t)((bq * a.Hkv + kvh) * a.S_total + a.s0 + s) * G) * D;
   for (int i = t; i < G * D; i += NW * 64) {
     const int h = i / D;
@@ -1568,7 +1576,7 @@ __global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_
 #pragma unroll
     for (int db = 0; db < D / 16; ++db) om[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (u < nwf) attn_wave_mfma<D, G, KT, MF, NCB>(a, w, b, jz, kvh, lane, u, nwf, nF, a.f_loc + (size_t)b * a.Nmax, xsb, om, mr, lr);
+  if (u < nwf) attn_wave_mfma<D, G, KT, MF, NCB>(a, w, b, jz, kvh, lane, u, nwf, nF, (a.old_mask ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax, xsb, om, mr, lr);
   else if (a.t2fmt == 0) attn_wave_mfma<D, G, KT, Q_INT8, NCB>(a, w, b, jz, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, om, mr, lr);
   else attn_wave_mfma<D, G, KT, Q_INT4, NCB>(a, w, b, jz, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, om, mr, lr);
   // ---- wave partial into LDS: lane (n, kb) has the statistics of column 16*cb + n and the outputs of columns
@@ -1621,117 +1629,181 @@ __global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_
 }
 
 // ---- finish: global softmax statistics, scores, output ------------------------------------------------------
-constexpr int FIN_LDS_FLOATS = 2048;   // room for the (m, l) of all splits of one sequence, Hkv * S * 2 * G floats, in all but the smallest batches (else they are read from memory)
+// Global (m, 1/l) of one query head out of the ns split partials at src (stride 2 * G floats).  A sequence with no live
+// position at all (every position evicted by a forced plan) has m = -inf, l = 0 in every split: its output is defined as
+// zero, not 0/0.
+template <int G>
+__device__ __forceinline__ void merge_stats(const float* __restrict__ src, int ns, float& m, float& il) {
+  float mm = -INFINITY, ll = 0.f;
+  if (ns == 1) {
+    mm = src[0]; ll = src[G];
+  } else if (ns <= 8) {               // all loads in flight together
+    float mv[8], lv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      mv[k] = k < ns ? src[k * 2 * G] : -INFINITY;
+      lv[k] = k < ns ? src[k * 2 * G + G] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) mm = fmaxf(mm, mv[k]);
+    if (mm > -INFINITY) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) ll = fmaf(lv[k], __builtin_amdgcn_exp2f((mv[k] - mm) * LOG2E), ll);
+    }
+  } else {
+#pragma unroll 8
+    for (int k = 0; k < ns; ++k) mm = fmaxf(mm, src[k * 2 * G]);
+    if (mm > -INFINITY) {
+#pragma unroll 8
+      for (int k = 0; k < ns; ++k) ll = fmaf(src[k * 2 * G + G], __builtin_amdgcn_exp2f((src[k * 2 * G] - mm) * LOG2E), ll);
+    }
+  }
+  m = mm > -INFINITY ? mm : 0.f;
+  il = ll > 0.f ? 1.0f / ll : 0.f;
+}
 
-template <int D, int G>
-__global__ __launch_bounds__(256) void k_attn_finish(const AttnArgs a, int n_tiles) {
-  __shared__ float sm_pm[FIN_LDS_FLOATS];
-  __shared__ float M[128], IL[128];
-  const int t = threadIdx.x, b = blockIdx.y;
-  int nF, nQ, nS;
-  if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
-  else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
-  nS = a.s_pos ? a.cnt[b * CNT_N + C_NS] : 0;
-  // logits columns: F tiles, Q tiles, then (streamed T1) the T1 list's tiles
-  const int cf = (nF + TB - 1) / TB, cq = (nQ + TB - 1) / TB, ns = a.S_total;
-  const bool is_tile = (int)blockIdx.x < n_tiles;
-  if (is_tile && (int)blockIdx.x * 64 >= (nS > 0 ? (cf + cq) * TB + nS : cf * TB + nQ)) return;
-  // tile workgroups: the entry's position, its first kv head's logits and its score so far are fetched before the
-  // (m, l) merge, so their latency runs beside it
-  const int e = t & 63, hg = t >> 6;
-  const int j = blockIdx.x * 64 + e;
-  int pos = -1;
-  float x0[G], score_old = 0.f;
-  if (is_tile) {
+// Grid (64-entry tiles + output workgroups, B); a launch finishes the a.nl layers its attention launch served.
+// Tile workgroups: 64 list entries; thread (e, hg, ls) sums the softmax weights of entry e over kv heads hg, hg+4, ...
+// (all G members of each) for layers ls, ls + LSN, ...; the four partial sums of a layer are added in the order hg = 0..3
+// and the layers into the score in layer order, so a whole step and per-layer calls give the same bits.  Latency-bound:
+// the logits of a thread's first XP layers are requested before anything they do not depend on, and a step's launch has
+// four times the threads, so that the (m, l) merges of all its layers are one round trip.
+// Output workgroups: 256 threads per (layer, query head).
+template <bool STEP>
+struct FinGeo {
+  static constexpr int LSN = STEP ? 4 : 1;          // layers in parallel
+  static constexpr int NT = 256 * LSN;
+  static constexpr int XP = STEP ? 3 : 1;
+  static constexpr int LB = STEP ? 32 : 1;          // layers per pass, at most
+  static constexpr int NST = STEP ? 2048 : 128;     // (layer, head) statistics per pass, at most
+  static constexpr int HPG = STEP ? 4 : 1;          // (layer, head) outputs per 256-thread group
+};
+template <int D, int G, bool STEP>
+__global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs a, int n_tiles) {
+  using FG = FinGeo<STEP>;
+  constexpr int LSN = FG::LSN, NT = FG::NT, XP = FG::XP;
+  __shared__ float2 sm_st[FG::NST];                         // (m, 1/l) of every (layer, head) of the pass
+  __shared__ float sm_part[(FG::LB > LSN * FG::HPG ? FG::LB : LSN * FG::HPG) * 256];
+  const int t = threadIdx.x, b = blockIdx.y, ns = a.S_total;
+  const size_t kv_ml = (size_t)ns * 2 * G;                  // statistics of one (layer, sequence, kv head)
+  if ((int)blockIdx.x < n_tiles) {
+    int nF, nQ, nS;
+    if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
+    else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
+    nS = a.s_pos ? a.cnt[b * CNT_N + C_NS] : 0;
+    // logits columns: F tiles, Q tiles, then (streamed T1) the T1 list's tiles
+    const int cf = (nF + TB - 1) / TB, cq = (nQ + TB - 1) / TB;
+    if ((int)blockIdx.x * 64 >= (nS > 0 ? (cf + cq) * TB + nS : cf * TB + nQ)) return;
+    const int e = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), hg = wv & 3, ls = wv >> 2;
+    const int j = blockIdx.x * 64 + e;
     const bool in_f = j < nF, in_q = j >= cf * TB && j - cf * TB < nQ, in_s = j >= (cf + cq) * TB && j - (cf + cq) * TB < nS;
-    const bool live = in_f || in_q || in_s;      // from the list lengths alone: the logits are fetched beside the position
+    const bool live = in_f || in_q || in_s;
+    int pos = -1;
     if (in_f) pos = a.f_pos[(size_t)b * a.Nmax + j];
     else if (in_q) pos = a.q_pos[(size_t)b * a.Nmax + (j - cf * TB)];
     else if (in_s) pos = a.s_pos[(size_t)b * a.Nmax + (j - (cf + cq) * TB)];
-#pragma unroll
-    for (int g = 0; g < G; ++g) x0[g] = (live && hg < a.Hkv) ? a.xs[((size_t)b * a.Hq + hg * G + g) * a.xs_stride + j] : 0.f;
-    if (hg == 0 && pos >= 0) score_old = a.score[(size_t)b * a.Nmax + pos];
-  }
-  // (m, l) of every split of this sequence: part_ml[b][kvh][s][2][G], s < ns
-  const float* pmb = a.part_ml + (size_t)b * a.Hkv * a.S_total * 2 * G;
-  const int per_kvh = ns * 2 * G;
-  const bool in_lds = a.Hkv * per_kvh <= FIN_LDS_FLOATS;
-  if (in_lds) {
-    for (int i = t; i < a.Hkv * per_kvh; i += 256) {
-      const int kvh = i / per_kvh, rem = i % per_kvh;
-      sm_pm[i] = pmb[(size_t)kvh * a.S_total * 2 * G + rem];
-    }
-    __syncthreads();
-  }
-  if (t < a.Hq) {
-    const int kvh = t / G, g = t % G;
-    const float* src = in_lds ? (sm_pm + kvh * per_kvh) : (pmb + (size_t)kvh * a.S_total * 2 * G);
-    float mm = -INFINITY;
-    for (int k = 0; k < ns; ++k) mm = fmaxf(mm, src[k * 2 * G + g]);
-    float ll = 0.f;
-    for (int k = 0; k < ns; ++k) ll = fmaf(src[k * 2 * G + G + g], __builtin_amdgcn_exp2f((src[k * 2 * G + g] - mm) * LOG2E), ll);
-    // a sequence with no live position at all (every position evicted by a forced plan) has m = -inf, l = 0 in every
-    // split: its output is defined as zero, not 0/0
-    M[t] = mm > -INFINITY ? mm : 0.f;
-    IL[t] = ll > 0.f ? 1.0f / ll : 0.f;
-  }
-  __syncthreads();
-  if (is_tile) {
-    // 64 list entries per workgroup; thread (e, hg) sums the softmax weights of kv heads hg, hg+4, ... (all G members
-    // of each), then the four partial sums of an entry are added in the fixed order hg = 0, 1, 2, 3
+    float score = 0.f;
     const float pen = a.red ? a.red_w * (float)G / (float)(nF + nQ + nS) : 0.f;
-    float acc = 0.f;
-    if (pos >= 0) {
-      for (int kvh = hg; kvh < a.Hkv; kvh += 4) {
-        float x[G];
+    const int per_pass = STEP ? (FG::NST / a.Hq < FG::LB ? FG::NST / a.Hq : FG::LB) : 1;
+    for (int l0 = 0; l0 < a.nl; l0 += per_pass) {
+      const int nb = a.nl - l0 < per_pass ? a.nl - l0 : per_pass;
+      float x0[XP][G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) x[g] = (kvh == hg) ? x0[g] : a.xs[((size_t)b * a.Hq + kvh * G + g) * a.xs_stride + j];
-        if (a.vnorm) {
-          // value-aware scorer: the group's weights times the norm of the value row its heads read
-          float w = 0.f;
+      for (int q = 0; q < XP; ++q)
+        if (ls + q * LSN < nb) {
+          const float* xr = a.xs + xs_at(a, (l0 + ls + q * LSN) * a.B + b, hg * G, j);
 #pragma unroll
-          for (int g = 0; g < G; ++g) w += __builtin_amdgcn_exp2f((x[g] - M[kvh * G + g]) * LOG2E) * IL[kvh * G + g];
-          acc = fmaf(w, a.vnorm[((size_t)b * a.Hkv + kvh) * a.Nmax + pos], acc);
-        } else {
-#pragma unroll
-          for (int g = 0; g < G; ++g) acc += __builtin_amdgcn_exp2f((x[g] - M[kvh * G + g]) * LOG2E) * IL[kvh * G + g];
+          for (int g = 0; g < G; ++g) x0[q][g] = (live && hg < a.Hkv) ? xr[(size_t)g * a.xs_stride] : 0.f;
         }
-        // redundancy-penalised scorers: the G heads of the group each take red_w * rho / (positions attended) off
-        if (a.red) acc = fmaf(-pen, a.red[((size_t)b * a.Hkv + kvh) * a.Nmax + pos], acc);
+      if (l0 == 0 && wv == 0 && live) score = a.score[(size_t)b * a.Nmax + pos];
+      for (int i = t; i < nb * a.Hq; i += NT) {
+        const int u = STEP ? i / a.Hq : 0, hq = i - u * a.Hq, kvh = hq / G, g = hq % G;
+        float m, il;
+        merge_stats<G>(a.part_ml + ((size_t)((l0 + u) * a.B + b) * a.Hkv + kvh) * kv_ml + g, ns, m, il);
+        sm_st[i] = make_float2(m, il);
+      }
+      __syncthreads();
+      auto layer_sum = [&](int u, const float (&xf)[G], bool have) {
+        const int bl = (l0 + u) * a.B + b;
+        float acc = 0.f;
+        if (live) {
+          for (int kvh = hg; kvh < a.Hkv; kvh += 4) {
+            float x[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) x[g] = (have && kvh == hg) ? xf[g] : a.xs[xs_at(a, bl, kvh * G + g, j)];
+            const float2* stt = sm_st + u * a.Hq + kvh * G;
+            if (a.vnorm) {
+              // value-aware scorer: the group's weights times the norm of the value row its heads read
+              float w = 0.f;
+#pragma unroll
+              for (int g = 0; g < G; ++g) w += __builtin_amdgcn_exp2f((x[g] - stt[g].x) * LOG2E) * stt[g].y;
+              acc = fmaf(w, a.vnorm[((size_t)bl * a.Hkv + kvh) * a.Nmax + pos], acc);
+            } else {
+#pragma unroll
+              for (int g = 0; g < G; ++g) acc += __builtin_amdgcn_exp2f((x[g] - stt[g].x) * LOG2E) * stt[g].y;
+            }
+            // redundancy-penalised scorers: the G heads of the group each take red_w * rho / (positions attended) off
+            if (a.red) acc = fmaf(-pen, a.red[((size_t)bl * a.Hkv + kvh) * a.Nmax + pos], acc);
+          }
+        }
+        sm_part[(u * 4 + hg) * 64 + e] = acc;
+      };
+#pragma unroll
+      for (int q = 0; q < XP; ++q)
+        if (ls + q * LSN < nb) layer_sum(ls + q * LSN, x0[q], true);
+      if constexpr (STEP)
+        for (int u = ls + XP * LSN; u < nb; u += LSN) layer_sum(u, x0[0], false);
+      __syncthreads();
+      if (wv == 0)
+        for (int u = 0; u < nb; ++u) {
+          const float* s4 = sm_part + u * 256 + e;
+          score = score + a.score_scale * (((s4[0] + s4[64]) + s4[128]) + s4[192]);
+        }
+      if (STEP && l0 + per_pass < a.nl) __syncthreads();
+    }
+    if (wv == 0 && live) a.score[(size_t)b * a.Nmax + pos] = score;
+  } else {
+    // thread (d, sg) of a (layer, head) sums the splits sg, sg+NSG, ... of output element d, then the NSG partial sums
+    // are added in the fixed order sg = 0, 1, ...
+    constexpr int NSG = 256 / D;
+    constexpr int HPG = FG::HPG;                            // (layer, head)s per 256-thread group, their loads in flight together
+    const int r0 = ((blockIdx.x - n_tiles) * LSN + (t >> 8)) * HPG, tl = t & 255;
+    const int d = tl % D, sg = tl / D;
+    float il[HPG], acc[HPG];
+#pragma unroll
+    for (int q = 0; q < HPG; ++q) {
+      const int r = r0 + q;
+      il[q] = 0.f; acc[q] = 0.f;
+      if (r < a.nl * a.Hq) {
+        const int li = STEP ? r / a.Hq : 0, hq = r - li * a.Hq, kvh = hq / G, h = hq % G, bl = li * a.B + b;
+        const float* pm = a.part_ml + ((size_t)bl * a.Hkv + kvh) * kv_ml + h;
+        const float* pob = a.part_o + ((size_t)(bl * a.Hkv + kvh) * ns * G) * D + h * D + d;
+        float mg;
+        merge_stats<G>(pm, ns, mg, il[q]);
+#pragma unroll 8
+        for (int k = sg; k < ns; k += NSG)
+          acc[q] = fmaf(__builtin_amdgcn_exp2f((pm[k * 2 * G] - mg) * LOG2E), pob[(size_t)k * G * D], acc[q]);
       }
     }
-    __syncthreads();          // sm_pm is free now: reuse it for the partial sums
-    sm_pm[hg * 64 + e] = acc;
-    __syncthreads();
-    if (hg == 0 && pos >= 0) {
-      const float tot = ((sm_pm[e] + sm_pm[64 + e]) + sm_pm[128 + e]) + sm_pm[192 + e];
-      a.score[(size_t)b * a.Nmax + pos] = score_old + a.score_scale * tot;
-    }
-  } else {
-    // one workgroup per query head: thread (d, sg) sums the splits sg, sg+NSG, ... of output element d, then the NSG
-    // partial sums are added in the fixed order sg = 0, 1, ...
-    constexpr int NSG = 256 / D;
-    const int hq = blockIdx.x - n_tiles, kvh = hq / G, h = hq % G;
-    const int d = t % D, sg = t / D;
-    const float* pm = in_lds ? (sm_pm + kvh * per_kvh) : (pmb + (size_t)kvh * a.S_total * 2 * G);
-    const float* pob = a.part_o + ((size_t)(b * a.Hkv + kvh) * a.S_total * G) * D + h * D + d;
-    const float mg = M[hq];
-    float acc = 0.f;
-#pragma unroll 8
-    for (int k = sg; k < ns; k += NSG)
-      acc = fmaf(__builtin_amdgcn_exp2f((pm[k * 2 * G + h] - mg) * LOG2E), pob[(size_t)k * G * D], acc);
-    __syncthreads();          // every thread has read what it needs from sm_pm
-    sm_pm[sg * D + d] = acc;
+    float* sp = sm_part + (t >> 8) * (256 * HPG) + sg * D + d;
+#pragma unroll
+    for (int q = 0; q < HPG; ++q) sp[q * 256] = acc[q];
     __syncthreads();
     if (sg == 0) {
-      float tot = sm_pm[d];
 #pragma unroll
-      for (int g2 = 1; g2 < NSG; ++g2) tot += sm_pm[g2 * D + d];
-      tot *= IL[hq];
-      const size_t oi = ((size_t)b * a.o_bs + hq) * D + d;
-      if (a.out_kind == KT_BF16) ((uint16_t*)a.out)[oi] = f32_to_bf16(tot);
-      else if (a.out_kind == KT_F16) ((_Float16*)a.out)[oi] = (_Float16)tot;    // round to nearest even
-      else ((float*)a.out)[oi] = tot;
+      for (int q = 0; q < HPG; ++q) {
+        const int r = r0 + q;
+        if (r >= a.nl * a.Hq) continue;
+        float tot = acc[q];
+#pragma unroll
+        for (int g2 = 1; g2 < NSG; ++g2) tot += sp[q * 256 + g2 * D];
+        tot *= il[q];
+        const int li = STEP ? r / a.Hq : 0, hq = r - li * a.Hq;
+        const size_t oi = ((size_t)(li * a.B + b) * a.o_bs + hq) * D + d;
+        if (a.out_kind == KT_BF16) ((uint16_t*)a.out)[oi] = f32_to_bf16(tot);
+        else if (a.out_kind == KT_F16) ((_Float16*)a.out)[oi] = (_Float16)tot;    // round to nearest even
+        else ((float*)a.out)[oi] = tot;
+      }
     }
   }
 }
@@ -1794,7 +1866,7 @@ __global__ __launch_bounds__(256) void k_attn_finish_chunk(const AttnArgs a, int
           for (int kvh = hg; kvh < a.Hkv; kvh += 4) {
             float x[G];
 #pragma unroll
-            for (int g = 0; g < G; ++g) x[g] = a.xs[((size_t)(b * nq + jt) * a.Hq + kvh * G + g) * a.xs_stride + col];
+            for (int g = 0; g < G; ++g) x[g] = a.xs[xs_at(a, b * nq + jt, kvh * G + g, col)];
             if (a.vnorm) {
               float w = 0.f;
 #pragma unroll
@@ -1870,7 +1942,7 @@ __global__ __launch_bounds__(256) void k_attn_finish_chunk(const AttnArgs a, int
 // With a pair of events the launch is timed by the dispatch's own begin / end timestamps (no bracket overhead).
 template <int D, int G, int KT>
 static hipError_t run_tiered(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  dim3 grid(a.S, a.Hkv, a.B * a.n_q);
+  dim3 grid(a.S, a.Hkv, a.B * a.n_q * a.nl);
   // One query token per workgroup (a decode step; binary32 rows always): the vector kernel, G dot products per row.
   // Several query tokens as columns of one workgroup (16-bit rows): a (rows x D) by (D x G * cq) contraction, on the
   // matrix cores.
@@ -1926,12 +1998,18 @@ template <> hipError_t tiered_by_group<64, KT_BF16>(const AttnArgs&, int, hipStr
 template <> hipError_t tiered_by_group<64, KT_F32>(const AttnArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);
 template <> hipError_t tiered_by_group<64, KT_F16>(const AttnArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);
 
+template <int D, int G, bool STEP>
+static hipError_t run_finish_layers(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  using FG = FinGeo<STEP>;
+  const int opw = FG::LSN * FG::HPG;
+  const dim3 grid(a.n_tiles + (a.nl * a.Hq + opw - 1) / opw, a.B);
+  if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_finish<D, G, STEP>), grid, dim3(FG::NT), 0, st, ev0, ev1, 0, a, a.n_tiles);
+  else hipLaunchKernelGGL((k_attn_finish<D, G, STEP>), grid, dim3(FG::NT), 0, st, a, a.n_tiles);
+  return hipGetLastError();
+}
 template <int D, int G, int KT>
 static hipError_t run_finish(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  const int tiles = a.n_tiles;
-  if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_finish<D, G>), dim3(tiles + a.Hq, a.B), dim3(256), 0, st, ev0, ev1, 0, a, tiles);
-  else hipLaunchKernelGGL((k_attn_finish<D, G>), dim3(tiles + a.Hq, a.B), dim3(256), 0, st, a, tiles);
-  return hipGetLastError();
+  return a.nl > 1 ? run_finish_layers<D, G, true>(a, st, ev0, ev1) : run_finish_layers<D, G, false>(a, st, ev0, ev1);
 }
 
 hipError_t launch_attn_tiered(const AttnArgs& a, int D, int G, int kt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {

@@ -72,6 +72,8 @@ struct tkv_cache {
   // attention scratch
   float* xs = nullptr; float* part_ml = nullptr; float* part_o = nullptr;
   float* xs_chunk = nullptr; float* ml_chunk = nullptr; float* po_chunk = nullptr;   // the same for chunk launches
+  float* xs_step = nullptr; float* ml_step = nullptr; float* po_step = nullptr;      // the same for several layers at once
+  int step_layers = 0;             // layers one launch of a decode step serves (0: not decided yet)
   int S_alloc = 0, xs_stride = 0;
   char* static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (tkv_attend_and_score_noalloc)
   // T1 store and transport
@@ -631,16 +633,18 @@ static tkv_status chunk_scratch(tkv_cache* c) {
 // o_bs: query heads between consecutive sequences in q / out, the m queries of a sequence being Hq heads apart; last:
 // the layer's last call of this step (the streamed frame is released and refilled, queued transfers are pumped).
 // noalloc: the scratch of the call lives in the library's fixed device array, and nothing on the way may allocate
-// (no event pools, no queued transfers are issued).
+// (no event pools, no queued transfers are issued).  nl: consecutive layers served by the call's launches (a decode
+// step, after step_scratch; q and out then hold the layers one after the other).
 static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* out, int trim, int q_bs, int o_bs, bool last,
-                             hipStream_t st, bool noalloc = false, int m = 1) {
+                             hipStream_t st, bool noalloc = false, int m = 1, int nl = 1) {
   const DevView& v = c->dv;
+  if (nl > 1 && (c->streamed || noalloc || m > 1 || nl > c->step_layers)) return fail(c, TKV_EINVAL, "attend_one: %d layers per launch not possible here", nl);
   if (m > 1) {
     if (c->streamed || noalloc || m > chunk_tokens_per_launch(c)) return fail(c, TKV_EINVAL, "attend_one: %d queries per launch not possible here", m);
     tkv_status cs = chunk_scratch(c);
     if (cs != TKV_OK) return cs;
   }
-  bool use_old = false;
+  uint64_t old_mask = 0;
   const int fr = layer & 1;
   if (c->streamed) {
     // the layer's T1 rows must be in its frame (normally the fill was issued two layers ago)
@@ -651,22 +655,26 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
       HIPCHK(c, hipStreamWaitEvent(st, c->ev_filled[fr], 0));
       c->st.attend_waits++;
     }
-  } else if (c->layer_wait[layer]) {
-    if (c->cfg.prefetch_mode == TKV_PREFETCH_WAIT) {
-      while (!noalloc && !c->layer_enq[layer] && c->jobs_next < c->jobs.size()) {
-        tkv_status ps = pump_transfers(c, 1);
-        if (ps != TKV_OK) return ps;
+  } else {
+    for (int li = 0; li < nl; ++li) {
+      const int l = layer + li;
+      if (!c->layer_wait[l]) continue;
+      if (c->cfg.prefetch_mode == TKV_PREFETCH_WAIT) {
+        while (!noalloc && !c->layer_enq[l] && c->jobs_next < c->jobs.size()) {
+          tkv_status ps = pump_transfers(c, 1);
+          if (ps != TKV_OK) return ps;
+        }
+        if (!c->layer_enq[l]) return fail(c, TKV_ESTATE, "tkv_attend_and_score: the transfers of layer %d have not been queued", l);
+        HIPCHK(c, hipStreamWaitEvent(st, c->ev_ready[l], 0));
+        c->layer_wait[l] = 0;
+        c->st.attend_waits++;
+      } else {
+        // a layer whose pieces are still queued on the host keeps its old slots, like one whose copies are in flight
+        hipError_t e = c->layer_enq[l] ? hipEventQuery(c->ev_ready[l]) : hipErrorNotReady;
+        if (e == hipSuccess) c->layer_wait[l] = 0;
+        else if (e == hipErrorNotReady) { old_mask |= 1ull << li; c->st.lazy_old_reads++; }
+        else return fail(c, TKV_EDEVICE, "hipEventQuery failed: %s", hipGetErrorString(e));
       }
-      if (!c->layer_enq[layer]) return fail(c, TKV_ESTATE, "tkv_attend_and_score: the transfers of layer %d have not been queued", layer);
-      HIPCHK(c, hipStreamWaitEvent(st, c->ev_ready[layer], 0));
-      c->layer_wait[layer] = 0;
-      c->st.attend_waits++;
-    } else {
-      // a layer whose pieces are still queued on the host keeps its old slots, like one whose copies are in flight
-      hipError_t e = c->layer_enq[layer] ? hipEventQuery(c->ev_ready[layer]) : hipErrorNotReady;
-      if (e == hipSuccess) c->layer_wait[layer] = 0;
-      else if (e == hipErrorNotReady) { use_old = true; c->st.lazy_old_reads++; }
-      else return fail(c, TKV_EDEVICE, "hipEventQuery failed: %s", hipGetErrorString(e));
     }
   }
   auto tiles = [](int n) { return (n + TOK_PER_BLOCK - 1) / TOK_PER_BLOCK; };
@@ -686,11 +694,12 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   a.c2K = v.c2K + lrows * v.cap2 * v.cb; a.c2V = v.c2V + lrows * v.cap2 * v.cb;
   a.s2K = v.s2K + lrows * v.cap2 * v.sb; a.s2V = v.s2V + lrows * v.cap2 * v.sb;
   a.q = q; a.out = out;
-  a.f_loc = use_old ? v.f_loc_old : v.f_loc; a.f_pos = v.f_pos; a.q_loc = v.q_loc; a.q_pos = v.q_pos;
+  a.f_loc = v.f_loc; a.f_loc_old = v.f_loc_old; a.old_mask = old_mask; a.nl = nl; a.f_pos = v.f_pos; a.q_loc = v.q_loc; a.q_pos = v.q_pos;
   a.vnorm = v.vnorm ? v.vnorm + lrows * v.Nmax : nullptr;
   a.red = v.red ? v.red + lrows * v.Nmax : nullptr;
   a.red_w = c->cfg.redundancy_weight > 0.f ? c->cfg.redundancy_weight : 1.0f;
   a.cnt = v.cnt; a.score = v.score; a.xs = c->xs; a.part_ml = c->part_ml; a.part_o = c->part_o;
+  if (nl > 1) { a.xs = c->xs_step; a.part_ml = c->ml_step; a.part_o = c->po_step; }
   if (m > 1) { a.xs = c->xs_chunk; a.part_ml = c->ml_chunk; a.part_o = c->po_chunk; }
   if (noalloc) {
     // the same three arrays, carved out of the fixed scratch array (256-byte aligned each)
@@ -733,7 +742,7 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     // streamed T1: the same kernel over the T1 list, rows in the frame; its splits follow the first launch's
     AttnArgs a2 = a;
     a2.fpK = c->frameK[fr]; a2.fpV = c->frameV[fr]; a2.capF = v.cap1;
-    a2.f_loc = v.s_loc; a2.f_pos = v.s_pos;
+    a2.f_loc = v.s_loc; a2.f_pos = v.s_pos; a2.old_mask = 0;
     a2.S = S2; a2.s0 = S; a2.second = 1;
     HIPCHK(c, launch_attn_tiered(a2, v.D, c->G, c->kt, st, pe2 ? pe2->a : nullptr, pe2 ? pe2->b : nullptr));
   }
@@ -749,9 +758,9 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     if (nxt < L && nxt != layer) { tkv_status fs = issue_fill(c, nxt, fr); if (fs != TKV_OK) return fs; }
     return TKV_OK;
   }
-  // lazy mode spreads the issue of a re-tiering event's copies over the following attention calls, one layer each,
-  // so the compute stream is never left empty while the host queues them
-  if (c->jobs_next < c->jobs.size()) return pump_transfers(c, 1);
+  // lazy mode spreads the issue of a re-tiering event's copies over the following attention calls, one layer for each
+  // layer attended, so the compute stream is never left empty while the host queues them
+  if (c->jobs_next < c->jobs.size()) return pump_transfers(c, nl);
   return TKV_OK;
 }
 
@@ -794,6 +803,32 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
   return TKV_OK;
 }
 
+// Scratch for the launches of a decode step that serve several layers at once: logits and split partials per (layer,
+// sequence).  As many layers as fit STEP_SCRATCH_BYTES: by then the launch's fixed cost (a few us of fill and drain, the
+// finishing kernel, two dispatches) is small beside its work, and the logits are still in the last-level cache when the
+// finishing kernel reads them.  Allocated on the first decode step and kept; without the memory for it (or where one
+// layer fills it) the step goes layer by layer as before.
+constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20;
+// A step that is being captured into a graph may not allocate: it goes layer by layer if it is the first one.
+static void step_scratch(tkv_cache* c, hipStream_t st) {
+  if (c->step_layers) return;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+  const DevView& v = c->dv;
+  const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = (size_t)v.B * v.Hkv * c->S_alloc * 2 * c->G;
+  const size_t po_n = (size_t)v.B * v.Hkv * c->S_alloc * c->G * v.D;
+  const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
+  int nl = (int)std::min<size_t>({STEP_SCRATCH_BYTES / per_layer, (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
+  c->step_layers = 1;
+  if (c->streamed || nl < 2) return;
+  // groups of equal size: 48 layers of which 10 fit go as 5 groups of 10, 10, 10, 9, 9
+  nl = (v.L + (v.L + nl - 1) / nl - 1) / ((v.L + nl - 1) / nl);
+  float* p = (float*)dev_alloc(c, nl * per_layer);
+  if (!p) return;
+  c->xs_step = p; c->ml_step = p + nl * xs_n; c->po_step = c->ml_step + nl * ml_n;
+  c->step_layers = nl;
+}
+
 tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, const void* q_all, void* out_all,
                            void* hip_stream) {
   if (!c) return TKV_EINVAL;
@@ -819,9 +854,20 @@ tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, c
     c->ntier[0] += v.B;
     c->n_assigned += 1;
     for (int l = 0; l < v.L; ++l) c->len[l] = n + 1;
-    for (int l = 0; l < v.L; ++l) {
-      tkv_status s = tkv_attend_and_score(c, l, (const char*)q_all + l * q_stride, (char*)out_all + l * o_stride, hip_stream);
+    step_scratch(c, (hipStream_t)hip_stream);
+    const int per_launch = std::max(1, c->step_layers);
+    for (int l = 0; l < v.L;) {
+      // one launch pair for a group of layers; with WAIT a layer that still has to wait for its prefetch goes alone, so
+      // that the layers before it do not wait with it
+      const auto waits = [&](int k) { return c->cfg.prefetch_mode == TKV_PREFETCH_WAIT && c->layer_wait[k]; };
+      const int groups = (v.L - l + per_launch - 1) / per_launch;
+      int nl = (v.L - l + groups - 1) / groups;
+      for (int k = 0; k < nl; ++k)
+        if (waits(l + k)) { nl = std::max(k, 1); break; }
+      tkv_status s = attend_one(c, l, (const char*)q_all + l * q_stride, (char*)out_all + l * o_stride, 0, v.Hq, v.Hq, true,
+                                (hipStream_t)hip_stream, false, 1, nl);
       if (s != TKV_OK) return s;
+      l += nl;
     }
     if (se) HIPCHK(c, hipEventRecord(se->b, (hipStream_t)hip_stream));
     return TKV_OK;

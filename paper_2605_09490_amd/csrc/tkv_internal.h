@@ -27,6 +27,7 @@ enum Cnt : int {
 constexpr int TOK_PER_BLOCK = 64;    // list entries per attention tile (one per lane of a wave)
 constexpr int PLAN_THREADS = 1024;
 constexpr int MAX_G = 8;
+constexpr int MAX_LAYERS_PER_LAUNCH = 64;   // one bit of AttnArgs::old_mask per layer
 constexpr int ATTN_ARG_SEQS = 64;    // list lengths travel as kernel arguments up to this batch size
 
 // Device view of one cache, passed by value to the tier-management kernels.
@@ -110,6 +111,11 @@ struct AttnArgs {
                     // a sequence is jt * Hq heads further on in q and out, leaves n_q * cq - 1 - jt more entries of
                     // list F out (it is that many positions older), and has logits and split partials of its own
                     // (index b * n_q * cq + jt)
+  int nl;           // consecutive layers served by this launch (tkv_decode_step: 1 .. MAX_LAYERS_PER_LAUNCH; every other call:
+                    // 1).  All per-layer arrays above are [layer][B]..., so layer li of sequence b is entry li * B + b of
+                    // rows, q, out, xs and the partials; lists, counters and scores belong to sequence b alone
+  const int* f_loc_old;   // slots of list F for the layers whose bit is set in old_mask (lazy prefetch: the copies are in flight)
+  uint64_t old_mask;
   int B, Hq, Hkv, Nmax, capF, cap2, xs_stride, cb, sb, t2fmt, out_kind, q_es;   // out_kind: 0 binary32, 1 bfloat16, 2 binary16
   float softmax_scale, score_scale;
   int nF[ATTN_ARG_SEQS], nQ[ATTN_ARG_SEQS];   // list lengths per sequence (host mirror), used when B <= ATTN_ARG_SEQS

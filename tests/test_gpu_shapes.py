@@ -147,6 +147,42 @@ def test_decode_step_equals_per_layer_calls():
     a.close(); b.close()
 
 
+@pytest.mark.parametrize("mode,scorer,shape", [
+    ("lazy", "attention", dict(n_layers=7, batch=24, n_q_heads=64, n_kv_heads=8, head_dim=64, context=1990)),   # groups of 4 and 3 layers
+    ("wait", "combined", dict(n_layers=5, batch=3, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700)),
+    ("lazy", "vatp", dict(n_layers=40, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=333)),        # two passes of the finishing kernel
+    ("wait", "attention", dict(n_layers=4, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=200)),
+])
+def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
+    """A decode step's launches serve groups of layers: outputs and scores are the bits of per-layer calls, also right
+    behind a re-tiering whose transfers are in flight (lazy: some layers read their rows' old slots; wait: layers that
+    wait for their prefetch go alone), where a step takes several groups, and above 64 sequences."""
+    import paper_2605_09490_amd as tkv
+    from tkv_synth import Workload
+    cfg = small_config(name="groups", kv_dtype="bf16", decode_steps=4, k_window=16, policy_ppm=(300_000, 400_000, 250_000, 50_000), **shape)
+    print(f"[case] {mode} {scorer} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    kv = [tkv.TieredKV(cfg.n_layers, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype="bf16",
+                       k_window=16, prefetch_mode=mode, scorer=scorer) for _ in range(2)]
+    for l in range(cfg.n_layers):
+        k, v = wl.context_kv(l)
+        for c in kv:
+            c.append(l, k, v)
+    k_all, v_all, q_all = wl.decode_inputs(0, 4)
+    for s in range(4):
+        oa = kv[0].decode_step(k_all[s], v_all[s], q_all[s])
+        for l in range(cfg.n_layers):
+            kv[1].append(l, k_all[s, l], v_all[s, l])
+            assert torch.equal(oa[l], kv[1].attend_and_score(l, q_all[s, l])), (s, l)
+        assert np.array_equal(kv[0].get_scores().view(np.uint32), kv[1].get_scores().view(np.uint32)), s
+        if s in (0, 2):
+            for c in kv:
+                c.classify(cfg.policy_ppm)
+                c.migrate()
+    for c in kv:
+        c.close()
+
+
 def test_many_tiles_per_wave():
     """256 (sequence, kv head) pairs leave two workgroups per pair: every wave walks 8+ tiles of list F and the Q waves
     several of list Q, so the steady-state part of the fetch pipeline (not only its first and last tile) is compared
