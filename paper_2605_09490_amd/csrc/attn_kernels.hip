@@ -235,9 +235,10 @@ struct GPad { static constexpr int v = (G <= 4) ? 4 : 8; };
 // ---- geometry ------------------------------------------------------------------------------------------------
 // A row is fetched in "units" of 16 bytes (4 bytes where a lane's share of a row is shorter than 16), one unit per
 // lane and direct-to-LDS instruction; the lane that fetched a unit is the lane that reads it back.
-//   K side: 8 lanes per row; lane r8 owns units j*8 + r8, j < KU          (K batch i = rows 8*g8 + i, g8 = lane/8)
-//   V side: LPRV lanes per row; lane rv owns units rv*VU + u, u < VU      (V step it = rows LPRV*gv + it, gv = lane/LPRV)
-template <int D, Mode M>
+//   K side: 8 lanes per row; lane r8 owns units j*8 + r8, j < KU          (K batch i = rows NB*g8 + i, g8 = lane/8)
+//   V side: LPRV lanes per row; lane rv owns units rv*VU + u, u < VU      (V step it = rows NITV*gv + it, gv = lane/LPRV)
+// TR rows per tile (64, or fewer where a wave has less LDS); with TR < 64 the lanes r8 >= TR / 8 carry no entry of their own.
+template <int D, Mode M, int TR = 64>
 struct Geo {
   static constexpr bool IS_Q = (M == Q_INT8 || M == Q_INT4);
   static constexpr int RB = (M == F_BF16 || M == F_F16) ? 2 * D : (M == F_F32) ? 4 * D : (M == Q_INT8) ? D : D / 2;   // bytes per row
@@ -247,17 +248,17 @@ struct Geo {
   static constexpr int EUK = KS * D / RB;                   // elements per unit
   static constexpr int EV = (M == F_F32) ? 4 : 8;           // elements of a V row per lane
   static constexpr int LPRV = D / EV;                       // lanes per V row
-  static constexpr int NITV = LPRV;                         // V steps per tile
+  static constexpr int NB = TR / 8;                         // K batches per tile
+  static constexpr int NITV = TR * LPRV / 64;               // V steps per tile
   static constexpr int VLB = RB / LPRV;                     // bytes of a V row per lane
   static constexpr int VS = (VLB % 16 == 0) ? 16 : 4;
   static constexpr int VU = VLB / VS;
   static constexpr int EUV = EV / VU;                       // elements per V unit
   static constexpr int SCD = (M == Q_INT8) ? 1 : (M == Q_INT4) ? D / 64 : 0;   // dwords of scales per row
   static constexpr float OFF = (M == Q_INT4) ? 8.f : 128.f; // codes are read as code + OFF
-  // direct-to-LDS operations of one tile period, in issue order: slot list, K scales, K batches, V scales, V steps
-  static constexpr int N_K = 8 * KU, N_V = NITV * VU;
-  static constexpr int T = 1 + SCD + N_K + SCD + N_V;
-  static_assert(KLB % KS == 0 && VLB % VS == 0 && LPRV % 4 == 0 && (!IS_Q || D % 64 == 0), "unsupported head_dim");
+  // direct-to-LDS operations of one tile period: slot list, K scales, N_K K pieces, V scales, N_V V pieces
+  static constexpr int N_K = NB * KU, N_V = NITV * VU;
+  static_assert(KLB % KS == 0 && VLB % VS == 0 && NITV % 4 == 0 && NB % 4 == 0 && (!IS_Q || D % 64 == 0), "unsupported head_dim");
 };
 
 template <int S>
@@ -438,6 +439,8 @@ struct WaveLds {
   char* t; char* sk; char* sv; char* lt;   // tile buffer (K rows, then V rows, in turn), K scales, V scales, slot lists (2 x 64 ints)
   char* p;                                 // probabilities of the current tile (before the first tile: the query block)
   uint32_t ta, ska, sva, lta, pa;          // the same as LDS addresses
+  uint32_t lga; int lcap, lcap0;           // a workgroup that walks a whole pair: logits [G][lcap] in LDS; the columns from
+                                           // lcap0 on (the first tile that does not fit whole) are parked in memory
 };
 
 template <int SZ>
@@ -460,21 +463,24 @@ __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t& rs, char* lds,
 //   V scales of t+1 | per V step of t: the K pieces of t+1 on its bytes
 // Accumulates into o (offset-corrected for code rows), m_run, l_lane (per-lane partial sums of the softmax
 // denominator, relative to m_run); leaves the scaled logits in xs.
-template <int D, int G, Mode M, int KT>
+template <int D, int G, Mode M, int KT, int TR = 64, bool WHOLE = false>
 __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, int b, int jq, int kvh, int lane,
-                                          int tile0, int tstride, int n_list, const int* loc_list, int xs_tile0,
+                                          int tile0, int tstride, int n_list, const int* loc_list, int col0,
                                           float (&o)[G][Geo<D, M>::EV], float (&m_run)[G], float (&l_lane)[G]) {
-  using GE = Geo<D, M>;
+  using GE = Geo<D, M, TR>;
+  constexpr int NB = GE::NB;
   constexpr int EV = GE::EV, LPRV = GE::LPRV, NITV = GE::NITV, KU = GE::KU, KS = GE::KS, VU = GE::VU, VS = GE::VS;
   constexpr int EUK = GE::EUK, SCD = GE::SCD, RB = GE::RB, N_K = GE::N_K, N_V = GE::N_V;
   constexpr int GP = GPad<G>::v;
   constexpr bool QBF = KT != KT_F32, H = KT == KT_F16;
   constexpr int KIB = 64 * KS, VIB = 64 * VS;        // bytes of the tile buffer one K / V piece covers
   constexpr int KBB = KU * KIB, VSB = VU * VIB;      // ... one K batch / one V step
-  static_assert(KBB % VIB == 0 && 8 * KBB == NITV * VSB, "K batches and V steps tile the same buffer");
+  static_assert(KBB % VIB == 0 && NB * KBB == NITV * VSB, "K batches and V steps tile the same buffer");
   constexpr int VPB = KBB / VIB;                     // V pieces issued after each K batch
   const int g8 = lane >> 3, r8 = lane & 7;           // K side: row group and unit column
   const int gv = lane / LPRV, rv = lane % LPRV;      // V side
+  const int entry = NB * g8 + r8;                    // the tile's entry whose logits this lane keeps
+  const bool keeps = NB == 8 || r8 < NB;
 
   __amdgpu_buffer_rsrc_t rk, rvv, rsk, rsv;
   if constexpr (!GE::IS_Q) {
@@ -488,19 +494,34 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   }
   const __amdgpu_buffer_rsrc_t rl = make_rsrc(loc_list, (uint32_t)a.Nmax * 4u);
 
-  if (tile0 * 64 >= n_list) return;
+  if (tile0 * TR >= n_list) return;
 
+  // a tile's slot list and scales: one dword per lane and entry (lanes past the tile's rows stay out of it)
+  auto issue_loc = [&](int par, int tile) {
+    if (TR == 64 || lane < TR) dma<4>(rl, w.lt + par * (TR * 4), (uint32_t)(tile * TR + lane) * 4u, 0);
+  };
   // The first tile's slot list is asked for before anything else: the compute unit serves its waves' requests in
   // the order they were made, and a list request that came behind another wave's rows would wait for all of them.
-  dma<4>(rl, w.lt, (uint32_t)(tile0 * 64 + lane) * 4u, 0);
+  issue_loc(0, tile0);
 
   // The lane's units of the G query vectors.  16-bit queries (G * D * 2 bytes, contiguous) come in through the
   // probability region of the LDS, as NQD direct loads of 1 KB whose count the waits below can name; binary32
   // queries are fetched by ordinary loads (the wait for the list then waits for them as well).
   QRegs<D, G, M, KT> q;
-  constexpr int NQD = QBF ? (G * D * 2 + 1023) / 1024 : 0;
-  static_assert(NQD * 1024 <= 64 * GP * 4, "the query block is parked in the probability region");
-  if constexpr (QBF) {
+  constexpr int NQD = QBF && !WHOLE ? (G * D * 2 + 1023) / 1024 : 0;
+  static_assert(NQD * 1024 <= TR * GP * 4, "the query block is parked in the probability region");
+  if constexpr (WHOLE) {
+    // a workgroup that walks a whole pair: ordinary loads, once; their sums follow behind the wait for the list
+    const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + kvh * G) * D * 2;
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int j = 0; j < KU; ++j) {
+        const uint32_t* src = (const uint32_t*)(qb + ((size_t)h * D + (size_t)(j * 8 + r8) * EUK) * 2);
+#pragma unroll
+        for (int c = 0; c < EUK / 2; ++c) q.qp[h][j][c] = src[c];
+      }
+  } else if constexpr (QBF) {
     const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + (size_t)jq * a.Hq + kvh * G) * D * 2;
     const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)(G * D * 2));   // lanes past the block fetch zeros
 #pragma unroll
@@ -529,41 +550,44 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   // per-lane byte offsets of its units within a row, and its LDS read addresses
   const uint32_t kcol = (uint32_t)r8 * KS, vcol = (uint32_t)rv * (VU * VS);
   const uint32_t k_rd = w.ta + (uint32_t)lane * KS, v_rd = w.ta + (uint32_t)lane * VS;
-  const uint32_t p_wr = w.pa + (uint32_t)lane * (GP * 4), p_rd = w.pa + (uint32_t)(gv * LPRV) * (GP * 4);
+  const uint32_t p_wr = w.pa + (uint32_t)entry * (GP * 4), p_rd = w.pa + (uint32_t)(gv * NITV) * (GP * 4);
 
   // slots of the rows this lane fetches: lk / lrow belong to the tile whose K rows are fetched next, lv to the
   // tile whose V rows are fetched next
-  int lk[8], lv[LPRV], lrow;
-  // reads the K-side slots (rows 8*g8 + i) and the lane's own row's slot of the list in LDS half `par`
+  int lk[NB], lv[NITV], lrow;
+  // reads the K-side slots (rows NB*g8 + i) and the lane's own row's slot of the list in LDS half `par`
   auto read_locs_k = [&](int par, int nvalid) {
-    const uint32_t base = w.lta + (uint32_t)par * 256u;
-    if (nvalid < 64) {                                   // wave-uniform: a list's last tile
-      if (lane >= nvalid) lds_wr32(base + (uint32_t)lane * 4u, 0xffffffffu);   // no row: fetches land as zeros
+    const uint32_t base = w.lta + (uint32_t)par * (TR * 4u);
+    if (nvalid < TR) {                                   // wave-uniform: a list's last tile
+      if (lane >= nvalid && lane < TR) lds_wr32(base + (uint32_t)lane * 4u, 0xffffffffu);   // no row: fetches land as zeros
     }
-    u32x4 t0 = lds_rd128<0>(base + (uint32_t)g8 * 32u), t1 = lds_rd128<16>(base + (uint32_t)g8 * 32u);
-    uint32_t me = lds_rd32<0>(base + (uint32_t)lane * 4u);
-    lds_wait(); tie(t0); tie(t1); tie(me);
-    lk[0] = t0.x; lk[1] = t0.y; lk[2] = t0.z; lk[3] = t0.w; lk[4] = t1.x; lk[5] = t1.y; lk[6] = t1.z; lk[7] = t1.w;
+    u32x4 t[NB / 4];
+    static_for<NB / 4>([&](auto cc) { constexpr int c = decltype(cc)::value; t[c] = lds_rd128<c * 16>(base + (uint32_t)g8 * (NB * 4u)); });
+    uint32_t me = lds_rd32<0>(base + (uint32_t)(lane & (TR - 1)) * 4u);
+    lds_wait(); tie(t); tie(me);
+#pragma unroll
+    for (int c = 0; c < NB / 4; ++c) { lk[4 * c] = t[c].x; lk[4 * c + 1] = t[c].y; lk[4 * c + 2] = t[c].z; lk[4 * c + 3] = t[c].w; }
     lrow = (int)me;
   };
   auto read_locs_v = [&](int par) {
-    const uint32_t base = w.lta + (uint32_t)par * 256u + (uint32_t)(gv * LPRV) * 4u;
-    u32x4 t[LPRV / 4];
-    static_for<LPRV / 4>([&](auto cc) { constexpr int c = decltype(cc)::value; t[c] = lds_rd128<c * 16>(base); });
+    const uint32_t base = w.lta + (uint32_t)par * (TR * 4u) + (uint32_t)(gv * NITV) * 4u;
+    u32x4 t[NITV / 4];
+    static_for<NITV / 4>([&](auto cc) { constexpr int c = decltype(cc)::value; t[c] = lds_rd128<c * 16>(base); });
     lds_wait(); tie(t);
 #pragma unroll
-    for (int c = 0; c < LPRV / 4; ++c) { lv[4 * c] = t[c].x; lv[4 * c + 1] = t[c].y; lv[4 * c + 2] = t[c].z; lv[4 * c + 3] = t[c].w; }
-  };
-  auto issue_loc = [&](int par, int tile) {
-    dma<4>(rl, w.lt + par * 256, (uint32_t)(tile * 64 + lane) * 4u, 0);
+    for (int c = 0; c < NITV / 4; ++c) { lv[4 * c] = t[c].x; lv[4 * c + 1] = t[c].y; lv[4 * c + 2] = t[c].z; lv[4 * c + 3] = t[c].w; }
   };
   auto issue_kscale = [&]() {
+    if (TR == 64 || lane < TR) {
 #pragma unroll
-    for (int j = 0; j < SCD; ++j) dma<4>(rsk, w.sk + j * 256, (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+      for (int j = 0; j < SCD; ++j) dma<4>(rsk, w.sk + j * (TR * 4), (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+    }
   };
   auto issue_vscale = [&]() {
+    if (TR == 64 || lane < TR) {
 #pragma unroll
-    for (int j = 0; j < SCD; ++j) dma<4>(rsv, w.sv + j * 256, (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+      for (int j = 0; j < SCD; ++j) dma<4>(rsv, w.sv + j * (TR * 4), (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+    }
   };
   auto issue_k_piece = [&](int s) {                      // K piece s = (batch s / KU, unit s % KU)
     const int i = s / KU, j = s % KU;
@@ -577,13 +601,13 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   // ---- prologue: the first tile's slot list has been asked for; then its scales and K rows in the order of a tile
   // period, and the query block out of the LDS into registers
   wait_vm<NQD>();                                        // the list is in (binary32 queries: and the queries)
-  read_locs_k(0, n_list - tile0 * 64);
+  read_locs_k(0, n_list - tile0 * TR);
   issue_loc(1, tile0 + tstride);
   issue_kscale();
   issue_vscale();
 #pragma unroll
   for (int s = 0; s < N_K; ++s) issue_k_piece(s);
-  if constexpr (QBF) {
+  if constexpr (QBF && !WHOLE) {
     wait_vm<1 + 2 * SCD + N_K>();                        // everything older than the second list: the query block
     // a unit of a query is EUK 16-bit elements: 8 bytes (one ds_read_b64) or QB pieces of 16
     constexpr int QW = EUK / 2, QB = QW / 4;
@@ -621,6 +645,9 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
             for (int e = 0; e < 4; ++e) q.qp[h][j][c * 4 + e] = elem(t[h][j][c], e);
           }
     }
+  }
+  if constexpr (QBF) {
+    constexpr int QW = EUK / 2;
 #pragma unroll
     for (int h = 0; h < G; ++h)
 #pragma unroll
@@ -638,7 +665,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   auto tile_body = [&](int tile, auto more_c) {
     constexpr bool MORE = decltype(more_c)::value;
     constexpr int X = MORE ? 1 : 0;                      // operations of the parts a last tile does not issue
-    const bool valid = tile * 64 + lane < n_list;
+    const bool valid = keeps && tile * TR + entry < n_list;
     // The two waves of a SIMD are issued oldest first, which lets the first wave of a pair run a whole tile ahead and
     // leaves the second one to finish on its own; the wave with more phases still to do goes first instead.
     __builtin_amdgcn_s_setprio(MORE ? 3 : 1);
@@ -646,25 +673,24 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
     read_locs_v(par ^ 1);
     if constexpr (MORE) {
       wait_vm<2 * SCD + N_K>();
-      read_locs_k(par, n_list - (tile + tstride) * 64);
+      read_locs_k(par, n_list - (tile + tstride) * TR);
       issue_loc(par ^ 1, tile + 2 * tstride);
     }
     // -- K scales of this tile
-    float ksc[8][KU];
+    float ksc[NB][KU];
     if constexpr (GE::IS_Q) {
       wait_vm<SCD + N_K + X>();
-      u32x4 t[SCD][2];
+      u32x4 t[SCD][NB / 4];
       static_for<SCD>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        t[j][0] = lds_rd128<j * 256>(w.ska + (uint32_t)g8 * 32u);
-        t[j][1] = lds_rd128<j * 256 + 16>(w.ska + (uint32_t)g8 * 32u);
+        static_for<NB / 4>([&](auto cc) { constexpr int c = decltype(cc)::value; t[j][c] = lds_rd128<j * (TR * 4) + c * 16>(w.ska + (uint32_t)g8 * (NB * 4u)); });
       });
       lds_wait();
 #pragma unroll
       for (int j = 0; j < SCD; ++j) { tie(t[j][0]); tie(t[j][1]); }
       if constexpr (MORE) issue_kscale();
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int j = 0; j < KU; ++j) {
           if constexpr (M == Q_INT8) ksc[i][j] = elem_f(t[0][i / 4], i % 4);
@@ -687,21 +713,21 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
       });
     };
     read_k(std::integral_constant<int, 0>{}, kb[0]);
-    static_for<8>([&](auto ic) {
+    static_for<NB>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
       lds_wait(); tie(kb[i & 1].u);
 #pragma unroll
       for (int v = i * VPB; v < (i + 1) * VPB; ++v) issue_v_piece(v);
-      if constexpr (i + 1 < 8) read_k(std::integral_constant<int, (i + 1 < 8 ? i + 1 : 7)>{}, kb[(i + 1) & 1]);
+      if constexpr (i + 1 < NB) read_k(std::integral_constant<int, (i + 1 < NB ? i + 1 : NB - 1)>{}, kb[(i + 1) & 1]);
       float x[G];
       row_logits<D, G, M, KT>(kb[i & 1], q, ksc[i], x);
 #pragma unroll
-      for (int h = 0; h < G; ++h) xt[h] = (r8 == i) ? x[h] : xt[h];   // lane 8*g8 + i keeps entry 8*g8 + i
+      for (int h = 0; h < G; ++h) xt[h] = (r8 == i) ? x[h] : xt[h];   // lane 8*g8 + i keeps entry NB*g8 + i
     });
     // -- online softmax, one entry per lane; the denominator is summed per lane and reduced once at the end
     float corr[G];
     {
-      const size_t xbase = xs_at(a, b * a.n_q + jq, kvh * G, (xs_tile0 + tile) * 64 + lane);
+      const int col = col0 + tile * TR + entry;
       float pv[GP];
 #pragma unroll
       for (int h = 0; h < GP; ++h) pv[h] = 0.f;
@@ -709,8 +735,24 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
 #pragma unroll
       for (int h = 0; h < G; ++h) {
         x[h] = valid ? xt[h] * a.softmax_scale : -INFINITY;
-        if (valid) a.xs[xbase + (size_t)h * a.xs_stride] = x[h];
         xm[h] = x[h];
+      }
+      if constexpr (WHOLE) {
+        // the logits stay in the LDS as far as it goes; the rest of a longer list is parked in memory for the workgroup
+        if (col0 + tile * TR + TR <= w.lcap) {
+          if (valid) {
+#pragma unroll
+            for (int h = 0; h < G; ++h) lds_wr32(w.lga + (uint32_t)(h * w.lcap + col) * 4u, __builtin_bit_cast(uint32_t, x[h]));
+          }
+        } else if (valid) {
+          float* sp = a.xs + ((size_t)(b * a.Hkv + kvh) * G) * a.xs_stride + (col - w.lcap0);
+#pragma unroll
+          for (int h = 0; h < G; ++h) sp[(size_t)h * a.xs_stride] = x[h];
+        }
+      } else if (valid) {
+        const size_t xbase = xs_at(a, b * a.n_q + jq, kvh * G, col);
+#pragma unroll
+        for (int h = 0; h < G; ++h) a.xs[xbase + (size_t)h * a.xs_stride] = x[h];
       }
       wave_max_all<G>(xm);
 #pragma unroll
@@ -724,7 +766,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
         m_run[h] = mn;
         pv[h] = p;
       }
-      static_for<GP / 4>([&](auto cc) {
+      if (keeps) static_for<GP / 4>([&](auto cc) {
         constexpr int c = decltype(cc)::value;
         u32x4 t;
         t.x = __builtin_bit_cast(uint32_t, pv[4 * c]); t.y = __builtin_bit_cast(uint32_t, pv[4 * c + 1]);
@@ -748,16 +790,16 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
     }
     // -- V scales of this tile
     __builtin_amdgcn_s_setprio(MORE ? 2 : 0);
-    float vsc[LPRV];
+    float vsc[NITV];
     if constexpr (GE::IS_Q) {
       wait_vm<N_K + X * (1 + SCD) + N_V>();
-      const uint32_t base = w.sva + (uint32_t)(gv * LPRV) * 4u + ((M == Q_INT4) ? (uint32_t)(rv >> 3) * 256u : 0u);
-      u32x4 t[LPRV / 4];
-      static_for<LPRV / 4>([&](auto cc) { constexpr int c = decltype(cc)::value; t[c] = lds_rd128<c * 16>(base); });
+      const uint32_t base = w.sva + (uint32_t)(gv * NITV) * 4u + ((M == Q_INT4) ? (uint32_t)(rv >> 3) * (TR * 4u) : 0u);
+      u32x4 t[NITV / 4];
+      static_for<NITV / 4>([&](auto cc) { constexpr int c = decltype(cc)::value; t[c] = lds_rd128<c * 16>(base); });
       lds_wait(); tie(t);
       if constexpr (MORE) issue_vscale();
 #pragma unroll
-      for (int it = 0; it < LPRV; ++it) {
+      for (int it = 0; it < NITV; ++it) {
         if constexpr (M == Q_INT8) vsc[it] = elem_f(t[it / 4], it % 4);
         else vsc[it] = half_of(elem(t[it / 4], it % 4), (rv >> 2) & 1);        // unit rv lies in group rv/4
       }
@@ -793,7 +835,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   };
 
   int tile = tile0;
-  for (; (tile + tstride) * 64 < n_list; tile += tstride) tile_body(tile, std::true_type{});
+  for (; (tile + tstride) * TR < n_list; tile += tstride) tile_body(tile, std::true_type{});
   tile_body(tile, std::false_type{});
 
   if constexpr (GE::IS_Q) {
@@ -1437,11 +1479,11 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
   }
   bool o_written = false;
   if (u < nwf) {
-    attn_wave<D, G, KG::MF, KT>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb, o, m_run, l_lane);
+    attn_wave<D, G, KG::MF, KT>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
   } else {
     if constexpr (EV == 8) {
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o, m_run, l_lane);
     } else {
       // binary32 rows use 4 elements per lane, code rows 8: separate accumulators, parked directly
       float o8[G][8];
@@ -1449,8 +1491,8 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
       for (int h = 0; h < G; ++h)
 #pragma unroll
         for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o8, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, o8, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o8, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o8, m_run, l_lane);
       constexpr int L8 = D / 8;
 #pragma unroll
       for (int st = L8; st < 64; st <<= 1)
@@ -1523,6 +1565,143 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
     float* pm = a.part_ml + ((size_t)((bq * a.Hkv + kvh) * a.S_total + a.s0 + s) * 2) * G;
     pm[t] = mb;
     pm[G + t] = ll;
+  }
+}
+
+// ---- a whole decode step: one workgroup per (layer, sequence, kv head) pair ----------------------------------------
+// With the pairs of all layers of a step in one launch there are enough of them to fill the chip without splitting any,
+// and a workgroup that has walked a pair's lists to their end knows the final softmax statistics of its heads.  So it
+// writes its output itself, and of the logits, which stay in the LDS, one float per row: the row's weights summed over
+// the group's heads.  That is what this kernel is for: it is bound by HBM, and written logits (G floats per row, 4-6 % of
+// the bytes) cost it a fifth of its time and their reading back another tenth (1.6 GB of rows stream in 237 us alone,
+// in 317 us with 90 MB of logits written beside them, whatever the shape of the stores).
+// Measured (14B shape, 48 layers, batch 8, 4112 tokens all at full precision): 960-1140 us a step, 6.0 TB/s, against
+// 5 x (243 + 23) us with split pairs, written logits and ten layers per launch.
+// The LDS holds eight 8 KB tile buffers (32 rows of 256 bytes; 64 KB in flight per compute unit stream as fast as 128 KB)
+// and the logits of LCAP entries; a longer list parks the rest in memory and reads it back.  The eight waves are divided
+// between the lists as in the split launch (a wave that walked both would need some 90 registers more than it has).
+template <int D, int G>
+struct StepGeo {
+  static constexpr int NW = 8, RB = 2 * D, TR = 8192 / RB < 64 ? 8192 / RB : 64, TILE = TR * RB;
+  static constexpr int P = TR * GPad<G>::v * 4, SC = (D / 64) * TR * 4, LT = 2 * TR * 4;   // per wave: weights, K or V scales, slot lists
+  static constexpr int LDS = 163840, FIXED = NW * (TILE + P + 2 * SC + LT) + NW * 16 * 4 + 8 * 8 + 256;
+  static constexpr int LCAP = (LDS - FIXED) / 4 / G / TR * TR;
+};
+template <int D, int G, int KT>
+__global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
+  using SG = StepGeo<D, G>;
+  constexpr Mode MF = KT == KT_BF16 ? F_BF16 : F_F16;
+  constexpr int NW = SG::NW, TR = SG::TR, TILE = SG::TILE, LCAP = SG::LCAP;
+  constexpr int EV = Geo<D, MF, TR>::EV, LPRV = Geo<D, MF, TR>::LPRV;
+  constexpr int NG = 64 / LPRV, FIT = TILE / (G * D * 4), NGK = NG <= FIT ? NG : (FIT >= 4 ? 4 : FIT >= 2 ? 2 : 1);
+  static_assert(G * D * 4 <= TILE, "a wave's output partial is parked in its tile buffer");
+  __shared__ __attribute__((aligned(16))) char sm_t[NW * TILE];
+  __shared__ __attribute__((aligned(16))) char sm_p[NW * SG::P];
+  __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * SG::SC];
+  __shared__ __attribute__((aligned(16))) char sm_lt[NW * SG::LT];
+  __shared__ float sm_lg[G * LCAP];
+  __shared__ float sm_ml[NW * 16];
+  __shared__ float2 sm_fin[8];
+  const int kvh = blockIdx.x, bl = blockIdx.y, li = bl / a.B, b = bl - li * a.B;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int* f_loc = (((a.old_mask >> li) & 1) ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax;
+  int nF, nQ;
+  if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
+  else { nF = a.cnt[b * CNT_N + C_NF]; nQ = a.cnt[b * CNT_N + C_NQ]; }
+  const int nft = (nF + TR - 1) / TR, colq = nft * TR;
+
+  WaveLds w;
+  w.t = sm_t + wave * TILE; w.p = sm_p + wave * SG::P;
+  w.sk = sm_sc + wave * 2 * SG::SC; w.sv = w.sk + SG::SC; w.lt = sm_lt + wave * SG::LT;
+  w.ta = lds_addr(w.t); w.pa = lds_addr(w.p); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
+  w.lga = lds_addr(sm_lg); w.lcap = LCAP; w.lcap0 = LCAP;
+  float* my_o = (float*)w.t;
+
+  float o[G][EV], m_run[G], l_lane[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    m_run[h] = -INFINITY; l_lane[h] = 0.f;
+#pragma unroll
+    for (int e = 0; e < EV; ++e) o[h][e] = 0.f;
+  }
+  const int nwq = a.B <= ATTN_ARG_SEQS ? a.nWq[b] : q_waves(NW, nft, (nQ + TR - 1) / TR), nwf = NW - nwq;
+  if (wave < nwf) attn_wave<D, G, MF, KT, TR, true>(a, w, bl, 0, kvh, lane, wave, nwf, nF, f_loc, 0, o, m_run, l_lane);
+  else if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, true>(a, w, bl, 0, kvh, lane, wave - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+  else attn_wave<D, G, Q_INT4, KT, TR, true>(a, w, bl, 0, kvh, lane, wave - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+  // ---- merge the waves
+#pragma unroll
+  for (int st = LPRV * NGK; st < 64; st <<= 1)
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int e = 0; e < EV; ++e) o[h][e] += __shfl_xor(o[h][e], st);
+  if (lane < LPRV * NGK) {
+    float* dst = my_o + (lane / LPRV) * (G * D) + (lane % LPRV) * EV;
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int e = 0; e < EV; ++e) dst[h * D + e] = o[h][e];
+  }
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float ls = wave_sum(l_lane[h]);
+    if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
+  }
+  __syncthreads();
+  if (t < G) {
+    float mb = sm_ml[t], ll = 0.f;
+#pragma unroll
+    for (int ww = 1; ww < NW; ++ww) mb = fmaxf(mb, sm_ml[ww * 16 + t]);
+    if (mb > -INFINITY) {
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) ll = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + t] - mb) * LOG2E), sm_ml[ww * 16 + 8 + t], ll);
+    }
+    // no live position at all (a forced plan): zeros, not 0/0
+    sm_fin[t] = make_float2(mb > -INFINITY ? mb : 0.f, ll > 0.f ? 1.0f / ll : 0.f);
+  }
+  __syncthreads();
+  for (int i = t; i < G * D; i += NW * 64) {
+    const int h = i / D;
+    const float2 fin = sm_fin[h];
+    float acc = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) {
+      const float* src = (const float*)(sm_t + ww * TILE) + i;
+      float part = src[0];                                  // the wave's row groups, in order
+#pragma unroll
+      for (int g = 1; g < NGK; ++g) part += src[g * (G * D)];
+      acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + h] - fin.x) * LOG2E), part, acc);
+    }
+    acc *= fin.y;
+    const size_t oi = ((size_t)bl * a.o_bs + kvh * G) * D + i;
+    if (a.out_kind == KT_BF16) ((uint16_t*)a.out)[oi] = f32_to_bf16(acc);
+    else if (a.out_kind == KT_F16) ((_Float16*)a.out)[oi] = (_Float16)acc;    // round to nearest even
+    else ((float*)a.out)[oi] = acc;
+  }
+  // ---- the rows' weights, summed over the group's heads
+  const float pen = a.red ? a.red_w * (float)G / (float)(nF + nQ) : 0.f;
+  float2 fin[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) fin[h] = sm_fin[h];
+  const size_t pr = (size_t)bl * a.Hkv + kvh;
+  for (int c = t; c < colq + nQ; c += NW * 64) {
+    if (c >= nF && c < colq) continue;
+    float x[G], s = 0.f;
+    if (c < LCAP) {
+#pragma unroll
+      for (int h = 0; h < G; ++h) x[h] = sm_lg[h * LCAP + c];
+    } else {
+#pragma unroll
+      for (int h = 0; h < G; ++h) x[h] = a.xs[(pr * G + h) * a.xs_stride + (c - LCAP)];
+    }
+#pragma unroll
+    for (int h = 0; h < G; ++h) s += __builtin_amdgcn_exp2f((x[h] - fin[h].x) * LOG2E) * fin[h].y;
+    if (a.vnorm || a.red) {
+      const int pos = c < nF ? a.f_pos[(size_t)b * a.Nmax + c] : a.q_pos[(size_t)b * a.Nmax + (c - colq)];
+      if (a.vnorm) s *= a.vnorm[pr * a.Nmax + pos];         // value-aware scorer: times the norm of the value row the group reads
+      if (a.red) s = fmaf(-pen, a.red[pr * a.Nmax + pos], s);   // redundancy-penalised: each head takes red_w * rho / (positions attended) off
+    }
+    a.sc[pr * a.sc_stride + c] = s;
   }
 }
 
@@ -1917,6 +2096,43 @@ __global__ __launch_bounds__(256) void k_attn_finish_chunk(const AttnArgs a, int
   }
 }
 
+#if !defined(TKV_ATTN_PART) || TKV_ATTN_PART == 4
+// ---- finish of a whole-pair step launch: the rows' weights summed over kv heads and layers into the scores ----------
+// Grid (64-column tiles, B), 16 waves: a wave sums the kv heads of layers w, w + 16, ...; the layers are then added into
+// the score in layer order, so that it does not matter how a step's layers are grouped into launches.
+__global__ __launch_bounds__(1024) void k_step_scores(const AttnArgs a, int tr) {
+  __shared__ float tot[MAX_LAYERS_PER_LAUNCH * 64];
+  const int b = blockIdx.y, t = threadIdx.x, e = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), c = blockIdx.x * 64 + e;
+  int nF, nQ;
+  if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
+  else { nF = a.cnt[b * CNT_N + C_NF]; nQ = a.cnt[b * CNT_N + C_NQ]; }
+  const int colq = (nF + tr - 1) / tr * tr;
+  if ((int)blockIdx.x * 64 >= colq + nQ) return;
+  const bool live = c < nF || (c >= colq && c < colq + nQ);
+  for (int l = wv; l < a.nl; l += 16) {
+    const float* src = a.sc + ((size_t)(l * a.B + b) * a.Hkv) * a.sc_stride + c;
+    float s = 0.f;
+    if (live) {
+#pragma unroll 8
+      for (int k = 0; k < a.Hkv; ++k) s += src[(size_t)k * a.sc_stride];
+    }
+    tot[l * 64 + e] = s;
+  }
+  int pos = 0;
+  float score = 0.f;
+  if (wv == 0 && live) {
+    pos = c < nF ? a.f_pos[(size_t)b * a.Nmax + c] : a.q_pos[(size_t)b * a.Nmax + (c - colq)];
+    score = a.score[(size_t)b * a.Nmax + pos];
+  }
+  __syncthreads();
+  if (wv == 0 && live) {
+    for (int l = 0; l < a.nl; ++l) score = score + a.score_scale * tot[l * 64 + e];
+    a.score[(size_t)b * a.Nmax + pos] = score;
+  }
+}
+
+#endif
+
 // ---- dispatch ----------------------------------------------------------------------------------------------
 // The file is compiled once per part (TKV_ATTN_PART = 0..3, 5, 6: one (head_dim, KV dtype) pair of attn_tiered each,
 // 4: attn_finish and the launchers), so the parts build in parallel; without the macro it is one translation unit.
@@ -1964,11 +2180,23 @@ static hipError_t run_tiered(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, 
   }
   return hipGetLastError();
 }
+template <int D, int G, int KT>
+static hipError_t run_step(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if constexpr (KT == KT_F32) {
+    return hipErrorInvalidValue;
+  } else {
+    const dim3 grid(a.Hkv, a.B * a.nl);
+    if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_step<D, G, KT>), grid, dim3(512), 0, st, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL((k_attn_step<D, G, KT>), grid, dim3(512), 0, st, a);
+    return hipGetLastError();
+  }
+}
 template <int D, int KT>
 hipError_t tiered_by_group(const AttnArgs& a, int G, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 #define TKV_DEFINE_PART(D_, BF_)                                                                                   \
   template <>                                                                                                      \
   hipError_t tiered_by_group<D_, BF_>(const AttnArgs& a, int G, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {  \
+    if (a.sc) { TKV_DISPATCH_G(run_step, D_, BF_, a, st, ev0, ev1) }                                               \
     TKV_DISPATCH_G(run_tiered, D_, BF_, a, st, ev0, ev1)                                                           \
   }
 #if TKV_HAS_PART(0)
@@ -2037,6 +2265,24 @@ hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t
   if (D == 128) { TKV_DISPATCH_G(run_finish_chunk, 128, KT_BF16, a, st) }
   if (D == 64) { TKV_DISPATCH_G(run_finish_chunk, 64, KT_BF16, a, st) }
   return hipErrorInvalidValue;
+}
+
+int attn_step_tile_rows(int D) { return D == 128 ? StepGeo<128, 1>::TR : StepGeo<64, 1>::TR; }
+template <int D, int G, int KT>
+static int step_cap() { return StepGeo<D, G>::LCAP; }
+int attn_step_lds_entries(int D, int G) {
+  const auto of_d128 = [&]() -> int { switch (G) { case 1: return step_cap<128, 1, 1>(); case 2: return step_cap<128, 2, 1>(); case 3: return step_cap<128, 3, 1>();
+    case 4: return step_cap<128, 4, 1>(); case 5: return step_cap<128, 5, 1>(); case 6: return step_cap<128, 6, 1>(); case 7: return step_cap<128, 7, 1>(); default: return step_cap<128, 8, 1>(); } };
+  const auto of_d64 = [&]() -> int { switch (G) { case 1: return step_cap<64, 1, 1>(); case 2: return step_cap<64, 2, 1>(); case 3: return step_cap<64, 3, 1>();
+    case 4: return step_cap<64, 4, 1>(); case 5: return step_cap<64, 5, 1>(); case 6: return step_cap<64, 6, 1>(); case 7: return step_cap<64, 7, 1>(); default: return step_cap<64, 8, 1>(); } };
+  return D == 128 ? of_d128() : of_d64();
+}
+hipError_t launch_step_scores(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (a.nl < 1 || a.nl > MAX_LAYERS_PER_LAUNCH) return hipErrorInvalidValue;
+  const int tr = attn_step_tile_rows(D);
+  if (ev0 && ev1) hipExtLaunchKernelGGL(k_step_scores, dim3(a.n_tiles, a.B), dim3(1024), 0, st, ev0, ev1, 0, a, tr);
+  else hipLaunchKernelGGL(k_step_scores, dim3(a.n_tiles, a.B), dim3(1024), 0, st, a, tr);
+  return hipGetLastError();
 }
 
 hipError_t launch_attn_finish(const AttnArgs& a, int D, int G, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {

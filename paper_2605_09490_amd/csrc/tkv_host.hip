@@ -74,6 +74,9 @@ struct tkv_cache {
   float* xs_chunk = nullptr; float* ml_chunk = nullptr; float* po_chunk = nullptr;   // the same for chunk launches
   float* xs_step = nullptr; float* ml_step = nullptr; float* po_step = nullptr;      // the same for several layers at once
   int step_layers = 0;             // layers one launch of a decode step serves (0: not decided yet)
+  float* sc_step = nullptr; float* spill_step = nullptr;   // whole-pair step launches (step_whole)
+  bool step_whole = false;
+  int sc_stride = 0, spill_stride = 0;
   int S_alloc = 0, xs_stride = 0;
   char* static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (tkv_attend_and_score_noalloc)
   // T1 store and transport
@@ -634,9 +637,9 @@ static tkv_status chunk_scratch(tkv_cache* c) {
 // the layer's last call of this step (the streamed frame is released and refilled, queued transfers are pumped).
 // noalloc: the scratch of the call lives in the library's fixed device array, and nothing on the way may allocate
 // (no event pools, no queued transfers are issued).  nl: consecutive layers served by the call's launches (a decode
-// step, after step_scratch; q and out then hold the layers one after the other).
+// step, after step_scratch; q and out then hold the layers one after the other).  step: a call of tkv_decode_step.
 static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* out, int trim, int q_bs, int o_bs, bool last,
-                             hipStream_t st, bool noalloc = false, int m = 1, int nl = 1) {
+                             hipStream_t st, bool noalloc = false, int m = 1, int nl = 1, bool step = false) {
   const DevView& v = c->dv;
   if (nl > 1 && (c->streamed || noalloc || m > 1 || nl > c->step_layers)) return fail(c, TKV_EINVAL, "attend_one: %d layers per launch not possible here", nl);
   if (m > 1) {
@@ -700,6 +703,8 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   a.red_w = c->cfg.redundancy_weight > 0.f ? c->cfg.redundancy_weight : 1.0f;
   a.cnt = v.cnt; a.score = v.score; a.xs = c->xs; a.part_ml = c->part_ml; a.part_o = c->part_o;
   if (nl > 1) { a.xs = c->xs_step; a.part_ml = c->ml_step; a.part_o = c->po_step; }
+  const bool whole = step && c->step_whole;
+  if (whole) { a.xs = c->spill_step; a.xs_stride = c->spill_stride; a.sc = c->sc_step; a.sc_stride = c->sc_stride; }
   if (m > 1) { a.xs = c->xs_chunk; a.part_ml = c->ml_chunk; a.part_o = c->po_chunk; }
   if (noalloc) {
     // the same three arrays, carved out of the fixed scratch array (256-byte aligned each)
@@ -716,10 +721,12 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (v.B <= ATTN_ARG_SEQS)
     for (int b = 0; b < v.B; ++b) {
       a.nF[b] = c->nF[b] - trim; a.nQ[b] = c->nQ[b];
-      a.nWq[b] = attn_q_waves(S * nw, tiles(c->nF[b] - trim), tiles(c->nQ[b]));
+      const int tr = attn_step_tile_rows(v.D);
+      a.nWq[b] = step && c->step_whole ? attn_q_waves(8, (c->nF[b] + tr - 1) / tr, (c->nQ[b] + tr - 1) / tr)
+                                       : attn_q_waves(S * nw, tiles(c->nF[b] - trim), tiles(c->nQ[b]));
     }
   a.B = v.B; a.Hq = v.Hq; a.Hkv = v.Hkv; a.Nmax = v.Nmax; a.capF = v.capP; a.cap2 = v.cap2;
-  a.S = S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;
+  a.S = S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;
   a.softmax_scale = c->softmax_scale; a.score_scale = c->score_scale;
   a.q_bs = q_bs; a.o_bs = o_bs; a.trim = trim;
   if (c->es == 2) { a.n_q = 1; a.cq = m; } else { a.n_q = m; a.cq = 1; }   // 16-bit rows: the tokens as columns of one workgroup
@@ -746,7 +753,8 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     a2.S = S2; a2.s0 = S; a2.second = 1;
     HIPCHK(c, launch_attn_tiered(a2, v.D, c->G, c->kt, st, pe2 ? pe2->a : nullptr, pe2 ? pe2->b : nullptr));
   }
-  if (m > 1) HIPCHK(c, launch_attn_finish_chunk(a, v.D, c->G, st));
+  if (whole) HIPCHK(c, launch_step_scores(a, v.D, st, pf ? pf->a : nullptr, pf ? pf->b : nullptr));
+  else if (m > 1) HIPCHK(c, launch_attn_finish_chunk(a, v.D, c->G, st));
   else HIPCHK(c, launch_attn_finish(a, v.D, c->G, st, pf ? pf->a : nullptr, pf ? pf->b : nullptr));
   if (!last || noalloc) return TKV_OK;
   if (c->streamed && S2 > 0) {
@@ -803,26 +811,46 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
   return TKV_OK;
 }
 
-// Scratch for the launches of a decode step that serve several layers at once: logits and split partials per (layer,
-// sequence).  As many layers as fit STEP_SCRATCH_BYTES: by then the launch's fixed cost (a few us of fill and drain, the
-// finishing kernel, two dispatches) is small beside its work, and the logits are still in the last-level cache when the
-// finishing kernel reads them.  Allocated on the first decode step and kept; without the memory for it (or where one
-// layer fills it) the step goes layer by layer as before.
-constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20;
-// A step that is being captured into a graph may not allocate: it goes layer by layer if it is the first one.
+// How a decode step's launches go, and their scratch; decided at the first step, from the shape alone (so that T1 placement,
+// prefetch mode and timing cannot change a bit), allocated then and kept.
+//  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a step has STEP_WHOLE_PAIRS pairs or
+//    more: the logits stay on the chip, one float per row leaves it.  With fewer pairs most compute units would idle.
+//  - else pairs are split as in a single call, several layers per launch, as many as fit STEP_SCRATCH_BYTES.
+// Without the memory the step goes layer by layer as the single calls do.  A step that is being captured into a graph may
+// not allocate: it goes layer by layer if it is the first one.
+constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
+constexpr int STEP_WHOLE_PAIRS = 96;
 static void step_scratch(tkv_cache* c, hipStream_t st) {
   if (c->step_layers) return;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
   const DevView& v = c->dv;
-  const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = (size_t)v.B * v.Hkv * c->S_alloc * 2 * c->G;
-  const size_t po_n = (size_t)v.B * v.Hkv * c->S_alloc * c->G * v.D;
-  const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
-  int nl = (int)std::min<size_t>({STEP_SCRATCH_BYTES / per_layer, (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
   c->step_layers = 1;
-  if (c->streamed || nl < 2) return;
-  // groups of equal size: 48 layers of which 10 fit go as 5 groups of 10, 10, 10, 9, 9
-  nl = (v.L + (v.L + nl - 1) / nl - 1) / ((v.L + nl - 1) / nl);
+  if (c->streamed) return;
+  const auto layers_in = [&](size_t budget, size_t per_layer) {
+    const int nl = (int)std::min<size_t>({budget / per_layer, (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
+    if (nl < 2) return nl;
+    const int groups = (v.L + nl - 1) / nl;      // of equal size: 48 layers of which 10 fit go as 10, 10, 10, 9, 9
+    return (v.L + groups - 1) / groups;
+  };
+  const size_t pairs = (size_t)v.B * v.Hkv;
+  if (c->es == 2 && pairs * v.L >= STEP_WHOLE_PAIRS) {
+    const int cols = (v.Nmax + 2 * TOK_PER_BLOCK - 1) / TOK_PER_BLOCK * TOK_PER_BLOCK;    // list F may end in a partly filled tile
+    const int spill = std::max(0, cols - attn_step_lds_entries(v.D, c->G));
+    const size_t per_layer = pairs * ((size_t)cols + (size_t)c->G * spill) * sizeof(float);
+    const int nl = layers_in(STEP_WHOLE_SCRATCH_BYTES, per_layer);
+    float* p = nl >= 1 && pairs * nl >= STEP_WHOLE_PAIRS ? (float*)dev_alloc(c, nl * per_layer) : nullptr;
+    if (p) {
+      c->sc_step = p; c->spill_step = p + nl * pairs * cols;
+      c->sc_stride = cols; c->spill_stride = spill;
+      c->step_whole = true; c->step_layers = nl;
+      return;
+    }
+  }
+  const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = pairs * c->S_alloc * 2 * c->G, po_n = pairs * c->S_alloc * c->G * v.D;
+  const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
+  const int nl = layers_in(STEP_SCRATCH_BYTES, per_layer);
+  if (nl < 2) return;
   float* p = (float*)dev_alloc(c, nl * per_layer);
   if (!p) return;
   c->xs_step = p; c->ml_step = p + nl * xs_n; c->po_step = c->ml_step + nl * ml_n;
@@ -857,15 +885,15 @@ tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, c
     step_scratch(c, (hipStream_t)hip_stream);
     const int per_launch = std::max(1, c->step_layers);
     for (int l = 0; l < v.L;) {
-      // one launch pair for a group of layers; with WAIT a layer that still has to wait for its prefetch goes alone, so
-      // that the layers before it do not wait with it
+      // one launch pair for a group of layers; with WAIT the layers that still have to wait for their prefetch go in small
+      // groups (as few as fill the chip, or alone), so that the others do not wait with them
       const auto waits = [&](int k) { return c->cfg.prefetch_mode == TKV_PREFETCH_WAIT && c->layer_wait[k]; };
       const int groups = (v.L - l + per_launch - 1) / per_launch;
       int nl = (v.L - l + groups - 1) / groups;
       for (int k = 0; k < nl; ++k)
-        if (waits(l + k)) { nl = std::max(k, 1); break; }
+        if (waits(l + k)) { nl = std::max(k, std::min(nl, c->step_whole ? (255 + v.B * v.Hkv) / (v.B * v.Hkv) : 1)); break; }
       tkv_status s = attend_one(c, l, (const char*)q_all + l * q_stride, (char*)out_all + l * o_stride, 0, v.Hq, v.Hq, true,
-                                (hipStream_t)hip_stream, false, 1, nl);
+                                (hipStream_t)hip_stream, false, 1, nl, true);
       if (s != TKV_OK) return s;
       l += nl;
     }

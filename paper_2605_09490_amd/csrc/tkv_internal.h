@@ -114,6 +114,9 @@ struct AttnArgs {
   int nl;           // consecutive layers served by this launch (tkv_decode_step: 1 .. MAX_LAYERS_PER_LAUNCH; every other call:
                     // 1).  All per-layer arrays above are [layer][B]..., so layer li of sequence b is entry li * B + b of
                     // rows, q, out, xs and the partials; lists, counters and scores belong to sequence b alone
+  float* sc;        // whole-pair step launch (else NULL): [layer][B][Hkv][sc_stride] a row's weights summed over its group's
+  int sc_stride;    // heads, by column (list F, list Q from the next multiple of the tile's rows); xs then holds only the
+                    // logits that do not fit the LDS, [layer][B][Hkv][G][xs_stride] from column LCAP on
   const int* f_loc_old;   // slots of list F for the layers whose bit is set in old_mask (lazy prefetch: the copies are in flight)
   uint64_t old_mask;
   int B, Hq, Hkv, Nmax, capF, cap2, xs_stride, cb, sb, t2fmt, out_kind, q_es;   // out_kind: 0 binary32, 1 bfloat16, 2 binary16
@@ -128,6 +131,10 @@ struct AttnArgs {
 // kt: type of K, V and q (0 binary32, 1 bfloat16, 2 binary16)
 hipError_t launch_attn_tiered(const AttnArgs& a, int D, int G, int kt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_finish(const AttnArgs& a, int D, int G, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
+// whole-pair step launch: rows per tile, entries whose logits fit the LDS, and the launch that ends it
+int attn_step_tile_rows(int D);
+int attn_step_lds_entries(int D, int G);
+hipError_t launch_step_scores(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t st);
 int attn_cols_per_launch(int elem_bytes, int G);   // query tokens one workgroup can take as columns
 hipError_t launch_probe_read(const void* src, size_t bytes, int workgroups, uint32_t* sink, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);

@@ -148,22 +148,32 @@ def test_decode_step_equals_per_layer_calls():
 
 
 @pytest.mark.parametrize("mode,scorer,shape", [
-    ("lazy", "attention", dict(n_layers=7, batch=24, n_q_heads=64, n_kv_heads=8, head_dim=64, context=1990)),   # groups of 4 and 3 layers
+    # split pairs (fewer than 96 pairs in the step)
     ("wait", "combined", dict(n_layers=5, batch=3, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700)),
-    ("lazy", "vatp", dict(n_layers=40, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=333)),        # two passes of the finishing kernel
+    ("lazy", "attention", dict(n_layers=40, batch=1, n_q_heads=5, n_kv_heads=1, head_dim=128, context=333)),    # two passes of the finishing kernel
+    ("lazy", "vatp", dict(n_layers=2, batch=8, n_q_heads=24, n_kv_heads=4, head_dim=64, context=129, kv_dtype="f32")),
+    # one workgroup per pair
+    ("lazy", "attention", dict(n_layers=7, batch=24, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2600)),   # logits beyond the LDS
+    ("wait", "vatp", dict(n_layers=40, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=333, t2_format="int4_g32")),
     ("wait", "attention", dict(n_layers=4, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=200)),
+    ("lazy", "redundancy", dict(n_layers=3, batch=9, n_q_heads=40, n_kv_heads=8, head_dim=128, context=31, kv_dtype="f16")),
+    ("lazy", "attention", dict(n_layers=70, batch=1, n_q_heads=6, n_kv_heads=2, head_dim=64, context=65, t2_format="int4_g32")),   # two groups of layers
 ])
 def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
-    """A decode step's launches serve groups of layers: outputs and scores are the bits of per-layer calls, also right
-    behind a re-tiering whose transfers are in flight (lazy: some layers read their rows' old slots; wait: layers that
-    wait for their prefetch go alone), where a step takes several groups, and above 64 sequences."""
+    """A decode step's launches serve groups of layers, against per-layer calls: also right behind a re-tiering whose
+    transfers are in flight (lazy: some layers read their rows' old slots; wait: layers that wait for their prefetch go in
+    small groups), where a step takes several groups, and above 64 sequences.  Where pairs are split as in single calls
+    the bits are the same.  With one workgroup per pair the same products are added in another order: outputs within 1e-5
+    of the head's largest value and scores within 1e-5 of the magnitudes added, the bounds a single call keeps against
+    the oracle for binary32 rows (each side's rounding is a few 1e-7)."""
     import paper_2605_09490_amd as tkv
     from tkv_synth import Workload
-    cfg = small_config(name="groups", kv_dtype="bf16", decode_steps=4, k_window=16, policy_ppm=(300_000, 400_000, 250_000, 50_000), **shape)
+    cfg = small_config(name="groups", **{**dict(kv_dtype="bf16", decode_steps=4, k_window=16, policy_ppm=(300_000, 400_000, 250_000, 50_000)), **shape})
+    same_bits = cfg.kv_dtype == "f32" or cfg.n_layers * cfg.batch * cfg.n_kv_heads < 96
     print(f"[case] {mode} {scorer} {shape}", flush=True)
     wl = Workload(cfg, device="cuda")
-    kv = [tkv.TieredKV(cfg.n_layers, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype="bf16",
-                       k_window=16, prefetch_mode=mode, scorer=scorer) for _ in range(2)]
+    kv = [tkv.TieredKV(cfg.n_layers, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype=cfg.kv_dtype,
+                       t2_format=cfg.t2_format, k_window=16, prefetch_mode=mode, scorer=scorer) for _ in range(2)]
     for l in range(cfg.n_layers):
         k, v = wl.context_kv(l)
         for c in kv:
@@ -173,11 +183,22 @@ def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
         oa = kv[0].decode_step(k_all[s], v_all[s], q_all[s])
         for l in range(cfg.n_layers):
             kv[1].append(l, k_all[s, l], v_all[s, l])
-            assert torch.equal(oa[l], kv[1].attend_and_score(l, q_all[s, l])), (s, l)
-        assert np.array_equal(kv[0].get_scores().view(np.uint32), kv[1].get_scores().view(np.uint32)), s
+            ob = kv[1].attend_and_score(l, q_all[s, l])
+            if same_bits:
+                assert torch.equal(oa[l], ob), (s, l)
+            else:
+                assert ((oa[l] - ob).abs() <= 1e-5 * ob.abs().amax(-1, keepdim=True)).all(), (s, l)
+        sa, sb = (c.get_scores() for c in kv)
+        if same_bits:
+            assert np.array_equal(sa.view(np.uint32), sb.view(np.uint32)), s
+        else:
+            # a penalised score is a difference of magnitudes of at most about 1 / cache length per step each
+            floor = 1e-5 * (s + 1) / cfg.context if scorer == "redundancy" else 1e-9
+            assert (np.abs(sa - sb) <= 1e-5 * np.abs(sb) + floor).all(), s
         if s in (0, 2):
+            kv[0].classify(cfg.policy_ppm)
+            kv[1].set_tiers(kv[0].get_pending_tiers())     # scores that differ in the last bit may rank differently
             for c in kv:
-                c.classify(cfg.policy_ppm)
                 c.migrate()
     for c in kv:
         c.close()
