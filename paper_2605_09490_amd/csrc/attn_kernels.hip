@@ -203,6 +203,54 @@ __device__ __forceinline__ float wave_sum(float x) {
   return a + b;
 }
 
+// Sums over the row groups of a wave: lane gv * LPRV + rv holds a partial of elements rv * EV + e (e < EV) for every group
+// gv; afterwards the 64 lanes hold each total once, EV * LPRV / 64 per lane, element `elem` of the returned pairs.  Two
+// values go through one swap of the wave's halves (then of its 16-lane rows, then of 8-lane half rows) and one addition:
+// a fraction of what a shuffle per value costs (1.4 us for 56 values per lane, 0.2 us this way).
+template <int EV, int LPRV>
+struct RowSum { static constexpr int N = EV * LPRV / 64; };
+__device__ __forceinline__ float add_swap32(float a, float b) {      // lanes 0..31: a's halves added; 32..63: b's
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ float add_swap16(float a, float b) {      // even rows: a's row pair added; odd rows: b's
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+template <int EV, int LPRV>
+__device__ __forceinline__ void row_sum(const float (&o)[EV], int lane, float (&t)[RowSum<EV, LPRV>::N]) {
+  static_assert(LPRV == 8 || LPRV == 16 || LPRV == 32, "rows of 8, 16 or 32 lanes");
+  float h[EV / 2];
+#pragma unroll
+  for (int k = 0; k < EV / 2; ++k) h[k] = add_swap32(o[2 * k], o[2 * k + 1]);
+  if constexpr (LPRV == 32) {
+#pragma unroll
+    for (int k = 0; k < EV / 2; ++k) t[k] = h[k];
+  } else {
+    float q[EV / 4];
+#pragma unroll
+    for (int k = 0; k < EV / 4; ++k) q[k] = add_swap16(h[2 * k], h[2 * k + 1]);
+    if constexpr (LPRV == 16) {
+#pragma unroll
+      for (int k = 0; k < EV / 4; ++k) t[k] = q[k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < EV / 8; ++k) {
+        const float a = q[2 * k] + dpp_f<0x128>(q[2 * k]), b = q[2 * k + 1] + dpp_f<0x128>(q[2 * k + 1]);   // row_ror:8
+        t[k] = (lane & 8) ? b : a;
+      }
+    }
+  }
+}
+// element (within the row's D) of t[k] of this lane
+template <int EV, int LPRV>
+__device__ __forceinline__ int row_sum_elem(int lane, int k) {
+  const int rv = lane % LPRV, hi = lane >> 5, odd = (lane >> 4) & 1, up = (lane >> 3) & 1;
+  if constexpr (LPRV == 32) return rv * EV + 2 * k + hi;
+  else if constexpr (LPRV == 16) return rv * EV + 4 * k + 2 * odd + hi;
+  else return rv * EV + 8 * k + 4 * up + 2 * odd + hi;
+}
+
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
@@ -463,7 +511,7 @@ __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t& rs, char* lds,
 //   V scales of t+1 | per V step of t: the K pieces of t+1 on its bytes
 // Accumulates into o (offset-corrected for code rows), m_run, l_lane (per-lane partial sums of the softmax
 // denominator, relative to m_run); leaves the scaled logits in xs.
-template <int D, int G, Mode M, int KT, int TR = 64, bool WHOLE = false>
+template <int D, int G, Mode M, int KT, int TR, bool WHOLE>
 __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, int b, int jq, int kvh, int lane,
                                           int tile0, int tstride, int n_list, const int* loc_list, int col0,
                                           float (&o)[G][Geo<D, M>::EV], float (&m_run)[G], float (&l_lane)[G]) {
@@ -508,11 +556,11 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   // probability region of the LDS, as NQD direct loads of 1 KB whose count the waits below can name; binary32
   // queries are fetched by ordinary loads (the wait for the list then waits for them as well).
   QRegs<D, G, M, KT> q;
-  constexpr int NQD = QBF && !WHOLE ? (G * D * 2 + 1023) / 1024 : 0;
-  static_assert(NQD * 1024 <= TR * GP * 4, "the query block is parked in the probability region");
-  if constexpr (WHOLE) {
-    // a workgroup that walks a whole pair: ordinary loads, once; their sums follow behind the wait for the list
-    const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + kvh * G) * D * 2;
+  constexpr bool QLDS = QBF && (G * D * 2 + 1023) / 1024 * 1024 <= TR * GP * 4;
+  constexpr int NQD = QLDS ? (G * D * 2 + 1023) / 1024 : 0;
+  if constexpr (QBF && !QLDS) {
+    // no room for the block in the probability region: ordinary loads, which the wait for the list then waits for as well
+    const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + (size_t)jq * a.Hq + kvh * G) * D * 2;
 #pragma unroll
     for (int h = 0; h < G; ++h)
 #pragma unroll
@@ -521,7 +569,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
 #pragma unroll
         for (int c = 0; c < EUK / 2; ++c) q.qp[h][j][c] = src[c];
       }
-  } else if constexpr (QBF) {
+  } else if constexpr (QLDS) {
     const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + (size_t)jq * a.Hq + kvh * G) * D * 2;
     const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)(G * D * 2));   // lanes past the block fetch zeros
 #pragma unroll
@@ -607,7 +655,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   issue_vscale();
 #pragma unroll
   for (int s = 0; s < N_K; ++s) issue_k_piece(s);
-  if constexpr (QBF && !WHOLE) {
+  if constexpr (QLDS) {
     wait_vm<1 + 2 * SCD + N_K>();                        // everything older than the second list: the query block
     // a unit of a query is EUK 16-bit elements: 8 bytes (one ds_read_b64) or QB pieces of 16
     constexpr int QW = EUK / 2, QB = QW / 4;
@@ -1390,23 +1438,22 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   }
 }
 
-// Waves per SIMD the kernel is compiled for: two while a wave's registers (query slices and output accumulators grow
-// with the group size) fit half a SIMD's file, else one.
-constexpr int waves_per_simd(int G) { return G <= 5 ? 2 : 1; }
-// One workgroup per compute unit: as many waves as the register budget allows (4 SIMDs) and as fit the LDS with a
-// whole-tile buffer each (64 rows: 16 KB at 256-byte rows, 32 KB at 512-byte rows).
-constexpr int waves_per_group(int row_bytes, int G) {
-  return (row_bytes > 256 && waves_per_simd(G) * 4 > 4) ? 4 : waves_per_simd(G) * 4;
-}
-
+// Geometry of the split launch: rows per tile and waves per workgroup (one workgroup per compute unit).  16-bit rows: 8 KB
+// tiles (32 rows of 256 bytes, 64 of 128) and eight waves, two per SIMD; 64 KB in flight per compute unit stream as fast
+// as 128 KB do, and the finer tiles keep more waves busy on short lists and end closer together on long ones.  binary32
+// rows: 32 rows of 256 bytes; 64 rows of 512 bytes with four waves, which large groups take in any case (their waves need
+// more than half a SIMD's registers).
 template <int D, int G, int KT>
 struct KernelGeo {
   static constexpr Mode MF = KT == KT_BF16 ? F_BF16 : KT == KT_F16 ? F_F16 : F_F32;
   static constexpr int RB = Geo<D, MF>::RB;
-  static constexpr int NW = waves_per_group(RB, G);
-  static constexpr int EV = Geo<D, MF>::EV;
-  static constexpr int LPRV = Geo<D, MF>::LPRV;
+  static constexpr int TR = RB == 256 ? 32 : 64, TILE = TR * RB;
+  static constexpr int NW = KT == KT_F32 && (G > 5 || RB > 256) ? 4 : 8;
+  static constexpr int EV = Geo<D, MF, TR>::EV;
+  static constexpr int LPRV = Geo<D, MF, TR>::LPRV;
 };
+constexpr int split_tile_rows(int D, int es) { return D * es == 256 ? 32 : 64; }
+constexpr int split_waves(int D, int es, int G) { return es == 4 && (G > 5 || D * es > 256) ? 4 : 8; }
 
 // Waves of a (sequence, kv head) pair that serve the Q list, out of nwv, for nft F tiles and nqt Q tiles: the split
 // that minimises the longest wave.  A code tile moves fewer bytes than a full-precision one but costs more vector
@@ -1427,46 +1474,49 @@ __host__ __device__ inline int q_waves(int nwv, int nft, int nqt) {
 template <int D, int G, int KT>
 __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT>::NW / 4)) void k_attn_tiered(const AttnArgs a) {
   using KG = KernelGeo<D, G, KT>;
-  constexpr int NW = KG::NW, EV = KG::EV, LPRV = KG::LPRV, GP = GPad<G>::v;
-  constexpr int TILE_BYTES = 64 * KG::RB;
+  constexpr int NW = KG::NW, EV = KG::EV, LPRV = KG::LPRV, GP = GPad<G>::v, TR = KG::TR;
+  constexpr int TILE_BYTES = KG::TILE, SC = (D / 64) * TR * 4;
   static_assert(G * D * 4 <= TILE_BYTES, "a wave's output partial is parked in its tile buffer");
   __shared__ __attribute__((aligned(16))) char sm_t[NW * TILE_BYTES];
-  __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * 512];
-  __shared__ __attribute__((aligned(16))) char sm_lt[NW * 512];
-  __shared__ __attribute__((aligned(16))) float sm_p[NW * 64 * GP];
+  __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * SC];
+  __shared__ __attribute__((aligned(16))) char sm_lt[NW * 2 * TR * 4];
+  __shared__ __attribute__((aligned(16))) float sm_p[NW * TR * GP];
   __shared__ float sm_ml[NW * 16];
-  // A wave's row groups (64 / LPRV of them) each hold a partial sum of every output element.  As many of them as the
-  // tile buffer has room for are parked side by side and added up by the merge below; only if there are more (64-byte
-  // rows) are the upper ones first folded into the lower ones by shuffles.
-  constexpr int NG = 64 / LPRV, FIT = TILE_BYTES / (G * D * 4);
-  constexpr int NGK = NG <= FIT ? NG : (FIT >= 4 ? 4 : FIT >= 2 ? 2 : 1);
   const int s = blockIdx.x, kvh = blockIdx.y;
-  // several query tokens per sequence: query jq of sequence b; it is n_q - 1 - jq positions older than the last one,
-  // and those positions (the tail of list F) are not its to see
-  // a whole decode step: layer li of the launch's a.nl; bl is the (layer, sequence) entry of rows, q, logits and partials
-  const int jq = a.n_q > 1 ? (int)blockIdx.z % a.n_q : 0, bl = a.n_q > 1 ? (int)blockIdx.z / a.n_q : (int)blockIdx.z;
-  const int li = a.nl > 1 ? bl / a.B : 0, b = bl - li * a.B;
+  // The arguments come over the host link (about a microsecond): a call's sequence is blockIdx.z, so its list lengths are
+  // asked for with everything else, not behind n_q, nl and B, and corrected where the launch is of another kind.
+  int b = blockIdx.z, jq = 0, li = 0, nF = a.nF[b & (ATTN_ARG_SEQS - 1)], nQ = a.nQ[b & (ATTN_ARG_SEQS - 1)];
+  int nwq = a.nWq[b & (ATTN_ARG_SEQS - 1)], xsb = 0;
+  const int nwv = a.S * NW;
+  if (a.n_q > 1 || a.nl > 1 || a.B > ATTN_ARG_SEQS || a.second) {
+    // several query tokens per sequence: query jq of sequence b; it is n_q - 1 - jq positions older than the last one,
+    // and those positions (the tail of list F) are not its to see
+    if (a.n_q > 1) { jq = b % a.n_q; b = b / a.n_q; }
+    // a whole decode step: layer li of the launch's a.nl
+    else if (a.nl > 1) { li = b / a.B; b -= li * a.B; }
+    if (a.second) {
+      nF = a.cnt[b * CNT_N + C_NS]; nQ = 0; nwq = 0;
+      xsb = ((a.cnt[b * CNT_N + C_NF] - a.trim + 63) >> 6) + ((a.cnt[b * CNT_N + C_NQ] + 63) >> 6);
+    } else {
+      if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; nwq = a.nWq[b]; }
+      else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
+      nF -= a.n_q - 1 - jq;
+      if (a.B > ATTN_ARG_SEQS || a.n_q > 1) nwq = q_waves(nwv, (nF + TR - 1) / TR, (nQ + TR - 1) / TR);
+    }
+  }
+  const int bl = li * a.B + b;                  // entry of rows, q, logits and partials
   const int* f_loc = ((a.old_mask >> li) & 1) ? a.f_loc_old : a.f_loc;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  int nF, nQ, xsb = 0;
-  if (!a.second) {
-    if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
-    else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
-    nF -= a.n_q - 1 - jq;
-  } else {
-    nF = a.cnt[b * CNT_N + C_NS]; nQ = 0;
-    xsb = ((a.cnt[b * CNT_N + C_NF] - a.trim + 63) >> 6) + ((a.cnt[b * CNT_N + C_NQ] + 63) >> 6);
-  }
-  const int nft = (nF + 63) >> 6, nqt = (nQ + 63) >> 6;
-  const int nwv = a.S * NW;
-  const int nwq = a.second ? 0 : (a.B <= ATTN_ARG_SEQS && a.n_q == 1) ? a.nWq[b] : q_waves(nwv, nft, nqt), nwf = nwv - nwq;
-  const int u = s * NW + wave;
+  const int nft = (nF + TR - 1) / TR, nqt = (nQ + TR - 1) / TR, nwf = nwv - nwq;
+  const int colq = (xsb + ((nF + 63) >> 6)) * TB;   // list Q's logits start at a 64-entry tile
+  // wave-major: where a pair has fewer tiles than waves, every workgroup has some to do, one per SIMD first
+  const int u = wave * a.S + s;
 
   WaveLds w;
   w.t = sm_t + wave * TILE_BYTES;
-  w.sk = sm_sc + wave * 1024; w.sv = w.sk + 512; w.lt = sm_lt + wave * 512;
+  w.sk = sm_sc + wave * 2 * SC; w.sv = w.sk + SC; w.lt = sm_lt + wave * 2 * TR * 4;
   w.ta = lds_addr(w.t); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
-  w.p = (char*)(sm_p + wave * 64 * GP);
+  w.p = (char*)(sm_p + wave * TR * GP);
   w.pa = lds_addr(w.p);
   float* my_o = (float*)w.t;          // after the wave's last tile: its output partial, [G][D]
 
@@ -1479,11 +1529,11 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
   }
   bool o_written = false;
   if (u < nwf) {
-    attn_wave<D, G, KG::MF, KT>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
+    attn_wave<D, G, KG::MF, KT, TR, false>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
   } else {
     if constexpr (EV == 8) {
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
     } else {
       // binary32 rows use 4 elements per lane, code rows 8: separate accumulators, parked directly
       float o8[G][8];
@@ -1491,40 +1541,27 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
       for (int h = 0; h < G; ++h)
 #pragma unroll
         for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o8, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, (xsb + nft) * TB, o8, m_run, l_lane);
-      constexpr int L8 = D / 8;
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
 #pragma unroll
-      for (int st = L8; st < 64; st <<= 1)
+      for (int h = 0; h < G; ++h) {
+        constexpr int L8 = D / 8;
+        float t8[RowSum<8, L8>::N];
+        row_sum<8, L8>(o8[h], lane, t8);
 #pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o8[h][e] += __shfl_xor(o8[h][e], st);
-      if (lane < L8) {
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) my_o[h * D + lane * 8 + e] = o8[h][e];
+        for (int k = 0; k < RowSum<8, L8>::N; ++k) my_o[h * D + row_sum_elem<8, L8>(lane, k)] = t8[k];
       }
-      // the merge adds NGK parked row groups per wave: this wave has one, the others are zero
-      for (int i = lane; i < (NGK - 1) * G * D; i += 64) my_o[G * D + i] = 0.f;
       o_written = true;
     }
   }
   // ---- wave partial: sum the row groups and the per-lane denominators, then merge the waves through LDS
   if (!o_written) {
 #pragma unroll
-    for (int st = LPRV * NGK; st < 64; st <<= 1)
+    for (int h = 0; h < G; ++h) {
+      float t1[RowSum<EV, LPRV>::N];
+      row_sum<EV, LPRV>(o[h], lane, t1);
 #pragma unroll
-      for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int e = 0; e < EV; ++e) o[h][e] += __shfl_xor(o[h][e], st);
-    if (lane < LPRV * NGK) {
-      float* dst = my_o + (lane / LPRV) * (G * D) + (lane % LPRV) * EV;
-#pragma unroll
-      for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int e = 0; e < EV; ++e) dst[h * D + e] = o[h][e];
+      for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t1[k];
     }
   }
 #pragma unroll
@@ -1545,10 +1582,7 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
 #pragma unroll
       for (int ww = 0; ww < NW; ++ww) {
         const float* src = (const float*)(sm_t + ww * TILE_BYTES) + i;
-        float part = src[0];                                // the wave's row groups, in order
-#pragma unroll
-        for (int g = 1; g < NGK; ++g) part += src[g * (G * D)];
-        acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + h] - mb) * LOG2E), part, acc);
+        acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + h] - mb) * LOG2E), src[0], acc);
       }
     }
     po[i] = acc;
@@ -1593,7 +1627,6 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   constexpr Mode MF = KT == KT_BF16 ? F_BF16 : F_F16;
   constexpr int NW = SG::NW, TR = SG::TR, TILE = SG::TILE, LCAP = SG::LCAP;
   constexpr int EV = Geo<D, MF, TR>::EV, LPRV = Geo<D, MF, TR>::LPRV;
-  constexpr int NG = 64 / LPRV, FIT = TILE / (G * D * 4), NGK = NG <= FIT ? NG : (FIT >= 4 ? 4 : FIT >= 2 ? 2 : 1);
   static_assert(G * D * 4 <= TILE, "a wave's output partial is parked in its tile buffer");
   __shared__ __attribute__((aligned(16))) char sm_t[NW * TILE];
   __shared__ __attribute__((aligned(16))) char sm_p[NW * SG::P];
@@ -1630,17 +1663,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   else attn_wave<D, G, Q_INT4, KT, TR, true>(a, w, bl, 0, kvh, lane, wave - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
   // ---- merge the waves
 #pragma unroll
-  for (int st = LPRV * NGK; st < 64; st <<= 1)
+  for (int h = 0; h < G; ++h) {
+    float t1[RowSum<EV, LPRV>::N];
+    row_sum<EV, LPRV>(o[h], lane, t1);
 #pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int e = 0; e < EV; ++e) o[h][e] += __shfl_xor(o[h][e], st);
-  if (lane < LPRV * NGK) {
-    float* dst = my_o + (lane / LPRV) * (G * D) + (lane % LPRV) * EV;
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int e = 0; e < EV; ++e) dst[h * D + e] = o[h][e];
+    for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t1[k];
   }
 #pragma unroll
   for (int h = 0; h < G; ++h) {
@@ -1667,10 +1694,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) {
       const float* src = (const float*)(sm_t + ww * TILE) + i;
-      float part = src[0];                                  // the wave's row groups, in order
-#pragma unroll
-      for (int g = 1; g < NGK; ++g) part += src[g * (G * D)];
-      acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + h] - fin.x) * LOG2E), part, acc);
+      acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + h] - fin.x) * LOG2E), src[0], acc);
     }
     acc *= fin.y;
     const size_t oi = ((size_t)bl * a.o_bs + kvh * G) * D + i;
@@ -1808,27 +1832,35 @@ __global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_
 }
 
 // ---- finish: global softmax statistics, scores, output ------------------------------------------------------
-// Global (m, 1/l) of one query head out of the ns split partials at src (stride 2 * G floats).  A sequence with no live
-// position at all (every position evicted by a forced plan) has m = -inf, l = 0 in every split: its output is defined as
-// zero, not 0/0.
+// Global (m, 1/l) of one query head out of the ns split partials at src (stride 2 * G floats), up to N of them with all
+// loads in flight together.  A sequence with no live position at all (every position evicted by a forced plan) has
+// m = -inf, l = 0 in every split: its output is defined as zero, not 0/0.
+template <int G, int N>
+__device__ __forceinline__ void merge_stats_n(const float* __restrict__ src, int ns, float& mm, float& ll) {
+  float mv[N], lv[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    mv[k] = k < ns ? src[k * 2 * G] : -INFINITY;
+    lv[k] = k < ns ? src[k * 2 * G + G] : 0.f;
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k) mm = fmaxf(mm, mv[k]);
+  if (mm > -INFINITY) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) ll = fmaf(lv[k], __builtin_amdgcn_exp2f((mv[k] - mm) * LOG2E), ll);
+  }
+}
 template <int G>
 __device__ __forceinline__ void merge_stats(const float* __restrict__ src, int ns, float& m, float& il) {
   float mm = -INFINITY, ll = 0.f;
   if (ns == 1) {
     mm = src[0]; ll = src[G];
-  } else if (ns <= 8) {               // all loads in flight together
-    float mv[8], lv[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      mv[k] = k < ns ? src[k * 2 * G] : -INFINITY;
-      lv[k] = k < ns ? src[k * 2 * G + G] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) mm = fmaxf(mm, mv[k]);
-    if (mm > -INFINITY) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) ll = fmaf(lv[k], __builtin_amdgcn_exp2f((mv[k] - mm) * LOG2E), ll);
-    }
+  } else if (ns <= 4) {
+    merge_stats_n<G, 4>(src, ns, mm, ll);
+  } else if (ns <= 8) {
+    merge_stats_n<G, 8>(src, ns, mm, ll);
+  } else if (ns <= 16) {
+    merge_stats_n<G, 16>(src, ns, mm, ll);
   } else {
 #pragma unroll 8
     for (int k = 0; k < ns; ++k) mm = fmaxf(mm, src[k * 2 * G]);
@@ -1866,9 +1898,8 @@ __global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs
   const int t = threadIdx.x, b = blockIdx.y, ns = a.S_total;
   const size_t kv_ml = (size_t)ns * 2 * G;                  // statistics of one (layer, sequence, kv head)
   if ((int)blockIdx.x < n_tiles) {
-    int nF, nQ, nS;
-    if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
-    else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
+    int nF = a.nF[b & (ATTN_ARG_SEQS - 1)], nQ = a.nQ[b & (ATTN_ARG_SEQS - 1)], nS;     // asked for beside B, not behind it
+    if (a.B > ATTN_ARG_SEQS) { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
     nS = a.s_pos ? a.cnt[b * CNT_N + C_NS] : 0;
     // logits columns: F tiles, Q tiles, then (streamed T1) the T1 list's tiles
     const int cf = (nF + TB - 1) / TB, cq = (nQ + TB - 1) / TB;
@@ -2250,8 +2281,9 @@ hipError_t launch_attn_tiered(const AttnArgs& a, int D, int G, int kt, hipStream
   return hipErrorInvalidValue;
 }
 int attn_waves_per_group(int D, int elem_bytes, int G, int cq) {
-  return (elem_bytes == 2 && cq > 1) ? mc_waves(cq * G <= 16 ? 1 : 2) : waves_per_group(D * elem_bytes, G);
+  return (elem_bytes == 2 && cq > 1) ? mc_waves(cq * G <= 16 ? 1 : 2) : split_waves(D, elem_bytes, G);
 }
+int attn_tile_rows(int D, int elem_bytes, int cq) { return elem_bytes == 2 && cq > 1 ? TB : split_tile_rows(D, elem_bytes); }
 int attn_cols_per_launch(int elem_bytes, int G) { return elem_bytes == 2 ? (32 / G < 16 ? 32 / G : 16) : 1; }
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles) { return q_waves(n_waves, n_f_tiles, n_q_tiles); }
 

@@ -687,10 +687,18 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     n_tiles_s = std::max(n_tiles_s, tiles(c->nS[b]));
   }
   if (n_tiles * TOK_PER_BLOCK > c->xs_stride) return fail(c, TKV_ESTATE, "tkv_attend_and_score: internal tile count %d exceeds the scratch", n_tiles);
-  // no more workgroups per pair than there are tiles for their waves
   const int nw = attn_waves_per_group(v.D, c->es, c->G, m);
-  const int S = std::max(1, std::min(c->S_alloc, (n_tiles - n_tiles_s + nw - 1) / nw));
-  const int S2 = n_tiles_s > 0 ? std::max(1, std::min(c->S_alloc, (n_tiles_s + nw - 1) / nw)) : 0;
+  const int tr = attn_tile_rows(v.D, c->es, m);
+  const auto wave_tiles = [&](int n) { return (n + tr - 1) / tr; };
+  int n_wt = 1, n_wt_s = 0;
+  for (int b = 0; b < v.B; ++b) {
+    n_wt = std::max(n_wt, wave_tiles(c->nF[b] - trim) + wave_tiles(c->nQ[b]));
+    n_wt_s = std::max(n_wt_s, wave_tiles(c->nS[b]));
+  }
+  // four tiles per workgroup, one per SIMD, until the pairs have all compute units; two waves of a SIMD that have one tile
+  // each take nearly twice as long as one
+  const int S = std::max(1, std::min(c->S_alloc, (n_wt + 3) / 4));
+  const int S2 = n_tiles_s > 0 ? std::max(1, std::min(c->S_alloc, (n_wt_s + 3) / 4)) : 0;
   AttnArgs a{};
   const size_t lrows = (size_t)layer * v.B * v.Hkv;
   a.fpK = v.fpK + lrows * v.capP * v.D * v.es; a.fpV = v.fpV + lrows * v.capP * v.D * v.es;
@@ -721,9 +729,7 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (v.B <= ATTN_ARG_SEQS)
     for (int b = 0; b < v.B; ++b) {
       a.nF[b] = c->nF[b] - trim; a.nQ[b] = c->nQ[b];
-      const int tr = attn_step_tile_rows(v.D);
-      a.nWq[b] = step && c->step_whole ? attn_q_waves(8, (c->nF[b] + tr - 1) / tr, (c->nQ[b] + tr - 1) / tr)
-                                       : attn_q_waves(S * nw, tiles(c->nF[b] - trim), tiles(c->nQ[b]));
+      a.nWq[b] = attn_q_waves(step && c->step_whole ? 8 : S * nw, wave_tiles(c->nF[b] - trim), wave_tiles(c->nQ[b]));
     }
   a.B = v.B; a.Hq = v.Hq; a.Hkv = v.Hkv; a.Nmax = v.Nmax; a.capF = v.capP; a.cap2 = v.cap2;
   a.S = S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;

@@ -24,7 +24,7 @@ enum Cnt : int {
   CNT_N = 29
 };
 
-constexpr int TOK_PER_BLOCK = 64;    // list entries per attention tile (one per lane of a wave)
+constexpr int TOK_PER_BLOCK = 64;    // list entries per tile of logits (one per lane of a wave)
 constexpr int PLAN_THREADS = 1024;
 constexpr int MAX_G = 8;
 constexpr int MAX_LAYERS_PER_LAUNCH = 64;   // one bit of AttnArgs::old_mask per layer
@@ -139,6 +139,7 @@ hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t
 int attn_cols_per_launch(int elem_bytes, int G);   // query tokens one workgroup can take as columns
 hipError_t launch_probe_read(const void* src, size_t bytes, int workgroups, uint32_t* sink, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 int attn_waves_per_group(int D, int elem_bytes, int G, int cq = 1);   // waves per attention workgroup (one workgroup per compute unit)
+int attn_tile_rows(int D, int elem_bytes, int cq = 1);   // list entries per wave tile of that launch
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles);   // how many of a pair's waves serve the Q list
 hipError_t launch_append(const DevView& v, int layer, const void* k, const void* v_, int pos0, int n_new,
                          bool assign, hipStream_t st);
