@@ -76,6 +76,7 @@ struct tkv_cache {
   int step_layers = 0;             // layers one launch of a decode step serves (0: not decided yet)
   float* sc_step = nullptr; float* spill_step = nullptr;   // whole-pair step launches (step_whole)
   bool step_whole = false;
+  bool call_whole = false;         // single calls too take one workgroup per pair (sc, then the spill, in xs)
   int sc_stride = 0, spill_stride = 0;
   int S_alloc = 0, xs_stride = 0;
   char* static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (tkv_attend_and_score_noalloc)
@@ -492,9 +493,9 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   if (cfg->scorer == TKV_SCORE_REDUNDANCY || cfg->scorer == TKV_SCORE_COMBINED)
     ok = ok && dalloc(c, v.red, (size_t)L * B * Hkv * N) && dalloc(c, v.last_k, (size_t)L * B * Hkv * D * v.es);
   v.host_base = c->d_host_base;
+  int cus = 0;
   {
     // one attention workgroup per compute unit: that many per (sequence, kv head) pair, as far as the pairs go round
-    int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device) != hipSuccess || cus <= 0) cus = 256;
     c->S_alloc = std::max(1, cus / std::max(1, B * Hkv));
   }
@@ -502,6 +503,16 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   // of one tile from falling on the same memory channels
   c->xs_stride = ((N / TOK_PER_BLOCK + (cfg->prefetch_mode == TKV_PREFETCH_STREAM ? 3 : 2)) | 1) * TOK_PER_BLOCK;
   ok = ok && dalloc(c, c->xs, (size_t)B * v.Hq * c->xs_stride);
+  {
+    // whole-pair launches: columns of a pair's row weights (list F may end in a partly filled tile), and of the logits that
+    // do not fit the LDS.  Single calls take them where there is a pair for every compute unit: then no pair is split in any
+    // case, and the scratch fits that of the split launch (64 sequences of 16384 tokens, int4 T2, 28/4 heads: 405 us a call against 421).
+    const int cols = (N + 2 * TOK_PER_BLOCK - 1) / TOK_PER_BLOCK * TOK_PER_BLOCK;
+    c->sc_stride = cols;
+    c->spill_stride = std::max(0, cols - attn_step_lds_entries(D, G));
+    c->call_whole = c->es == 2 && !c->streamed && c->S_alloc == 1 && (int64_t)B * Hkv >= cus &&
+                    (size_t)cols + (size_t)G * c->spill_stride <= (size_t)G * c->xs_stride;
+  }
   const int launches = c->streamed ? 2 : 1;   // streamed T1: a second attention launch serves the frame
   ok = ok && dalloc(c, c->part_ml, (size_t)B * Hkv * c->S_alloc * launches * 2 * G);
   ok = ok && dalloc(c, c->part_o, (size_t)B * Hkv * c->S_alloc * launches * G * D);
@@ -700,6 +711,7 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   const int S = std::max(1, std::min(c->S_alloc, (n_wt + 3) / 4));
   const int S2 = n_tiles_s > 0 ? std::max(1, std::min(c->S_alloc, (n_wt_s + 3) / 4)) : 0;
   AttnArgs a{};
+  const bool step_launch = step && c->step_whole, whole = step_launch || (m == 1 && c->call_whole);
   const size_t lrows = (size_t)layer * v.B * v.Hkv;
   a.fpK = v.fpK + lrows * v.capP * v.D * v.es; a.fpV = v.fpV + lrows * v.capP * v.D * v.es;
   a.c2K = v.c2K + lrows * v.cap2 * v.cb; a.c2V = v.c2V + lrows * v.cap2 * v.cb;
@@ -711,8 +723,9 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   a.red_w = c->cfg.redundancy_weight > 0.f ? c->cfg.redundancy_weight : 1.0f;
   a.cnt = v.cnt; a.score = v.score; a.xs = c->xs; a.part_ml = c->part_ml; a.part_o = c->part_o;
   if (nl > 1) { a.xs = c->xs_step; a.part_ml = c->ml_step; a.part_o = c->po_step; }
-  const bool whole = step && c->step_whole;
-  if (whole) { a.xs = c->spill_step; a.xs_stride = c->spill_stride; a.sc = c->sc_step; a.sc_stride = c->sc_stride; }
+  if (whole) { a.sc_stride = c->sc_stride; a.xs_stride = c->spill_stride; }
+  if (whole && step_launch) { a.xs = c->spill_step; a.sc = c->sc_step; }
+  else if (whole) { a.sc = c->xs; a.xs = c->xs + (size_t)v.B * v.Hkv * c->sc_stride; }
   if (m > 1) { a.xs = c->xs_chunk; a.part_ml = c->ml_chunk; a.part_o = c->po_chunk; }
   if (noalloc) {
     // the same three arrays, carved out of the fixed scratch array (256-byte aligned each)
@@ -724,12 +737,13 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
       return fail(c, TKV_ECAPACITY, "tkv_attend_and_score_noalloc: this cache needs %zu bytes of scratch per call, the fixed array holds %zu",
                   xs_b + ml_b + po_b, NOALLOC_SCRATCH_BYTES);
     a.xs = (float*)c->static_scratch; a.part_ml = (float*)(c->static_scratch + xs_b); a.part_o = (float*)(c->static_scratch + xs_b + ml_b);
+    if (whole) { a.sc = a.xs; a.xs += (size_t)v.B * v.Hkv * c->sc_stride; }
   }
   a.q_es = c->es;
   if (v.B <= ATTN_ARG_SEQS)
     for (int b = 0; b < v.B; ++b) {
       a.nF[b] = c->nF[b] - trim; a.nQ[b] = c->nQ[b];
-      a.nWq[b] = attn_q_waves(step && c->step_whole ? 8 : S * nw, wave_tiles(c->nF[b] - trim), wave_tiles(c->nQ[b]));
+      a.nWq[b] = attn_q_waves(whole ? 8 : S * nw, wave_tiles(c->nF[b] - trim), wave_tiles(c->nQ[b]));
     }
   a.B = v.B; a.Hq = v.Hq; a.Hkv = v.Hkv; a.Nmax = v.Nmax; a.capF = v.capP; a.cap2 = v.cap2;
   a.S = S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;
@@ -841,18 +855,16 @@ static void step_scratch(tkv_cache* c, hipStream_t st) {
   };
   const size_t pairs = (size_t)v.B * v.Hkv;
   if (c->es == 2 && pairs * v.L >= STEP_WHOLE_PAIRS) {
-    const int cols = (v.Nmax + 2 * TOK_PER_BLOCK - 1) / TOK_PER_BLOCK * TOK_PER_BLOCK;    // list F may end in a partly filled tile
-    const int spill = std::max(0, cols - attn_step_lds_entries(v.D, c->G));
-    const size_t per_layer = pairs * ((size_t)cols + (size_t)c->G * spill) * sizeof(float);
+    const size_t per_layer = pairs * ((size_t)c->sc_stride + (size_t)c->G * c->spill_stride) * sizeof(float);
     const int nl = layers_in(STEP_WHOLE_SCRATCH_BYTES, per_layer);
     float* p = nl >= 1 && pairs * nl >= STEP_WHOLE_PAIRS ? (float*)dev_alloc(c, nl * per_layer) : nullptr;
     if (p) {
-      c->sc_step = p; c->spill_step = p + nl * pairs * cols;
-      c->sc_stride = cols; c->spill_stride = spill;
+      c->sc_step = p; c->spill_step = p + nl * pairs * c->sc_stride;
       c->step_whole = true; c->step_layers = nl;
       return;
     }
   }
+  if (c->call_whole) return;
   const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = pairs * c->S_alloc * 2 * c->G, po_n = pairs * c->S_alloc * c->G * v.D;
   const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
   const int nl = layers_in(STEP_SCRATCH_BYTES, per_layer);

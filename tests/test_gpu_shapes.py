@@ -204,6 +204,73 @@ def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
         c.close()
 
 
+@pytest.mark.parametrize("shape", [
+    dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=97),
+    dict(batch=130, n_q_heads=4, n_kv_heads=2, head_dim=64, context=129, t2_format="int4_g32", kv_dtype="f16"),   # list lengths from device counters
+    dict(batch=32, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2600, sequences=2),                            # logits beyond the LDS
+])
+def test_single_calls_with_a_pair_for_every_compute_unit(shape):
+    """256 or more pairs: single calls take one workgroup per pair as a whole step does.  Outputs and scores against the
+    oracle, and the same bits from tkv_decode_step and from the call that allocates nothing (where its array is large
+    enough), before and after a re-tiering."""
+    from gpu_common import Pair, assert_out_close, assert_scores_close, to_f64
+    import paper_2605_09490_amd as tkv
+    shape = dict(shape)
+    check = shape.pop("sequences", None)      # sequences compared with the oracle (they are independent); None: all
+    cfg = small_config(name="pairs", n_layers=1, decode_steps=3, k_window=16, policy_ppm=(300_000, 400_000, 250_000, 50_000),
+                       **{**dict(kv_dtype="bf16"), **shape})
+    print(f"[case] {shape}", flush=True)
+    p = Pair(cfg, prefetch_mode="lazy") if check is None else None
+    if p is None:
+        p = Pair(dataclasses.replace(cfg, batch=check), prefetch_mode="lazy", preload=False)
+        p.gpu.close()
+        from tkv_synth import Workload
+        p.wl = Workload(cfg, device="cuda")
+    def cache():
+        return tkv.TieredKV(1, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype=cfg.kv_dtype,
+                            t2_format=cfg.t2_format, k_sink=cfg.k_sink, k_window=cfg.k_window, score_scale=p.score_scale,
+                            prefetch_mode="lazy")
+    nb = check or cfg.batch
+    ctx = p.wl.context_kv(0)
+    gpus = [cache() for _ in range(3)]
+    for g in gpus:
+        g.append(0, *ctx)
+    if check is not None:
+        p.orc.append(0, to_f64(ctx[0][:nb]), to_f64(ctx[1][:nb]))
+    for step in range(3):
+        k, v = p.wl.step_kv(step, 0)
+        q = p.wl.step_q(step, 0)
+        p.orc.append(0, to_f64(k[:nb]), to_f64(v[:nb]))
+        ref = p.orc.attend_and_score(0, to_f64(q[:nb]))
+        gpus[0].append(0, k, v)
+        out = gpus[0].attend_and_score(0, q)
+        assert_out_close(to_f64(out[:nb]), ref, cfg.kv_dtype, f"step {step}")
+        assert torch.equal(out, gpus[1].decode_step(k[None], v[None], q[None])[0])
+        gpus[2].append(0, k, v)
+        try:
+            assert torch.equal(out, gpus[2].attend_and_score_noalloc(0, q, torch.full_like(out, float("nan"))))
+        except tkv.TkvError as e:
+            assert e.status == tkv.TKV_ECAPACITY and cfg.batch * cfg.n_q_heads * cfg.max_tokens * 4 > 8 << 20
+            gpus[2].attend_and_score(0, q)
+        scores = [g.get_scores() for g in gpus]
+        assert np.array_equal(scores[0].view(np.uint32), scores[1].view(np.uint32))
+        assert np.array_equal(scores[0].view(np.uint32), scores[2].view(np.uint32))
+        if step == 0:
+            n = gpus[0].layer_length(0)
+            gpus[0].classify(cfg.policy_ppm)
+            plan = gpus[0].get_pending_tiers()[:, :n]
+            for g in gpus[1:]:
+                g.set_tiers(plan)
+            for g in gpus:
+                g.migrate()
+            p.orc.set_tiers(plan[:nb])
+            p.orc.migrate()
+    assert_scores_close(gpus[0].get_scores()[:nb], p.orc.score, gpus[0].layer_length(0), 3 * cfg.n_q_heads * p.score_scale)
+    for g in gpus:
+        g.close()
+    p.close()
+
+
 def test_many_tiles_per_wave():
     """256 (sequence, kv head) pairs leave two workgroups per pair: every wave walks 8+ tiles of list F and the Q waves
     several of list Q, so the steady-state part of the fetch pipeline (not only its first and last tile) is compared
