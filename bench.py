@@ -319,7 +319,7 @@ def link_probe(launch_bytes):
     # a bare read-only kernel with the attention kernel's launch shape: over 1 GiB, and over one launch's bytes
     big = torch.empty(1 << 30, dtype=torch.uint8, device="cuda").zero_()
     out["read_1GiB_GBps"] = round(tkv.probe_hbm_read(big, iters=4), 1)
-    nb = max(1 << 20, int(launch_bytes) // 4096 * 4096)
+    nb = min(big.numel(), max(1 << 20, int(launch_bytes) // 4096 * 4096))
     out["read_one_launch_GBps"] = round(tkv.probe_hbm_read(big[:nb], iters=16), 1)
     out["read_one_launch_bytes"] = nb
     return out
@@ -562,12 +562,12 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(kernel_GBps, 1) if kernel_GBps else None, "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": round(kernel_GBps / HBM_PEAK_GBPS, 4) if kernel_GBps else None,
                      "traffic": measured_traffic(cfg.name),
-                     "kernel": "k_attn_tiered_mc" if cfg.kv_dtype != "f32" else "k_attn_tiered", "avg_us": round(main_res.get("kernel_avg_us", 0), 2),
+                     "kernel": "k_attn_step" if cfg.kv_dtype != "f32" else "k_attn_tiered", "avg_us": round(main_res.get("kernel_avg_us", 0), 2),
                      "algorithmic_bytes_per_launch": int(main_res.get("kernel_bytes_per_launch", 0)),
                      "launches_timed": main_res.get("kernel_launches"),
                      "achievable": achievable,
                      "frac_of_achievable": round(kernel_GBps / achievable, 4) if kernel_GBps and achievable else None,
-                     "call": {"what": "one tkv_attend_and_score (attention launch + k_attn_finish) as the timed region ran it: every "
+                     "call": {"what": "one layer's share of a decode step (attention launch + score launch) as the timed region ran it: every "
                                       "decode step bracketed by one pair of HIP events on the compute stream, divided by its layer calls",
                               "avg_us": round(main_res.get("call_avg_us", 0), 2),
                               "finish_kernel_avg_us": round(main_res.get("finish_avg_us", 0), 2),
