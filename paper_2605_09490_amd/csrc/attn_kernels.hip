@@ -1,8 +1,8 @@
 // Decode attention over the tiered KV cache, with cumulative-score emission (Eq. 1, Eq. 2-3 of the paper).
 //
 //   attn_tiered : grid (S, Hkv, B), one workgroup per compute unit.  The per-sequence lists F (T0 u T1 rows at full
-//                 precision, ascending position) and Q (T2 rows, int8 / int4 codes) are cut into tiles of 64 entries;
-//                 T3 positions are in neither list.  The S * NW waves of a (sequence, kv head) pair are divided
+//                 precision, ascending position) and Q (T2 rows, int8 / int4 codes) are cut into tiles of 32 or 64
+//                 entries; T3 positions are in neither list.  The S * NW waves of a (sequence, kv head) pair are divided
 //                 between the two lists so that the longest wave is shortest, and every wave walks its tiles with a stride,
 //                 on its own, with no workgroup barrier until the end.
 //                 Rows never pass through registers on their way in: every lane fetches 16-byte (4-byte for short
@@ -17,6 +17,9 @@
 //                   V rows  - D/EV lanes per row, probabilities broadcast from LDS, per-lane fp32 output slices.
 //                 The waves of a workgroup are merged through LDS into one split partial (m, l, o[G][D]); the scaled
 //                 logits go to a scratch array.
+//   attn_step   : a whole decode step's layers (or a single call over many pairs), one workgroup per (layer, sequence, kv
+//                 head) pair: the same waves, but the logits stay in the LDS, the workgroup writes its output itself and
+//                 one float per row (the weights summed over the group) for step_scores / call_scores.
 //   attn_finish : grid (64-entry tiles + Hq, B).  Every workgroup first merges the (m, l) of all splits of its sequence
 //                 into the global (m, 1/l) of every query head.  Tile workgroups then turn the stored logits
 //                 into softmax weights, summed over all query heads in a fixed order, into score[b, pos]; the
