@@ -17,6 +17,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+def diagnostics(stderr: str) -> str:
+    """The compiler's output without the host pass's remark that it does not know the target feature above."""
+    return "\n".join(ln for ln in stderr.splitlines() if "packed-fp32-ops" not in ln).strip()
+
+
 def _hipcc() -> str:
     for p in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
         if p and (os.path.isabs(p) and os.path.exists(p) or not os.path.isabs(p)):
@@ -34,10 +39,12 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(objdir, name)
         cmd = [hipcc, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
-        err = "\n".join(ln for ln in r.stderr.splitlines() if "packed-fp32-ops" not in ln)
+        err = diagnostics(r.stderr)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for {src}:\n{err}")
-        if verbose and err.strip():
+        if verbose:
+            print(" ".join(cmd), file=sys.stderr)
+        if err:
             print(err, file=sys.stderr)
         return obj
 

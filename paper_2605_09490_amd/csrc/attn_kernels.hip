@@ -738,7 +738,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
       });
       lds_wait();
 #pragma unroll
-      for (int j = 0; j < SCD; ++j) { tie(t[j][0]); tie(t[j][1]); }
+      for (int j = 0; j < SCD; ++j) tie(t[j]);
       if constexpr (MORE) issue_kscale();
 #pragma unroll
       for (int i = 0; i < NB; ++i)
