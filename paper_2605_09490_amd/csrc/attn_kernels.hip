@@ -306,7 +306,6 @@ struct Geo {
   static constexpr int VU = VLB / VS;
   static constexpr int EUV = EV / VU;                       // elements per V unit
   static constexpr int SCD = (M == Q_INT8) ? 1 : (M == Q_INT4) ? D / 64 : 0;   // dwords of scales per row
-  static constexpr float OFF = (M == Q_INT4) ? 8.f : 128.f; // codes are read as code + OFF
   // direct-to-LDS operations of one tile period: slot list, K scales, N_K K pieces, V scales, N_V V pieces
   static constexpr int N_K = NB * KU, N_V = NITV * VU;
   static_assert(KLB % KS == 0 && VLB % VS == 0 && NITV % 4 == 0 && NB % 4 == 0 && (!IS_Q || D % 64 == 0), "unsupported head_dim");
@@ -326,35 +325,36 @@ __device__ __forceinline__ uint32_t unit_word(const typename UnitT<S>::type& u, 
   if constexpr (S == 16) return u[c]; else return u;
 }
 
-// codes of one unit as unsigned values code + OFF; the offset is removed once per row (sum q*(u-OFF) = sum q*u - OFF*sum q)
+// Codes of one unit, sign-extended.  (Read as unsigned code + offset, with the offset taken out of a wave's finished sums,
+// they cost a wave that walks many rows its last bits: the offsets' share of a sum grows with the rows, the sum itself with
+// their square root.  One workgroup per pair, 6000 tokens of which 15 % int4: outputs 9.7e-7 off 64 bits, 3.5e-7 so.)
 template <Mode M, int S, int E>
 __device__ __forceinline__ void unpack_unit(const typename UnitT<S>::type& u, float (&f)[E]) {
   if constexpr (M == Q_INT8) {
 #pragma unroll
     for (int i = 0; i < S / 4; ++i) {
-      const uint32_t w = unit_word<S>(u, i) ^ 0x80808080u;
+      const uint32_t w = unit_word<S>(u, i);
 #pragma unroll
-      for (int n = 0; n < 4; ++n) f[i * 4 + n] = (float)((w >> (8 * n)) & 0xFFu);
+      for (int n = 0; n < 4; ++n) f[i * 4 + n] = (float)(int8_t)(w >> (8 * n));
     }
   } else {
 #pragma unroll
     for (int i = 0; i < S / 4; ++i) {
-      const uint32_t w = unit_word<S>(u, i) ^ 0x88888888u;
+      const uint32_t w = unit_word<S>(u, i);
 #pragma unroll
-      for (int n = 0; n < 8; ++n) f[i * 8 + n] = (float)((w >> (4 * n)) & 0xFu);
+      for (int n = 0; n < 8; ++n) f[i * 8 + n] = (float)((int32_t)(w << (28 - 4 * n)) >> 28);
     }
   }
 }
 
 // The lane's units of the G query vectors.  bf16 queries stay packed (fed to the bf16 dot instruction); binary32
-// queries are kept as floats.  qs is the sum over a unit (Q modes only).
+// queries are kept as floats.
 template <int D, int G, Mode M, int KT>
 struct QRegs {
   using GE = Geo<D, M>;
   static constexpr bool QBF = KT != KT_F32;   // 16-bit queries stay packed in pairs
   uint32_t qp[QBF ? G : 1][GE::KU][GE::EUK / 2];
   float qf[QBF ? 1 : G][GE::KU][GE::EUK];
-  float qs[G][GE::KU];
 };
 
 template <int D, Mode M>
@@ -425,7 +425,7 @@ __device__ __forceinline__ void row_logits(const KBatch<D, M>& kr, const QRegs<D
       }
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        float acc = -GE::OFF * q.qs[h][j];
+        float acc = 0.f;
         if constexpr (QBF) {
 #pragma unroll
           for (int c = 0; c < EUK / 2; ++c) {
@@ -449,9 +449,9 @@ __device__ __forceinline__ void row_logits(const KBatch<D, M>& kr, const QRegs<D
   }
 }
 
-// o[h][e] += p[h] * v[e] for the lane's EV elements of one V row (Q modes: p scaled, offset handled through osub)
+// o[h][e] += p[h] * v[e] for the lane's EV elements of one V row (Q modes: p scaled)
 template <int D, int G, Mode M>
-__device__ __forceinline__ void row_accumulate(const VStep<D, G, M>& vr, float sc, float (&o)[G][Geo<D, M>::EV], float (&osub)[G]) {
+__device__ __forceinline__ void row_accumulate(const VStep<D, G, M>& vr, float sc, float (&o)[G][Geo<D, M>::EV]) {
   using GE = Geo<D, M>;
   constexpr int EV = GE::EV, VU = GE::VU, VS = GE::VS, EUV = GE::EUV;
   float p[GPad<G>::v];
@@ -479,7 +479,7 @@ __device__ __forceinline__ void row_accumulate(const VStep<D, G, M>& vr, float s
 #pragma unroll
   for (int h = 0; h < G; ++h) {
     float ph = p[h];
-    if constexpr (GE::IS_Q) { ph *= sc; osub[h] += ph; }
+    if constexpr (GE::IS_Q) ph *= sc;
 #pragma unroll
     for (int e = 0; e < EV; ++e) o[h][e] = fmaf(ph, vf[e], o[h][e]);
   }
@@ -512,8 +512,8 @@ __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t& rs, char* lds,
 // Issue order of one tile period (the vmcnt arguments below are counts of younger operations in this order):
 //   slot list of tile t+2 | K scales of t+1 | per K batch of t: the V pieces of t on its bytes |
 //   V scales of t+1 | per V step of t: the K pieces of t+1 on its bytes
-// Accumulates into o (offset-corrected for code rows), m_run, l_lane (per-lane partial sums of the softmax
-// denominator, relative to m_run); leaves the scaled logits in xs.
+// Accumulates into o, m_run, l_lane (per-lane partial sums of the softmax denominator, relative to m_run); leaves the
+// scaled logits in xs.
 template <int D, int G, Mode M, int KT, int TR, bool WHOLE>
 __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, int b, int jq, int kvh, int lane,
                                           int tile0, int tstride, int n_list, const int* loc_list, int col0,
@@ -523,7 +523,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   constexpr int EV = GE::EV, LPRV = GE::LPRV, NITV = GE::NITV, KU = GE::KU, KS = GE::KS, VU = GE::VU, VS = GE::VS;
   constexpr int EUK = GE::EUK, SCD = GE::SCD, RB = GE::RB, N_K = GE::N_K, N_V = GE::N_V;
   constexpr int GP = GPad<G>::v;
-  constexpr bool QBF = KT != KT_F32, H = KT == KT_F16;
+  constexpr bool QBF = KT != KT_F32;
   constexpr int KIB = 64 * KS, VIB = 64 * VS;        // bytes of the tile buffer one K / V piece covers
   constexpr int KBB = KU * KIB, VSB = VU * VIB;      // ... one K batch / one V step
   static_assert(KBB % VIB == 0 && NB * KBB == NITV * VSB, "K batches and V steps tile the same buffer");
@@ -584,19 +584,10 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
 #pragma unroll
       for (int j = 0; j < KU; ++j) {
         const char* src = qb + ((size_t)h * D + (size_t)(j * 8 + r8) * EUK) * 4;
-        float sacc = 0.f;
 #pragma unroll
-        for (int c = 0; c < EUK; ++c) {
-          q.qf[h][j][c] = ((const float*)src)[c];
-          if constexpr (GE::IS_Q) sacc += q.qf[h][j][c];
-        }
-        q.qs[h][j] = sacc;
+        for (int c = 0; c < EUK; ++c) q.qf[h][j][c] = ((const float*)src)[c];
       }
   }
-
-  float osub[G];
-#pragma unroll
-  for (int h = 0; h < G; ++h) osub[h] = 0.f;
 
   // per-lane byte offsets of its units within a row, and its LDS read addresses
   const uint32_t kcol = (uint32_t)r8 * KS, vcol = (uint32_t)rv * (VU * VS);
@@ -696,20 +687,6 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
             for (int e = 0; e < 4; ++e) q.qp[h][j][c * 4 + e] = elem(t[h][j][c], e);
           }
     }
-  }
-  if constexpr (QBF) {
-    constexpr int QW = EUK / 2;
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int j = 0; j < KU; ++j) {
-        float sacc = 0.f;
-        if constexpr (GE::IS_Q) {
-#pragma unroll
-          for (int c = 0; c < QW; ++c) sacc += H ? f16_lo(q.qp[h][j][c]) + f16_hi(q.qp[h][j][c]) : bf_lo(q.qp[h][j][c]) + bf_hi(q.qp[h][j][c]);
-        }
-        q.qs[h][j] = sacc;
-      }
   }
 
   int par = 1;                                           // LDS half that holds the next tile's slot list
@@ -832,11 +809,9 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
       for (int h = 0; h < G; ++h) moved = moved || (corr[h] != 1.0f);
       if (moved) {
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-          osub[h] *= corr[h];
+        for (int h = 0; h < G; ++h)
 #pragma unroll
           for (int e = 0; e < EV; ++e) o[h][e] *= corr[h];
-        }
       }
     }
     // -- V scales of this tile
@@ -880,7 +855,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
         for (int s = (it * VSB) / KIB; s < ((it + 1) * VSB) / KIB; ++s) issue_k_piece(s);
       }
       if constexpr (it + 1 < NITV) read_v(std::integral_constant<int, (it + 1 < NITV ? it + 1 : NITV - 1)>{}, vb[(it + 1) & 1]);
-      row_accumulate<D, G, M>(vb[it & 1], GE::IS_Q ? vsc[it] : 0.f, o, osub);
+      row_accumulate<D, G, M>(vb[it & 1], GE::IS_Q ? vsc[it] : 0.f, o);
     });
     par ^= 1;
   };
@@ -888,13 +863,6 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
   int tile = tile0;
   for (; (tile + tstride) * TR < n_list; tile += tstride) tile_body(tile, std::true_type{});
   tile_body(tile, std::false_type{});
-
-  if constexpr (GE::IS_Q) {
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int e = 0; e < EV; ++e) o[h][e] = fmaf(-GE::OFF, osub[h], o[h][e]);
-  }
 }
 
 // ---- one wave on the matrix cores: tiles of list F with 16-bit rows ------------------------------------------------

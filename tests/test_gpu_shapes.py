@@ -271,6 +271,52 @@ def test_single_calls_with_a_pair_for_every_compute_unit(shape):
     p.close()
 
 
+@pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
+def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
+    """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
+    them.  Outputs of a step (one workgroup per pair) against 64 bits, beside those of per-layer calls (32 to 64 workgroups
+    per pair) on the same cache.  The rounding of a sum of n like terms grows as the root of n, here by a factor of sqrt(8) and
+    only in the part of the error that comes from that sum (a third or less of it): twice the per-layer calls' error."""
+    from gpu_common import to_f64
+    import paper_2605_09490_amd as tkv
+    from oracle import tkv_oracle as O
+    from tkv_synth import Workload
+    cfg = small_config(name="precision", n_layers=12, batch=1, n_q_heads=40, n_kv_heads=8, head_dim=128, kv_dtype=kv_dtype,
+                       t2_format=t2, context=6001, decode_steps=2, k_window=16, sigma=1.0)
+    cfg = dataclasses.replace(cfg, recipe="bias")
+    print(f"[case] {kv_dtype} {t2}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    kv = [tkv.TieredKV(cfg.n_layers, 1, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype=kv_dtype,
+                       t2_format=t2, k_window=16, prefetch_mode="lazy", host_rows=64, staging_rows=64) for _ in range(2)]
+    orc = O.OracleCache(2, 1, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype=kv_dtype, t2_format=t2, k_window=16)
+    for l in range(cfg.n_layers):
+        k, v = wl.context_kv(l)
+        for c in kv:
+            c.append(l, k, v)
+        if l < 2:
+            orc.append(l, to_f64(k), to_f64(v))
+    tiers = np.where(np.random.default_rng(5).random((1, cfg.context)) < 0.15, 2, 0).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    for c in (*kv, orc):
+        c.set_tiers(tiers)
+        c.migrate()
+    k_all, v_all, q_all = wl.decode_inputs(0, 1)
+    step = kv[0].decode_step(k_all[0], v_all[0], q_all[0])
+    err = np.zeros((2, 2))
+    for l in range(cfg.n_layers):
+        kv[1].append(l, k_all[0, l], v_all[0, l])
+        call = kv[1].attend_and_score(l, q_all[0, l])
+        if l < 2:
+            orc.append(l, to_f64(k_all[0, l]), to_f64(v_all[0, l]))
+            ref = orc.attend_and_score(l, to_f64(q_all[0, l]))
+            err[0, l], err[1, l] = (np.linalg.norm(to_f64(o) - ref) / np.linalg.norm(ref) for o in (step[l], call))
+    print(f"[case] error of a step {err[0]}, of per-layer calls {err[1]}", flush=True)
+    assert (err[0] <= 2 * err[1]).all(), err
+    for c in kv:
+        c.close()
+
+
 def test_many_tiles_per_wave():
     """256 (sequence, kv head) pairs leave two workgroups per pair: every wave walks 8+ tiles of list F and the Q waves
     several of list Q, so the steady-state part of the fetch pipeline (not only its first and last tile) is compared
