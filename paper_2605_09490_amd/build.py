@@ -87,6 +87,23 @@ def build_host_check(verbose: bool = False) -> str:
     return HOST_CHECK
 
 
+FAKE_CHECK = os.path.join(HERE, "_build", "fake_runtime_check")
+
+
+def build_fake_check() -> str:
+    """The library's objects linked with tests/native/fake_runtime_check.cpp, which takes the HIP runtime's place: the
+    host code's launches and allocations on a machine without a GPU.  Uses the objects build() leaves in _build/."""
+    objs = [os.path.join(HERE, "_build", n) for _, _, n in UNITS]
+    if not all(os.path.exists(o) for o in objs):
+        build()
+    src = os.path.join(os.path.dirname(HERE), "tests", "native", "fake_runtime_check.cpp")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", src, *objs,
+                        "-lpthread", "-o", FAKE_CHECK], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + r.stderr)
+    return FAKE_CHECK
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
     print(build_host_check(verbose=True))

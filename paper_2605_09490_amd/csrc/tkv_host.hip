@@ -144,6 +144,7 @@ void* dev_alloc(tkv_cache* c, size_t bytes) {
   if (c->cfg.dev_alloc) p = c->cfg.dev_alloc(bytes, c->cfg.alloc_ctx);
   else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
   if (p) { c->dev_allocs.push_back(p); c->st.device_bytes += (int64_t)bytes; }
+  else (void)hipGetLastError();   // the runtime keeps a failed call's error; the next launch is not to report it as its own
   return p;
 }
 void* pin_alloc(tkv_cache* c, size_t bytes) {
@@ -152,6 +153,7 @@ void* pin_alloc(tkv_cache* c, size_t bytes) {
   if (c->cfg.pin_alloc) p = c->cfg.pin_alloc(bytes, c->cfg.alloc_ctx);
   else if (hipHostMalloc(&p, bytes, hipHostMallocDefault) != hipSuccess) p = nullptr;
   if (p) { c->pin_allocs.push_back(p); c->st.pinned_bytes += (int64_t)bytes; }
+  else (void)hipGetLastError();
   return p;
 }
 

@@ -1,0 +1,208 @@
+// Drives the library's host code on a machine without a GPU.  This file defines the HIP functions that the library's objects
+// call: memory is address ranges without backing, streams and events are tokens, a launch is written down with its arguments
+// and runs nothing.  Like the HIP runtime (7.0 on) it keeps the last error of a failed call until hipGetLastError reads it.
+// Every attention launch is checked against the allocations alive: scratch that a kernel would write outside of them fails.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../../include/tkv.h"
+#include "../../paper_2605_09490_amd/csrc/tkv_internal.h"
+
+#define CHECK(cond)                                                                                        \
+  do {                                                                                                     \
+    if (!(cond)) { std::printf("FAILED %s (line %d)\n", #cond, __LINE__); std::fflush(stdout); std::exit(1); } \
+  } while (0)
+#define OK(call)                                                                                              \
+  do {                                                                                                        \
+    tkv_status s_ = (call);                                                                                   \
+    if (s_ != TKV_OK) { std::printf("FAILED %s -> %d: %s (line %d)\n", #call, s_, tkv_last_error(c), __LINE__); std::exit(1); } \
+  } while (0)
+
+// ---- the runtime ---------------------------------------------------------------------------------------------------
+struct Launch { std::string kernel; dim3 grid; tkv::AttnArgs a; hipStream_t st; };
+static std::map<const void*, std::string> g_kernels;
+static std::map<uintptr_t, size_t> g_mem;           // live device ranges
+static uintptr_t g_next = (uintptr_t)1 << 40;
+static hipError_t g_last = hipSuccess;
+static std::vector<Launch> g_launches;
+static std::string g_log;                           // A: device allocation, S: device synchronised, M: memset, L: launch
+static int g_allocs = 0, g_fail_at = -1, g_cus = 256;
+static size_t g_fail_above = SIZE_MAX;
+static hipStream_t g_capturing = nullptr;
+static dim3 g_cfg_grid, g_cfg_block;
+static size_t g_cfg_lds;
+static hipStream_t g_cfg_stream;
+
+static hipError_t err(hipError_t e) { if (e != hipSuccess) g_last = e; return e; }
+static void* range(size_t n) { void* p = (void*)g_next; g_mem[g_next] = n; g_next += (n + 511) / 256 * 256; return p; }
+static bool inside(const void* p, size_t n) {
+  auto it = g_mem.upper_bound((uintptr_t)p);
+  if (it == g_mem.begin()) return false;
+  --it;
+  return (uintptr_t)p + n <= it->first + it->second;
+}
+static bool refused(size_t n) { return g_allocs++ == g_fail_at || n > g_fail_above; }
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  g_log += 'A';
+  if (refused(n)) return err(hipErrorOutOfMemory);
+  *p = range(n);
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) { CHECK(g_mem.erase((uintptr_t)p) == 1); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  if (refused(n)) return err(hipErrorOutOfMemory);
+  *p = std::calloc(n, 1);
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
+const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
+hipError_t hipDeviceSynchronize() { g_log += 'S'; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  static void* s = range((size_t)16 << 20);
+  *p = s;
+  return hipSuccess;
+}
+hipError_t hipMemset(void* p, int, size_t n) { CHECK(inside(p, n)); g_log += 'M'; return hipSuccess; }
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
+  *c = g_capturing && s == g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+
+void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { g_kernels[host] = name; }
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) { g_cfg_grid = g; g_cfg_block = b; g_cfg_lds = lds; g_cfg_stream = s; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* s) { *g = g_cfg_grid; *b = g_cfg_block; *lds = g_cfg_lds; *s = g_cfg_stream; return hipSuccess; }
+
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t st) {
+  Launch l{g_kernels.at(f), grid, {}, st};
+  g_log += 'L';
+  const auto is = [&](const char* n) { return l.kernel.find(n) != std::string::npos; };
+  if (is("k_attn") || is("k_step_scores") || is("k_call_scores")) {
+    const tkv::AttnArgs& a = l.a = *(const tkv::AttnArgs*)args[0];
+    CHECK(grid.x >= 1 && grid.y >= 1 && grid.y <= 65535 && grid.z >= 1 && grid.z <= 65535);
+    const size_t seqs = (size_t)a.nl * a.B * a.n_q * a.cq, G = a.Hq / a.Hkv;
+    CHECK(a.xs_stride == 0 || inside(a.xs, seqs * a.Hq * a.xs_stride * 4));
+    if (a.sc) {
+      const size_t sc = seqs * a.Hkv * a.sc_stride * 4;
+      CHECK(inside(a.sc, sc));
+      CHECK(a.xs_stride == 0 || (char*)a.xs >= (char*)a.sc + sc || (char*)a.xs + seqs * a.Hq * a.xs_stride * 4 <= (char*)a.sc);
+    } else {
+      CHECK(inside(a.part_ml, seqs * a.Hkv * a.S_total * 2 * G * 4) && inside(a.part_o, seqs * a.Hkv * a.S_total * G * 64 * 4));
+    }
+    g_launches.push_back(l);
+  }
+  return hipSuccess;
+}
+hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t st, hipEvent_t, hipEvent_t, int) {
+  return hipLaunchKernel(f, g, b, args, lds, st);
+}
+}
+
+// ---- scenarios -------------------------------------------------------------------------------------------------------
+static tkv_config config(int L, int B, int Hq, int Hkv, int D, int n) {
+  tkv_config cfg;
+  std::memset(&cfg, 0, sizeof cfg);
+  cfg.n_layers = L; cfg.batch = B; cfg.n_q_heads = Hq; cfg.n_kv_heads = Hkv; cfg.head_dim = D; cfg.max_tokens = n;
+  cfg.kv_dtype = TKV_BF16; cfg.staging_rows = 64; cfg.t2_rows = 64; cfg.host_rows = 64; cfg.prefetch_mode = TKV_PREFETCH_LAZY;
+  return cfg;
+}
+static char* const DATA = (char*)0x1000;            // stands for the caller's tensors, never read
+static hipStream_t const STREAM = (hipStream_t)0x2000;
+
+static void fill(tkv_cache* c, const tkv_config& cfg, int n) {
+  for (int l = 0; l < cfg.n_layers; ++l) OK(tkv_append(c, l, DATA, DATA, n, STREAM));
+}
+static int count(const char* kernel) {
+  int n = 0;
+  for (auto& l : g_launches) n += l.kernel.find(kernel) != std::string::npos;
+  return n;
+}
+// one decode step; its attention launches must cover every layer once, in order
+static std::vector<Launch> step(tkv_cache* c, const tkv_config& cfg, hipStream_t st = STREAM) {
+  g_launches.clear();
+  OK(tkv_decode_step(c, DATA, DATA, DATA, DATA, st));
+  size_t out = (size_t)DATA;
+  std::vector<Launch> attn;
+  for (auto& l : g_launches)
+    if (l.kernel.find("k_attn_step") != std::string::npos || l.kernel.find("k_attn_tiered") != std::string::npos) {
+      CHECK((size_t)l.a.out == out && l.st == st);
+      out += (size_t)l.a.nl * cfg.batch * cfg.n_q_heads * cfg.head_dim * 4;
+      attn.push_back(l);
+    }
+  CHECK(out == (size_t)DATA + (size_t)cfg.n_layers * cfg.batch * cfg.n_q_heads * cfg.head_dim * 4);
+  CHECK(count("k_attn_step") + count("k_attn_tiered") == count("k_attn_finish") + count("scores"));
+  return attn;
+}
+
+static const int SHAPES[][6] = {   // layers, sequences, query heads, kv heads, head_dim, max_tokens
+    {28, 1, 28, 4, 128, 1500}, {5, 3, 10, 2, 128, 700}, {48, 8, 40, 8, 128, 4200}, {1, 64, 28, 4, 128, 16500}, {70, 1, 6, 2, 64, 100},
+    {2, 130, 4, 2, 64, 200}, {12, 1, 40, 8, 128, 70000}, {28, 16, 64, 8, 64, 3000}};
+
+// A refused allocation leaves no error behind for the next launch to report, and a cache that could be created works.
+static void refused_allocations() {
+  for (auto& s : SHAPES) {
+    tkv_config cfg = config(s[0], s[1], s[2], s[3], s[4], s[5]);
+    tkv_cache* c = nullptr;
+    g_fail_at = -1; g_allocs = 0;
+    CHECK(tkv_create(&cfg, &c) == TKV_OK);
+    const int total = g_allocs;
+    fill(c, cfg, 60);
+    g_fail_above = 0;                               // nothing more is to be had
+    step(c, cfg);
+    CHECK(hipGetLastError() == hipSuccess);
+    for (int l = 0; l < cfg.n_layers; ++l) OK(tkv_append(c, l, DATA, DATA, 3, STREAM));
+    CHECK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, 3, STREAM) == TKV_ENOMEM);
+    OK(tkv_attend_and_score(c, 0, DATA, DATA, STREAM));
+    g_fail_above = SIZE_MAX;
+    OK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, 3, STREAM));
+    tkv_destroy(c);
+    for (int k = 0; k < total; ++k) {
+      g_fail_at = k; g_allocs = 0;
+      const tkv_status st = tkv_create(&cfg, &c);
+      g_fail_at = -1;
+      CHECK(hipGetLastError() == hipSuccess);
+      CHECK((st == TKV_OK) == (c != nullptr) && (st == TKV_OK || st == TKV_ENOMEM));
+      if (!c) continue;
+      fill(c, cfg, 60);
+      step(c, cfg);
+      tkv_destroy(c);
+    }
+    CHECK(g_mem.size() == 1);                       // the library's own array; everything else was given back
+  }
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "refused_allocations") refused_allocations();
+  else { std::printf("no scenario %s\n", what.c_str()); return 2; }
+  std::printf("%s: ok\n", what.c_str());
+  return 0;
+}

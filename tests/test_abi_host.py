@@ -124,3 +124,13 @@ def test_sources_compile_without_warnings():
     with ThreadPoolExecutor(max_workers=4) as ex:
         said = [d for d in ex.map(check, build.UNITS) if d]
     assert not said, said[0][:2000]
+
+
+@pytest.mark.parametrize("scenario", ["refused_allocations"])
+def test_host_code_on_a_runtime_that_launches_nothing(scenario):
+    """tests/native/fake_runtime_check.cpp: the host code against a stand-in for the HIP runtime; allocations can be refused,
+    and every launch is compared with the memory alive."""
+    import subprocess
+    from paper_2605_09490_amd import build
+    r = subprocess.run([build.build_fake_check(), scenario], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and f"{scenario}: ok" in r.stdout, r.stdout + r.stderr
