@@ -123,7 +123,9 @@ typedef struct {
   int32_t scorer;                      /* tkv_scorer */
   int32_t device;                      /* HIP device ordinal */
   float redundancy_weight;             /* weight of the redundancy penalty (REDUNDANCY, COMBINED); 0 -> 1 */
-  void* (*dev_alloc)(size_t bytes, void* ctx); /* device memory, 256-byte aligned; NULL -> hipMalloc */
+  void* (*dev_alloc)(size_t bytes, void* ctx); /* device memory, 256-byte aligned; NULL -> hipMalloc.  Called by tkv_create,
+                                          which synchronises the device before it uses any of it, and by a handle's first
+                                          tkv_attend_and_score_chunk */
   void (*dev_free)(void* p, void* ctx);
   void* (*pin_alloc)(size_t bytes, void* ctx); /* pinned host memory; NULL -> hipHostMalloc */
   void (*pin_free)(void* p, void* ctx);
@@ -217,7 +219,7 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
  * kv_dtype; out_all [n_layers, batch, n_q_heads, head_dim] out_dtype.  Same errors as the two calls.  All capacity and
  * state checks are made before anything is enqueued; when all layers are at the same length the new rows of every
  * layer go in with one launch and the attention of consecutive layers in groups (as many layers per launch as fit the
- * step's scratch of at most 256 MiB, allocated at the first step), so a later failure at layer l (a HIP error) leaves the
+ * step's scratch of at most 256 MiB, which tkv_create takes if it can have it), so a later failure at layer l (a HIP error) leaves the
  * step's rows appended to ALL layers and only layers < l attended: finish the step with tkv_attend_and_score for
  * layers >= l, or destroy the handle.  A step of 96 or more (layer, sequence, kv head) pairs of 16-bit rows takes a
  * launch of its own kind: its outputs and scores agree with the per-layer calls' to binary32 rounding (the summation

@@ -73,7 +73,7 @@ struct tkv_cache {
   float* xs = nullptr; float* part_ml = nullptr; float* part_o = nullptr;
   float* xs_chunk = nullptr; float* ml_chunk = nullptr; float* po_chunk = nullptr;   // the same for chunk launches
   float* xs_step = nullptr; float* ml_step = nullptr; float* po_step = nullptr;      // the same for several layers at once
-  int step_layers = 0;             // layers one launch of a decode step serves (0: not decided yet)
+  int step_layers = 1;             // layers one launch of a decode step serves
   float* sc_step = nullptr; float* spill_step = nullptr;   // whole-pair step launches (step_whole)
   bool step_whole = false;
   bool call_whole = false;         // single calls too take one workgroup per pair (sc, then the spill, in xs)
@@ -404,6 +404,46 @@ tkv_status rehome_store(tkv_cache* c, int n, hipStream_t st) {
   return TKV_OK;
 }
 
+// How a decode step's launches go, and their scratch; decided when the cache is created, from the shape (so that T1 placement,
+// prefetch mode and timing cannot change a bit).  A call that runs must not take device memory: an allocator may hand out
+// a block that work on another stream still uses, and a step may be captured into a graph.
+//  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a step has STEP_WHOLE_PAIRS pairs or
+//    more: the logits stay on the chip, one float per row leaves it.  With fewer pairs most compute units would idle.
+//  - else pairs are split as in a single call, several layers per launch, as many as fit STEP_SCRATCH_BYTES.
+// Without the memory the step goes layer by layer as the single calls do.
+constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
+constexpr int STEP_WHOLE_PAIRS = 96;
+void step_scratch(tkv_cache* c) {
+  const DevView& v = c->dv;
+  if (c->streamed) return;
+  const auto layers_in = [&](size_t budget, size_t per_layer) {
+    const int nl = (int)std::min<size_t>({budget / per_layer, (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
+    if (nl < 2) return nl;
+    const int groups = (v.L + nl - 1) / nl;      // of equal size: 48 layers of which 10 fit go as 10, 10, 10, 9, 9
+    return (v.L + groups - 1) / groups;
+  };
+  const size_t pairs = (size_t)v.B * v.Hkv;
+  if (c->es == 2 && pairs * v.L >= STEP_WHOLE_PAIRS) {
+    const size_t per_layer = pairs * ((size_t)c->sc_stride + (size_t)c->G * c->spill_stride) * sizeof(float);
+    const int nl = layers_in(STEP_WHOLE_SCRATCH_BYTES, per_layer);
+    float* p = nl >= 1 && pairs * nl >= STEP_WHOLE_PAIRS ? (float*)dev_alloc(c, nl * per_layer) : nullptr;
+    if (p) {
+      c->sc_step = p; c->spill_step = p + nl * pairs * c->sc_stride;
+      c->step_whole = true; c->step_layers = nl;
+      return;
+    }
+  }
+  if (c->call_whole) return;
+  const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = pairs * c->S_alloc * 2 * c->G, po_n = pairs * c->S_alloc * c->G * v.D;
+  const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
+  const int nl = layers_in(STEP_SCRATCH_BYTES, per_layer);
+  if (nl < 2) return;
+  float* p = (float*)dev_alloc(c, nl * per_layer);
+  if (!p) return;
+  c->xs_step = p; c->ml_step = p + nl * xs_n; c->po_step = c->ml_step + nl * ml_n;
+  c->step_layers = nl;
+}
+
 }  // namespace
 
 extern "C" {
@@ -529,9 +569,6 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
     ok = ok && dalloc(c, v.s_pos, BN) && dalloc(c, v.s_loc, BN) && dalloc(c, v.h_clr, BN);
     ok = ok && dalloc(c, v.h_seq, (size_t)c->host_rows) && dalloc(c, v.h_dst, (size_t)c->host_rows);
     ok = ok && dalloc(c, c->d_base2, (size_t)B) && dalloc(c, c->g2_seq, BN) && dalloc(c, c->g2_src, BN) && dalloc(c, c->hloc2, BN);
-    if (ok && (hipMemset(v.h_seq, 0xFF, (size_t)c->host_rows * sizeof(int)) != hipSuccess ||
-               hipMemset(v.h_dst, 0xFF, (size_t)c->host_rows * sizeof(int)) != hipSuccess))
-      return die(TKV_EDEVICE, "tkv_create: state initialisation failed");
     v.frK = c->frameK[0]; v.frV = c->frameV[0];
   }
   if (ok) {
@@ -541,6 +578,7 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
     ok = c->hstore && c->pin_cnt && c->pin_base;
   }
   if (!ok) return die(TKV_ENOMEM, "tkv_create: an allocation failed");
+  step_scratch(c);
 
   c->len.assign(L, 0);
   c->nF.assign(B, 0); c->nQ.assign(B, 0); c->nS.assign(B, 0);
@@ -566,7 +604,11 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   if (c->streamed && hipStreamCreateWithFlags(&c->sC, hipStreamNonBlocking) != hipSuccess)
     return die(TKV_EDEVICE, "tkv_create: hipStreamCreate failed");
   if (!evok) return die(TKV_EDEVICE, "tkv_create: hipEventCreate failed");
-  if (launch_init_state(v, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
+  // an allocator callback may have handed out blocks that queued work, on whatever stream, still uses
+  if (hipDeviceSynchronize() != hipSuccess ||
+      (c->streamed && (hipMemset(v.h_seq, 0xFF, (size_t)c->host_rows * sizeof(int)) != hipSuccess ||
+                       hipMemset(v.h_dst, 0xFF, (size_t)c->host_rows * sizeof(int)) != hipSuccess)) ||
+      launch_init_state(v, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
     return die(TKV_EDEVICE, "tkv_create: state initialisation failed");
   *out = c;
   return TKV_OK;
@@ -650,7 +692,7 @@ static tkv_status chunk_scratch(tkv_cache* c) {
 // the layer's last call of this step (the streamed frame is released and refilled, queued transfers are pumped).
 // noalloc: the scratch of the call lives in the library's fixed device array, and nothing on the way may allocate
 // (no event pools, no queued transfers are issued).  nl: consecutive layers served by the call's launches (a decode
-// step, after step_scratch; q and out then hold the layers one after the other).  step: a call of tkv_decode_step.
+// step; q and out then hold the layers one after the other).  step: a call of tkv_decode_step.
 static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* out, int trim, int q_bs, int o_bs, bool last,
                              hipStream_t st, bool noalloc = false, int m = 1, int nl = 1, bool step = false) {
   const DevView& v = c->dv;
@@ -833,50 +875,6 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
   return TKV_OK;
 }
 
-// How a decode step's launches go, and their scratch; decided at the first step, from the shape alone (so that T1 placement,
-// prefetch mode and timing cannot change a bit), allocated then and kept.
-//  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a step has STEP_WHOLE_PAIRS pairs or
-//    more: the logits stay on the chip, one float per row leaves it.  With fewer pairs most compute units would idle.
-//  - else pairs are split as in a single call, several layers per launch, as many as fit STEP_SCRATCH_BYTES.
-// Without the memory the step goes layer by layer as the single calls do.  A step that is being captured into a graph may
-// not allocate: it goes layer by layer if it is the first one.
-constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
-constexpr int STEP_WHOLE_PAIRS = 96;
-static void step_scratch(tkv_cache* c, hipStream_t st) {
-  if (c->step_layers) return;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
-  const DevView& v = c->dv;
-  c->step_layers = 1;
-  if (c->streamed) return;
-  const auto layers_in = [&](size_t budget, size_t per_layer) {
-    const int nl = (int)std::min<size_t>({budget / per_layer, (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
-    if (nl < 2) return nl;
-    const int groups = (v.L + nl - 1) / nl;      // of equal size: 48 layers of which 10 fit go as 10, 10, 10, 9, 9
-    return (v.L + groups - 1) / groups;
-  };
-  const size_t pairs = (size_t)v.B * v.Hkv;
-  if (c->es == 2 && pairs * v.L >= STEP_WHOLE_PAIRS) {
-    const size_t per_layer = pairs * ((size_t)c->sc_stride + (size_t)c->G * c->spill_stride) * sizeof(float);
-    const int nl = layers_in(STEP_WHOLE_SCRATCH_BYTES, per_layer);
-    float* p = nl >= 1 && pairs * nl >= STEP_WHOLE_PAIRS ? (float*)dev_alloc(c, nl * per_layer) : nullptr;
-    if (p) {
-      c->sc_step = p; c->spill_step = p + nl * pairs * c->sc_stride;
-      c->step_whole = true; c->step_layers = nl;
-      return;
-    }
-  }
-  if (c->call_whole) return;
-  const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = pairs * c->S_alloc * 2 * c->G, po_n = pairs * c->S_alloc * c->G * v.D;
-  const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
-  const int nl = layers_in(STEP_SCRATCH_BYTES, per_layer);
-  if (nl < 2) return;
-  float* p = (float*)dev_alloc(c, nl * per_layer);
-  if (!p) return;
-  c->xs_step = p; c->ml_step = p + nl * xs_n; c->po_step = c->ml_step + nl * ml_n;
-  c->step_layers = nl;
-}
-
 tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, const void* q_all, void* out_all,
                            void* hip_stream) {
   if (!c) return TKV_EINVAL;
@@ -902,8 +900,7 @@ tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, c
     c->ntier[0] += v.B;
     c->n_assigned += 1;
     for (int l = 0; l < v.L; ++l) c->len[l] = n + 1;
-    step_scratch(c, (hipStream_t)hip_stream);
-    const int per_launch = std::max(1, c->step_layers);
+    const int per_launch = c->step_layers;
     for (int l = 0; l < v.L;) {
       // one launch pair for a group of layers; with WAIT the layers that still have to wait for their prefetch go in small
       // groups (as few as fill the chip, or alone), so that the others do not wait with them

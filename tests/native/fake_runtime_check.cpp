@@ -199,9 +199,40 @@ static void refused_allocations() {
   }
 }
 
+// Device memory is taken by tkv_create (and by the first chunk) only, and nothing of it is used before the device has been
+// synchronised: a block may come from an allocator whose last owner's work is still queued on another stream.
+static void allocations_before_use() {
+  for (auto& s : SHAPES)
+    for (int mode : {TKV_PREFETCH_WAIT, TKV_PREFETCH_LAZY, TKV_PREFETCH_STREAM}) {
+      tkv_config cfg = config(s[0], s[1], s[2], s[3], s[4], s[5]);
+      cfg.prefetch_mode = mode;
+      tkv_cache* c = nullptr;
+      g_log.clear();
+      CHECK(tkv_create(&cfg, &c) == TKV_OK);
+      const size_t used = g_log.find_first_of("LM"), synced = g_log.rfind('S', used);
+      CHECK(used != std::string::npos && synced != std::string::npos && g_log.find('A', synced) == std::string::npos);
+      fill(c, cfg, 60);
+      g_log.clear();
+      const auto first = step(c, cfg), second = step(c, cfg);
+      CHECK(g_log.find('A') == std::string::npos);
+      // a step that is being captured is launched like any other, the first one included
+      tkv_cache* d = nullptr;
+      CHECK(tkv_create(&cfg, &d) == TKV_OK);
+      fill(d, cfg, 60);
+      g_capturing = STREAM;
+      const auto captured = step(d, cfg);
+      g_capturing = nullptr;
+      CHECK(captured.size() == first.size() && first.size() == second.size());
+      for (size_t i = 0; i < first.size(); ++i) CHECK(captured[i].kernel == first[i].kernel && captured[i].a.nl == first[i].a.nl && captured[i].a.S == first[i].a.S);
+      tkv_destroy(c);
+      tkv_destroy(d);
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_allocations") refused_allocations();
+  else if (what == "allocations_before_use") allocations_before_use();
   else { std::printf("no scenario %s\n", what.c_str()); return 2; }
   std::printf("%s: ok\n", what.c_str());
   return 0;
