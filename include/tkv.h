@@ -125,7 +125,8 @@ typedef struct {
   float redundancy_weight;             /* weight of the redundancy penalty (REDUNDANCY, COMBINED); 0 -> 1 */
   void* (*dev_alloc)(size_t bytes, void* ctx); /* device memory, 256-byte aligned; NULL -> hipMalloc.  Called by tkv_create,
                                           which synchronises the device before it uses any of it, and by a handle's first
-                                          tkv_attend_and_score_chunk */
+                                          tkv_attend_and_score_chunk, which uses the memory on its hip_stream at once: no
+                                          work on another stream may still be using it then */
   void (*dev_free)(void* p, void* ctx);
   void* (*pin_alloc)(size_t bytes, void* ctx); /* pinned host memory; NULL -> hipHostMalloc */
   void (*pin_free)(void* p, void* ctx);

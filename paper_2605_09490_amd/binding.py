@@ -151,6 +151,7 @@ class TieredKV:
         self.torch_dtype = torch_types[kv_dtype]
         self.out_torch_dtype = torch_types[out_dtype]
         self._held = {}
+        self._call_stream = None         # during a call that may allocate: the stream it enqueues its work on
         cfg = tkv_config()
         cfg.n_layers, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim = n_layers, batch, n_q_heads, n_kv_heads, head_dim
         cfg.max_tokens = max_tokens
@@ -173,7 +174,9 @@ class TieredKV:
 
             def _dev_alloc(nbytes, _ctx):
                 try:
-                    t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+                    # the allocator keeps a pool per stream; a block of another stream's pool may still be in use there
+                    with torch.cuda.stream(self._call_stream):
+                        t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
                 except RuntimeError as e:
                     self._alloc_error = f"device allocation of {int(nbytes)} bytes failed: {str(e)[:200]}"
                     return None
@@ -259,9 +262,13 @@ class TieredKV:
         n_q = int(q.shape[1])
         if out is None:
             out = torch.empty((B, n_q, Hq, D), dtype=self.out_torch_dtype, device=self.device)
-        self._check(self.lib.tkv_attend_and_score_chunk(self._h, layer, self._dev_tensor(q, (B, n_q, Hq, D)),
-                                                        self._dev_tensor(out, (B, n_q, Hq, D), self.out_torch_dtype),
-                                                        n_q, self._stream(stream)))
+        self._call_stream = stream       # the first chunk allocates its scratch
+        try:
+            self._check(self.lib.tkv_attend_and_score_chunk(self._h, layer, self._dev_tensor(q, (B, n_q, Hq, D)),
+                                                            self._dev_tensor(out, (B, n_q, Hq, D), self.out_torch_dtype),
+                                                            n_q, self._stream(stream)))
+        finally:
+            self._call_stream = None
         return out
 
     def decode_step(self, k_all, v_all, q_all, out_all=None, stream=None):

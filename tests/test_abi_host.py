@@ -134,3 +134,39 @@ def test_host_code_on_a_runtime_that_launches_nothing(scenario):
     from paper_2605_09490_amd import build
     r = subprocess.run([build.build_fake_check(), scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and f"{scenario}: ok" in r.stdout, r.stdout + r.stderr
+
+
+def test_chunk_scratch_comes_from_the_calls_own_stream(monkeypatch):
+    """PyTorch's allocator keeps a pool per stream.  The scratch of a handle's first chunk is written on the stream that the
+    call names, so it has to come from that stream's pool, not from the one of whatever stream is current."""
+    import contextlib
+    import types
+
+    import torch
+    taken, current = [], [None]
+
+    @contextlib.contextmanager
+    def on_stream(s):
+        before, current[0] = current[0], s or current[0]
+        yield
+        current[0] = before
+
+    def create(cfg, h):
+        lib.dev_alloc = cfg._obj.dev_alloc
+        lib.dev_alloc(64, None)
+        return tkv.TKV_OK
+
+    def chunk(*_):
+        lib.dev_alloc(64, None)
+        return tkv.TKV_OK
+
+    lib = types.SimpleNamespace(tkv_create=create, tkv_attend_and_score_chunk=chunk, tkv_destroy=lambda h: None)
+    empty = torch.empty
+    monkeypatch.setattr(binding, "load_library", lambda: lib)
+    monkeypatch.setattr(torch.cuda, "stream", on_stream)
+    monkeypatch.setattr(torch, "empty", lambda *a, **kw: (taken.append(current[0]), empty(64, dtype=torch.uint8))[1])
+    monkeypatch.setattr(tkv.TieredKV, "_dev_tensor", lambda self, t, shape, dtype=None: None)
+    kv = tkv.TieredKV(1, 1, 4, 2, 64, 128)
+    side = types.SimpleNamespace(cuda_stream=7)
+    kv.attend_and_score_chunk(0, np.zeros((1, 2)), out=np.zeros(1), stream=side)
+    assert taken == [None, side]
