@@ -1999,13 +1999,13 @@ __global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs
 // query: wave (hg, ls) sums kv heads hg, hg+4, ... for queries ls, ls+LSN, ..., the four partial sums are added in the order
 // hg = 0..3).  Query jt does not see the last queries - 1 - jt entries of list F; its Q-list logits start where the F tiles
 // of its group (the cq tokens of one workgroup, laid out for the group's last token) end.  Latency-bound like k_attn_finish
-// and built like it: the first logits are requested before the statistics; as many queries go side by side (LSN, 256
-// threads each) as leave room for all workgroups at once (2048 threads per compute unit): 34 x 8 tiles take 9.3 us with
-// LSN = 4 and 10.5 with 1, 67 x 8 tiles 13.0 us with 4 and 11.4 with 1.  The other workgroups merge the splits of
-// LSN * HPG (query, head)s into out.
+// and built like it: the first logits are requested before the statistics, LSN queries go side by side (256 threads each).
+// The other workgroups merge the splits of LSN * hpg (query, head)s into out, hpg of them one after the other in a thread:
+// two where the merge is one round of loads, one where it is a chain (more than 16 splits; 16384 tokens, one sequence, 28/4
+// heads, two tokens: 35 us a call with hpg = 2 and LSN = 4, 23 with 1 and 2).
 constexpr int CHUNK_HPG = 2;
 template <int D, int G, int LSN>
-__global__ __launch_bounds__(LSN * 256) void k_attn_finish_chunk(const AttnArgs a, int n_tiles) {
+__global__ __launch_bounds__(LSN * 256) void k_attn_finish_chunk(const AttnArgs a, int n_tiles, int hpg) {
   constexpr int XP = LSN == 1 ? 4 : 2;
   extern __shared__ __attribute__((aligned(8))) float sm_dyn[];    // statistics [nq][Hq], then partial sums [nq][4][64] / [LSN][HPG][256]
   const int t = threadIdx.x, b = blockIdx.y, nq = a.n_q * a.cq, ns = a.S_total;
@@ -2086,14 +2086,14 @@ __global__ __launch_bounds__(LSN * 256) void k_attn_finish_chunk(const AttnArgs 
     }
   } else {
     constexpr int NSG = 256 / D, HPG = CHUNK_HPG;
-    const int r0 = ((blockIdx.x - n_tiles) * LSN + (t >> 8)) * HPG, tl = t & 255;
+    const int r0 = ((blockIdx.x - n_tiles) * LSN + (t >> 8)) * hpg, tl = t & 255;
     const int d = tl % D, sg = tl / D;
     float il[HPG], acc[HPG];
 #pragma unroll
     for (int q = 0; q < HPG; ++q) {
       const int r = r0 + q;
       il[q] = 0.f; acc[q] = 0.f;
-      if (r < nq * a.Hq) {
+      if (q < hpg && r < nq * a.Hq) {
         const int jt = r / a.Hq, hq = r - jt * a.Hq, kvh = hq / G, h = hq % G;
         const float* pm = a.part_ml + (size_t)((b * nq + jt) * a.Hkv + kvh) * kv_ml + h;
         const float* pob = a.part_o + ((size_t)((b * nq + jt) * a.Hkv + kvh) * ns * G) * D + h * D + d;
@@ -2112,7 +2112,7 @@ __global__ __launch_bounds__(LSN * 256) void k_attn_finish_chunk(const AttnArgs 
 #pragma unroll
       for (int q = 0; q < HPG; ++q) {
         const int r = r0 + q;
-        if (r >= nq * a.Hq) continue;
+        if (q >= hpg || r >= nq * a.Hq) continue;
         float tot = acc[q];
 #pragma unroll
         for (int g2 = 1; g2 < NSG; ++g2) tot += sp[q * 256 + g2 * D];
@@ -2315,16 +2315,29 @@ int attn_tile_rows(int D, int elem_bytes, int cq) { return elem_bytes == 2 && cq
 int attn_cols_per_launch(int elem_bytes, int G) { return elem_bytes == 2 ? (32 / G < 16 ? 32 / G : 16) : 1; }
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles) { return q_waves(n_waves, n_f_tiles, n_q_tiles); }
 
+static int chunk_hpg(const AttnArgs& a) { return a.S_total <= 16 ? CHUNK_HPG : 1; }
+static int chunk_workgroups(const AttnArgs& a, int lsn) {   // per sequence
+  const int per_wg = lsn * chunk_hpg(a);
+  return a.n_tiles + (a.Hq * a.n_q * a.cq + per_wg - 1) / per_wg;
+}
 template <int D, int G, int LSN>
 static hipError_t run_finish_chunk_n(const AttnArgs& a, hipStream_t st) {
-  const int per_wg = LSN * CHUNK_HPG, nq = a.n_q * a.cq, lds = nq * a.Hq * 8 + (nq > per_wg ? nq : per_wg) * 1024;   // at most 32 KB
-  hipLaunchKernelGGL((k_attn_finish_chunk<D, G, LSN>), dim3(a.n_tiles + (a.Hq * nq + per_wg - 1) / per_wg, a.B), dim3(LSN * 256), lds, st, a, a.n_tiles);
+  const int nq = a.n_q * a.cq, lds = nq * a.Hq * 8 + (nq > LSN * CHUNK_HPG ? nq : LSN * CHUNK_HPG) * 1024;   // at most 32 KB
+  hipLaunchKernelGGL((k_attn_finish_chunk<D, G, LSN>), dim3(chunk_workgroups(a, LSN), a.B), dim3(LSN * 256), lds, st, a, a.n_tiles, chunk_hpg(a));
   return hipGetLastError();
 }
 template <int D, int G, int KT>
 static hipError_t run_finish_chunk(const AttnArgs& a, hipStream_t st) {
-  const int wgs = a.n_tiles * a.B;
-  if (wgs <= 384) return run_finish_chunk_n<D, G, 4>(a, st);
+  // Queries side by side.  Many tiles fill the chip by themselves (67 x 8 tiles take 13.0 us with LSN = 4, 11.4 with 1; 34 x 8
+  // 9.3 and 10.5).  Two queries have nothing for a third and fourth group of threads.  From three on as many as leave room for
+  // the output workgroups beside the tiles (2048 threads per compute unit; 32 sequences of 600 tokens, 12/2 heads, four
+  // tokens: 26.6 us a call with LSN = 4, 22.9 with 2; 300 tokens, 28/4 heads: 29.3 with 4, 27.3 with 1), but above eight the
+  // queries of a thread one after the other weigh more (300 tokens, 8/8 heads, 13 tokens: 29.8 us with 4, 35.2 with 2).
+  const int nq = a.n_q * a.cq;
+  const auto fits = [&](int lsn) { return (int64_t)chunk_workgroups(a, lsn) * a.B * lsn <= 256 * 8; };
+  if ((int64_t)a.n_tiles * a.B > 384) return run_finish_chunk_n<D, G, 1>(a, st);
+  if (nq > 8 || (nq > 2 && fits(4))) return run_finish_chunk_n<D, G, 4>(a, st);
+  if (nq <= 2 || fits(2)) return run_finish_chunk_n<D, G, 2>(a, st);
   return run_finish_chunk_n<D, G, 1>(a, st);
 }
 hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t st) {

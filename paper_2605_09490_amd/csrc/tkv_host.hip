@@ -750,9 +750,11 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     n_wt = std::max(n_wt, wave_tiles(c->nF[b] - trim) + wave_tiles(c->nQ[b]));
     n_wt_s = std::max(n_wt_s, wave_tiles(c->nS[b]));
   }
-  // four tiles per workgroup, one per SIMD, until the pairs have all compute units; two waves of a SIMD that have one tile
-  // each take nearly twice as long as one
-  const int S = std::max(1, std::min(c->S_alloc, (n_wt + 3) / 4));
+  // Four tiles per workgroup, one per SIMD, until the pairs have all compute units; two waves of a SIMD that have one tile
+  // each take nearly twice as long as one.  A chunk's workgroups leave more behind (every token's partials and logits), so
+  // from nine tiles on theirs have a tile for every wave: one sequence of 16384 tokens, 12/2 heads, two tokens takes 33 us a
+  // call so and 45 with four tiles each; 300 tokens 16.2 and 14.4.
+  const int S = std::max(1, std::min(c->S_alloc, m > 1 && n_wt > 8 ? (n_wt + nw - 1) / nw : (n_wt + 3) / 4));
   const int S2 = n_tiles_s > 0 ? std::max(1, std::min(c->S_alloc, (n_wt_s + 3) / 4)) : 0;
   AttnArgs a{};
   const bool step_launch = step && c->step_whole, whole = step_launch || (m == 1 && c->call_whole);

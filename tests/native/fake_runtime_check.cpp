@@ -229,10 +229,30 @@ static void allocations_before_use() {
     }
 }
 
+// A chunk's workgroups leave a partial per query token behind, and the finishing kernel merges a pair's one by one: no more
+// of them than have a (64-row) tile for each of their waves, but for lists of up to eight tiles.
+static void chunk_splits() {
+  for (int n : {300, 700, 2000, 9000, 16384})
+    for (int m : {2, 4}) {
+      tkv_config cfg = config(1, 1, 28, 4, 128, n + m);
+      tkv_cache* c = nullptr;
+      CHECK(tkv_create(&cfg, &c) == TKV_OK);
+      fill(c, cfg, n + m);
+      g_launches.clear();
+      OK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, m, STREAM));
+      CHECK(count("k_attn_tiered_mc") == 1 && g_launches.size() == 2);
+      const int tiles = (n + m + 63) / 64, waves = m * 7 <= 16 ? 8 : 4;
+      CHECK(g_launches[0].a.S == (int)g_launches[0].grid.x);
+      CHECK(tiles <= 8 || (g_launches[0].a.S - 1) * waves < tiles);
+      tkv_destroy(c);
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_allocations") refused_allocations();
   else if (what == "allocations_before_use") allocations_before_use();
+  else if (what == "chunk_splits") chunk_splits();
   else { std::printf("no scenario %s\n", what.c_str()); return 2; }
   std::printf("%s: ok\n", what.c_str());
   return 0;

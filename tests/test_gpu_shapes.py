@@ -271,6 +271,34 @@ def test_single_calls_with_a_pair_for_every_compute_unit(shape):
     p.close()
 
 
+@pytest.mark.parametrize("n_q,shape", [
+    (2, dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=64, context=9001)),     # more than 16 splits per pair, eight waves
+    (4, dict(batch=1, n_q_heads=14, n_kv_heads=2, head_dim=128, context=4500)),    # ... four waves, four queries side by side
+    (3, dict(batch=32, n_q_heads=16, n_kv_heads=2, head_dim=64, context=600)),     # no room for four side by side: two
+    (4, dict(batch=32, n_q_heads=28, n_kv_heads=4, head_dim=128, context=300)),    # ... one
+    (13, dict(batch=32, n_q_heads=3, n_kv_heads=3, head_dim=64, context=300)),     # many queries in one launch
+])
+def test_chunks_by_split_count_and_queries_side_by_side(n_q, shape):
+    """The finishing kernel of a chunk in each of its launch shapes: outputs and scores of a chunk over all four tiers
+    against the oracle."""
+    from gpu_common import Pair, assert_out_close, assert_scores_close
+    cfg = small_config(name="chunk", n_layers=1, kv_dtype="bf16", decode_steps=n_q, k_window=16, sigma=1.0, **shape)
+    print(f"[case] chunk of {n_q}, {shape}", flush=True)
+    p = Pair(cfg, prefetch_mode="lazy")
+    tiers = np.random.default_rng(3).choice(4, size=(cfg.batch, cfg.context), p=(0.4, 0.3, 0.2, 0.1)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    p.force_tiers(tiers)
+    ks, vs = zip(*[p.wl.step_kv(j, 0) for j in range(n_q)])
+    p.append(0, torch.cat(ks, dim=1), torch.cat(vs, dim=1))
+    got, ref = p.attend_chunk(0, torch.stack([p.wl.step_q(j, 0) for j in range(n_q)], dim=1).contiguous())
+    for j in range(n_q):
+        assert_out_close(got[:, j], ref[:, j], cfg.kv_dtype, f"query {j}")
+    n = cfg.context + n_q
+    assert_scores_close(p.gpu.get_scores(), p.orc.score, n, n_q * cfg.n_q_heads * p.score_scale)
+    p.close()
+
+
 @pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
 def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
