@@ -79,6 +79,7 @@ struct tkv_cache {
   bool call_whole = false;         // single calls too take one workgroup per pair (sc, then the spill, in xs)
   int sc_stride = 0, spill_stride = 0;
   int S_alloc = 0, xs_stride = 0;
+  int cus = 0;                     // compute units of the device
   char* static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (tkv_attend_and_score_noalloc)
   // T1 store and transport
   char* hstore = nullptr;
@@ -404,44 +405,53 @@ tkv_status rehome_store(tkv_cache* c, int n, hipStream_t st) {
   return TKV_OK;
 }
 
-// How a decode step's launches go, and their scratch; decided when the cache is created, from the shape (so that T1 placement,
-// prefetch mode and timing cannot change a bit).  A call that runs must not take device memory: an allocator may hand out
-// a block that work on another stream still uses, and a step may be captured into a graph.
-//  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a step has STEP_WHOLE_PAIRS pairs or
+// How a decode step's launches go; decided when the cache is created, from its shape, and not from what memory there is: the two
+// kinds of launch add in different orders, and neither T1 placement nor prefetch mode nor memory nor timing may change a bit.
+//  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a launch has STEP_WHOLE_PAIRS pairs or
 //    more: the logits stay on the chip, one float per row leaves it.  With fewer pairs most compute units would idle.
-//  - else pairs are split as in a single call, several layers per launch, as many as fit STEP_SCRATCH_BYTES.
-// Without the memory the step goes layer by layer as the single calls do.
+//  - else pairs are split as in a single call.
+// Either way several layers per launch, as many as fit a scratch (step_scratch).
 constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
 constexpr int STEP_WHOLE_PAIRS = 96;
-void step_scratch(tkv_cache* c) {
+size_t step_floats_per_layer(const tkv_cache* c) {
+  const DevView& v = c->dv;
+  const size_t pairs = (size_t)v.B * v.Hkv;
+  if (c->step_whole) return pairs * ((size_t)c->sc_stride + (size_t)c->G * c->spill_stride);
+  return (size_t)v.B * v.Hq * c->xs_stride + pairs * c->S_alloc * c->G * (2 + v.D);
+}
+int step_layers(const tkv_cache* c) {
+  const DevView& v = c->dv;
+  const size_t budget = (c->step_whole ? STEP_WHOLE_SCRATCH_BYTES : STEP_SCRATCH_BYTES) / sizeof(float);
+  const int nl = (int)std::min<size_t>({budget / step_floats_per_layer(c), (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
+  if (nl < 2) return 1;
+  const int groups = (v.L + nl - 1) / nl;        // of equal size: 48 layers of which 10 fit go as 10, 10, 10, 9, 9
+  return (v.L + groups - 1) / groups;
+}
+// Sets step_whole and step_layers (as if all memory were to be had).
+void step_route(tkv_cache* c) {
   const DevView& v = c->dv;
   if (c->streamed) return;
-  const auto layers_in = [&](size_t budget, size_t per_layer) {
-    const int nl = (int)std::min<size_t>({budget / per_layer, (size_t)v.L, (size_t)MAX_LAYERS_PER_LAUNCH, (size_t)65535 / v.B});
-    if (nl < 2) return nl;
-    const int groups = (v.L + nl - 1) / nl;      // of equal size: 48 layers of which 10 fit go as 10, 10, 10, 9, 9
-    return (v.L + groups - 1) / groups;
-  };
-  const size_t pairs = (size_t)v.B * v.Hkv;
-  if (c->es == 2 && pairs * v.L >= STEP_WHOLE_PAIRS) {
-    const size_t per_layer = pairs * ((size_t)c->sc_stride + (size_t)c->G * c->spill_stride) * sizeof(float);
-    const int nl = layers_in(STEP_WHOLE_SCRATCH_BYTES, per_layer);
-    float* p = nl >= 1 && pairs * nl >= STEP_WHOLE_PAIRS ? (float*)dev_alloc(c, nl * per_layer) : nullptr;
-    if (p) {
-      c->sc_step = p; c->spill_step = p + nl * pairs * c->sc_stride;
-      c->step_whole = true; c->step_layers = nl;
-      return;
-    }
+  c->step_whole = c->es == 2;
+  c->step_layers = step_layers(c);
+  if (c->step_whole && (step_floats_per_layer(c) * sizeof(float) > STEP_WHOLE_SCRATCH_BYTES ||
+                        (int64_t)v.B * v.Hkv * c->step_layers < STEP_WHOLE_PAIRS)) {
+    c->step_whole = c->call_whole;
+    c->step_layers = step_layers(c);
   }
-  if (c->call_whole) return;
-  const size_t xs_n = (size_t)v.B * v.Hq * c->xs_stride, ml_n = pairs * c->S_alloc * 2 * c->G, po_n = pairs * c->S_alloc * c->G * v.D;
-  const size_t per_layer = (xs_n + ml_n + po_n) * sizeof(float);
-  const int nl = layers_in(STEP_SCRATCH_BYTES, per_layer);
-  if (nl < 2) return;
-  float* p = (float*)dev_alloc(c, nl * per_layer);
-  if (!p) return;
-  c->xs_step = p; c->ml_step = p + nl * xs_n; c->po_step = c->ml_step + nl * ml_n;
-  c->step_layers = nl;
+}
+// The scratch of a launch that serves several layers, taken when the cache is created: a call that runs must not take device
+// memory, an allocator may hand out a block that work on another stream still uses, and a step may be captured into a
+// graph.  With less memory than that the launches serve fewer layers, down to one in the scratch of the single calls.
+void step_scratch(tkv_cache* c) {
+  const DevView& v = c->dv;
+  for (; c->step_layers > 1; c->step_layers /= 2) {
+    const size_t nl = c->step_layers, pairs = (size_t)v.B * v.Hkv;
+    float* p = (float*)dev_alloc(c, nl * step_floats_per_layer(c) * sizeof(float));
+    if (!p) continue;
+    if (c->step_whole) { c->sc_step = p; c->spill_step = p + nl * pairs * c->sc_stride; }
+    else { c->xs_step = p; c->ml_step = p + nl * v.B * v.Hq * c->xs_stride; c->po_step = c->ml_step + nl * pairs * c->S_alloc * 2 * c->G; }
+    return;
+  }
 }
 
 }  // namespace
@@ -535,16 +545,14 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   if (cfg->scorer == TKV_SCORE_REDUNDANCY || cfg->scorer == TKV_SCORE_COMBINED)
     ok = ok && dalloc(c, v.red, (size_t)L * B * Hkv * N) && dalloc(c, v.last_k, (size_t)L * B * Hkv * D * v.es);
   v.host_base = c->d_host_base;
-  int cus = 0;
   {
     // one attention workgroup per compute unit: that many per (sequence, kv head) pair, as far as the pairs go round
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device) != hipSuccess || cus <= 0) cus = 256;
-    c->S_alloc = std::max(1, cus / std::max(1, B * Hkv));
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, cfg->device) != hipSuccess || c->cus <= 0) c->cus = 256;
+    c->S_alloc = std::max(1, c->cus / std::max(1, B * Hkv));
   }
   // every list may end in a partly filled tile; an odd number of 256-byte tiles per row keeps the rows of the heads
   // of one tile from falling on the same memory channels
   c->xs_stride = ((N / TOK_PER_BLOCK + (cfg->prefetch_mode == TKV_PREFETCH_STREAM ? 3 : 2)) | 1) * TOK_PER_BLOCK;
-  ok = ok && dalloc(c, c->xs, (size_t)B * v.Hq * c->xs_stride);
   {
     // whole-pair launches: columns of a pair's row weights (list F may end in a partly filled tile), and of the logits that
     // do not fit the LDS.  Single calls take them where there is a pair for every compute unit: then no pair is split in any
@@ -552,9 +560,12 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
     const int cols = (N + 2 * TOK_PER_BLOCK - 1) / TOK_PER_BLOCK * TOK_PER_BLOCK;
     c->sc_stride = cols;
     c->spill_stride = std::max(0, cols - attn_step_lds_entries(D, G));
-    c->call_whole = c->es == 2 && !c->streamed && c->S_alloc == 1 && (int64_t)B * Hkv >= cus &&
+    c->call_whole = c->es == 2 && !c->streamed && c->S_alloc == 1 && (int64_t)B * Hkv >= c->cus &&
                     (size_t)cols + (size_t)G * c->spill_stride <= (size_t)G * c->xs_stride;
   }
+  step_route(c);
+  // (a whole-pair launch of one layer may need a little more than a split one: lists beyond some 20000 tokens)
+  ok = ok && dalloc(c, c->xs, std::max((size_t)B * v.Hq * c->xs_stride, c->step_whole ? step_floats_per_layer(c) : 0));
   const int launches = c->streamed ? 2 : 1;   // streamed T1: a second attention launch serves the frame
   ok = ok && dalloc(c, c->part_ml, (size_t)B * Hkv * c->S_alloc * launches * 2 * G);
   ok = ok && dalloc(c, c->part_o, (size_t)B * Hkv * c->S_alloc * launches * G * D);
@@ -753,7 +764,7 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   // Four tiles per workgroup, one per SIMD, until the pairs have all compute units; two waves of a SIMD that have one tile
   // each take nearly twice as long as one.  A chunk's workgroups leave more behind (every token's partials and logits), so
   // from nine tiles on theirs have a tile for every wave: one sequence of 16384 tokens, 12/2 heads, two tokens takes 33 us a
-  // call so and 45 with four tiles each; 300 tokens 16.2 and 14.4.
+  // call so and 45 with four tiles each; eight sequences of 300 tokens 16.2 and 14.4.
   const int S = std::max(1, std::min(c->S_alloc, m > 1 && n_wt > 8 ? (n_wt + nw - 1) / nw : (n_wt + 3) / 4));
   const int S2 = n_tiles_s > 0 ? std::max(1, std::min(c->S_alloc, (n_wt_s + 3) / 4)) : 0;
   AttnArgs a{};
@@ -768,9 +779,9 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   a.red = v.red ? v.red + lrows * v.Nmax : nullptr;
   a.red_w = c->cfg.redundancy_weight > 0.f ? c->cfg.redundancy_weight : 1.0f;
   a.cnt = v.cnt; a.score = v.score; a.xs = c->xs; a.part_ml = c->part_ml; a.part_o = c->part_o;
-  if (nl > 1) { a.xs = c->xs_step; a.part_ml = c->ml_step; a.part_o = c->po_step; }
+  if (nl > 1 && !whole) { a.xs = c->xs_step; a.part_ml = c->ml_step; a.part_o = c->po_step; }
   if (whole) { a.sc_stride = c->sc_stride; a.xs_stride = c->spill_stride; }
-  if (whole && step_launch) { a.xs = c->spill_step; a.sc = c->sc_step; }
+  if (whole && step_launch && c->sc_step) { a.xs = c->spill_step; a.sc = c->sc_step; }
   else if (whole) { a.sc = c->xs; a.xs = c->xs + (size_t)v.B * v.Hkv * c->sc_stride; }
   if (m > 1) { a.xs = c->xs_chunk; a.part_ml = c->ml_chunk; a.part_o = c->po_chunk; }
   if (noalloc) {
@@ -910,7 +921,7 @@ tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, c
       const int groups = (v.L - l + per_launch - 1) / per_launch;
       int nl = (v.L - l + groups - 1) / groups;
       for (int k = 0; k < nl; ++k)
-        if (waits(l + k)) { nl = std::max(k, std::min(nl, c->step_whole ? (255 + v.B * v.Hkv) / (v.B * v.Hkv) : 1)); break; }
+        if (waits(l + k)) { nl = std::max(k, std::min(nl, c->step_whole ? (c->cus - 1 + v.B * v.Hkv) / (v.B * v.Hkv) : 1)); break; }
       tkv_status s = attend_one(c, l, (const char*)q_all + l * q_stride, (char*)out_all + l * o_stride, 0, v.Hq, v.Hq, true,
                                 (hipStream_t)hip_stream, false, 1, nl, true);
       if (s != TKV_OK) return s;

@@ -4,6 +4,7 @@
 // Every attention launch is checked against the allocations alive: scratch that a kernel would write outside of them fails.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -32,7 +33,7 @@ static uintptr_t g_next = (uintptr_t)1 << 40;
 static hipError_t g_last = hipSuccess;
 static std::vector<Launch> g_launches;
 static std::string g_log;                           // A: device allocation, S: device synchronised, M: memset, L: launch
-static int g_allocs = 0, g_fail_at = -1, g_cus = 256;
+static int g_allocs = 0, g_fail_at = -1, g_fail_from = 1 << 30, g_cus = 256;
 static size_t g_fail_above = SIZE_MAX;
 static hipStream_t g_capturing = nullptr;
 static dim3 g_cfg_grid, g_cfg_block;
@@ -47,7 +48,7 @@ static bool inside(const void* p, size_t n) {
   --it;
   return (uintptr_t)p + n <= it->first + it->second;
 }
-static bool refused(size_t n) { return g_allocs++ == g_fail_at || n > g_fail_above; }
+static bool refused(size_t n) { const int k = g_allocs++; return k == g_fail_at || k >= g_fail_from || n > g_fail_above; }
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
@@ -229,6 +230,36 @@ static void allocations_before_use() {
     }
 }
 
+// The kind of launch that serves a decode step (whole pairs or split ones: two orders of addition) and the splits of a pair
+// follow from the cache's shape.  However little memory there is beyond what tkv_create must have, and in whatever prefetch
+// mode, only the number of layers per launch may change.
+static void route_follows_from_the_shape() {
+  for (auto& s : SHAPES) {
+    std::string kernel;
+    int S = 0, fewest = 1 << 30, most = 0;
+    for (int mode : {TKV_PREFETCH_WAIT, TKV_PREFETCH_LAZY})
+      for (int from = 1 << 30, total = 0; from > 0; from = from == 1 << 30 ? total - 1 : from - 1) {
+        tkv_config cfg = config(s[0], s[1], s[2], s[3], s[4], s[5]);
+        cfg.prefetch_mode = mode;
+        tkv_cache* c = nullptr;
+        g_fail_from = from; g_allocs = 0;
+        const tkv_status st = tkv_create(&cfg, &c);
+        if (from == 1 << 30) total = g_allocs;
+        if (st == TKV_ENOMEM && from < total) break;      // now it is memory that the cache must have
+        CHECK(st == TKV_OK);
+        fill(c, cfg, 60);
+        for (auto& l : step(c, cfg)) {
+          if (kernel.empty()) { kernel = l.kernel; S = l.a.S; }
+          CHECK(l.kernel == kernel && l.a.S == S);
+          fewest = std::min(fewest, l.a.nl); most = std::max(most, l.a.nl);
+        }
+        tkv_destroy(c);
+        g_fail_from = 1 << 30;
+      }
+    CHECK(most == 1 || fewest < most);                    // the refusals did bite
+  }
+}
+
 // A chunk's workgroups leave a partial per query token behind, and the finishing kernel merges a pair's one by one: no more
 // of them than have a (64-row) tile for each of their waves, but for lists of up to eight tiles.
 static void chunk_splits() {
@@ -252,6 +283,7 @@ int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_allocations") refused_allocations();
   else if (what == "allocations_before_use") allocations_before_use();
+  else if (what == "route_follows_from_the_shape") route_follows_from_the_shape();
   else if (what == "chunk_splits") chunk_splits();
   else { std::printf("no scenario %s\n", what.c_str()); return 2; }
   std::printf("%s: ok\n", what.c_str());

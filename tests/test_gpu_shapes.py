@@ -205,6 +205,69 @@ def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
 
 
 @pytest.mark.parametrize("shape", [
+    dict(n_layers=28, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100),                    # logits beyond the LDS
+    dict(n_layers=3, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=150, kv_dtype="f16"),       # list lengths from device counters
+    dict(n_layers=4, batch=64, n_q_heads=24, n_kv_heads=4, head_dim=128, context=90, t2_format="int4_g32"),   # WAIT: layers one by one
+    dict(n_layers=5, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700),                      # split pairs
+])
+def test_prop1_of_whole_steps(shape, monkeypatch):
+    """T1 placement, prefetch mode and the memory there is for a step's scratch change no bit of a decode step: the same rows
+    in T1 with attention reading old slots while the copies are in flight (LAZY), behind them (WAIT: small groups of
+    layers), with the rows in T0 all along, and with every allocation refused that the cache can do without (one layer per
+    launch).  Steps straddle two plans."""
+    import paper_2605_09490_amd as tkv
+    from tkv_synth import Workload
+    cfg = small_config(name="prop1", **{**dict(kv_dtype="bf16", decode_steps=6, k_window=16, sigma=1.0), **shape})
+    print(f"[case] {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    empty, pinned = torch.empty, []
+
+    def scarce(*a, **kw):                 # the pinned store is the last thing a cache must have
+        if kw.get("pin_memory"):
+            pinned.append(1)
+        elif pinned:
+            raise RuntimeError("refused")
+        return empty(*a, **kw)
+
+    def cache(mode, refuse=False):
+        with monkeypatch.context() as m:
+            if refuse:
+                m.setattr(torch, "empty", scarce)
+            return tkv.TieredKV(cfg.n_layers, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens,
+                                kv_dtype=cfg.kv_dtype, t2_format=cfg.t2_format, k_window=16, prefetch_mode=mode)
+
+    kv = {"lazy": cache("lazy"), "wait": cache("wait"), "all in T0": cache("lazy"), "scarce": cache("lazy", refuse=True)}
+    assert kv["scarce"].get_stats()["device_bytes"] < kv["lazy"].get_stats()["device_bytes"]
+    for l in range(cfg.n_layers):
+        k, v = wl.context_kv(l)
+        for c in kv.values():
+            c.append(l, k, v)
+    k_all, v_all, q_all = wl.decode_inputs(0, 6)
+    rng = np.random.default_rng(11)
+    tiers = rng.choice(4, size=(cfg.batch, cfg.context), p=(0.3, 0.4, 0.25, 0.05)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    for s in range(6):
+        outs = {n: c.decode_step(k_all[s], v_all[s], q_all[s]) for n, c in kv.items()}
+        scores = {n: c.get_scores().view(np.uint32) for n, c in kv.items()} if s != 2 else None   # (reading them waits)
+        for n in kv:
+            assert torch.equal(outs[n], outs["lazy"]), (s, n)
+            assert scores is None or np.array_equal(scores[n], scores["lazy"]), (s, n)
+        if s in (1, 3):
+            for n, c in kv.items():
+                c.set_tiers(np.where(tiers == 1, 0, tiers) if n == "all in T0" else tiers)
+                c.migrate()
+            swap = (tiers <= 1) & (rng.random(tiers.shape) < 0.3)
+            swap[:, :4] = False
+            swap[:, -16:] = False
+            tiers = np.where(swap, 1 - tiers, tiers).astype(np.uint8)
+    assert kv["wait"].get_stats()["attend_waits"] > 0
+    assert kv["lazy"].get_stats()["lazy_old_reads"] > 0
+    for c in kv.values():
+        c.close()
+
+
+@pytest.mark.parametrize("shape", [
     dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=97),
     dict(batch=130, n_q_heads=4, n_kv_heads=2, head_dim=64, context=129, t2_format="int4_g32", kv_dtype="f16"),   # list lengths from device counters
     dict(batch=32, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2600, sequences=2),                            # logits beyond the LDS
