@@ -409,10 +409,24 @@ tkv_status rehome_store(tkv_cache* c, int n, hipStream_t st) {
 // kinds of launch add in different orders, and neither T1 placement nor prefetch mode nor memory nor timing may change a bit.
 //  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a launch has STEP_WHOLE_PAIRS pairs or
 //    more: the logits stay on the chip, one float per row leaves it.  With fewer pairs most compute units would idle.
+//    With long lists the idle units of a partly filled round cost more than splitting does: beyond STEP_LONG_LIST tokens
+//    pairs are split if fewer than 60 % of a launch's units, round by round, would have one, and a layer has eight pairs
+//    or more (with fewer every layer takes its share of workgroups that leave a partial and little else).
 //  - else pairs are split as in a single call.
+// us a step with whole / split pairs (15 % int8 T2; the split launch also several layers at a time):
+//   pairs x heads   1500 tokens   4096        16384       32768         49152         65536
+//   96 x 1                                    187 / 160   404 / 288                   817 / 553
+//   96 x 5          35 / 55       68 / 124    225 / 220   445 / 400     672 / 551     887 / 742
+//   128 x 5                                               510 / 497
+//   160 x 5         38 / 77       75 / 186    281 / 344   578 / 617                   1168 / 1213
+//   264 x 4         61 / 97       131 / 240   530 / 518   1084 / 945    1639 / 1371   2019 / 1805
+//   384 x 5         73 / 156      156 / 426   624 / 815   1289 / 1480
+//   512 x 5         85 / 202      191 / 570   760 / 1086  1575 / 1921
+//   112 x 7, four pairs a layer   43 / 69     83 / 143    275 / 403     538 / 580     795 / 831     1053 / 1086
+//   128 x 7, four pairs a layer                           558 / 692                   1105 / 1196
 // Either way several layers per launch, as many as fit a scratch (step_scratch).
 constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
-constexpr int STEP_WHOLE_PAIRS = 96;
+constexpr int STEP_WHOLE_PAIRS = 96, STEP_LONG_LIST = 20480;
 size_t step_floats_per_layer(const tkv_cache* c) {
   const DevView& v = c->dv;
   const size_t pairs = (size_t)v.B * v.Hkv;
@@ -433,8 +447,10 @@ void step_route(tkv_cache* c) {
   if (c->streamed) return;
   c->step_whole = c->es == 2;
   c->step_layers = step_layers(c);
-  if (c->step_whole && (step_floats_per_layer(c) * sizeof(float) > STEP_WHOLE_SCRATCH_BYTES ||
-                        (int64_t)v.B * v.Hkv * c->step_layers < STEP_WHOLE_PAIRS)) {
+  if (!c->step_whole) return;
+  const int64_t pairs = (int64_t)v.B * v.Hkv * c->step_layers, units = (pairs + c->cus - 1) / c->cus * c->cus;
+  if (step_floats_per_layer(c) * sizeof(float) > STEP_WHOLE_SCRATCH_BYTES || pairs < STEP_WHOLE_PAIRS ||
+      (v.Nmax > STEP_LONG_LIST && v.B * v.Hkv >= 8 && pairs * 10 < units * 6)) {
     c->step_whole = c->call_whole;
     c->step_layers = step_layers(c);
   }

@@ -260,6 +260,27 @@ static void route_follows_from_the_shape() {
   }
 }
 
+// Whole pairs where they fill the chip, their lists are short or a layer has few; with other compute unit counts too.
+static void long_lists_fill_the_chip() {
+  const struct { int L, Hq, Hkv, n, cus; bool whole; } cases[] = {
+      {12, 40, 8, 16400, 256, true}, {12, 40, 8, 33000, 256, false}, {12, 40, 8, 20480, 256, true}, {12, 40, 8, 20481, 256, false},
+      {28, 28, 4, 33000, 256, true}, {28, 28, 4, 65600, 256, true}, {28, 28, 4, 131100, 256, false},
+      {20, 40, 8, 33000, 256, true}, {33, 32, 8, 33000, 256, false}, {48, 40, 8, 33000, 256, true}, {48, 40, 8, 65600, 256, false},
+      {32, 32, 8, 33000, 256, true}, {12, 40, 8, 33000, 128, true}, {32, 32, 8, 33000, 192, true}, {11, 40, 8, 1000, 256, false}};
+  for (auto& t : cases) {
+    tkv_config cfg = config(t.L, 1, t.Hq, t.Hkv, 128, t.n);
+    g_cus = t.cus;
+    tkv_cache* c = nullptr;
+    CHECK(tkv_create(&cfg, &c) == TKV_OK);
+    fill(c, cfg, 60);
+    step(c, cfg);
+    if ((count("k_attn_step") > 0) != t.whole) std::printf("%d layers, %d/%d heads, %d tokens, %d units\n", t.L, t.Hq, t.Hkv, t.n, t.cus);
+    CHECK((count("k_attn_step") > 0) == t.whole);
+    tkv_destroy(c);
+  }
+  g_cus = 256;
+}
+
 // A chunk's workgroups leave a partial per query token behind, and the finishing kernel merges a pair's one by one: no more
 // of them than have a (64-row) tile for each of their waves, but for lists of up to eight tiles.
 static void chunk_splits() {
@@ -284,6 +305,7 @@ int main(int argc, char** argv) {
   if (what == "refused_allocations") refused_allocations();
   else if (what == "allocations_before_use") allocations_before_use();
   else if (what == "route_follows_from_the_shape") route_follows_from_the_shape();
+  else if (what == "long_lists_fill_the_chip") long_lists_fill_the_chip();
   else if (what == "chunk_splits") chunk_splits();
   else { std::printf("no scenario %s\n", what.c_str()); return 2; }
   std::printf("%s: ok\n", what.c_str());
