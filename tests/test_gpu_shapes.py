@@ -158,6 +158,10 @@ def test_decode_step_equals_per_layer_calls():
     ("wait", "attention", dict(n_layers=4, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=200)),
     ("lazy", "redundancy", dict(n_layers=3, batch=9, n_q_heads=40, n_kv_heads=8, head_dim=128, context=31, kv_dtype="f16")),
     ("lazy", "attention", dict(n_layers=70, batch=1, n_q_heads=6, n_kv_heads=2, head_dim=64, context=65, t2_format="int4_g32")),   # two groups of layers
+    ("lazy", "vatp", dict(n_layers=25, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100, t2_format="int4_g32")),   # beyond the LDS: value norms
+    ("wait", "redundancy", dict(n_layers=13, batch=1, n_q_heads=48, n_kv_heads=8, head_dim=128, context=3700)),                  # ... the penalty
+    ("lazy", "combined", dict(n_layers=12, batch=1, n_q_heads=8, n_kv_heads=8, head_dim=128, context=300)),
+    ("lazy", "attention", dict(n_layers=6, batch=2, n_q_heads=32, n_kv_heads=8, head_dim=128, context=300, t2_format="int4_g32", kv_dtype="f16")),
 ])
 def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
     """A decode step's launches serve groups of layers, against per-layer calls: also right behind a re-tiering whose
@@ -271,6 +275,7 @@ def test_prop1_of_whole_steps(shape, monkeypatch):
     dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=97),
     dict(batch=130, n_q_heads=4, n_kv_heads=2, head_dim=64, context=129, t2_format="int4_g32", kv_dtype="f16"),   # list lengths from device counters
     dict(batch=32, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2600, sequences=2),                            # logits beyond the LDS
+    dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100, t2_format="int4_g32", sequences=2),    # ... the production batch's kernel
 ])
 def test_single_calls_with_a_pair_for_every_compute_unit(shape):
     """256 or more pairs: single calls take one workgroup per pair as a whole step does.  Outputs and scores against the
