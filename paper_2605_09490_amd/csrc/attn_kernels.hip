@@ -490,8 +490,8 @@ struct WaveLds {
   char* t; char* sk; char* sv; char* lt;   // tile buffer (K rows, then V rows, in turn), K scales, V scales, slot lists (2 x 64 ints)
   char* p;                                 // probabilities of the current tile (before the first tile: the query block)
   uint32_t ta, ska, sva, lta, pa;          // the same as LDS addresses
-  uint32_t lga; int lcap, lcap0;           // a workgroup that walks a whole pair: logits [G][lcap] in LDS; the columns from
-                                           // lcap0 on (the first tile that does not fit whole) are parked in memory
+  uint32_t lga; int lcap;                  // a workgroup that walks a whole pair: logits [G][lcap] in LDS; the columns from
+                                           // lcap (whole tiles) on are parked in memory
 };
 
 template <int SZ>
@@ -773,7 +773,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
             for (int h = 0; h < G; ++h) lds_wr32(w.lga + (uint32_t)(h * w.lcap + col) * 4u, __builtin_bit_cast(uint32_t, x[h]));
           }
         } else if (valid) {
-          float* sp = a.xs + ((size_t)(b * a.Hkv + kvh) * G) * a.xs_stride + (col - w.lcap0);
+          float* sp = a.xs + ((size_t)(b * a.Hkv + kvh) * G) * a.xs_stride + (col - w.lcap);
 #pragma unroll
           for (int h = 0; h < G; ++h) sp[(size_t)h * a.xs_stride] = x[h];
         }
@@ -1582,8 +1582,8 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
 // and a workgroup that has walked a pair's lists to their end knows the final softmax statistics of its heads.  So it
 // writes its output itself, and of the logits, which stay in the LDS, one float per row: the row's weights summed over
 // the group's heads.  That is what this kernel is for: it is bound by HBM, and written logits (G floats per row, 4-6 % of
-// the bytes) cost it a fifth of its time and their reading back another tenth (1.6 GB of rows stream in 237 us alone,
-// in 317 us with 90 MB of logits written beside them, whatever the shape of the stores).
+// the bytes) add a third to its time and their reading back another tenth (1.6 GB of rows stream in 237 us alone, in 317 us
+// with 90 MB of logits written beside them, whatever the shape of the stores).
 // Measured (14B shape, 48 layers, batch 8, 4112 tokens all at full precision): 960-1140 us a step, 6.0 TB/s, against
 // 5 x (243 + 23) us with split pairs, written logits and ten layers per launch.
 // The LDS holds eight 8 KB tile buffers (32 rows of 256 bytes; 64 KB in flight per compute unit stream as fast as 128 KB)
@@ -1622,7 +1622,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   w.t = sm_t + wave * TILE; w.p = sm_p + wave * SG::P;
   w.sk = sm_sc + wave * 2 * SG::SC; w.sv = w.sk + SG::SC; w.lt = sm_lt + wave * SG::LT;
   w.ta = lds_addr(w.t); w.pa = lds_addr(w.p); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
-  w.lga = lds_addr(sm_lg); w.lcap = LCAP; w.lcap0 = LCAP;
+  w.lga = lds_addr(sm_lg); w.lcap = LCAP;
   float* my_o = (float*)w.t;
 
   float o[G][EV], m_run[G], l_lane[G];
