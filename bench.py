@@ -193,7 +193,7 @@ def run_job(cfg, policy, mode, steps, warmup, profile_steps, label, rule=0, tigh
         st3 = gpu.get_stats()
         gpu.set_profile(0)
         launches = st3["attn_kernel_launches"] - st2["attn_kernel_launches"]
-        res.update({"kernel_launches": launches,
+        res.update({"kernel_launches": launches, "profile_steps": profile_steps,
                     "kernel_avg_us": (st3["attn_kernel_ms"] - st2["attn_kernel_ms"]) * 1e3 / max(launches, 1),
                     "finish_avg_us": (st3["attn_finish_ms"] - st2["attn_finish_ms"]) * 1e3 / max(launches, 1),
                     "call_avg_us_with_kernel_events": (st3["attn_call_ms"] - st2["attn_call_ms"]) * 1e3 / max(launches, 1)})
@@ -298,6 +298,15 @@ def cpu_baseline(cfg, res, budget_s=20.0, workers=None):
             "s_per_classify_event": classify_s}
 
 
+def attention_kernel(cfg, mode, res):
+    """Which launch the timed steps' attention went through: whole pairs (16-bit rows, 96 or more (layer, sequence, kv head)
+    pairs per launch, T1 not streamed) or split ones."""
+    if not res.get("kernel_launches"):
+        return None
+    layers = cfg.n_layers * res["profile_steps"] / res["kernel_launches"]
+    return "k_attn_step" if cfg.kv_dtype != "f32" and mode != "stream" and layers * cfg.batch * cfg.n_kv_heads >= 96 else "k_attn_tiered"
+
+
 def link_probe(launch_bytes):
     import torch
     import paper_2605_09490_amd as tkv
@@ -316,7 +325,7 @@ def link_probe(launch_bytes):
         gb = 4 * n / (time.perf_counter() - t0) / 1e9
         out[name + "_GBps"] = round(gb * (2 if name == "d2d_copy" else 1), 1)   # d2d: read + write
     del d2, h
-    # a bare read-only kernel with the attention kernel's launch shape: over 1 GiB, and over one launch's bytes
+    # a bare read-only kernel with the attention kernel's launch shape: over 1 GiB, and over one launch's bytes (1 GiB at most)
     big = torch.empty(1 << 30, dtype=torch.uint8, device="cuda").zero_()
     out["read_1GiB_GBps"] = round(tkv.probe_hbm_read(big, iters=4), 1)
     nb = min(big.numel(), max(1 << 20, int(launch_bytes) // 4096 * 4096))
@@ -562,10 +571,10 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(kernel_GBps, 1) if kernel_GBps else None, "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": round(kernel_GBps / HBM_PEAK_GBPS, 4) if kernel_GBps else None,
                      "traffic": measured_traffic(cfg.name),
-                     "kernel": "k_attn_step" if cfg.kv_dtype != "f32" else "k_attn_tiered", "avg_us": round(main_res.get("kernel_avg_us", 0), 2),
+                     "kernel": attention_kernel(cfg, args.mode, main_res), "avg_us": round(main_res.get("kernel_avg_us", 0), 2),
                      "algorithmic_bytes_per_launch": int(main_res.get("kernel_bytes_per_launch", 0)),
                      "launches_timed": main_res.get("kernel_launches"),
-                     "achievable": achievable,
+                     "achievable": achievable, "achievable_over_bytes": probe.get("read_one_launch_bytes"),
                      "frac_of_achievable": round(kernel_GBps / achievable, 4) if kernel_GBps and achievable else None,
                      "call": {"what": "one layer's share of a decode step (attention launch + score launch) as the timed region ran it: every "
                                       "decode step bracketed by one pair of HIP events on the compute stream, divided by its layer calls",
