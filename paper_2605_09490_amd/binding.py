@@ -174,9 +174,11 @@ class TieredKV:
 
             def _dev_alloc(nbytes, _ctx):
                 try:
-                    # the allocator keeps a pool per stream; a block of another stream's pool may still be in use there
-                    with torch.cuda.stream(self._call_stream):
+                    if self._call_stream is None:
                         t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+                    else:   # the allocator keeps a pool per stream; a block of another stream's pool may still be in use there
+                        with torch.cuda.stream(self._call_stream):
+                            t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
                 except RuntimeError as e:
                     self._alloc_error = f"device allocation of {int(nbytes)} bytes failed: {str(e)[:200]}"
                     return None
