@@ -220,12 +220,12 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
  * kv_dtype; out_all [n_layers, batch, n_q_heads, head_dim] out_dtype.  Same errors as the two calls.  All capacity and
  * state checks are made before anything is enqueued; when all layers are at the same length the new rows of every
  * layer go in with one launch and the attention of consecutive layers in groups (as many layers per launch as fit the
- * step's scratch of at most 256 MiB, which tkv_create takes if it can have it), so a later failure at layer l (a HIP error) leaves the
- * step's rows appended to ALL layers and only layers < l attended: finish the step with tkv_attend_and_score for
- * layers >= l, or destroy the handle.  A step of 96 or more (layer, sequence, kv head) pairs of 16-bit rows (not with lists
- * beyond 20480 tokens where that would leave much of the GPU idle) takes a launch of its own kind: its outputs and scores agree with the per-layer
- * calls' to binary32 rounding (the summation order differs), other steps' bit for bit.  The shape alone decides; T1
- * placement stays bit-invisible (Prop. 1). */
+ * step's scratch of at most 256 MiB, which tkv_create takes if it can have it), so a later failure at layer l (a HIP
+ * error) leaves the step's rows appended to ALL layers and only layers < l attended: finish the step with
+ * tkv_attend_and_score for layers >= l, or destroy the handle.  A step of 96 or more (layer, sequence, kv head) pairs
+ * of 16-bit rows takes a launch of its own kind (not with lists beyond 20480 tokens where that would leave much of the
+ * GPU idle): its outputs and scores agree with the per-layer calls' to binary32 rounding (the summation order
+ * differs), other steps' bit for bit.  The shape alone decides; T1 placement stays bit-invisible (Prop. 1). */
 tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, const void* q_all, void* out_all,
                            void* hip_stream);
 
