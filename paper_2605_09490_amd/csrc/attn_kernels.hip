@@ -25,17 +25,19 @@
 //                 into softmax weights, summed over all query heads in a fixed order, into score[b, pos]; the
 //                 Hq remaining workgroups merge the split outputs of one query head each into out[b, hq].
 //   attn_tiered_mc : the same launch for a chunk of query tokens (tkv_attend_and_score_chunk, 16-bit rows).  The
-//                 tokens ride as extra columns beside the G heads of the group (up to 32 columns per workgroup), so
-//                 a tile is fetched once for all of them: per tile a (64 rows x D) by (D x columns) product and its
+//                 tokens ride as extra columns beside the G heads of the group (up to 32 columns per workgroup, as many
+//                 groups of them as there are along grid z): per tile a (64 rows x D) by (D x columns) product and its
 //                 transpose-side twin for the output, which is a dense contraction and runs on the matrix cores
-//                 (16x16x32 instructions; code rows widened to 16-bit values in LDS first).  attn_finish_chunk
-//                 adds the tokens' weights to the scores in token order.
+//                 (16x16x32 instructions; code rows widened to 16-bit values in LDS first).  No logits are written:
+//                 attn_chunk_scores has the products once more and adds the weights to the scores.  binary32 rows: one
+//                 set of attn_tiered's workgroups per token, and attn_finish_chunk.
 // The tile boundaries, the wave assignment and the fp32 summation order depend only on the lists' logical order and
 // lengths, never on whether a row lives in the HBM pool or the staging buffer (both are one slot space), which is
 // what makes T1 placement bit-invisible (Prop. 1).  A decode step (one query token) uses no matrix instructions: the
 // launch is bound by HBM, and the per-row work is G dot products.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "tkv_internal.h"
@@ -866,13 +868,12 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
 }
 
 // ---- one wave on the matrix cores: tiles of list F with 16-bit rows ------------------------------------------------
-// The G query heads of the kv head are padded to the 16 columns of a 16x16x32 matrix instruction.
-//   logits  : C[entry][head] = K[entry][:] . q[head][:], 16 entries per instruction, D/32 instructions deep.  Lane
-//             (head = lane % 16, kb = lane / 16) ends up with the logits of entries 16*rb + 4*kb + 0..3 of its head,
+//   logits  : C[entry][column] = K[entry][:] . q[column][:], 16 entries per instruction, D/32 instructions deep.  Lane
+//             (column = lane % 16, kb = lane / 16) ends up with the logits of entries 16*rb + 4*kb + 0..3 of its column,
 //             which is exactly the layout of the left operand of the second product, so the probabilities never leave
 //             the registers.
-//   softmax : online per head; a lane's 16 entries of a tile, the maximum completed over the 4 lanes of the head.
-//   output  : O[head][d] += P[head][entry] * V[entry][d], 32 entries per instruction; the right operand needs, per
+//   softmax : online per column; a quarter of a tile's entries per lane, the maximum completed over the column's 4 lanes.
+//   output  : O[column][d] += P[column][entry] * V[entry][d], 32 entries per instruction; the right operand needs, per
 //             lane, the same column of 4 + 4 rows: a transposing LDS read delivers it.  P is fed as two 16-bit terms
 //             (leading bits and remainder), so the product carries 16 significant bits of every weight.
 // Rows still come in by direct-to-LDS loads of 1 KB (8 rows x 8 pieces of 16 bytes, 128 contiguous bytes per row).
@@ -891,11 +892,22 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(const u32x4& x, const u32x4& y, f
   else
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), c, 0, 0, 0);
 }
-// value of lane (lane ^ MASK)
-template <int MASK>
-__device__ __forceinline__ float lane_xor(float x, int lane) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((lane ^ MASK) << 2, __builtin_bit_cast(int, x)));
+// maximum / sum over the four lanes n, n + 16, n + 32, n + 48, in all of them
+__device__ __forceinline__ float quad_max(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  x = fmaxf(__builtin_bit_cast(float, (uint32_t)h[0]), __builtin_bit_cast(float, (uint32_t)h[1]));
+  const uint32_t v = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
+__device__ __forceinline__ float quad_sum(float x) {
+  x = add_swap32(x, x);
+  return add_swap16(x, x);
+}
+// quotient of small non-negative integers (below 2^13): exact, a conversion and a product instead of a division
+__device__ __forceinline__ int small_div(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+
 // A binary32 weight as a sum of 16-bit terms, each the leading bits (by truncation) of what the terms before it left.
 // bfloat16: three terms of 8 significant bits are the weight exactly.  binary16: two terms of 11 bits (22 of the 24);
 // the weights are taken times 2^P_SHIFT there, so that small ones stay clear of binary16's narrow exponent range
@@ -926,58 +938,55 @@ __device__ __forceinline__ void split_pair(float p0, float p1, uint32_t (&t)[PSp
   }
 }
 
-// 16 code values (one byte each, or two per byte) as 16-bit floating point: the matrix cores multiply them exactly
-// (a code + 128, or + 8, has at most 8 significant bits).  Two values per 32-bit word, low element first.
+// Code values (one byte each, or two per byte) as 16-bit floating point, sign-extended: at most 7 significant bits, so the
+// matrix cores multiply them exactly.  Two values per 32-bit word, low element first.
 template <int KT>
 __device__ __forceinline__ uint32_t pack16(float lo, float hi) {
   if constexpr (KT == KT_BF16) return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x07060302u);
   else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
 }
-__device__ __forceinline__ float ubyte_f(uint32_t w, int n) {    // byte n of w as a float (one conversion instruction)
-  return (float)((w >> (8 * n)) & 0xFFu);
-}
-// one word of int8 codes (4, as code + 128) -> two words; one word of int4 codes (8, as code + 8) -> four words
+__device__ __forceinline__ float sbyte_f(uint32_t w, int n) { return (float)(int8_t)(w >> (8 * n)); }              // byte n of w
+__device__ __forceinline__ float snib_f(uint32_t w, int n) { return (float)((int32_t)(w << (28 - 4 * n)) >> 28); }   // nibble n of w
+// one word of int8 codes (4) -> two words; one word of int4 codes (8) -> four words
 template <int KT>
 __device__ __forceinline__ void widen_int8(uint32_t w, uint32_t& o0, uint32_t& o1) {
-  w ^= 0x80808080u;
-  o0 = pack16<KT>(ubyte_f(w, 0), ubyte_f(w, 1));
-  o1 = pack16<KT>(ubyte_f(w, 2), ubyte_f(w, 3));
+  o0 = pack16<KT>(sbyte_f(w, 0), sbyte_f(w, 1));
+  o1 = pack16<KT>(sbyte_f(w, 2), sbyte_f(w, 3));
 }
 template <int KT>
 __device__ __forceinline__ u32x4 widen_int4(uint32_t w) {
-  w ^= 0x88888888u;
-  const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;    // elements 0, 2, 4, 6 and 1, 3, 5, 7
-  return u32x4{pack16<KT>(ubyte_f(lo, 0), ubyte_f(hi, 0)), pack16<KT>(ubyte_f(lo, 1), ubyte_f(hi, 1)),
-               pack16<KT>(ubyte_f(lo, 2), ubyte_f(hi, 2)), pack16<KT>(ubyte_f(lo, 3), ubyte_f(hi, 3))};
+  return u32x4{pack16<KT>(snib_f(w, 0), snib_f(w, 1)), pack16<KT>(snib_f(w, 2), snib_f(w, 3)),
+               pack16<KT>(snib_f(w, 4), snib_f(w, 5)), pack16<KT>(snib_f(w, 6), snib_f(w, 7))};
 }
 
-// M: F_BF16 / F_F16 (list F; the element type is KT's) or Q_INT8 / Q_INT4 (list Q).  NCB: blocks of 16 columns; a
-// column is one (query token, head of the group) pair, query-major, a.cq query tokens in all (a decode step: one).
+// M: F_BF16 / F_F16 (list F; the element type is KT's) or Q_INT8 / Q_INT4 (list Q).  NCB: blocks of 16 columns, the first
+// of them column c0 of the chunk's a.cq * a.G; a column is one (query token, head of the group) pair, query-major.
+// n_list: entries the launch's last token sees (list F: its earlier tokens see fewer); n_walk: those of them that one of
+// these columns sees.
 // Code rows (list Q) are fetched as they are stored (16-byte pieces, consecutive lanes along a row), and half a tile at
-// a time is widened to 16-bit values of code + OFF into the free upper half of the wave's tile buffer, in the layout the
+// a time is widened to 16-bit values into the free upper half of the wave's tile buffer, in the layout the
 // full-precision rows arrive in, where the same operand reads pick it up.  Scales stay outside the products: a K row's
-// scale multiplies its logits (per 32-element group: one product per group), a V row's scale its weights; the offset
-// comes out through the sums of the query elements and of the scaled weights.
-template <int D, int G, int KT, Mode M, int NCB>
-__device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds& w, int b, int jz, int kvh, int lane,
-                                               int tile0, int tstride, int n_list, const int* loc_list, int xs_tile0,
+// scale multiplies its logits (per 32-element group: one product per group), a V row's scale its weights.
+template <int D, int KT, Mode M, int NCB, bool LOG>
+__device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds& w, int b, int c0, int kvh, int lane,
+                                               int tile0, int tstride, int n_list, int n_walk, const int* loc_list, int xcol0,
                                                f32x4 (&o)[NCB][D / 16], float (&m_run)[NCB], float (&l_run)[NCB]) {
   static_assert(KT == KT_BF16 || KT == KT_F16, "16-bit operands");
   static_assert(D % 64 == 0, "head_dim in whole 128-byte row halves");
   constexpr bool IS_Q = (M == Q_INT8 || M == Q_INT4);
   constexpr int RB = 2 * D;                    // bytes per row as the matrix cores read it
+  constexpr int TR = 8192 / RB;                // rows per tile: 8 KB
+  constexpr int NRB = TR / 16, NTV = TR / 32;  // 16-entry blocks (logits), 32-entry steps (output)
   constexpr int KU = RB / 128;                 // 1 KB pieces per batch of 8 rows (operand layout)
   constexpr int NKS = D / 32, NDB = D / 16;    // instructions deep (logits), output column blocks
   constexpr int PB = 1024;
   constexpr int CRB = !IS_Q ? RB : (M == Q_INT8 ? D : D / 2);   // bytes per row as fetched
-  constexpr int NP = IS_Q ? CRB / 16 : 8 * KU;                  // 1 KB pieces per tile, K or V
-  constexpr int NPH = NP / 2;
+  constexpr int NP = TR * CRB / PB, NPH = NP / 2;               // 1 KB pieces per tile, K or V; of half a tile
   constexpr int LPR = CRB / 16, RPP = 64 / LPR;                 // list Q: lanes per row, rows per piece
   constexpr int SCD = (M == Q_INT8) ? 1 : (M == Q_INT4) ? D / 64 : 0;   // dwords of scales per row
-  constexpr int NGD = (M == Q_INT4) ? D / 32 : 1;               // scale groups along a row
-  constexpr float OFF = (M == Q_INT4) ? 8.f : 128.f;
-  constexpr uint32_t SCR = IS_Q ? 32 * RB : 0;                  // where the widened half tile sits
-  static_assert(NP >= 2 && (!IS_Q || 64 * CRB <= 32 * RB), "two halves; code rows leave the upper half of the buffer free");
+  constexpr int HR = TR / 2;                                    // rows widened at a time (list Q)
+  constexpr uint32_t SCR = IS_Q ? HR * RB : 0;                  // where the widened half tile sits
+  static_assert(NP >= 2 && (!IS_Q || TR * CRB <= HR * RB), "two halves; code rows leave the upper half of the buffer free");
   const int g = lane >> 3, r = lane & 7;       // F fetch side: row of a batch, piece of the row's 128 bytes
   const int n = lane & 15, kb = lane >> 4;     // operand side
 
@@ -992,29 +1001,13 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     rsk = make_rsrc(a.s2K + rows * a.sb, (uint32_t)a.cap2 * a.sb); rsv = make_rsrc(a.s2V + rows * a.sb, (uint32_t)a.cap2 * a.sb);
   }
   const __amdgpu_buffer_rsrc_t rl = make_rsrc(loc_list, (uint32_t)a.Nmax * 4u);
-  if (tile0 * 64 >= n_list) return;
+  if (tile0 * TR >= n_walk) return;
 
+  auto issue_loc = [&](int par, int tile) {
+    if (TR == 64 || lane < TR) dma<4>(rl, w.lt + par * (TR * 4), (uint32_t)(tile * TR + lane) * 4u, 0);
+  };
   // the first tile's slot list before anything else (requests are served in the order they were made)
-  dma<4>(rl, w.lt, (uint32_t)(tile0 * 64 + lane) * 4u, 0);
-
-  // columns of this lane: (query token, head); right operand of the logits: elements 32*ks + 8*kb .. +7 of the
-  // column's query vector (zeros for a column past the last)
-  const int ncol = a.cq * G;
-  bool live[NCB];
-  int n_seen[NCB];                             // list entries the column's query may see (the chunk's later tokens are cut off list F)
-  size_t xrow[NCB];
-  u32x4 qreg[NCB][NKS];
-#pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) {
-    const int col = 16 * cb + n, jq = col / G, h = col % G;
-    live[cb] = col < ncol;
-    n_seen[cb] = IS_Q ? n_list : n_list - (live[cb] ? a.cq - 1 - jq : 0);
-    const int qi = live[cb] ? jq * a.Hq + kvh * G + h : kvh * G;
-    xrow[cb] = xs_at(a, (b * a.n_q + jz) * a.cq + (live[cb] ? jq : 0), kvh * G + (live[cb] ? h : 0), 4 * kb);
-    const u32x4* qp = (const u32x4*)((const char*)a.q + (((size_t)b * a.q_bs + (size_t)jz * a.cq * a.Hq + qi) * D + 8 * kb) * 2);
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qreg[cb][ks] = live[cb] ? qp[ks * 4] : u32x4{0u, 0u, 0u, 0u};
-  }
+  issue_loc(0, tile0);
 
   // F fetch side.  Batch i holds entries 8*i + g; its K rows are rotated by 2*(g/2) + (i & 1) pieces, its V rows by g & 6.
   const uint32_t kcol0 = (uint32_t)((r + 2 * (g >> 1)) & 7) * 16u, kcol1 = (uint32_t)((r + 2 * (g >> 1) + 1) & 7) * 16u;
@@ -1037,6 +1030,33 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     for (int dl = 0; dl < 4; ++dl)
       v_rd[dl] = w.ta + SCR + (uint32_t)(ii * KU * PB) + (uint32_t)(8 * gg + ((2 * dl - (gg & 6)) & 7) + (qq >> 1)) * 16u + (uint32_t)(qq & 1) * 8u;
   }
+
+  // The columns' query vectors, right operand of the logits: fetched like K rows (a column past the last: zeros) through
+  // the tile buffer, where they arrive with the slot list, and read from there as K operands are.
+  int n_seen[NCB];                             // list entries the column's query may see (the chunk's later tokens are cut off list F)
+  size_t xrow[NCB];                            // LOG: where the column's logits go
+  bool live[NCB];
+  u32x4 qreg[NCB][NKS];
+  {
+    const int ncol = a.cq * a.G;
+    const __amdgpu_buffer_rsrc_t rq = make_rsrc((const char*)a.q + (size_t)b * a.q_bs * RB, (uint32_t)(a.cq * a.Hq) * RB);
+    const float inv_g = 1.0f / (float)a.G;
+#pragma unroll
+    for (int i = 0; i < 2 * NCB; ++i) {
+      const int col = c0 + 8 * i + g, jq = small_div(col, inv_g);
+      const uint32_t off = (col < ncol ? (uint32_t)(jq * a.Hq + kvh * a.G + (col - jq * a.G)) : 0x00ffffffu) * (uint32_t)RB + ((i & 1) ? kcol1 : kcol0);
+#pragma unroll
+      for (int j = 0; j < KU; ++j) dma<16>(rq, w.t + (i * KU + j) * PB, off + (uint32_t)j * 128u, 0);
+    }
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const int col = c0 + 16 * cb + n;
+      const int jq = small_div(col, inv_g);
+      live[cb] = col < ncol;
+      n_seen[cb] = IS_Q || !live[cb] ? n_list : n_list - (a.cq - 1 - jq);
+      if constexpr (LOG) xrow[cb] = live[cb] ? xs_at(a, b * a.cq + jq, kvh * a.G + (col - jq * a.G), xcol0 + 4 * kb) : 0;
+    }
+  }
   // list Q: the lane's piece of a code row is widened and stored where the operand reads expect it.  Piece sl of a
   // half tile holds the half's entries RPP*sl + lane/LPR; the lane's 16 bytes are CPL 16-byte pieces of the wide row.
   constexpr int CPL = IS_Q ? RB / CRB : 1;
@@ -1045,32 +1065,50 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     const int rot = v_side ? (gg & 6) : 2 * (gg >> 1) + (i & 1);
     return w.ta + SCR + (uint32_t)((i * KU + (cc >> 3)) * PB) + (uint32_t)(8 * gg + (((cc & 7) - rot) & 7)) * 16u;
   };
+  auto widen = [&](const u32x4 (&cu)[NPH], bool v_side) {
+#pragma unroll
+    for (int sl = 0; sl < NPH; ++sl) {
+      if constexpr (M == Q_INT8) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          uint32_t w0, w1, w2, w3;
+          widen_int8<KT>(elem(cu[sl], 2 * k), w0, w1);
+          widen_int8<KT>(elem(cu[sl], 2 * k + 1), w2, w3);
+          lds_wr128<0>(wide_addr(sl, k, v_side), u32x4{w0, w1, w2, w3});
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) lds_wr128<0>(wide_addr(sl, k, v_side), widen_int4<KT>(elem(cu[sl], k)));
+      }
+    }
+  };
 
-  constexpr int NLK = IS_Q ? NP : 8;
+  constexpr int NLK = IS_Q ? NP : TR / 8;
   int lk[NLK], lrow = 0;                       // slots of the rows this lane fetches next (K side), and of entry `lane`
   auto read_locs = [&](int par, int nvalid) {
-    const uint32_t base = w.lta + (uint32_t)par * 256u;
-    if (nvalid < 64) {                                   // wave-uniform: a list's last tile
-      if (lane >= nvalid) lds_wr32(base + (uint32_t)lane * 4u, 0xffffffffu);   // no row: fetches land as zeros
+    const uint32_t base = w.lta + (uint32_t)par * (TR * 4u);
+    if (nvalid < TR) {                                   // wave-uniform: a list's last tile
+      if (lane >= nvalid && lane < TR) lds_wr32(base + (uint32_t)lane * 4u, 0xffffffffu);   // no row: fetches land as zeros
     }
     uint32_t t[NLK], me = 0;
     if constexpr (!IS_Q) {
-      static_for<8>([&](auto ic) { constexpr int i = decltype(ic)::value; t[i] = lds_rd32<i * 32>(base + (uint32_t)g * 4u); });
+      static_for<NLK>([&](auto ic) { constexpr int i = decltype(ic)::value; t[i] = lds_rd32<i * 32>(base + (uint32_t)g * 4u); });
     } else {
       static_for<NP>([&](auto ic) { constexpr int i = decltype(ic)::value; t[i] = lds_rd32<i * RPP * 4>(base + (uint32_t)(lane / LPR) * 4u); });
-      me = lds_rd32<0>(base + (uint32_t)lane * 4u);
+      me = lds_rd32<0>(base + (uint32_t)(lane & (TR - 1)) * 4u);
     }
     lds_wait(); tie(t); tie(me);
 #pragma unroll
     for (int i = 0; i < NLK; ++i) lk[i] = (int)t[i];
     lrow = (int)me;
   };
-  auto issue_loc = [&](int par, int tile) { dma<4>(rl, w.lt + par * 256, (uint32_t)(tile * 64 + lane) * 4u, 0); };
   auto issue_scales = [&]() {                            // K scales, then V scales, of the entry `lane`
+    if (TR == 64 || lane < TR) {
 #pragma unroll
-    for (int j = 0; j < SCD; ++j) dma<4>(rsk, w.sk + j * 256, (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+      for (int j = 0; j < SCD; ++j) dma<4>(rsk, w.sk + j * (TR * 4), (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
 #pragma unroll
-    for (int j = 0; j < SCD; ++j) dma<4>(rsv, w.sv + j * 256, (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+      for (int j = 0; j < SCD; ++j) dma<4>(rsv, w.sv + j * (TR * 4), (uint32_t)lrow * (uint32_t)a.sb + j * 4u, 0);
+    }
   };
   auto issue_k_piece = [&](int s) {
     if constexpr (!IS_Q) {                               // (batch s / KU, row half s % KU)
@@ -1081,34 +1119,30 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     }
   };
 
-  wait_vm<0>();                                          // the list is in (and the query vectors)
-  read_locs(0, n_list - tile0 * 64);
+  wait_vm<0>();                                          // the list and the query vectors are in
+  read_locs(0, n_walk - tile0 * TR);
+  static_for<NCB>([&](auto cc) {
+    constexpr int cb = decltype(cc)::value;
+    static_for<NKS>([&](auto kc) { constexpr int ks = decltype(kc)::value; qreg[cb][ks] = lds_rd128<(2 * cb * KU + (ks >> 1)) * PB>(k_rd[ks & 1] - SCR); });
+  });
+  lds_wait();
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) tie(qreg[cb]);
   issue_loc(1, tile0 + tstride);
   issue_scales();
 #pragma unroll
   for (int s = 0; s < NP; ++s) issue_k_piece(s);
-
-  // sums of the query elements, per scale group (the codes' offset comes out through them): a product with ones
-  float qsum[NCB][NGD];
-  if constexpr (IS_Q) {
-    const uint32_t one2 = KT == KT_BF16 ? 0x3f803f80u : 0x3c003c00u;
-    const u32x4 ones = u32x4{one2, one2, one2, one2};
+  // the pair's first wave leaves the operand as it is for the score launch, which then reads it in lane order
+  if (!LOG && !IS_Q && tile0 == 0) {
+    const int blocks = (a.cq * a.G + 15) / 16;
+    u32x4* pk = (u32x4*)a.xs + ((size_t)(b * a.Hkv + kvh) * blocks + c0 / 16) * (NKS * 64) + lane;
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      float tot = 0.f;
+    for (int cb = 0; cb < NCB; ++cb)
+      if (c0 / 16 + cb < blocks) {
 #pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) {
-        const f32x4 s4 = mfma_16x16x32<KT>(ones, qreg[cb][ks], f32x4{0.f, 0.f, 0.f, 0.f});
-        if constexpr (M == Q_INT4) qsum[cb][ks] = s4[0]; else tot += s4[0];
+        for (int ks = 0; ks < NKS; ++ks) pk[(cb * NKS + ks) * 64] = qreg[cb][ks];
       }
-      if constexpr (M == Q_INT8) qsum[cb][0] = tot;
-    }
   }
-  float osub[NCB][NGD];                                  // sums of the scaled weights, per lane (list Q)
-#pragma unroll
-  for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-    for (int gd = 0; gd < NGD; ++gd) osub[cb][gd] = 0.f;
 
   int par = 1;                                           // LDS half that holds the next tile's slot list
   auto tile_body = [&](int tile, auto more_c) {
@@ -1128,17 +1162,17 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     };
     if constexpr (MORE) {
       wait_vm<2 * SCD + NP>();                           // younger than the next list: this tile's scales and K pieces
-      read_locs(par, n_list - (tile + tstride) * 64);
+      read_locs(par, n_walk - (tile + tstride) * TR);
       issue_loc(par ^ 1, tile + 2 * tstride);
     }
     // -- logits, 16 entries at a time
-    f32x4 c[NCB][4];
+    f32x4 c[NCB][NRB];
     auto logits_of = [&](auto rc, const u32x4 (&ka)[NKS]) {    // rc: the 16-entry block
       constexpr int rb = decltype(rc)::value;
       if constexpr (M == Q_INT4) {
         // one product per scale group; the four entries' scales of dword ks/2, half ks & 1
         u32x4 sc[SCD];
-        static_for<SCD>([&](auto jc) { constexpr int j = decltype(jc)::value; sc[j] = lds_rd128<j * 256 + rb * 64>(w.ska + (uint32_t)kb * 16u); });
+        static_for<SCD>([&](auto jc) { constexpr int j = decltype(jc)::value; sc[j] = lds_rd128<j * (TR * 4) + rb * 64>(w.ska + (uint32_t)kb * 16u); });
         lds_wait(); tie(sc);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
@@ -1147,25 +1181,24 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           for (int ks = 0; ks < NKS; ++ks) {
             const f32x4 part = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j] = fmaf(half_of(elem(sc[ks >> 1], j), ks & 1), fmaf(-OFF, qsum[cb][ks], part[j]), acc[j]);
+            for (int j = 0; j < 4; ++j) acc[j] = fmaf(half_of(elem(sc[ks >> 1], j), ks & 1), part[j], acc[j]);
           }
           c[cb][rb] = acc;
         }
       } else {
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int cb = 0; cb < NCB; ++cb) c[cb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int ks = 0; ks < NKS; ++ks) acc = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], acc);
-          c[cb][rb] = acc;
-        }
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) c[cb][rb] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], c[cb][rb]);
         if constexpr (M == Q_INT8) {
           u32x4 sc = lds_rd128<rb * 64>(w.ska + (uint32_t)kb * 16u);
           lds_wait(); tie(sc);
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) c[cb][rb][j] = elem_f(sc, j) * fmaf(-OFF, qsum[cb][0], c[cb][rb][j]);
+            for (int j = 0; j < 4; ++j) c[cb][rb][j] *= elem_f(sc, j);
         }
       }
     };
@@ -1182,12 +1215,12 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         });
       };
       read_k(std::integral_constant<int, 0>{}, ka[0]);
-      static_for<4>([&](auto rc) {
+      static_for<NRB>([&](auto rc) {
         constexpr int rb = decltype(rc)::value;
         lds_wait(); tie(ka[rb & 1]);
 #pragma unroll
         for (int v = 2 * rb * KU; v < (2 * rb + 2) * KU; ++v) issue_v_piece(v);
-        if constexpr (rb + 1 < 4) read_k(std::integral_constant<int, (rb + 1 < 4 ? rb + 1 : 3)>{}, ka[(rb + 1) & 1]);
+        if constexpr (rb + 1 < NRB) read_k(std::integral_constant<int, (rb + 1 < NRB ? rb + 1 : NRB - 1)>{}, ka[(rb + 1) & 1]);
         logits_of(rc, ka[rb & 1]);
       });
     } else {
@@ -1201,22 +1234,8 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         lds_wait(); tie(cu);
 #pragma unroll
         for (int v = hf * NPH; v < (hf + 1) * NPH; ++v) issue_v_piece(v);
-#pragma unroll
-        for (int sl = 0; sl < NPH; ++sl) {
-          if constexpr (M == Q_INT8) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-              uint32_t w0, w1, w2, w3;
-              widen_int8<KT>(elem(cu[sl], 2 * k), w0, w1);
-              widen_int8<KT>(elem(cu[sl], 2 * k + 1), w2, w3);
-              lds_wr128<0>(wide_addr(sl, k, false), u32x4{w0, w1, w2, w3});
-            }
-          } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) lds_wr128<0>(wide_addr(sl, k, false), widen_int4<KT>(elem(cu[sl], k)));
-          }
-        }
-        static_for<2>([&](auto rlc) {
+        widen(cu, false);
+        static_for<NRB / 2>([&](auto rlc) {
           constexpr int rl2 = decltype(rlc)::value;
           u32x4 ka[NKS];
           static_for<NKS>([&](auto kc) {
@@ -1224,46 +1243,54 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
             ka[ks] = lds_rd128<(rl2 * 2 * KU + (ks >> 1)) * PB>(k_rd[ks & 1]);
           });
           lds_wait(); tie(ka);
-          logits_of(std::integral_constant<int, 2 * hf + rl2>{}, ka);
+          logits_of(std::integral_constant<int, NRB / 2 * hf + rl2>{}, ka);
         });
       });
     }
     // -- online softmax: the lane has entries 16*rb + 4*kb + j of its column
-    float p[NCB][4][4];
+    float p[NCB][NRB][4];
     {
-      const int e0 = tile * 64 + 4 * kb;
+      const int e0 = tile * TR + 4 * kb;
+      const bool edge = (tile + 1) * TR > n_list - (IS_Q ? 0 : a.cq - 1);   // wave-uniform: some column does not see the whole tile
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
         float mx = -INFINITY;
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
-          f32x4 x;
+        for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            x[j] = (e0 + 16 * rb + j < n_seen[cb]) ? c[cb][rb][j] * a.softmax_scale : -INFINITY;
-            p[cb][rb][j] = x[j];
-            mx = fmaxf(mx, x[j]);
-          }
-          if (live[cb]) *(f32x4*)(a.xs + xrow[cb] + (size_t)(xs_tile0 + tile) * 64 + 16 * rb) = x;
+          for (int j = 0; j < 4; ++j) p[cb][rb][j] = c[cb][rb][j] * a.softmax_scale;
+        if (edge) {
+#pragma unroll
+          for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) p[cb][rb][j] = (e0 + 16 * rb + j < n_seen[cb]) ? p[cb][rb][j] : -INFINITY;
         }
-        mx = fmaxf(mx, lane_xor<16>(mx, lane));
-        mx = fmaxf(mx, lane_xor<32>(mx, lane));
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) mx = fmaxf(mx, p[cb][rb][j]);
+        if constexpr (LOG) {
+          if (live[cb]) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+              *(f32x4*)(a.xs + xrow[cb] + (size_t)tile * TR + 16 * rb) = f32x4{p[cb][rb][0], p[cb][rb][1], p[cb][rb][2], p[cb][rb][3]};
+          }
+        }
         // m_run starts at -inf: corr = exp2(-inf) = 0 against zero accumulators.  A tile of which the column sees
         // nothing (an early token of a chunk, the list's last tile) leaves mn at -inf: nothing to add, nothing to rescale.
-        const float mn = fmaxf(m_run[cb], mx);
+        const float mn = fmaxf(m_run[cb], quad_max(mx));
         const float corr = mn > -INFINITY ? __builtin_amdgcn_exp2f((m_run[cb] - mn) * LOG2E) : 1.0f;
+        const float ms = mn > -INFINITY ? mn : 0.f;      // (all weights are exp2(-inf) = 0 then)
         float ps = 0.f;
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb)
+        for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            p[cb][rb][j] = mn > -INFINITY ? __builtin_amdgcn_exp2f(fmaf(p[cb][rb][j] - mn, LOG2E, PSplit<KT>::P_SHIFT)) : 0.f;
+            p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(p[cb][rb][j] - ms, LOG2E, PSplit<KT>::P_SHIFT));
             ps += p[cb][rb][j];
           }
         l_run[cb] = fmaf(l_run[cb], corr, ps);
         m_run[cb] = mn;
-#pragma unroll
-        for (int gd = 0; gd < NGD; ++gd) osub[cb][gd] *= corr;
         // the output accumulators of this lane belong to columns 4*kb + j: their factors come from those columns'
         // lanes; once the maxima have settled nothing needs rescaling (x * 1.0f is exact)
         if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {
@@ -1278,22 +1305,22 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         }
       }
     }
-    // -- output: 32 entries per instruction; half a tile of V rows that has been read is replaced by K pieces
+    // -- output: 32 entries per instruction; V rows that have been read are replaced by K pieces
     __builtin_amdgcn_s_setprio(MORE ? 2 : 0);
     constexpr int NT = PSplit<KT>::N;
     // V scales of the tile: the 4 entries' of each 16-entry block (all older than the K pieces: they are in)
-    u32x4 vsc[IS_Q ? SCD : 1][4];
+    u32x4 vsc[IS_Q ? SCD : 1][NRB];
     if constexpr (IS_Q) {
       static_for<SCD>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        static_for<4>([&](auto rc) { constexpr int rb = decltype(rc)::value; vsc[j][rb] = lds_rd128<j * 256 + rb * 64>(w.sva + (uint32_t)kb * 16u); });
+        static_for<NRB>([&](auto rc) { constexpr int rb = decltype(rc)::value; vsc[j][rb] = lds_rd128<j * (TR * 4) + rb * 64>(w.sva + (uint32_t)kb * 16u); });
       });
       lds_wait();
 #pragma unroll
       for (int j = 0; j < SCD; ++j) tie(vsc[j]);
       if constexpr (MORE) issue_scales();                // both scale regions are free: the next tile's
     }
-    // weights of the half's 32 entries as operand terms; list Q: times the V row's scale (of scale group gd)
+    // weights of 32 entries as operand terms; list Q: times the V row's scale (of scale group gd)
     auto weights = [&](auto tc, int cb, int gd, u32x4 (&pt)[NT]) {
       constexpr int t = decltype(tc)::value;
       float pw[2][4];
@@ -1304,7 +1331,6 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           float v = p[cb][2 * t + r2][j];
           if constexpr (M == Q_INT8) v *= elem_f(vsc[0][2 * t + r2], j);
           if constexpr (M == Q_INT4) v *= half_of(elem(vsc[gd >> 1][2 * t + r2], j), gd & 1);
-          if constexpr (IS_Q) osub[cb][gd] += v;
           pw[r2][j] = v;
         }
       uint32_t s0[NT], s1[NT], s2[NT], s3[NT];
@@ -1315,47 +1341,55 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
 #pragma unroll
       for (int i = 0; i < NT; ++i) pt[i] = u32x4{s0[i], s1[i], s2[i], s3[i]};
     };
-    static_for<2>([&](auto tc) {
-      constexpr int t = decltype(tc)::value;
+    // list Q: half a tile of V codes (hf) is widened, its place refilled with the next tile's K pieces
+    auto widen_v = [&](auto hc) {
+      constexpr int hf = decltype(hc)::value;
       // younger than this half's V pieces: the other half's, the next tile's scales, the K pieces issued after the first half
-      wait_vm<NPH * (1 - t) + X * (2 * SCD + t * NPH)>();
-      if constexpr (IS_Q) {
-        u32x4 cu[NPH];
-        static_for<NPH>([&](auto sc) { constexpr int sl = decltype(sc)::value; cu[sl] = lds_rd128<(t * NPH + sl) * PB>(w.ta + (uint32_t)lane * 16u); });
-        lds_wait(); tie(cu);
-        if constexpr (MORE) {
+      wait_vm<NPH * (1 - hf) + X * (2 * SCD + hf * NPH)>();
+      u32x4 cu[NPH];
+      static_for<NPH>([&](auto sc) { constexpr int sl = decltype(sc)::value; cu[sl] = lds_rd128<(hf * NPH + sl) * PB>(w.ta + (uint32_t)lane * 16u); });
+      lds_wait(); tie(cu);
+      if constexpr (MORE) {
 #pragma unroll
-          for (int s = t * NPH; s < (t + 1) * NPH; ++s) issue_k_piece(s);
-        }
-#pragma unroll
-        for (int sl = 0; sl < NPH; ++sl) {
-          if constexpr (M == Q_INT8) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-              uint32_t w0, w1, w2, w3;
-              widen_int8<KT>(elem(cu[sl], 2 * k), w0, w1);
-              widen_int8<KT>(elem(cu[sl], 2 * k + 1), w2, w3);
-              lds_wr128<0>(wide_addr(sl, k, true), u32x4{w0, w1, w2, w3});
-            }
-          } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) lds_wr128<0>(wide_addr(sl, k, true), widen_int4<KT>(elem(cu[sl], k)));
-          }
-        }
+        for (int s = hf * NPH; s < (hf + 1) * NPH; ++s) issue_k_piece(s);
       }
-      constexpr int RB0 = IS_Q ? 0 : 2 * t;              // the widened half sits at the start of its area
+      widen(cu, true);
+    };
+    static_for<NTV>([&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      constexpr int NPV = NP / NTV;                      // V pieces of this step
       u32x2 vv[2][NDB];
-      static_for<2>([&](auto r2c) {
-        constexpr int r2 = decltype(r2c)::value;
+      auto read_vv = [&](auto rc, auto bc) {             // 16 entries (rc of the step), which sit bc 16-row blocks into their area
+        constexpr int r2 = decltype(rc)::value, rb = decltype(bc)::value;
         static_for<NDB>([&](auto dc) {
           constexpr int db = decltype(dc)::value;
-          vv[r2][db] = lds_rd64_tr16<((RB0 + r2) * 2 * KU + (db >> 2)) * PB>(v_rd[db & 3]);
+          vv[r2][db] = lds_rd64_tr16<(rb * 2 * KU + (db >> 2)) * PB>(v_rd[db & 3]);
         });
-      });
-      lds_wait(); tie(vv[0]); tie(vv[1]);
-      if constexpr (!IS_Q && MORE) {
+      };
+      constexpr std::integral_constant<int, 0> I0{};
+      constexpr std::integral_constant<int, 1> I1{};
+      if constexpr (!IS_Q) {
+        // younger than this step's V pieces: the later steps', the next tile's K pieces so far
+        wait_vm<NPV * (NTV - 1 - t) + X * t * NPV>();
+        read_vv(I0, std::integral_constant<int, 2 * t>{});
+        read_vv(I1, std::integral_constant<int, 2 * t + 1>{});
+        lds_wait(); tie(vv[0]); tie(vv[1]);
+        if constexpr (MORE) {
 #pragma unroll
-        for (int s = t * NPH; s < (t + 1) * NPH; ++s) issue_k_piece(s);
+          for (int s = t * NPV; s < (t + 1) * NPV; ++s) issue_k_piece(s);
+        }
+      } else if constexpr (NTV == 2) {                   // a half tile is a step
+        widen_v(tc);
+        read_vv(I0, I0);
+        read_vv(I1, I1);
+        lds_wait(); tie(vv[0]); tie(vv[1]);
+      } else {                                           // a half tile is 16 entries
+        widen_v(I0);
+        read_vv(I0, I0);
+        lds_wait(); tie(vv[0]);
+        widen_v(I1);
+        read_vv(I1, I0);
+        lds_wait(); tie(vv[1]);
       }
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
@@ -1374,28 +1408,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   };
 
   int tile = tile0;
-  for (; (tile + tstride) * 64 < n_list; tile += tstride) tile_body(tile, std::true_type{});
+  for (; (tile + tstride) * TR < n_walk; tile += tstride) tile_body(tile, std::true_type{});
   tile_body(tile, std::false_type{});
 
-  if constexpr (IS_Q) {
-    // the codes went in as code + OFF: take OFF times the sum of the scaled weights back out, per column (the
-    // accumulators of this lane belong to columns 4*kb + j)
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-      for (int gd = 0; gd < NGD; ++gd) {
-        float s = osub[cb][gd];
-        s += lane_xor<16>(s, lane);
-        s += lane_xor<32>(s, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float sj = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((4 * kb + j) << 2, __builtin_bit_cast(int, s)));
-#pragma unroll
-          for (int db = 0; db < NDB; ++db)
-            if (NGD == 1 || db / 2 == gd) o[cb][db][j] = fmaf(-OFF, sj, o[cb][db][j]);
-        }
-      }
-  }
   if constexpr (PSplit<KT>::P_SHIFT != 0.f) {
     const float back = __builtin_amdgcn_exp2f(-PSplit<KT>::P_SHIFT);
 #pragma unroll
@@ -1704,44 +1719,47 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   }
 }
 
-// ---- the same launch for 16-bit rows: every wave on the matrix cores ------------------------------------------------
-// Eight waves per workgroup whatever the group size (the accumulators are 16 columns wide either way), a 64-row tile
-// buffer each; with a second block of 16 columns (chunks of query tokens) the registers allow four.  A wave's result
-// arrives complete (no row-group partials): [column][D] parked in its tile buffer.
-constexpr int mc_waves(int ncb) { return ncb == 1 ? 8 : 4; }
-template <int D, int G, int KT, int NCB>
-__global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_tiered_mc(const AttnArgs a) {
-  constexpr int NW = mc_waves(NCB), RB = 2 * D, TILE_BYTES = 64 * RB;
+// ---- a chunk of query tokens, 16-bit rows: every wave on the matrix cores -------------------------------------------
+// The chunk's a.cq * a.G columns go in groups of 16 * NCB along grid z (x batch), whatever token a group begins with, so
+// that one launch serves them all: 13 tokens of seven heads are three groups of 32 columns.  Eight waves per workgroup, two
+// per SIMD, with 8 KB tiles.  A wave's result arrives complete (no row-group partials): [column][D], parked in the LDS.
+// LOG: one group of columns; the logits go to memory and attn_finish_chunk reads them.  Else no logits leave the kernel: a float per row and column
+// is a quarter of the rows' bytes at 32 columns and costs more than that (stores beside the row stream), while the score
+// launch below has the products again for half of the rows' bytes, once for all columns.
+constexpr int MC_WAVES = 8;
+constexpr int mc_tile_rows(int D) { return 8192 / (2 * D); }
+constexpr int chunk_blocks(int ncol) { return ncol <= 16 ? 1 : 2; }      // of 16 columns, per workgroup
+// With one group of columns the logits are written (LOG), with more they are not.  us a call, written / not: 8 sequences x 16384
+// tokens, 12/2 heads, two query tokens (12 columns) 41 / 61; 32 x 1000, 8/8, two (2) 30 / 45; 8 x 4133, 40/8, four (20) 44 / 47.
+// From two groups on: 8 x 2081, 28/4, 13 (91 columns) 105 written (a launch pair per group) / 39; over 172 shapes 1.1 to 4.5
+// times as fast, least with 48 columns.  (attn_finish_chunk takes 16 tokens at most.)
+constexpr bool chunk_logits(int cq, int G) { return cq * G <= 32 && cq <= 16; }
+template <int D, int KT, int NCB, bool LOG>
+__global__ __launch_bounds__(MC_WAVES * 64, MC_WAVES / 4) void k_attn_tiered_mc(const AttnArgs a) {
+  constexpr int NW = MC_WAVES, TR = mc_tile_rows(D), TILE = 8192, SC = (D / 64) * TR * 4;
+  constexpr int PART = 16 * NCB * D * 4, TILE_BYTES = PART > TILE ? PART : TILE;   // a wave's output partial takes its tile buffer's place
   constexpr Mode MF = KT == KT_BF16 ? F_BF16 : F_F16;
-  static_assert(16 * NCB * D * 4 <= TILE_BYTES, "a wave's output partial is parked in its tile buffer");
   __shared__ __attribute__((aligned(16))) char sm_t[NW * TILE_BYTES];
-  __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * 512];
-  __shared__ __attribute__((aligned(16))) char sm_lt[NW * 512];
+  __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * SC];
+  __shared__ __attribute__((aligned(16))) char sm_lt[NW * 2 * TR * 4];
   __shared__ float sm_ml[NW * 64];                       // per wave: m of 32 columns, then l
   const int s = blockIdx.x, kvh = blockIdx.y;
-  // query tokens beyond one per sequence: a.cq of them as columns of this workgroup, a.n_q such groups along grid z.
-  // The group's last token is (n_q - 1 - jz) * cq positions older than the chunk's last, and that many entries at the
-  // end of list F are not the group's to see (its earlier tokens cut off more, column by column).
-  const int b = a.n_q > 1 ? (int)blockIdx.z / a.n_q : (int)blockIdx.z, jz = a.n_q > 1 ? (int)blockIdx.z % a.n_q : 0;
+  const int b = a.groups > 1 ? (int)blockIdx.z / a.groups : (int)blockIdx.z, jz = a.groups > 1 ? (int)blockIdx.z % a.groups : 0;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  int nF, nQ, xsb = 0;
-  if (!a.second) {
-    if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
-    else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
-    nF -= (a.n_q - 1 - jz) * a.cq;
-  } else {
-    nF = a.cnt[b * CNT_N + C_NS]; nQ = 0;
-    xsb = ((a.cnt[b * CNT_N + C_NF] - a.trim + 63) >> 6) + ((a.cnt[b * CNT_N + C_NQ] + 63) >> 6);
-  }
-  const int nft = (nF + 63) >> 6, nqt = (nQ + 63) >> 6;
+  int nF, nQ;
+  if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
+  else { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
+  // this group's columns; its last one's token is cq - 1 - token positions older than the launch's last, and that many
+  // entries at the end of list F are not the group's to see (its earlier tokens cut off more, column by column)
+  const int ncol = a.cq * a.G, c0 = jz * 16 * NCB, nc = ncol - c0 < 16 * NCB ? ncol - c0 : 16 * NCB;
+  const int nFw = nF - (a.cq - 1 - (c0 + nc - 1) / a.G);
   const int nwv = a.S * NW;
-  const int nwq = a.second ? 0 : (a.B <= ATTN_ARG_SEQS && a.n_q == 1) ? a.nWq[b] : q_waves(nwv, nft, nqt), nwf = nwv - nwq;
+  const int nwq = a.B <= ATTN_ARG_SEQS ? a.nWq[b] : q_waves(nwv, (nF + TR - 1) / TR, (nQ + TR - 1) / TR), nwf = nwv - nwq;
   const int u = s * NW + wave;
-  const int ncol = a.cq * G;
 
   WaveLds w;
   w.t = sm_t + wave * TILE_BYTES;
-  w.sk = sm_sc + wave * 1024; w.sv = w.sk + 512; w.lt = sm_lt + wave * 512;
+  w.sk = sm_sc + wave * 2 * SC; w.sv = w.sk + SC; w.lt = sm_lt + wave * 2 * TR * 4;
   w.ta = lds_addr(w.t); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
   w.p = nullptr; w.pa = 0;
   float* my_o = (float*)w.t;          // after the wave's last tile: its output partial, [column][D]
@@ -1754,31 +1772,31 @@ __global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_
 #pragma unroll
     for (int db = 0; db < D / 16; ++db) om[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (u < nwf) attn_wave_mfma<D, G, KT, MF, NCB>(a, w, b, jz, kvh, lane, u, nwf, nF, (a.old_mask ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax, xsb, om, mr, lr);
-  else if (a.t2fmt == 0) attn_wave_mfma<D, G, KT, Q_INT8, NCB>(a, w, b, jz, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, om, mr, lr);
-  else attn_wave_mfma<D, G, KT, Q_INT4, NCB>(a, w, b, jz, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, xsb + nft, om, mr, lr);
+  if (u < nwf) attn_wave_mfma<D, KT, MF, NCB, LOG>(a, w, b, c0, kvh, lane, u, nwf, nF, nFw, (a.old_mask ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax, 0, om, mr, lr);
+  else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, NCB, LOG>(a, w, b, c0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, ((nF + 63) >> 6) * TB, om, mr, lr);
+  else attn_wave_mfma<D, KT, Q_INT4, NCB, LOG>(a, w, b, c0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, ((nF + 63) >> 6) * TB, om, mr, lr);
   // ---- wave partial into LDS: lane (n, kb) has the statistics of column 16*cb + n and the outputs of columns
   // 16*cb + 4*kb + j, element 16*db + n
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
-    float ls = lr[cb];
-    ls += lane_xor<16>(ls, lane);
-    ls += lane_xor<32>(ls, lane);
+    const float ls = quad_sum(lr[cb]);
     const int col = 16 * cb + lane;
-    if (lane < 16 && col < ncol) { sm_ml[wave * 64 + col] = mr[cb]; sm_ml[wave * 64 + 32 + col] = ls; }
+    if (lane < 16 && col < nc) { sm_ml[wave * 64 + col] = mr[cb]; sm_ml[wave * 64 + 32 + col] = ls; }
 #pragma unroll
     for (int db = 0; db < D / 16; ++db)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int c = 16 * cb + 4 * (lane >> 4) + j;
-        if (c < ncol) my_o[c * D + 16 * db + (lane & 15)] = om[cb][db][j];
+        if (c < nc) my_o[c * D + 16 * db + (lane & 15)] = om[cb][db][j];
       }
   }
   __syncthreads();
-  // ---- merge the waves: one split partial (m, l, o[G][D]) per query token
-  const int bq0 = (b * a.n_q + jz) * a.cq;
-  for (int i = t; i < ncol * D; i += NW * 64) {
-    const int col = i / D, d = i % D, jq = col / G, h = col % G;
+  // ---- merge the waves: one split partial (m, l, o[D]) per column; LOG: laid out by query token, as attn_finish_chunk merges them
+  const size_t sp = (size_t)(b * a.Hkv + kvh) * a.S + s;
+  const float inv_g = 1.0f / (float)a.G;
+  const auto by_token = [&](int jq) { return ((size_t)(b * a.cq + jq) * a.Hkv + kvh) * a.S + s; };
+  for (int i = t; i < nc * D; i += NW * 64) {
+    const int col = i / D;
     float mb = sm_ml[col];
 #pragma unroll
     for (int ww = 1; ww < NW; ++ww) mb = fmaxf(mb, sm_ml[ww * 64 + col]);
@@ -1788,10 +1806,10 @@ __global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_
       for (int ww = 0; ww < NW; ++ww)
         acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 64 + col] - mb) * LOG2E), ((const float*)(sm_t + ww * TILE_BYTES))[i], acc);
     }
-    a.part_o[((size_t)(((bq0 + jq) * a.Hkv + kvh) * a.S_total + a.s0 + s) * G + h) * D + d] = acc;
+    if constexpr (LOG) { const int jq = small_div(col, inv_g); a.part_o[(by_token(jq) * a.G + (col - jq * a.G)) * D + i % D] = acc; }
+    else a.part_o[(sp * ncol + c0) * D + i] = acc;
   }
-  if (t < ncol) {
-    const int jq = t / G, h = t % G;
+  if (t < nc) {
     float mb = sm_ml[t];
 #pragma unroll
     for (int ww = 1; ww < NW; ++ww) mb = fmaxf(mb, sm_ml[ww * 64 + t]);
@@ -1800,10 +1818,407 @@ __global__ __launch_bounds__(mc_waves(NCB) * 64, mc_waves(NCB) / 4) void k_attn_
 #pragma unroll
       for (int ww = 0; ww < NW; ++ww) ll = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 64 + t] - mb) * LOG2E), sm_ml[ww * 64 + 32 + t], ll);
     }
-    float* pm = a.part_ml + ((size_t)(((bq0 + jq) * a.Hkv + kvh) * a.S_total + a.s0 + s) * 2) * G;
-    pm[h] = mb;
-    pm[G + h] = ll;
+    const int jq = small_div(t, inv_g);
+    float* pm = LOG ? a.part_ml + by_token(jq) * 2 * a.G + (t - jq * a.G) : a.part_ml + sp * 2 * ncol + c0 + t;
+    pm[0] = mb;
+    pm[LOG ? a.G : ncol] = ll;
   }
+}
+
+// ---- the scores of a chunk (16-bit rows), and its outputs ------------------------------------------------------------
+// Grid (runs of tpw tiles of list F, then of list Q, of CS_ROWS entries, then output workgroups; B).  A workgroup has its K rows once more, for all
+// kv heads and all of the chunk's columns, and adds every entry's weights, summed, to its score: wave w takes kv heads
+// w / nsub, + 8 / nsub, ... and of their columns blocks w % nsub, + nsub, ...; a kv head's blocks, then the kv heads are
+// added in that order.  The weights are exp2 of the same products (same instructions, same operand order) less the merged
+// maximum, times the merged 1 / l, so they sum to one like the ones that went into the output.  The last workgroups of a
+// sequence (n_out) merge its splits into out; beside the rows, in the other workgroups, that took 4 us more.
+// Bound by rows arriving, half of what the launch before fetched.  Two tiles per wave are in flight (64-128 KB per compute
+// unit); nothing else goes through the vector memory pipe in the loop, because waiting for it would mean waiting for the
+// rows before it: the query vectors stay in registers, CS_QB blocks at a time, slots and statistics come from the LDS.
+constexpr int CHUNK_TOKENS = 32;                   // query tokens of a launch, at most
+constexpr int CS_THREADS = 512, CS_WAVES = CS_THREADS / 64;
+constexpr int CS_RB = 2, CS_ROWS = 16 * CS_RB, CS_QB = 4;
+constexpr size_t cs_tiles(int D) { return CS_WAVES * 2 * CS_ROWS * 2 * D; }   // bytes of the tile buffers
+constexpr size_t cs_lds(int D) { return 163840 - cs_tiles(D); }               // what is left beside them
+// (m, 1/l) of one column out of ns split partials `stride` floats apart (l follows m by `lofs`), by one wave: all lanes get them
+__device__ __forceinline__ void merge_stats_wave(const float* __restrict__ src, int ns, size_t stride, int lofs, int lane, float& m, float& il) {
+  float mx[1] = {-INFINITY}, lsum = 0.f;
+  for (int k = lane; k < ns; k += 64) mx[0] = fmaxf(mx[0], src[k * stride]);
+  wave_max_all<1>(mx);
+  const float mm = rdlane(mx[0], 63);
+  if (mm > -INFINITY)
+    for (int k = lane; k < ns; k += 64) lsum = fmaf(src[k * stride + lofs], __builtin_amdgcn_exp2f((src[k * stride] - mm) * LOG2E), lsum);
+  lsum = wave_sum(lsum);
+  m = mm > -INFINITY ? mm : 0.f;
+  il = lsum > 0.f ? 1.0f / lsum : 0.f;
+}
+// the same by one thread
+__device__ __forceinline__ void merge_stats_thread(const float* __restrict__ src, int ns, size_t stride, int lofs, float& m, float& il) {
+  float mm = -INFINITY, ll = 0.f;
+  if (ns <= 4) {
+    float mv[4], lv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { mv[k] = k < ns ? src[k * stride] : -INFINITY; lv[k] = k < ns ? src[k * stride + lofs] : 0.f; }
+    mm = fmaxf(fmaxf(mv[0], mv[1]), fmaxf(mv[2], mv[3]));
+    if (mm > -INFINITY) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ll = fmaf(lv[k], __builtin_amdgcn_exp2f((mv[k] - mm) * LOG2E), ll);
+    }
+  } else {
+#pragma unroll 8
+    for (int k = 0; k < ns; ++k) mm = fmaxf(mm, src[k * stride]);
+    if (mm > -INFINITY) {
+#pragma unroll 8
+      for (int k = 0; k < ns; ++k) ll = fmaf(src[k * stride + lofs], __builtin_amdgcn_exp2f((src[k * stride] - mm) * LOG2E), ll);
+    }
+  }
+  m = mm > -INFINITY ? mm : 0.f;
+  il = ll > 0.f ? 1.0f / ll : 0.f;
+}
+// waves that share a kv head's columns
+__host__ __device__ inline int chunk_nsub(int Hkv, int ncol) {
+  const int blocks = (ncol + 15) / 16, n = Hkv >= CS_WAVES ? 1 : CS_WAVES / Hkv;
+  return n < blocks ? n : blocks;
+}
+inline size_t chunk_scores_lds(int Hq, int Hkv, int cq, int G, int tpw) {
+  return (size_t)(cq * Hq + 1) / 2 * 16 + ((size_t)Hkv * chunk_nsub(Hkv, cq * G) + 1) * tpw * CS_ROWS * 4 + CS_WAVES * 4 * CS_ROWS * 4;
+}
+// the workgroup's share (of n_wgs, number u) of the output rows (kv head, column) of sequence b
+template <int D>
+__device__ __forceinline__ void chunk_outputs(const AttnArgs& a, int b, int u, int n_wgs, float* sm_red) {
+  constexpr int PAR = CS_THREADS / D;                                        // rows, or shares of one row's splits, side by side
+  const int t = threadIdx.x, lane = t & 63, d = t % D, g = t / D, ncol = a.cq * a.G, rows = a.Hkv * ncol, S = a.S;
+  const int rpw = (rows + n_wgs - 1) / n_wgs, r0 = u * rpw, r1 = r0 + rpw < rows ? r0 + rpw : rows;
+  const size_t mls = (size_t)2 * ncol;                                       // floats between a pair's split statistics
+  const float inv_g = 1.0f / (float)a.G, inv_c = 1.0f / (float)ncol;
+  auto store = [&](int kvh, int col, float v) {
+    const int jq = small_div(col, inv_g);
+    const size_t oi = ((size_t)b * a.o_bs + (size_t)jq * a.Hq + kvh * a.G + (col - jq * a.G)) * D + d;
+    if (a.out_kind == KT_BF16) ((uint16_t*)a.out)[oi] = f32_to_bf16(v);
+    else if (a.out_kind == KT_F16) ((_Float16*)a.out)[oi] = (_Float16)v;
+    else ((float*)a.out)[oi] = v;
+  };
+  if (S <= 4) {
+    constexpr int NRW = 4;                                                   // rows of a thread whose loads are in flight together
+    for (int rr = r0 + g; rr < r1; rr += NRW * PAR) {
+      int kvh[NRW], col[NRW];
+      float po[NRW][4], mv[NRW][4], lv[NRW][4];
+#pragma unroll
+      for (int i = 0; i < NRW; ++i) {
+        const int r = rr + i * PAR < r1 ? rr + i * PAR : r0;
+        kvh[i] = small_div(r, inv_c); col[i] = r - kvh[i] * ncol;
+        const size_t sp = ((size_t)b * a.Hkv + kvh[i]) * S;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float* ml = a.part_ml + (sp + (k < S ? k : 0)) * mls + col[i];
+          po[i][k] = a.part_o[((sp + (k < S ? k : 0)) * ncol + col[i]) * D + d];
+          mv[i][k] = k < S ? ml[0] : -INFINITY; lv[i][k] = k < S ? ml[ncol] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NRW; ++i) {
+        if (rr + i * PAR >= r1) break;
+        const float mm = fmaxf(fmaxf(mv[i][0], mv[i][1]), fmaxf(mv[i][2], mv[i][3]));
+        float ll = 0.f, acc = 0.f;
+        if (mm > -INFINITY) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float w = __builtin_amdgcn_exp2f((mv[i][k] - mm) * LOG2E);
+            ll = fmaf(lv[i][k], w, ll); acc = fmaf(w, po[i][k], acc);
+          }
+        }
+        store(kvh[i], col[i], ll > 0.f ? acc * (1.0f / ll) : 0.f);
+      }
+    }
+  } else {
+    for (int r = r0; r < r1; ++r) {
+      const int kvh = small_div(r, inv_c), col = r - kvh * ncol;
+      const size_t sp = ((size_t)b * a.Hkv + kvh) * S;
+      float m, il, acc = 0.f;
+      merge_stats_wave(a.part_ml + sp * mls + col, S, mls, ncol, lane, m, il);
+#pragma unroll 4
+      for (int k = g; k < S; k += PAR) acc = fmaf(__builtin_amdgcn_exp2f((a.part_ml[(sp + k) * mls + col] - m) * LOG2E), a.part_o[((sp + k) * ncol + col) * D + d], acc);
+      sm_red[t] = acc;
+      __syncthreads();
+      if (g == 0) {
+        float tot = acc;
+#pragma unroll
+        for (int k = 1; k < PAR; ++k) tot += sm_red[k * D + d];
+        store(kvh, col, tot * il);
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// Entries e0 .. of one list, tpw tiles, by the whole workgroup.
+template <int D, int KT, Mode M>
+__device__ __forceinline__ void chunk_scores(const AttnArgs& a, int b, int e0, int tpw, int nF, int nQ, char* sm_t, char* sm) {
+  constexpr bool IS_Q = (M == Q_INT8 || M == Q_INT4);
+  constexpr int RB = 2 * D, NKS = D / 32, CRB = !IS_Q ? RB : (M == Q_INT8 ? D : D / 2);
+  constexpr int SCD = (M == Q_INT8) ? 1 : (M == Q_INT4) ? D / 64 : 0;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n = lane & 15, kb = lane >> 4, ncol = a.cq * a.G, S = a.S, n_list = IS_Q ? nQ : nF;
+  const int prow = tpw * CS_ROWS, n_rows = n_list - e0 < prow ? n_list - e0 : prow, nt = (n_rows + CS_ROWS - 1) / CS_ROWS;
+  const int nsub = chunk_nsub(a.Hkv, ncol), kv_step = CS_WAVES / nsub, sub = wave % nsub, kvh0 = wave / nsub;
+  const int blocks = (ncol + 15) / 16, my_blocks = (blocks - sub + nsub - 1) / nsub, ng = (my_blocks + CS_QB - 1) / CS_QB;
+  const float inv_g = 1.0f / (float)a.G, inv_c = 1.0f / (float)ncol;
+  float2* sm_st = (float2*)sm;                                               // (m, 1/l) of every (kv head, column)
+  float* sm_part = (float*)(sm_st + ((a.Hkv * ncol + 1) & ~1));               // [kv head][sub][prow]: sums over a block set's columns
+  int* sm_list = (int*)(sm_part + a.Hkv * nsub * prow);                      // slots of the workgroup's entries
+  char* sm_scl = (char*)(sm_list + prow) + wave * 4 * CS_ROWS * 4;      // a wave's scales, two tiles
+  const int* list = (IS_Q ? a.q_loc : a.old_mask ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax + e0;
+
+  // The K rows come in by direct-to-LDS loads, 1 KB of consecutive pieces per instruction (the operand's own order, 16 rows
+  // at a time, keeps the address path busy four times as long).  F: as in attn_wave_mfma, eight rows x 128 bytes, the pieces
+  // rotated.  Code rows: whole rows, the 16-byte pieces rotated by row.
+  constexpr int LPR = CRB / 16, RPP = 64 / LPR, NP = CS_ROWS * CRB / 1024, KU = RB / 128, TILE = CS_ROWS * CRB;
+  constexpr int NR = IS_Q ? NP : CS_ROWS / 8;                                // rows of a tile that this lane fetches from
+  constexpr int ROWP = IS_Q ? RPP : 8;                                       // ... and their distance
+  const int row0 = IS_Q ? lane / LPR : lane >> 3, srow = lane & (CS_ROWS - 1);
+  char* tb = sm_t + wave * (2 * CS_ROWS * RB);
+  uint32_t col16[2];
+  if constexpr (IS_Q) {
+    col16[0] = col16[1] = (uint32_t)((lane - (M == Q_INT8 ? row0 : row0 >> 1)) & (LPR - 1)) * 16u;   // (RPP is a multiple of the rotation's period)
+  } else {
+    const int r = lane & 7;
+    col16[0] = (uint32_t)((r + 2 * (row0 >> 1)) & 7) * 16u; col16[1] = (uint32_t)((r + 2 * (row0 >> 1) + 1) & 7) * 16u;
+  }
+  // the tile that is fetched next: tile f_ti of the workgroup's, for kv head f_kvh and the f_g-th set of its blocks
+  int f_ti = 0, f_g = 0, f_kvh = kvh0;
+  bool f_more = wave < kv_step * nsub && kvh0 < a.Hkv;
+  auto fetch = [&](int buf, const int (&slot)[NR], int sslot) {              // slots (none: -1, which gives zeros)
+    const size_t pr = (size_t)b * a.Hkv + f_kvh;
+    const __amdgpu_buffer_rsrc_t rk = IS_Q ? make_rsrc(a.c2K + pr * a.cap2 * CRB, (uint32_t)a.cap2 * CRB) : make_rsrc(a.fpK + pr * a.capF * RB, (uint32_t)a.capF * RB);
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      dma<16>(rk, tb + buf * TILE + i * 1024, (uint32_t)slot[IS_Q ? i : i / KU] * (uint32_t)CRB + (IS_Q ? 0 : (i % KU) * 128) + col16[(i / KU) & 1], 0);
+    if constexpr (IS_Q) {
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.s2K + pr * a.cap2 * a.sb, (uint32_t)a.cap2 * a.sb);
+      if (lane < CS_ROWS) {
+#pragma unroll
+        for (int j = 0; j < SCD; ++j) dma<4>(rs, sm_scl + (buf * 2 + j) * (CS_ROWS * 4), (uint32_t)sslot * (uint32_t)a.sb + 4 * j, 0);
+      }
+    }
+    if (++f_ti == nt) {
+      f_ti = 0;
+      if (++f_g == ng) { f_g = 0; f_kvh += kv_step; f_more = f_kvh < a.Hkv; }
+    }
+  };
+  constexpr int NOPS = NP + SCD;                                             // vector-memory operations of a fetch
+  // addresses of a lane's operand pieces: row n of a 16-row block, elements 32 * ks + 8 * kb .. + 7
+  uint32_t k_rd[NKS];
+  {
+    const uint32_t ta = lds_addr(tb);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      if constexpr (!IS_Q) { const int ii = n >> 3, gg = n & 7, rot = 2 * (gg >> 1) + ii; k_rd[ks] = ta + (ii * KU + (ks >> 1)) * 1024 + (8 * gg + ((4 * (ks & 1) + kb - rot) & 7)) * 16; }
+      else if constexpr (M == Q_INT8) k_rd[ks] = ta + n * CRB + ((2 * ks + (kb >> 1) + n) & (LPR - 1)) * 16 + (kb & 1) * 8;
+      else k_rd[ks] = ta + n * CRB + ((ks + (n >> 1)) & (LPR - 1)) * 16 + kb * 4;
+    }
+  }
+  const uint32_t part_a = lds_addr(sm_part), list_a = lds_addr(sm_list), scl_a = lds_addr(sm_scl);
+  {
+    int s0[NR], s1[NR], z0 = -1, z1 = -1;                                    // the first two fetches: tiles 0 and 1, or 0 again
+    const int o1 = nt > 1 ? CS_ROWS : 0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int r = row0 + i * ROWP;
+      s0[i] = r < n_rows ? list[r] : -1;
+      s1[i] = o1 + r < n_rows ? list[o1 + r] : -1;
+    }
+    if constexpr (IS_Q) { z0 = srow < n_rows ? list[srow] : -1; z1 = o1 + srow < n_rows ? list[o1 + srow] : -1; }
+    if (f_more) fetch(0, s0, z0);
+    if (f_more) fetch(1, s1, z1);
+  }
+  int my_slot = -1, pos = 0;                                                 // of entry e0 + t
+  if (t < n_rows) { my_slot = list[t]; pos = (IS_Q ? a.q_pos : a.f_pos)[(size_t)b * a.Nmax + e0 + t]; }
+
+  // the statistics of the columns
+  const size_t mls = (size_t)2 * ncol;                                       // floats between a pair's split statistics
+  const float* ml = a.part_ml + (size_t)b * a.Hkv * S * mls;
+  if (S > 16) {
+    for (int i = wave; i < a.Hkv * ncol; i += CS_WAVES) {
+      const int kvh = i / ncol;
+      float m, il;
+      merge_stats_wave(ml + (size_t)kvh * S * mls + (i - kvh * ncol), S, mls, ncol, lane, m, il);
+      if (lane == 0) sm_st[i] = make_float2(m, il);
+    }
+  } else {
+    for (int i = t; i < a.Hkv * ncol; i += CS_THREADS) {
+      const int kvh = small_div(i, inv_c);
+      float m, il;
+      merge_stats_thread(ml + (size_t)kvh * S * mls + (i - kvh * ncol), S, mls, ncol, m, il);
+      sm_st[i] = make_float2(m, il);
+    }
+  }
+  if (t < prow) sm_list[t] = my_slot;
+  __syncthreads();
+  float score = 0.f;
+  if (t < n_rows) score = a.score[(size_t)b * a.Nmax + pos];
+  if (wave < kv_step * nsub) {
+    int buf = 0;
+    for (int kvh = kvh0; kvh < a.Hkv; kvh += kv_step)
+      for (int g = 0; g < ng; ++g) {
+        u32x4 q[CS_QB][NKS];
+        float2 st[CS_QB];
+        int seen[CS_QB];                                                     // entries the column's query sees (a column past the last: none)
+#pragma unroll
+        for (int i = 0; i < CS_QB; ++i) {
+          const int blk = sub + (g * CS_QB + i) * nsub, col = blk * 16 + n;
+          const u32x4* qp = (const u32x4*)a.xs + ((size_t)(b * a.Hkv + kvh) * blocks + (blk < blocks ? blk : 0)) * (NKS * 64) + lane;
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks) q[i][ks] = qp[ks * 64];
+          st[i] = col < ncol ? sm_st[kvh * ncol + col] : make_float2(0.f, 0.f);   // (no column: zeros times zero)
+          seen[i] = (col < ncol ? IS_Q ? n_list : nF - (a.cq - 1 - small_div(col, inv_g)) : 0) - e0 - 4 * kb;
+        }
+        for (int ti = 0; ti < nt; ++ti, buf ^= 1) {
+          // this tile's rows are in (one later fetch at most has been asked for: the one f_ runs ahead by)
+          const bool last = ti + 1 == nt && g + 1 == ng && kvh + kv_step >= a.Hkv;
+          if (last) wait_vm<0>(); else wait_vm<NOPS>();
+          const uint32_t kofs = (uint32_t)buf * TILE;
+          u32x4 k[CS_RB][NKS], ksc[IS_Q ? SCD : 1][CS_RB];
+          int slot[NR], sslot = -1;
+          const uint32_t la = list_a + (uint32_t)(f_ti * CS_ROWS) * 4u;
+          static_for<NR>([&](auto ic) { constexpr int i = decltype(ic)::value; slot[i] = (int)lds_rd32<i * ROWP * 4>(la + row0 * 4u); });
+          if constexpr (IS_Q) {
+            sslot = (int)lds_rd32<0>(la + srow * 4u);
+            static_for<SCD>([&](auto jc) {
+              constexpr int j = decltype(jc)::value;
+              static_for<CS_RB>([&](auto rc) { constexpr int rb = decltype(rc)::value; ksc[j][rb] = lds_rd128<j * CS_ROWS * 4 + rb * 64>(scl_a + buf * (2 * CS_ROWS * 4) + kb * 16u); });
+            });
+          }
+          u32x2 c8[CS_RB][NKS];
+          uint32_t c4[CS_RB][NKS];
+          static_for<CS_RB>([&](auto rc) {
+            constexpr int rb = decltype(rc)::value;
+            static_for<NKS>([&](auto kc) {
+              constexpr int ks = decltype(kc)::value;
+              if constexpr (!IS_Q) k[rb][ks] = lds_rd128<rb * 2 * KU * 1024>(k_rd[ks] + kofs);
+              else if constexpr (M == Q_INT8) c8[rb][ks] = lds_rd64<rb * 16 * CRB>(k_rd[ks] + kofs);
+              else c4[rb][ks] = lds_rd32<rb * 16 * CRB>(k_rd[ks] + kofs);
+            });
+          });
+          lds_wait();
+#pragma unroll
+          for (int i = 0; i < NR; ++i) { uint32_t v = (uint32_t)slot[i]; tie(v); slot[i] = (int)v; }
+          if constexpr (IS_Q) {
+            uint32_t v = (uint32_t)sslot;
+            tie(v);
+            sslot = (int)v;
+#pragma unroll
+            for (int j = 0; j < SCD; ++j) tie(ksc[j]);
+          }
+#pragma unroll
+          for (int rb = 0; rb < CS_RB; ++rb) {
+            if constexpr (!IS_Q) tie(k[rb]);
+            else if constexpr (M == Q_INT8) tie(c8[rb]);
+            else tie(c4[rb]);
+          }
+          if (f_more) fetch(buf, slot, sslot);                               // the buffer has been read
+          if constexpr (IS_Q) {
+#pragma unroll
+            for (int rb = 0; rb < CS_RB; ++rb)
+#pragma unroll
+              for (int ks = 0; ks < NKS; ++ks) {
+                if constexpr (M == Q_INT8) {
+                  uint32_t w0, w1, w2, w3;
+                  widen_int8<KT>(c8[rb][ks].x, w0, w1);
+                  widen_int8<KT>(c8[rb][ks].y, w2, w3);
+                  k[rb][ks] = u32x4{w0, w1, w2, w3};
+                } else {
+                  k[rb][ks] = widen_int4<KT>(c4[rb][ks]);
+                }
+              }
+          }
+          const bool edge = (ti + 1) * CS_ROWS > n_list - (IS_Q ? 0 : a.cq - 1) - e0;   // some column does not see the whole tile
+          float acc[CS_RB][4];
+#pragma unroll
+          for (int rb = 0; rb < CS_RB; ++rb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[rb][j] = 0.f;
+#pragma unroll
+          for (int i = 0; i < CS_QB; ++i) {
+            if (g * CS_QB + i >= my_blocks) break;
+            const int lim = seen[i] - ti * CS_ROWS;
+            f32x4 xx[CS_RB];
+#pragma unroll
+            for (int rb = 0; rb < CS_RB; ++rb) {
+              f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int ks = 0; ks < NKS; ++ks) {
+                if constexpr (M == Q_INT4) {
+                  const f32x4 part = mfma_16x16x32<KT>(k[rb][ks], q[i][ks], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                  for (int j = 0; j < 4; ++j) x[j] = fmaf(half_of(elem(ksc[ks >> 1][rb], j), ks & 1), part[j], x[j]);
+                } else {
+                  x = mfma_16x16x32<KT>(k[rb][ks], q[i][ks], x);
+                }
+              }
+              xx[rb] = x;
+            }
+#pragma unroll
+            for (int rb = 0; rb < CS_RB; ++rb)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                float x = xx[rb][j];
+                if constexpr (M == Q_INT8) x *= elem_f(ksc[0][rb], j);
+                x = fmaf(x, a.softmax_scale, -st[i].x);
+                if (edge) x = 16 * rb + j < lim ? x : -INFINITY;
+                acc[rb][j] = fmaf(__builtin_amdgcn_exp2f(x * LOG2E), st[i].y, acc[rb][j]);
+              }
+          }
+          // summed over the block's 16 columns: lane (n, kb) of the first eight n keeps entry 16 * (n / 4) + 4 * kb + n % 4
+          float v = 0.f;
+#pragma unroll
+          for (int rb = 0; rb < CS_RB; ++rb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const float tot = group_sum<16>(acc[rb][j]); v = n == 4 * rb + j ? tot : v; }
+          const uint32_t at = part_a + (uint32_t)((kvh * nsub + sub) * prow + ti * CS_ROWS + 16 * (n >> 2) + 4 * kb + (n & 3)) * 4u;
+          if (n < 4 * CS_RB) {
+            if (g > 0) { uint32_t old = lds_rd32<0>(at); lds_wait(); tie(old); v = __builtin_bit_cast(float, old) + v; }
+            lds_wr32(at, __builtin_bit_cast(uint32_t, v));
+          }
+        }
+      }
+  }
+  lds_wait();
+  __syncthreads();
+  if (t < n_rows) {
+    float pen = 0.f;
+    if (a.red)           // redundancy-penalised scorers: every token that sees the entry takes red_w * rho / (positions attended) off per head
+      for (int jt = 0; jt < a.cq; ++jt) {
+        const int later = a.cq - 1 - jt;
+        if (IS_Q || e0 + t < nF - later) pen += a.red_w * (float)a.G / (float)(nF - later + nQ);
+      }
+    float sum = 0.f;
+    for (int kvh = 0; kvh < a.Hkv; ++kvh) {
+      const float* src = sm_part + kvh * nsub * prow + t;
+      float s = src[0];
+      for (int w = 1; w < nsub; ++w) s += src[w * prow];
+      const size_t o = ((size_t)b * a.Hkv + kvh) * a.Nmax + pos;
+      if (a.vnorm) s *= a.vnorm[o];                // value-aware scorer: times the norm of the value row the heads read
+      if (a.red) s = fmaf(-pen, a.red[o], s);
+      sum += s;
+    }
+    a.score[(size_t)b * a.Nmax + pos] = score + a.score_scale * sum;
+  }
+}
+
+template <int D, int KT>
+__global__ __launch_bounds__(CS_THREADS, 2) void k_attn_chunk_scores(const AttnArgs a, int n_wgs, int tpw) {
+  extern __shared__ __attribute__((aligned(16))) char sm_cs[];
+  __shared__ __attribute__((aligned(16))) char sm_t[cs_tiles(D)];   // K rows of each wave, two tiles
+  constexpr Mode MF = KT == KT_BF16 ? F_BF16 : F_F16;
+  const int b = blockIdx.y, u = blockIdx.x, rows = tpw * CS_ROWS;
+  int nF = a.nF[b & (ATTN_ARG_SEQS - 1)], nQ = a.nQ[b & (ATTN_ARG_SEQS - 1)];
+  if (a.B > ATTN_ARG_SEQS) { nF = a.cnt[b * CNT_N + C_NF] - a.trim; nQ = a.cnt[b * CNT_N + C_NQ]; }
+  if (u >= n_wgs) { chunk_outputs<D>(a, b, u - n_wgs, gridDim.x - n_wgs, (float*)sm_cs); return; }
+  const int wf = (nF + rows - 1) / rows;
+  if (u >= wf + (nQ + rows - 1) / rows) return;
+  if (u < wf) chunk_scores<D, KT, MF>(a, b, u * rows, tpw, nF, nQ, sm_t, sm_cs);
+  else if (a.t2fmt == 0) chunk_scores<D, KT, Q_INT8>(a, b, (u - wf) * rows, tpw, nF, nQ, sm_t, sm_cs);
+  else chunk_scores<D, KT, Q_INT4>(a, b, (u - wf) * rows, tpw, nF, nQ, sm_t, sm_cs);
 }
 
 // ---- finish: global softmax statistics, scores, output ------------------------------------------------------
@@ -1993,16 +2408,15 @@ __global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs
   }
 }
 
-// ---- finish for several query tokens per sequence (one launch served n_q * cq of them) --------------------------
+// ---- finish for several query tokens per sequence whose logits were written (one launch served n_q * cq of them) ------
 // Grid (64-entry slots of the last token's lists + output workgroups, B).  Slot workgroups: every list entry gets the
 // weights of the queries added in query order (what single-token calls would have done, with the same arithmetic per
 // query: wave (hg, ls) sums kv heads hg, hg+4, ... for queries ls, ls+LSN, ..., the four partial sums are added in the order
-// hg = 0..3).  Query jt does not see the last queries - 1 - jt entries of list F; its Q-list logits start where the F tiles
-// of its group (the cq tokens of one workgroup, laid out for the group's last token) end.  Latency-bound like k_attn_finish
-// and built like it: the first logits are requested before the statistics, LSN queries go side by side (256 threads each).
-// The other workgroups merge the splits of LSN * hpg (query, head)s into out, hpg of them one after the other in a thread:
-// two where the merge is one round of loads, one where it is a chain (more than 16 splits; 16384 tokens, one sequence, 28/4
-// heads, two tokens: 35 us a call with hpg = 2 and LSN = 4, 23 with 1 and 2).
+// hg = 0..3).  Query jt does not see the last n_q - 1 - jt entries of list F; its Q-list logits start where its F tiles
+// end (16-bit rows, all in one column group: where the last token's do).  Latency-bound like k_attn_finish and built like it: the first logits are requested before the statistics, LSN
+// queries go side by side (256 threads each).  The other workgroups merge the splits of LSN * hpg (query, head)s into out,
+// hpg of them one after the other in a thread: two where the merge is one round of loads, one where it is a chain (more
+// than 16 splits).
 constexpr int CHUNK_HPG = 2;
 template <int D, int G, int LSN>
 __global__ __launch_bounds__(LSN * 256) void k_attn_finish_chunk(const AttnArgs a, int n_tiles, int hpg) {
@@ -2021,8 +2435,8 @@ __global__ __launch_bounds__(LSN * 256) void k_attn_finish_chunk(const AttnArgs 
     const int sl = blockIdx.x * 64 + e;                     // slot in the last query's layout
     const bool is_f = sl < nF, is_q = sl >= cf * TB && sl - cf * TB < nQ;
     auto sees = [&](int jt) { return is_q || (is_f && sl < nF - (nq - 1 - jt)); };   // wave-divergent at most in a list's last tile
-    auto column = [&](int jt) {                             // F tiles in the layout of the query's group
-      const int cfz = (nF - (a.n_q - 1 - jt / a.cq) * a.cq + TB - 1) / TB;
+    auto column = [&](int jt) {                             // binary32: F tiles in the query's own layout
+      const int cfz = a.cq > 1 ? cf : (nF - (nq - 1 - jt) + TB - 1) / TB;
       return is_q ? cfz * TB + (sl - cf * TB) : sl;
     };
     float x0[XP][G];
@@ -2217,26 +2631,39 @@ __global__ __launch_bounds__(256) void k_call_scores(const AttnArgs a, int tr) {
 // With a pair of events the launch is timed by the dispatch's own begin / end timestamps (no bracket overhead).
 template <int D, int G, int KT>
 static hipError_t run_tiered(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  dim3 grid(a.S, a.Hkv, a.B * a.n_q * a.nl);
-  // One query token per workgroup (a decode step; binary32 rows always): the vector kernel, G dot products per row.
-  // Several query tokens as columns of one workgroup (16-bit rows): a (rows x D) by (D x G * cq) contraction, on the
-  // matrix cores.
-  if (a.cq == 1) {
-    constexpr int threads = KernelGeo<D, G, KT>::NW * 64;
-    if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_tiered<D, G, KT>), grid, dim3(threads), 0, st, ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((k_attn_tiered<D, G, KT>), grid, dim3(threads), 0, st, a);
-  } else if constexpr (KT == KT_F32) {
-    return hipErrorInvalidValue;
-  } else {
-    if (a.cq < 1 || a.cq * G > 32) return hipErrorInvalidValue;
-    if (a.cq * G <= 16) {
-      if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_tiered_mc<D, G, KT, 1>), grid, dim3(mc_waves(1) * 64), 0, st, ev0, ev1, 0, a);
-      else hipLaunchKernelGGL((k_attn_tiered_mc<D, G, KT, 1>), grid, dim3(mc_waves(1) * 64), 0, st, a);
-    } else {
-      if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_tiered_mc<D, G, KT, 2>), grid, dim3(mc_waves(2) * 64), 0, st, ev0, ev1, 0, a);
-      else hipLaunchKernelGGL((k_attn_tiered_mc<D, G, KT, 2>), grid, dim3(mc_waves(2) * 64), 0, st, a);
-    }
-  }
+  // one query token per workgroup: the vector kernel, G dot products per row
+  const dim3 grid(a.S, a.Hkv, a.B * a.n_q * a.nl);
+  constexpr int threads = KernelGeo<D, G, KT>::NW * 64;
+  if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_tiered<D, G, KT>), grid, dim3(threads), 0, st, ev0, ev1, 0, a);
+  else hipLaunchKernelGGL((k_attn_tiered<D, G, KT>), grid, dim3(threads), 0, st, a);
+  return hipGetLastError();
+}
+// Several query tokens as columns of one workgroup (16-bit rows): a (rows x D) by (D x columns) contraction, on the matrix
+// cores; then the scores and the outputs.
+// Tiles per workgroup of the score launch: one workgroup for every compute unit but some for the outputs, as far as the LDS
+// has room.
+static int chunk_tiles_per_wg(const AttnArgs& a, int D, int tiles) {
+  int tpw = (int)std::min<int64_t>(CS_THREADS / CS_ROWS, ((int64_t)(tiles + 1) * a.B + 223) / 224);
+  while (tpw > 1 && chunk_scores_lds(a.Hq, a.Hkv, a.cq, a.G, tpw) > cs_lds(D)) --tpw;
+  return tpw < 1 ? 1 : tpw;
+}
+template <int D, int KT>
+static hipError_t run_chunk(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  const int ncol = a.cq * a.G, ncb = a.xs_stride ? chunk_blocks(ncol) : 2;
+  const dim3 grid(a.S, a.Hkv, a.B * a.groups);
+  if (a.cq < 2 || a.cq > CHUNK_TOKENS || a.groups != (ncol + 16 * ncb - 1) / (16 * ncb)) return hipErrorInvalidValue;
+  if (a.xs_stride && a.groups > 1) return hipErrorInvalidValue;
+  const auto kernel = !a.xs_stride ? k_attn_tiered_mc<D, KT, 2, false> : ncb == 1 ? k_attn_tiered_mc<D, KT, 1, true> : k_attn_tiered_mc<D, KT, 2, true>;
+  if (ev0 && ev1) hipExtLaunchKernelGGL(kernel, grid, dim3(MC_WAVES * 64), 0, st, ev0, ev1, 0, a);
+  else hipLaunchKernelGGL(kernel, grid, dim3(MC_WAVES * 64), 0, st, a);
+  if (a.xs_stride) return hipGetLastError();             // the logits are written: launch_attn_finish_chunk ends the call
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  const int tiles = a.n_tiles * (64 / CS_ROWS), tpw = chunk_tiles_per_wg(a, D, tiles);
+  const int n_wgs = (tiles + tpw - 1) / tpw + 1;         // (list F and list Q both end in a partly filled run)
+  // output workgroups: the compute units left over, with at least a row and at most 16 rows for every D threads
+  const int rows = a.Hkv * ncol, par = CS_THREADS / D;
+  const int n_out = a.S > 4 ? rows : std::max((rows + 16 * par - 1) / (16 * par), std::min((rows + par - 1) / par, 256 / a.B - n_wgs));
+  hipLaunchKernelGGL((k_attn_chunk_scores<D, KT>), dim3(n_wgs + n_out, a.B), dim3(CS_THREADS), chunk_scores_lds(a.Hq, a.Hkv, a.cq, a.G, tpw), st, a, n_wgs, tpw);
   return hipGetLastError();
 }
 template <int D, int G, int KT>
@@ -2255,6 +2682,10 @@ hipError_t tiered_by_group(const AttnArgs& a, int G, hipStream_t st, hipEvent_t 
 #define TKV_DEFINE_PART(D_, BF_)                                                                                   \
   template <>                                                                                                      \
   hipError_t tiered_by_group<D_, BF_>(const AttnArgs& a, int G, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {  \
+    if (a.groups) {                                                                                                \
+      if constexpr (BF_ != KT_F32) return run_chunk<D_, BF_>(a, st, ev0, ev1);                                     \
+      return hipErrorInvalidValue;                                                                                 \
+    }                                                                                                              \
     if (a.sc) { TKV_DISPATCH_G(run_step, D_, BF_, a, st, ev0, ev1) }                                               \
     TKV_DISPATCH_G(run_tiered, D_, BF_, a, st, ev0, ev1)                                                           \
   }
@@ -2308,11 +2739,19 @@ hipError_t launch_attn_tiered(const AttnArgs& a, int D, int G, int kt, hipStream
   if (D == 64 && kt == KT_F16) return tiered_by_group<64, KT_F16>(a, G, st, ev0, ev1);
   return hipErrorInvalidValue;
 }
-int attn_waves_per_group(int D, int elem_bytes, int G, int cq) {
-  return (elem_bytes == 2 && cq > 1) ? mc_waves(cq * G <= 16 ? 1 : 2) : split_waves(D, elem_bytes, G);
+int attn_waves_per_group(int D, int elem_bytes, int G) { return split_waves(D, elem_bytes, G); }
+int attn_tile_rows(int D, int elem_bytes) { return split_tile_rows(D, elem_bytes); }
+int attn_chunk_blocks(int n_cols) { return chunk_blocks(n_cols); }
+bool attn_chunk_logits(int n_tokens, int G) { return chunk_logits(n_tokens, G); }
+int attn_chunk_waves() { return MC_WAVES; }
+int attn_chunk_tile_rows(int D) { return mc_tile_rows(D); }
+// Query tokens of a chunk that one launch serves: as many as the score launch's LDS and grid z have room for.
+int attn_chunk_tokens(int B, int Hq, int Hkv, int D) {
+  const int G = Hq / Hkv;
+  int m = CHUNK_TOKENS;
+  while (m > 1 && (chunk_scores_lds(Hq, Hkv, m, G, 1) > cs_lds(D) || (int64_t)B * ((m * G + 15) / 16) > 65535)) --m;
+  return m;
 }
-int attn_tile_rows(int D, int elem_bytes, int cq) { return elem_bytes == 2 && cq > 1 ? TB : split_tile_rows(D, elem_bytes); }
-int attn_cols_per_launch(int elem_bytes, int G) { return elem_bytes == 2 ? (32 / G < 16 ? 32 / G : 16) : 1; }
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles) { return q_waves(n_waves, n_f_tiles, n_q_tiles); }
 
 static int chunk_hpg(const AttnArgs& a) { return a.S_total <= 16 ? CHUNK_HPG : 1; }

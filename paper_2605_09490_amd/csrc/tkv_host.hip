@@ -692,23 +692,30 @@ tkv_status tkv_append(tkv_cache* c, int32_t layer, const void* k, const void* v,
   return TKV_OK;
 }
 
-// Most query tokens of a chunk that one launch serves; longer chunks go in groups.  16-bit rows: as many as fit the
-// 16 columns of a workgroup's accumulators beside the group's heads (the cache is read once for all of them); binary32
-// rows: one workgroup set per token along the grid.
-static int chunk_tokens_per_launch(const tkv_cache* c) {
-  return c->es == 2 ? attn_cols_per_launch(2, c->G) : 8;
-}
+// Most query tokens of a chunk that one launch serves; longer chunks go in groups.  16-bit rows: as columns of matrix
+// products, whatever the number; binary32 rows: one workgroup set per token along the grid.
+static int chunk_tokens_per_launch(const tkv_cache* c) { return c->es == 2 ? attn_chunk_tokens(c->dv.B, c->dv.Hq, c->dv.Hkv, c->dv.D) : 8; }
 
-// Scratch for launches that serve several query tokens per sequence: logits and split partials per (sequence, query).
-// Allocated on the first such call, for as many queries as one launch takes, and kept until the cache is destroyed.
+// 16-bit rows: groups of columns that a chunk of m tokens goes in, and the most workgroups a (pair, group) is split over
+static int chunk_groups(const tkv_cache* c, int m) { return (m * c->G + 31) / 32; }
+static int chunk_max_splits(const tkv_cache* c, int m) { return std::max(1, c->cus / (c->dv.B * c->dv.Hkv * chunk_groups(c, m))); }
+
+// Scratch for launches that serve several query tokens per sequence: logits (or, where they are not written, packed query
+// vectors) and split partials per (sequence, query).  Allocated on the first such call, for as many queries as one launch
+// takes, and kept until the cache is destroyed.
 static tkv_status chunk_scratch(tkv_cache* c) {
-  if (c->xs_chunk) return TKV_OK;
+  if (c->po_chunk) return TKV_OK;
   const DevView& v = c->dv;
-  const size_t nb = (size_t)v.B * chunk_tokens_per_launch(c);
+  const int per = chunk_tokens_per_launch(c);
+  size_t xs = 0, cols = 0;                               // floats of xs; (pair, split, column)s
+  for (int m = 2; m <= per; ++m) {
+    const bool logits = c->es != 2 || attn_chunk_logits(m, c->G);
+    xs = std::max(xs, logits ? (size_t)v.B * m * v.Hq * c->xs_stride : (size_t)v.B * v.Hkv * ((m * c->G + 15) / 16) * 16 * v.D / 2);
+    cols = std::max(cols, (size_t)v.B * v.Hkv * (c->es == 2 ? chunk_max_splits(c, m) : c->S_alloc) * m * c->G);
+  }
   float *x = nullptr, *ml = nullptr, *po = nullptr;
-  if (!dalloc(c, x, nb * v.Hq * c->xs_stride) || !dalloc(c, ml, nb * v.Hkv * c->S_alloc * 2 * c->G) ||
-      !dalloc(c, po, nb * v.Hkv * c->S_alloc * c->G * v.D))
-    return fail(c, TKV_ENOMEM, "tkv_attend_and_score_chunk: no device memory for the scratch of %d query tokens per launch", chunk_tokens_per_launch(c));
+  if (!dalloc(c, x, xs) || !dalloc(c, ml, cols * 2) || !dalloc(c, po, cols * v.D))
+    return fail(c, TKV_ENOMEM, "tkv_attend_and_score_chunk: no device memory for the scratch of %d query tokens per launch", per);
   c->xs_chunk = x; c->ml_chunk = ml; c->po_chunk = po;
   return TKV_OK;
 }
@@ -769,8 +776,9 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     n_tiles_s = std::max(n_tiles_s, tiles(c->nS[b]));
   }
   if (n_tiles * TOK_PER_BLOCK > c->xs_stride) return fail(c, TKV_ESTATE, "tkv_attend_and_score: internal tile count %d exceeds the scratch", n_tiles);
-  const int nw = attn_waves_per_group(v.D, c->es, c->G, m);
-  const int tr = attn_tile_rows(v.D, c->es, m);
+  const bool cols = m > 1 && c->es == 2, logits = m > 1 && (!cols || attn_chunk_logits(m, c->G));   // a chunk's tokens as columns; its logits written
+  const int nw = cols ? attn_chunk_waves() : attn_waves_per_group(v.D, c->es, c->G);
+  const int tr = cols ? attn_chunk_tile_rows(v.D) : attn_tile_rows(v.D, c->es);
   const auto wave_tiles = [&](int n) { return (n + tr - 1) / tr; };
   int n_wt = 1, n_wt_s = 0;
   for (int b = 0; b < v.B; ++b) {
@@ -779,9 +787,11 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   }
   // Four tiles per workgroup, one per SIMD, until the pairs have all compute units; two waves of a SIMD that have one tile
   // each take nearly twice as long as one.  A chunk's workgroups leave more behind (every token's partials and logits), so
-  // from nine tiles on theirs have a tile for every wave: one sequence of 16384 tokens, 12/2 heads, two tokens takes 33 us a
-  // call so and 45 with four tiles each; eight sequences of 300 tokens 16.2 and 14.4.
-  const int S = std::max(1, std::min(c->S_alloc, m > 1 && n_wt > 8 ? (n_wt + nw - 1) / nw : (n_wt + 3) / 4));
+  // from 512 entries on theirs have a tile for every wave, and 64 entries for every wave where they have one block of columns.
+  int per_wg = 4;
+  if (cols) per_wg = tr == 32 ? (n_wt > 16 && attn_chunk_blocks(m * c->G) == 1 ? 16 : 8) : n_wt > 8 ? 8 : 4;
+  else if (m > 1 && n_wt > 8) per_wg = nw;
+  const int S = std::max(1, std::min(cols ? chunk_max_splits(c, m) : c->S_alloc, (n_wt + per_wg - 1) / per_wg));
   const int S2 = n_tiles_s > 0 ? std::max(1, std::min(c->S_alloc, (n_wt_s + 3) / 4)) : 0;
   AttnArgs a{};
   const bool step_launch = step && c->step_whole, whole = step_launch || (m == 1 && c->call_whole);
@@ -822,7 +832,8 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   a.S = S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;
   a.softmax_scale = c->softmax_scale; a.score_scale = c->score_scale;
   a.q_bs = q_bs; a.o_bs = o_bs; a.trim = trim;
-  if (c->es == 2) { a.n_q = 1; a.cq = m; } else { a.n_q = m; a.cq = 1; }   // 16-bit rows: the tokens as columns of one workgroup
+  if (cols) { a.n_q = 1; a.cq = m; a.groups = chunk_groups(c, m); a.G = c->G; if (!logits) a.xs_stride = 0; }
+  else { a.n_q = m; a.cq = 1; }
   EvPair* pe = nullptr;
   EvPair* pe2 = nullptr;
   EvPair* pf = nullptr;
@@ -847,8 +858,8 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
     HIPCHK(c, launch_attn_tiered(a2, v.D, c->G, c->kt, st, pe2 ? pe2->a : nullptr, pe2 ? pe2->b : nullptr));
   }
   if (whole) HIPCHK(c, launch_step_scores(a, v.D, st, pf ? pf->a : nullptr, pf ? pf->b : nullptr));
-  else if (m > 1) HIPCHK(c, launch_attn_finish_chunk(a, v.D, c->G, st));
-  else HIPCHK(c, launch_attn_finish(a, v.D, c->G, st, pf ? pf->a : nullptr, pf ? pf->b : nullptr));
+  else if (logits) HIPCHK(c, launch_attn_finish_chunk(a, v.D, c->G, st));
+  else if (m == 1) HIPCHK(c, launch_attn_finish(a, v.D, c->G, st, pf ? pf->a : nullptr, pf ? pf->b : nullptr));
   if (!last || noalloc) return TKV_OK;
   if (c->streamed && S2 > 0) {
     HIPCHK(c, hipEventRecord(c->ev_free[fr], st));
@@ -892,7 +903,7 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
     return fail(c, TKV_ESTATE, "tkv_attend_and_score_chunk: %d query tokens, but only %d positions were appended since the last tkv_migrate", n_q, c->n_assigned - c->n_at_plan);
   const DevView& v = c->dv;
   const size_t q_tok = (size_t)v.Hq * v.D * c->es, o_tok = (size_t)v.Hq * v.D * (c->cfg.out_dtype == TKV_F32 ? 4 : 2);
-  // The chunk's tokens go in groups of as many as one launch takes (16-bit rows: the cache is read once per group).
+  // The chunk's tokens go in groups of as many as one launch takes.
   // The streamed mode, whose frame serves one launch pair at a time, takes the tokens one by one.
   const int per = c->streamed ? 1 : chunk_tokens_per_launch(c);
   for (int j = 0; j < n_q; j += per) {

@@ -106,11 +106,14 @@ struct AttnArgs {
   int q_bs, o_bs;   // query heads between consecutive sequences in q and in out: Hq, or n_q * Hq for the tokens of a chunk
   int trim;         // entries at the end of list F this call leaves out (the chunk's later tokens); nF[] has them
                     // taken off already, the device counter has not
-  int n_q, cq;      // query tokens per sequence served by this launch: n_q groups along grid z (grid z = B * n_q) of cq
-                    // tokens each (columns of one workgroup; 16-bit rows only, cq * G <= 32).  Token jt = jz * cq + jc of
-                    // a sequence is jt * Hq heads further on in q and out, leaves n_q * cq - 1 - jt more entries of
-                    // list F out (it is that many positions older), and has logits and split partials of its own
-                    // (index b * n_q * cq + jt)
+  int n_q, cq;      // query tokens per sequence served by this launch: binary32 rows n_q along grid z (grid z = B * n_q),
+                    // 16-bit rows cq as columns (cq * G of them, in `groups` groups along grid z).  Token jt is jt * Hq heads
+                    // further on in q and out and leaves n_q * cq - 1 - jt more entries of list F out (it is that many
+                    // positions older).  It has logits and split partials of its own
+                    // (index b * n_q * cq + jt), but for chunks whose logits are not written (xs_stride == 0): part_ml is then
+                    // [B][Hkv][S][2][cq * G], part_o [B][Hkv][S][cq * G][D], and xs holds the query vectors as the matrix
+                    // instructions take them, [B][Hkv][blocks of 16 columns][D / 32][64 lanes]
+  int groups, G;    // chunks of 16-bit rows (else 0): column groups; query heads per kv head
   int nl;           // consecutive layers served by this launch (tkv_decode_step: 1 .. MAX_LAYERS_PER_LAUNCH; every other call:
                     // 1).  All per-layer arrays above are [layer][B]..., so layer li of sequence b is entry li * B + b of
                     // rows, q, out, xs and the partials; lists, counters and scores belong to sequence b alone
@@ -136,10 +139,16 @@ int attn_step_tile_rows(int D);
 int attn_step_lds_entries(int D, int G);
 hipError_t launch_step_scores(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t st);
-int attn_cols_per_launch(int elem_bytes, int G);   // query tokens one workgroup can take as columns
+// chunks of 16-bit rows (launch_attn_tiered with groups > 0 and xs_stride == 0 is then the whole call): blocks of 16 columns a workgroup takes,
+// its waves, their tiles, and the query tokens of one launch
+int attn_chunk_blocks(int n_cols);
+bool attn_chunk_logits(int n_tokens, int G);   // whether the logits are written, which launch_attn_finish_chunk then ends the call with
+int attn_chunk_waves();
+int attn_chunk_tile_rows(int D);
+int attn_chunk_tokens(int B, int Hq, int Hkv, int D);
 hipError_t launch_probe_read(const void* src, size_t bytes, int workgroups, uint32_t* sink, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
-int attn_waves_per_group(int D, int elem_bytes, int G, int cq = 1);   // waves per attention workgroup (one workgroup per compute unit)
-int attn_tile_rows(int D, int elem_bytes, int cq = 1);   // list entries per wave tile of that launch
+int attn_waves_per_group(int D, int elem_bytes, int G);   // waves per attention workgroup (one workgroup per compute unit)
+int attn_tile_rows(int D, int elem_bytes);   // list entries per wave tile of that launch
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles);   // how many of a pair's waves serve the Q list
 hipError_t launch_append(const DevView& v, int layer, const void* k, const void* v_, int pos0, int n_new,
                          bool assign, hipStream_t st);

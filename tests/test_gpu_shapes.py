@@ -367,6 +367,37 @@ def test_chunks_by_split_count_and_queries_side_by_side(n_q, shape):
     p.close()
 
 
+@pytest.mark.parametrize("n_q,kv_dtype,t2,scorer,shape", [
+    (17, "bf16", "int8_row", "attention", dict(batch=2, n_q_heads=2, n_kv_heads=2, head_dim=128, context=31)),     # G = 1, one group; a list of one tile
+    (33, "f16", "int4_g32", "attention", dict(batch=2, n_q_heads=3, n_kv_heads=1, head_dim=64, context=333)),      # 32 tokens in a launch, one behind them
+    (7, "bf16", "int4_g32", "combined", dict(batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=1500)),    # 35 columns: the second group nearly empty
+    (13, "f16", "int8_row", "vatp", dict(batch=3, n_q_heads=45, n_kv_heads=9, head_dim=128, context=700)),         # nine kv heads, 65 columns: more blocks than a wave keeps
+    (20, "bf16", "int8_row", "attention", dict(batch=1, n_q_heads=7, n_kv_heads=1, head_dim=128, context=6100)),   # more than 16 splits per pair
+    (5, "bf16", "int4_g32", "attention", dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=64, context=2500)),    # five to 16 splits, 64-row tiles
+    (6, "bf16", "int8_row", "attention", dict(batch=66, n_q_heads=7, n_kv_heads=1, head_dim=64, context=190)),     # list lengths from the device counters
+])
+def test_chunks_whose_logits_are_not_written(n_q, kv_dtype, t2, scorer, shape):
+    """More columns (query token, head) than one group of a workgroup takes: outputs and scores of a chunk over all four
+    tiers against the oracle, at the edges of column groups, list runs and split counts.  Tolerances as everywhere: the
+    products are exact in 16 bits and added in binary32."""
+    from gpu_common import Pair, assert_out_close, assert_scores_close
+    cfg = small_config(name="chunk", n_layers=1, kv_dtype=kv_dtype, t2_format=t2, decode_steps=n_q, k_window=8, sigma=1.0, **shape)
+    print(f"[case] chunk of {n_q}, {kv_dtype} {t2} {scorer}, {shape}", flush=True)
+    p = Pair(cfg, prefetch_mode="lazy", scorer=scorer)
+    tiers = np.random.default_rng(5).choice(4, size=(cfg.batch, cfg.context), p=(0.4, 0.3, 0.2, 0.1)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -8:] = 0
+    p.force_tiers(tiers)
+    ks, vs = zip(*[p.wl.step_kv(j, 0) for j in range(n_q)])
+    p.append(0, torch.cat(ks, dim=1), torch.cat(vs, dim=1))
+    got, ref = p.attend_chunk(0, torch.stack([p.wl.step_q(j, 0) for j in range(n_q)], dim=1).contiguous())
+    for j in range(n_q):
+        assert_out_close(got[:, j], ref[:, j], kv_dtype, f"query {j}")
+    total = n_q * cfg.n_q_heads * p.score_scale if scorer == "attention" else float(p.orc.score_mag.sum(axis=1).max())
+    assert_scores_close(p.gpu.get_scores(), p.orc.score, cfg.context + n_q, total, mag64=p.orc.score_mag)
+    p.close()
+
+
 @pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
 def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
