@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/tkv.h"
@@ -548,15 +549,32 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   ok = ok && dalloc(c, v.fpK, rows * v.capP * D * c->es) && dalloc(c, v.fpV, rows * v.capP * D * c->es);
   ok = ok && dalloc(c, v.c2K, rows * v.cap2 * v.cb) && dalloc(c, v.c2V, rows * v.cap2 * v.cb);
   ok = ok && dalloc(c, v.s2K, rows * v.cap2 * v.sb) && dalloc(c, v.s2V, rows * v.cap2 * v.sb);
-  ok = ok && dalloc(c, v.tier, BN) && dalloc(c, v.tier_new, BN) && dalloc(c, v.loc, BN) && dalloc(c, v.hloc, BN);
-  ok = ok && dalloc(c, v.score, BN) && dalloc(c, v.f_pos, BN) && dalloc(c, v.f_loc, BN) && dalloc(c, v.f_loc_old, BN);
-  ok = ok && dalloc(c, v.q_pos, BN) && dalloc(c, v.q_loc, BN) && dalloc(c, v.idx, 4 * BN) && dalloc(c, v.cnt, (size_t)B * CNT_N);
-  ok = ok && dalloc(c, v.free0, (size_t)B * v.cap0) && dalloc(c, v.free1, (size_t)B * v.cap1) && dalloc(c, v.free2, (size_t)B * v.cap2);
-  ok = ok && dalloc(c, v.pend, BN) && dalloc(c, v.rel0, BN) && dalloc(c, v.rel1, BN) && dalloc(c, v.rel2, BN);
-  ok = ok && dalloc(c, v.mv10_src, BN) && dalloc(c, v.mv10_dst, BN) && dalloc(c, v.mvq_src, BN) && dalloc(c, v.mvq_dst, BN);
-  ok = ok && dalloc(c, v.mvd_src, BN) && dalloc(c, v.mvd_dst, BN);
-  ok = ok && dalloc(c, v.g_seq, BN) && dalloc(c, v.g_src, BN) && dalloc(c, v.g_dst, BN);
-  ok = ok && dalloc(c, c->d_host_base, (size_t)B);
+  // The bookkeeping arrays, a few integers a position each, share one allocation: apart they are 29 of the 45 allocations of a
+  // cache, whose callbacks and frees a short request waits for (28 layers, 1422 tokens, 32 steps: 2695 us, 2624 this way).
+  {
+    char* base = nullptr;
+    size_t used = 0;
+    const auto place = [&](auto*& p, size_t count) {
+      if (base) p = (std::remove_reference_t<decltype(p)>)(base + used);
+      used += (count * sizeof(*p) + 255) & ~(size_t)255;
+    };
+    const auto arrays = [&] {
+      used = 0;
+      place(v.tier, BN); place(v.tier_new, BN); place(v.loc, BN); place(v.hloc, BN);
+      place(v.score, BN); place(v.f_pos, BN); place(v.f_loc, BN); place(v.f_loc_old, BN);
+      place(v.q_pos, BN); place(v.q_loc, BN); place(v.idx, 4 * BN); place(v.cnt, (size_t)B * CNT_N);
+      place(v.free0, (size_t)B * v.cap0); place(v.free1, (size_t)B * v.cap1); place(v.free2, (size_t)B * v.cap2);
+      place(v.pend, BN); place(v.rel0, BN); place(v.rel1, BN); place(v.rel2, BN);
+      place(v.mv10_src, BN); place(v.mv10_dst, BN); place(v.mvq_src, BN); place(v.mvq_dst, BN);
+      place(v.mvd_src, BN); place(v.mvd_dst, BN);
+      place(v.g_seq, BN); place(v.g_src, BN); place(v.g_dst, BN);
+      place(c->d_host_base, (size_t)B);
+    };
+    arrays();
+    base = ok ? (char*)dev_alloc(c, used) : nullptr;
+    ok = base != nullptr;
+    if (ok) arrays();
+  }
   if (cfg->scorer == TKV_SCORE_VATP || cfg->scorer == TKV_SCORE_COMBINED) ok = ok && dalloc(c, v.vnorm, (size_t)L * B * Hkv * N);
   if (cfg->scorer == TKV_SCORE_REDUNDANCY || cfg->scorer == TKV_SCORE_COMBINED)
     ok = ok && dalloc(c, v.red, (size_t)L * B * Hkv * N) && dalloc(c, v.last_k, (size_t)L * B * Hkv * D * v.es);
