@@ -1031,8 +1031,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
       v_rd[dl] = w.ta + SCR + (uint32_t)(ii * KU * PB) + (uint32_t)(8 * gg + ((2 * dl - (gg & 6)) & 7) + (qq >> 1)) * 16u + (uint32_t)(qq & 1) * 8u;
   }
 
-  // The columns' query vectors, right operand of the logits: fetched like K rows (a column past the last: zeros) through
-  // the tile buffer, where they arrive with the slot list, and read from there as K operands are.
+  // The columns' query vectors, right operand of the logits: fetched like K rows through the tile buffer, where they arrive
+  // with the slot list, and read from there as K operands are.  A column past the last repeats the last one: its products
+  // are then numbers wherever a real column's are (zeros times an infinite key element would not be).
   int n_seen[NCB];                             // list entries the column's query may see (the chunk's later tokens are cut off list F)
   size_t xrow[NCB];                            // LOG: where the column's logits go
   bool live[NCB];
@@ -1043,8 +1044,8 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     const float inv_g = 1.0f / (float)a.G;
 #pragma unroll
     for (int i = 0; i < 2 * NCB; ++i) {
-      const int col = c0 + 8 * i + g, jq = small_div(col, inv_g);
-      const uint32_t off = (col < ncol ? (uint32_t)(jq * a.Hq + kvh * a.G + (col - jq * a.G)) : 0x00ffffffu) * (uint32_t)RB + ((i & 1) ? kcol1 : kcol0);
+      const int col = c0 + 8 * i + g < ncol ? c0 + 8 * i + g : ncol - 1, jq = small_div(col, inv_g);
+      const uint32_t off = (uint32_t)(jq * a.Hq + kvh * a.G + (col - jq * a.G)) * (uint32_t)RB + ((i & 1) ? kcol1 : kcol0);
 #pragma unroll
       for (int j = 0; j < KU; ++j) dma<16>(rq, w.t + (i * KU + j) * PB, off + (uint32_t)j * 128u, 0);
     }
@@ -2062,15 +2063,16 @@ __device__ __forceinline__ void chunk_scores(const AttnArgs& a, int b, int e0, i
       for (int g = 0; g < ng; ++g) {
         u32x4 q[CS_QB][NKS];
         float2 st[CS_QB];
-        int seen[CS_QB];                                                     // entries the column's query sees (a column past the last: none)
+        int seen[CS_QB];                                                     // entries the column's query sees
 #pragma unroll
         for (int i = 0; i < CS_QB; ++i) {
           const int blk = sub + (g * CS_QB + i) * nsub, col = blk * 16 + n;
           const u32x4* qp = (const u32x4*)a.xs + ((size_t)(b * a.Hkv + kvh) * blocks + (blk < blocks ? blk : 0)) * (NKS * 64) + lane;
 #pragma unroll
           for (int ks = 0; ks < NKS; ++ks) q[i][ks] = qp[ks * 64];
-          st[i] = col < ncol ? sm_st[kvh * ncol + col] : make_float2(0.f, 0.f);   // (no column: zeros times zero)
-          seen[i] = (col < ncol ? IS_Q ? n_list : nF - (a.cq - 1 - small_div(col, inv_g)) : 0) - e0 - 4 * kb;
+          st[i] = sm_st[kvh * ncol + (col < ncol ? col : ncol - 1)];
+          if (col >= ncol) st[i].y = 0.f;                                    // the last column once more, with no weight
+          seen[i] = (IS_Q ? n_list : col < ncol ? nF - (a.cq - 1 - small_div(col, inv_g)) : nF) - e0 - 4 * kb;
         }
         for (int ti = 0; ti < nt; ++ti, buf ^= 1) {
           // this tile's rows are in (one later fetch at most has been asked for: the one f_ runs ahead by)

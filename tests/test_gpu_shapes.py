@@ -398,6 +398,53 @@ def test_chunks_whose_logits_are_not_written(n_q, kv_dtype, t2, scorer, shape):
     p.close()
 
 
+def _chunk_pair(cfg, tiers, k, v, k_new, v_new):
+    """A one-layer cache and its oracle over the given context rows, tiers forced, with the chunk's rows appended."""
+    from gpu_common import Pair
+    p = Pair(cfg, prefetch_mode="lazy", preload=False)
+    p.append(0, k, v)
+    p.force_tiers(tiers)
+    p.append(0, k_new, v_new)
+    return p
+
+
+def _step_rows(wl, n_q):
+    ks, vs = zip(*[wl.step_kv(j, 0) for j in range(n_q)])
+    return torch.cat(ks, dim=1), torch.cat(vs, dim=1), torch.stack([wl.step_q(j, 0) for j in range(n_q)], dim=1).contiguous()
+
+
+@pytest.mark.parametrize("n_q,heads,dim,kv_dtype,t2", [
+    (13, 7, 128, "bf16", "int8_row"),      # 91 columns: five past the last in the last block
+    (9, 5, 64, "f16", "int4_g32"),         # 45 columns
+    (3, 5, 128, "f16", "int8_row"),        # 15 columns: logits written
+])
+def test_chunk_over_keys_with_infinities(n_q, heads, dim, kv_dtype, t2):
+    """A key row with an element of -inf that every query multiplies by a positive number has a logit of -inf and no weight.
+    Its score stays what it was: the columns past a chunk's last (zeros times infinity) have no part in it."""
+    from gpu_common import assert_out_close, assert_scores_close
+    from tkv_synth import Workload
+    cfg = small_config(name="inf", n_layers=1, batch=2, n_q_heads=heads, n_kv_heads=1, head_dim=dim, kv_dtype=kv_dtype,
+                       t2_format=t2, context=700, decode_steps=n_q, k_window=16, sigma=1.0)
+    print(f"[case] infinite keys, chunk of {n_q}, {heads} heads, {dim}, {kv_dtype}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    k, v = wl.context_kv(0)
+    k_new, v_new, q = _step_rows(wl, n_q)
+    q[..., 3] = q[..., 3].abs() + 0.5
+    rows = [5, 100, 350, 690]
+    k[:, rows, :, 3] = float("-inf")
+    tiers = np.random.default_rng(7).choice(4, size=(cfg.batch, cfg.context), p=(0.4, 0.3, 0.2, 0.1)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    tiers[:, rows] = (0, 0, 1, 0)
+    p = _chunk_pair(cfg, tiers, k, v, k_new, v_new)
+    got, ref = p.attend_chunk(0, q)
+    assert_out_close(got, ref, kv_dtype)
+    scores = p.gpu.get_scores()
+    assert (scores[:, rows] == 0).all(), scores[:, rows]
+    assert_scores_close(scores, p.orc.score, cfg.context + n_q, n_q * heads * p.score_scale)
+    p.close()
+
+
 @pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
 def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
