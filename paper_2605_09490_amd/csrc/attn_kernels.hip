@@ -50,7 +50,7 @@ typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) char lds_char;
 
-constexpr float LOG2E = 1.4426950408889634f;
+constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
 constexpr int TB = TOK_PER_BLOCK;
 static_assert(TB == 64, "a tile is one list entry per lane");
 
@@ -916,6 +916,7 @@ template <int KT>
 struct PSplit {
   static constexpr int N = KT == KT_BF16 ? 3 : 2;
   static constexpr float P_SHIFT = KT == KT_BF16 ? 0.f : 14.f;
+  static constexpr float SCALE_MAX = 3.75f;   // binary16: what a weight of 1 can be multiplied by and stay in range (65504) with the shift
 };
 template <int KT>
 __device__ __forceinline__ void split_pair(float p0, float p1, uint32_t (&t)[PSplit<KT>::N]) {
@@ -1253,6 +1254,21 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     {
       const int e0 = tile * TR + 4 * kb;
       const bool edge = (tile + 1) * TR > n_list - (IS_Q ? 0 : a.cq - 1);   // wave-uniform: some column does not see the whole tile
+      // binary16 code rows: a weight times its V row's scale has to stay in binary16's range.  Where the tile has a scale
+      // beyond what the shift leaves room for (V of some 26 and more in an int4 group, 480 in an int8 row), such an entry counts
+      // with the logit of its scaled weight in the running reference, which is then above the largest logit: any reference
+      // does, the statistics are merged relative to it.
+      constexpr bool BOUND = IS_Q && KT == KT_F16;
+      bool big = false;                                  // wave-uniform
+      if constexpr (BOUND) {
+        uint32_t sv[SCD];
+        static_for<SCD>([&](auto jc) { constexpr int j = decltype(jc)::value; sv[j] = lds_rd32<j * (TR * 4)>(w.sva + (uint32_t)(lane & (TR - 1)) * 4u); });
+        lds_wait(); tie(sv);
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < SCD; ++j) s = fmaxf(s, M == Q_INT8 ? __builtin_bit_cast(float, sv[j]) : fmaxf(half_of(sv[j], 0), half_of(sv[j], 1)));
+        big = __builtin_amdgcn_ballot_w64(s > PSplit<KT>::SCALE_MAX) != 0;
+      }
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
         float mx = -INFINITY;
@@ -1270,6 +1286,23 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
           for (int j = 0; j < 4; ++j) mx = fmaxf(mx, p[cb][rb][j]);
+        if constexpr (BOUND) {
+          if (big)
+            static_for<NRB>([&](auto rc) {
+              constexpr int rb = decltype(rc)::value;
+              u32x4 sv[SCD];
+              static_for<SCD>([&](auto jc) { constexpr int i = decltype(jc)::value; sv[i] = lds_rd128<i * (TR * 4) + rb * 64>(w.sva + (uint32_t)kb * 16u); });
+              lds_wait(); tie(sv);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                float s = PSplit<KT>::SCALE_MAX;
+#pragma unroll
+                for (int i = 0; i < SCD; ++i) s = fmaxf(s, M == Q_INT8 ? elem_f(sv[i], j) : fmaxf(half_of(elem(sv[i], j), 0), half_of(elem(sv[i], j), 1)));
+                s = fminf(s, 65536.f);                   // (a scale is at most 65504 / 7; infinite ones stay infinite in the product)
+                mx = fmaxf(mx, fmaf(__builtin_amdgcn_logf(s * (1.0f / PSplit<KT>::SCALE_MAX)), LN2, p[cb][rb][j]));
+              }
+            });
+        }
         if constexpr (LOG) {
           if (live[cb]) {
 #pragma unroll

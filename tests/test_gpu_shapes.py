@@ -445,6 +445,37 @@ def test_chunk_over_keys_with_infinities(n_q, heads, dim, kv_dtype, t2):
     p.close()
 
 
+@pytest.mark.parametrize("every", [1, 9])
+@pytest.mark.parametrize("n_q,heads,dim,t2", [
+    (3, 5, 128, "int8_row"),               # 15 columns, one block, logits written
+    (5, 5, 64, "int4_g32"),                # 25 columns, two blocks
+    (9, 5, 128, "int4_g32"),               # 45 columns: logits not written
+    (13, 7, 64, "int8_row"),
+])
+def test_chunk_over_large_values_in_binary16(n_q, heads, dim, t2, every):
+    """T2 rows of a binary16 cache whose V scales are far above one (int8 rows up to some 5000, int4 groups up to 200 and 8000):
+    the weight times such a scale does not fit binary16 beside the weights' own shift.  Every row, or every ninth."""
+    from gpu_common import assert_out_close, assert_scores_close
+    from tkv_synth import Workload
+    cfg = small_config(name="large", n_layers=1, batch=2, n_q_heads=heads, n_kv_heads=1, head_dim=dim, kv_dtype="f16",
+                       t2_format=t2, context=900, decode_steps=n_q, k_window=16, sigma=1.0)
+    wl = Workload(cfg, device="cuda")
+    k, v = wl.context_kv(0)
+    k_new, v_new, q = _step_rows(wl, n_q)
+    tiers = np.random.default_rng(11).choice(4, size=(cfg.batch, cfg.context), p=(0.2, 0.1, 0.6, 0.1)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    for amp in (2.0, 100.0, 2000.0):
+        print(f"[case] values of {amp}, chunk of {n_q}, {heads} heads, {dim}, {t2}, every {every}", flush=True)
+        vv = v.clone()
+        vv[:, ::every] *= amp
+        p = _chunk_pair(cfg, tiers, k, vv, k_new, v_new)
+        got, ref = p.attend_chunk(0, q)
+        print(f"[case] worst error {assert_out_close(got, ref, 'f16', f'values of {amp}'):.2e} of the head max-norm", flush=True)
+        assert_scores_close(p.gpu.get_scores(), p.orc.score, cfg.context + n_q, n_q * heads * p.score_scale)
+        p.close()
+
+
 @pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
 def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
