@@ -496,6 +496,8 @@ struct WaveLds {
                                            // lcap (whole tiles) on are parked in memory
 };
 
+struct __attribute__((packed, aligned(2))) PackedU32x4 { u32x4 v; };   // 16 bytes at any 16-bit element
+
 template <int SZ>
 __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t& rs, char* lds, uint32_t voff, int aux) {
   static_assert(SZ == 16 || SZ == 4, "unit sizes");
@@ -1035,20 +1037,36 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   // The columns' query vectors, right operand of the logits: fetched like K rows through the tile buffer, where they arrive
   // with the slot list, and read from there as K operands are.  A column past the last repeats the last one: its products
   // are then numbers wherever a real column's are (zeros times an infinite key element would not be).
+  // Direct-to-LDS loads want the alignment that the cache's own rows have; queries that begin elsewhere come by plain loads.
   int n_seen[NCB];                             // list entries the column's query may see (the chunk's later tokens are cut off list F)
   size_t xrow[NCB];                            // LOG: where the column's logits go
   bool live[NCB];
   u32x4 qreg[NCB][NKS];
+  const bool q_aligned = ((uintptr_t)a.q & 15) == 0;
   {
     const int ncol = a.cq * a.G;
-    const __amdgpu_buffer_rsrc_t rq = make_rsrc((const char*)a.q + (size_t)b * a.q_bs * RB, (uint32_t)(a.cq * a.Hq) * RB);
+    const char* qb = (const char*)a.q + (size_t)b * a.q_bs * RB;
     const float inv_g = 1.0f / (float)a.G;
+    auto q_row = [&](int col) {                  // byte offset of a column's query vector
+      col = col < ncol ? col : ncol - 1;
+      const int jq = small_div(col, inv_g);
+      return (uint32_t)(jq * a.Hq + kvh * a.G + (col - jq * a.G)) * (uint32_t)RB;
+    };
+    if (q_aligned) {
+      const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)(a.cq * a.Hq) * RB);
 #pragma unroll
-    for (int i = 0; i < 2 * NCB; ++i) {
-      const int col = c0 + 8 * i + g < ncol ? c0 + 8 * i + g : ncol - 1, jq = small_div(col, inv_g);
-      const uint32_t off = (uint32_t)(jq * a.Hq + kvh * a.G + (col - jq * a.G)) * (uint32_t)RB + ((i & 1) ? kcol1 : kcol0);
+      for (int i = 0; i < 2 * NCB; ++i) {
+        const uint32_t off = q_row(c0 + 8 * i + g) + ((i & 1) ? kcol1 : kcol0);
 #pragma unroll
-      for (int j = 0; j < KU; ++j) dma<16>(rq, w.t + (i * KU + j) * PB, off + (uint32_t)j * 128u, 0);
+        for (int j = 0; j < KU; ++j) dma<16>(rq, w.t + (i * KU + j) * PB, off + (uint32_t)j * 128u, 0);
+      }
+    } else {
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        const char* src = qb + q_row(c0 + 16 * cb + n) + 16 * kb;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) qreg[cb][ks] = ((const PackedU32x4*)(src + 64 * ks))->v;
+      }
     }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
@@ -1123,11 +1141,13 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
 
   wait_vm<0>();                                          // the list and the query vectors are in
   read_locs(0, n_walk - tile0 * TR);
-  static_for<NCB>([&](auto cc) {
-    constexpr int cb = decltype(cc)::value;
-    static_for<NKS>([&](auto kc) { constexpr int ks = decltype(kc)::value; qreg[cb][ks] = lds_rd128<(2 * cb * KU + (ks >> 1)) * PB>(k_rd[ks & 1] - SCR); });
-  });
-  lds_wait();
+  if (q_aligned) {
+    static_for<NCB>([&](auto cc) {
+      constexpr int cb = decltype(cc)::value;
+      static_for<NKS>([&](auto kc) { constexpr int ks = decltype(kc)::value; qreg[cb][ks] = lds_rd128<(2 * cb * KU + (ks >> 1)) * PB>(k_rd[ks & 1] - SCR); });
+    });
+    lds_wait();
+  }
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) tie(qreg[cb]);
   issue_loc(1, tile0 + tstride);

@@ -476,6 +476,34 @@ def test_chunk_over_large_values_in_binary16(n_q, heads, dim, t2, every):
         p.close()
 
 
+@pytest.mark.parametrize("n_q,dim,kv_dtype", [
+    (3, 128, "bf16"),                      # 15 columns, logits written
+    (6, 64, "f16"),                        # 30 columns, logits written
+    (7, 128, "f16"),                       # 35 columns: logits not written
+    (9, 64, "bf16"),
+])
+def test_chunk_queries_may_begin_at_any_element(n_q, dim, kv_dtype):
+    """Queries that are contiguous but begin 2, 8 or 16 bytes into an allocation: the same bits as aligned ones."""
+    import paper_2605_09490_amd as tkv
+    cfg = small_config(name="offset", n_layers=1, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=dim, kv_dtype=kv_dtype,
+                       context=333, decode_steps=n_q, k_window=16, sigma=1.0)
+    print(f"[case] queries at an offset, chunk of {n_q}, {dim}, {kv_dtype}", flush=True)
+    from tkv_synth import Workload
+    wl = Workload(cfg, device="cuda")
+    k_new, v_new, q = _step_rows(wl, n_q)
+    seen = []
+    for off in (0, 1, 4, 8):
+        kv = tkv.TieredKV(1, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, dim, cfg.max_tokens, kv_dtype=kv_dtype, k_window=16, prefetch_mode="lazy")
+        kv.append(0, *wl.context_kv(0))
+        kv.append(0, k_new, v_new)
+        q_off = torch.empty(q.numel() + 8, dtype=q.dtype, device="cuda")[off:off + q.numel()].view(q.shape)
+        assert q_off.copy_(q).data_ptr() % 16 == 2 * off % 16
+        seen.append((kv.attend_and_score_chunk(0, q_off).cpu(), kv.get_scores().copy()))
+        kv.close()
+    for out, scores in seen[1:]:
+        assert torch.equal(out, seen[0][0]) and np.array_equal(scores.view(np.uint32), seen[0][1].view(np.uint32))
+
+
 @pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
 def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
