@@ -2800,11 +2800,15 @@ int attn_chunk_blocks(int n_cols) { return chunk_blocks(n_cols); }
 bool attn_chunk_logits(int n_tokens, int G) { return chunk_logits(n_tokens, G); }
 int attn_chunk_waves() { return MC_WAVES; }
 int attn_chunk_tile_rows(int D) { return mc_tile_rows(D); }
-// Query tokens of a chunk that one launch serves: as many as the score launch's LDS and grid z have room for.
+// Query tokens of a chunk that one launch serves: as many as grid z and, where the score launch is the second one, its LDS have
+// room for (128 kv heads at head_dim 128: 11 there, 16 with written logits).
 int attn_chunk_tokens(int B, int Hq, int Hkv, int D) {
   const int G = Hq / Hkv;
+  const auto room = [&](int m) {
+    return (int64_t)B * ((m * G + 15) / 16) <= 65535 && (chunk_logits(m, G) || chunk_scores_lds(Hq, Hkv, m, G, 1) <= cs_lds(D));
+  };
   int m = CHUNK_TOKENS;
-  while (m > 1 && (chunk_scores_lds(Hq, Hkv, m, G, 1) > cs_lds(D) || (int64_t)B * ((m * G + 15) / 16) > 65535)) --m;
+  while (m > 1 && !room(m)) --m;
   return m;
 }
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles) { return q_waves(n_waves, n_f_tiles, n_q_tiles); }

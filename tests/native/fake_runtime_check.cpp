@@ -300,6 +300,25 @@ static void chunk_splits() {
     }
 }
 
+// Chunks whose logits are written (up to 32 columns and 16 tokens) go in one launch pair whatever the number of heads; longer
+// ones in as many as the score launch's LDS makes of them, each with a sensible share.
+static void chunk_tokens_per_launch() {
+  const struct { int Hq, Hkv, D, m, launches; } cases[] = {
+      {128, 128, 128, 16, 1}, {128, 128, 128, 12, 1}, {128, 128, 128, 20, 2}, {128, 128, 64, 16, 1}, {128, 128, 64, 32, 1},
+      {96, 96, 128, 16, 1}, {128, 64, 128, 16, 1}, {28, 4, 128, 32, 1}, {28, 4, 128, 33, 2}, {128, 16, 128, 4, 1}};
+  for (auto& t : cases) {
+    tkv_config cfg = config(1, 2, t.Hq, t.Hkv, t.D, 400);
+    tkv_cache* c = nullptr;
+    CHECK(tkv_create(&cfg, &c) == TKV_OK);
+    fill(c, cfg, 100);
+    g_launches.clear();
+    OK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, t.m, STREAM));
+    if (count("k_attn_tiered") != t.launches) std::printf("%d/%d heads, head_dim %d, %d tokens: %d launches\n", t.Hq, t.Hkv, t.D, t.m, count("k_attn_tiered"));
+    CHECK(count("k_attn_tiered") == t.launches);
+    tkv_destroy(c);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_allocations") refused_allocations();
@@ -307,6 +326,7 @@ int main(int argc, char** argv) {
   else if (what == "route_follows_from_the_shape") route_follows_from_the_shape();
   else if (what == "long_lists_fill_the_chip") long_lists_fill_the_chip();
   else if (what == "chunk_splits") chunk_splits();
+  else if (what == "chunk_tokens_per_launch") chunk_tokens_per_launch();
   else { std::printf("no scenario %s\n", what.c_str()); return 2; }
   std::printf("%s: ok\n", what.c_str());
   return 0;

@@ -345,6 +345,7 @@ def test_single_calls_with_a_pair_for_every_compute_unit(shape):
     (3, dict(batch=32, n_q_heads=16, n_kv_heads=2, head_dim=64, context=600)),     # no room for four side by side: two
     (4, dict(batch=32, n_q_heads=28, n_kv_heads=4, head_dim=128, context=300)),    # ... one
     (13, dict(batch=32, n_q_heads=3, n_kv_heads=3, head_dim=64, context=300)),     # many queries in one launch
+    (16, dict(batch=1, n_q_heads=128, n_kv_heads=128, head_dim=128, context=150)), # ... of more heads than the score launch has LDS for
 ])
 def test_chunks_by_split_count_and_queries_side_by_side(n_q, shape):
     """The finishing kernel of a chunk in each of its launch shapes: outputs and scores of a chunk over all four tiers
