@@ -26,7 +26,7 @@
   } while (0)
 
 // ---- the runtime ---------------------------------------------------------------------------------------------------
-struct Launch { std::string kernel; dim3 grid; tkv::AttnArgs a; hipStream_t st; };
+struct Launch { std::string kernel; dim3 grid; tkv::AttnArgs a; hipStream_t st; size_t lds; };
 static std::map<const void*, std::string> g_kernels;
 static std::map<uintptr_t, size_t> g_mem;           // live device ranges
 static uintptr_t g_next = (uintptr_t)1 << 40;
@@ -102,21 +102,24 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) { g_cfg_grid = g; g_cfg_block = b; g_cfg_lds = lds; g_cfg_stream = s; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* s) { *g = g_cfg_grid; *b = g_cfg_block; *lds = g_cfg_lds; *s = g_cfg_stream; return hipSuccess; }
 
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t st) {
-  Launch l{g_kernels.at(f), grid, {}, st};
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t lds, hipStream_t st) {
+  Launch l{g_kernels.at(f), grid, {}, st, lds};
   g_log += 'L';
   const auto is = [&](const char* n) { return l.kernel.find(n) != std::string::npos; };
   if (is("k_attn") || is("k_step_scores") || is("k_call_scores")) {
     const tkv::AttnArgs& a = l.a = *(const tkv::AttnArgs*)args[0];
     CHECK(grid.x >= 1 && grid.y >= 1 && grid.y <= 65535 && grid.z >= 1 && grid.z <= 65535);
     const size_t seqs = (size_t)a.nl * a.B * a.n_q * a.cq, G = a.Hq / a.Hkv;
+    const size_t D = l.kernel.find("ILi128E") != std::string::npos ? 128 : 64;
     CHECK(a.xs_stride == 0 || inside(a.xs, seqs * a.Hq * a.xs_stride * 4));
+    // a chunk whose logits are not written keeps its packed query vectors there
+    if (a.groups && a.xs_stride == 0) CHECK(inside(a.xs, (size_t)a.B * a.Hkv * ((a.cq * G + 15) / 16) * (D / 32) * 64 * 16));
     if (a.sc) {
       const size_t sc = seqs * a.Hkv * a.sc_stride * 4;
       CHECK(inside(a.sc, sc));
       CHECK(a.xs_stride == 0 || (char*)a.xs >= (char*)a.sc + sc || (char*)a.xs + seqs * a.Hq * a.xs_stride * 4 <= (char*)a.sc);
     } else {
-      CHECK(inside(a.part_ml, seqs * a.Hkv * a.S_total * 2 * G * 4) && inside(a.part_o, seqs * a.Hkv * a.S_total * G * 64 * 4));
+      CHECK(inside(a.part_ml, seqs * a.Hkv * a.S_total * 2 * G * 4) && inside(a.part_o, seqs * a.Hkv * a.S_total * G * D * 4));
     }
     g_launches.push_back(l);
   }
@@ -281,23 +284,33 @@ static void long_lists_fill_the_chip() {
   g_cus = 256;
 }
 
-// A chunk's workgroups leave a partial per query token behind, and the finishing kernel merges a pair's one by one: no more
-// of them than have a (64-row) tile for each of their waves, but for lists of up to eight tiles.
+// A chunk's workgroups leave a partial per query token and head behind, which the second launch merges one by one: no more of
+// them than have a tile (8 KB of rows) for each of their eight waves, but for lists of up to eight 64-row tiles, and no more
+// than the compute units hold at once.  The second launch is the one that goes with written logits or the one that does
+// without, and what it asks of the LDS is there beside its tile buffers.
 static void chunk_splits() {
-  for (int n : {300, 700, 2000, 9000, 16384})
-    for (int m : {2, 4}) {
-      tkv_config cfg = config(1, 1, 28, 4, 128, n + m);
-      tkv_cache* c = nullptr;
-      CHECK(tkv_create(&cfg, &c) == TKV_OK);
-      fill(c, cfg, n + m);
-      g_launches.clear();
-      OK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, m, STREAM));
-      CHECK(count("k_attn_tiered_mc") == 1 && g_launches.size() == 2);
-      const int tiles = (n + m + 63) / 64, waves = m * 7 <= 16 ? 8 : 4;
-      CHECK(g_launches[0].a.S == (int)g_launches[0].grid.x);
-      CHECK(tiles <= 8 || (g_launches[0].a.S - 1) * waves < tiles);
-      tkv_destroy(c);
-    }
+  const struct { int B, Hq, Hkv, D; } shapes[] = {{1, 28, 4, 128}, {8, 28, 4, 128}, {1, 8, 8, 64}, {3, 40, 8, 64}, {64, 28, 4, 128}, {2, 128, 128, 64}, {70, 6, 2, 64}};
+  for (auto& t : shapes)
+    for (int n : {300, 700, 2000, 9000, 16384})
+      for (int m : {2, 3, 4, 5, 9, 16, 17, 32, 33}) {
+        tkv_config cfg = config(1, t.B, t.Hq, t.Hkv, t.D, n + m);
+        tkv_cache* c = nullptr;
+        CHECK(tkv_create(&cfg, &c) == TKV_OK);
+        fill(c, cfg, n + m);
+        g_launches.clear();
+        OK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, m, STREAM));
+        const int G = t.Hq / t.Hkv, first = m < 32 ? m : 32, cols = first * G;
+        const bool logits = cols <= 32 && first <= 16;
+        CHECK(g_launches.size() == (m > 32 ? 4u : 2u) && g_launches[0].kernel.find("k_attn_tiered_mc") != std::string::npos);
+        CHECK(g_launches[1].kernel.find(logits ? "k_attn_finish_chunk" : "k_attn_chunk_scores") != std::string::npos);
+        const Launch &l = g_launches[0], &l2 = g_launches[1];
+        const int rows = 4096 / t.D, tiles = (n + first + rows - 1) / rows, groups = (cols + 31) / 32;
+        CHECK(l.a.S == (int)l.grid.x && l.a.cq == first && (int)l.grid.y == t.Hkv && (int)l.grid.z == t.B * groups);
+        CHECK(l.a.S == 1 || l.a.S * t.B * t.Hkv * groups <= g_cus);
+        CHECK((tiles * rows <= 512 && t.D == 64) || (l.a.S - 1) * 8 < tiles);
+        if (!logits) CHECK(l2.lds + (size_t)8 * 2 * 32 * 2 * t.D <= 163840);   // two tiles of 32 rows for each of eight waves
+        tkv_destroy(c);
+      }
 }
 
 // Chunks whose logits are written (up to 32 columns and 16 tokens) go in one launch pair whatever the number of heads; longer
