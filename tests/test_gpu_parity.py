@@ -197,13 +197,21 @@ def test_prop1_t1_placement_is_bit_invisible(mode, kv_dtype, D, Hq, Hkv):
     assert np.array_equal(outs[0][1].view(np.uint32), outs[1][1].view(np.uint32))
 
 
-@pytest.mark.parametrize("kv_dtype,D,Hq,Hkv,t2", [("bf16", 128, 10, 2, "int8_row"), ("f16", 64, 8, 2, "int4_g32")])
-def test_prop1_holds_for_chunks_of_query_tokens(kv_dtype, D, Hq, Hkv, t2):
+@pytest.mark.parametrize("kv_dtype,D,Hq,Hkv,t2,chunks", [
+    ("bf16", 128, 10, 2, "int8_row", (5, 3)),                     # up to 32 columns: logits written
+    ("f16", 64, 8, 2, "int4_g32", (5, 3)),
+    ("bf16", 128, 10, 2, "int4_g32", (9, 4)),                     # 45 columns: the K rows are read once more for the scores
+    ("f16", 128, 10, 2, "int8_row", (13, 5)),
+    ("f16", 64, 8, 2, "int4_g32", (9, 5)),
+    ("bf16", 64, 8, 2, "int8_row", (12, 9)),
+])
+def test_prop1_holds_for_chunks_of_query_tokens(kv_dtype, D, Hq, Hkv, t2, chunks):
     """Zero-error offloading on the chunk path (several query tokens as columns of one launch): with rows in T1 the
-    outputs of every query token and the scores have the same bits as with those rows left in T0."""
+    outputs of every query token and the scores have the same bits as with those rows left in T0.  The first chunk comes
+    while transfers are still queued, so both of its launches read the rows from their old slots."""
     from gpu_common import Pair
     cfg = small_config(n_layers=2, batch=2, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, kv_dtype=kv_dtype,
-                       context=700, decode_steps=8, sigma=1.2, t2_format=t2)
+                       context=700, decode_steps=sum(chunks), sigma=1.2, t2_format=t2)
     rng = np.random.default_rng(13)
     tiers = _random_tiers(rng, cfg.batch, cfg.context, frac=(0.3, 0.45, 0.2, 0.05))
     twin = np.where(tiers == 1, 0, tiers).astype(np.uint8)
@@ -214,7 +222,7 @@ def test_prop1_holds_for_chunks_of_query_tokens(kv_dtype, D, Hq, Hkv, t2):
         p.gpu.set_tiers(tt)
         p.gpu.migrate()
         res, step = [], 0
-        for T in (5, 3):
+        for T in chunks:
             for l in range(cfg.n_layers):
                 ks, vs = zip(*[p.wl.step_kv(step + j, l) for j in range(T)])
                 p.gpu.append(l, torch.cat(ks, dim=1), torch.cat(vs, dim=1))
@@ -222,6 +230,7 @@ def test_prop1_holds_for_chunks_of_query_tokens(kv_dtype, D, Hq, Hkv, t2):
                 q = torch.stack([p.wl.step_q(step + j, l) for j in range(T)], dim=1).contiguous()
                 res.append(p.gpu.attend_and_score_chunk(l, q).cpu().reshape(-1))
             step += T
+        assert (p.gpu.get_stats()["lazy_old_reads"] > 0) == bool((tt == 1).any())
         outs.append((torch.cat(res), p.gpu.get_scores().copy()))
         p.close()
     assert torch.equal(outs[0][0].view(torch.uint8), outs[1][0].view(torch.uint8))

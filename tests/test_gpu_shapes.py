@@ -340,8 +340,11 @@ def test_single_calls_with_a_pair_for_every_compute_unit(shape):
 
 
 @pytest.mark.parametrize("n_q,shape", [
-    (2, dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=64, context=9001)),     # more than 16 splits per pair, eight waves
-    (4, dict(batch=1, n_q_heads=14, n_kv_heads=2, head_dim=128, context=4500)),    # ... four waves, four queries side by side
+    (2, dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=64, context=9001)),     # 16 splits per pair: one round of loads
+    (2, dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=64, context=9601)),     # more: a chain
+    (4, dict(batch=1, n_q_heads=14, n_kv_heads=2, head_dim=128, context=4500)),    # 16 splits, two blocks of columns, four queries side by side
+    (4, dict(batch=1, n_q_heads=14, n_kv_heads=2, head_dim=128, context=5200)),    # ... more
+    (2, dict(batch=1, n_q_heads=14, n_kv_heads=2, head_dim=128, context=9800)),    # more than 16 splits of 16 tiles, one block of columns
     (3, dict(batch=32, n_q_heads=16, n_kv_heads=2, head_dim=64, context=600)),     # no room for four side by side: two
     (4, dict(batch=32, n_q_heads=28, n_kv_heads=4, head_dim=128, context=300)),    # ... one
     (13, dict(batch=32, n_q_heads=3, n_kv_heads=3, head_dim=64, context=300)),     # many queries in one launch
@@ -376,6 +379,7 @@ def test_chunks_by_split_count_and_queries_side_by_side(n_q, shape):
     (20, "bf16", "int8_row", "attention", dict(batch=1, n_q_heads=7, n_kv_heads=1, head_dim=128, context=6100)),   # more than 16 splits per pair
     (5, "bf16", "int4_g32", "attention", dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=64, context=2500)),    # five to 16 splits, 64-row tiles
     (6, "bf16", "int8_row", "attention", dict(batch=66, n_q_heads=7, n_kv_heads=1, head_dim=64, context=190)),     # list lengths from the device counters
+    (32, "bf16", "int8_row", "attention", dict(batch=4, n_q_heads=128, n_kv_heads=128, head_dim=64, context=2300)),   # 68 KB of dynamic LDS, two runs of tiles
 ])
 def test_chunks_whose_logits_are_not_written(n_q, kv_dtype, t2, scorer, shape):
     """More columns (query token, head) than one group of a workgroup takes: outputs and scores of a chunk over all four
