@@ -161,9 +161,9 @@ typedef struct {
                                  (positions no longer in T1) would have cost more link time than the rewrite */
   int64_t device_bytes;       /* device memory the cache holds (pools, frames, lists, scratch) */
   int64_t pinned_bytes;       /* pinned host memory the cache holds */
-  double attn_finish_ms;      /* profile != 0: summed duration of the finishing kernels (merge, output, scores) */
+  double attn_finish_ms;      /* profile != 0: summed duration of the finishing kernels (merge, output, scores); not a chunk's */
   double attn_call_ms;        /* profile bit 0: summed time from the start of a call's first kernel to the end of its last
-                                 (the event pairs around every kernel stretch the gaps between them) */
+                                 (the event pairs around every kernel stretch the gaps between them); without chunks */
   double step_ms;             /* profile bit 1: summed device time of the tkv_decode_step calls, from an event before the
                                  append launch to one behind the last layer's finishing kernel */
   int64_t steps_timed;

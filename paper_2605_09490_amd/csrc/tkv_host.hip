@@ -858,13 +858,16 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if ((c->cfg.profile & 1) && !noalloc) {
     const size_t i0 = c->prof_used;
     if (!next_pair(c->prof_events, c->prof_used) || (S2 > 0 && !next_pair(c->prof_events, c->prof_used)) ||
-        !next_pair(c->prof_events, c->prof_used))
+        (m == 1 && !next_pair(c->prof_events, c->prof_used)))
       return fail(c, TKV_EDEVICE, "hipEventCreate failed");
     pe = &c->prof_events[i0];          // taken after the pool has stopped growing
     pe->dir = 0;
     if (S2 > 0) { pe2 = &c->prof_events[i0 + 1]; pe2->dir = 2; }
-    pf = &c->prof_events[c->prof_used - 1];
-    pf->dir = 3; pf->bytes = (int64_t)i0;   // index of the call's first kernel
+    // (a chunk's second launch is not timed: a pair taken for it would still hold the times of whoever had it before)
+    if (m == 1) {
+      pf = &c->prof_events[c->prof_used - 1];
+      pf->dir = 3; pf->bytes = (int64_t)i0;   // index of the call's first kernel
+    }
   }
   HIPCHK(c, launch_attn_tiered(a, v.D, c->G, c->kt, st, pe ? pe->a : nullptr, pe ? pe->b : nullptr));
   if (S2 > 0) {

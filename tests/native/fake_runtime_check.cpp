@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -36,6 +37,7 @@ static std::string g_log;                           // A: device allocation, S: 
 static int g_allocs = 0, g_fail_at = -1, g_fail_from = 1 << 30, g_cus = 256;
 static size_t g_fail_above = SIZE_MAX;
 static hipStream_t g_capturing = nullptr;
+static std::set<hipEvent_t> g_recorded;
 static dim3 g_cfg_grid, g_cfg_block;
 static size_t g_cfg_lds;
 static hipStream_t g_cfg_stream;
@@ -89,11 +91,15 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
 }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { g_recorded.erase(e); std::free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { g_recorded.insert(e); return hipSuccess; }
 hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {   // 1 ms between a kernel's two events
+  if (!g_recorded.count(a) || !g_recorded.count(b)) return err(hipErrorInvalidHandle);
+  *ms = 1.f;
+  return hipSuccess;
+}
 
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
 void __hipUnregisterFatBinary(void**) {}
@@ -125,7 +131,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t l
   }
   return hipSuccess;
 }
-hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t st, hipEvent_t, hipEvent_t, int) {
+hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t st, hipEvent_t e0, hipEvent_t e1, int) {
+  for (hipEvent_t e : {e0, e1}) if (e) g_recorded.insert(e);
   return hipLaunchKernel(f, g, b, args, lds, st);
 }
 }
@@ -332,6 +339,25 @@ static void chunk_tokens_per_launch() {
   }
 }
 
+// Kernel times count what was launched since they were last read: single calls their two launches, a chunk its first.
+static void kernel_times() {
+  tkv_config cfg = config(2, 2, 28, 4, 128, 400);
+  cfg.profile = 1;
+  tkv_cache* c = nullptr;
+  CHECK(tkv_create(&cfg, &c) == TKV_OK);
+  fill(c, cfg, 100);
+  tkv_stats st;
+  const auto read = [&](double kernel, double finish, double call) {
+    OK(tkv_get_stats(c, &st));
+    CHECK(st.attn_kernel_ms == kernel && st.attn_finish_ms == finish && st.attn_call_ms == call);
+  };
+  for (int i = 0; i < 6; ++i) OK(tkv_attend_and_score(c, i & 1, DATA, DATA, STREAM));
+  read(6, 6, 6);
+  for (int m : {4, 9, 33}) OK(tkv_attend_and_score_chunk(c, 0, DATA, DATA, m, STREAM));   // 33 tokens: 32 and a single call
+  read(10, 7, 7);
+  tkv_destroy(c);
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_allocations") refused_allocations();
@@ -340,6 +366,7 @@ int main(int argc, char** argv) {
   else if (what == "long_lists_fill_the_chip") long_lists_fill_the_chip();
   else if (what == "chunk_splits") chunk_splits();
   else if (what == "chunk_tokens_per_launch") chunk_tokens_per_launch();
+  else if (what == "kernel_times") kernel_times();
   else { std::printf("no scenario %s\n", what.c_str()); return 2; }
   std::printf("%s: ok\n", what.c_str());
   return 0;
