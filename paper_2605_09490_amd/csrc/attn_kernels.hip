@@ -578,9 +578,15 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
       }
   } else if constexpr (QLDS) {
     const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + (size_t)jq * a.Hq + kvh * G) * D * 2;
-    const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)(G * D * 2));   // lanes past the block fetch zeros
+    if (((uintptr_t)a.q & 15) == 0) {
+      const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)(G * D * 2));   // lanes past the block fetch zeros
 #pragma unroll
-    for (int i = 0; i < NQD; ++i) dma<16>(rq, w.p + i * 1024, (uint32_t)(i * 1024 + lane * 16), 0);
+      for (int i = 0; i < NQD; ++i) dma<16>(rq, w.p + i * 1024, (uint32_t)(i * 1024 + lane * 16), 0);
+    } else {                                             // (queries that begin between 16-byte boundaries: plain loads; none is left to wait for)
+#pragma unroll
+      for (int i = 0; i < NQD; ++i)
+        if (i * 1024 + lane * 16 < G * D * 2) lds_wr128<0>(w.pa + (uint32_t)(i * 1024 + lane * 16), ((const PackedU32x4*)(qb + i * 1024 + lane * 16))->v);
+    }
   } else {
     const char* qb = (const char*)a.q + ((size_t)b * a.q_bs + (size_t)jq * a.Hq + kvh * G) * D * 4;
 #pragma unroll

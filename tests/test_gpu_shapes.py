@@ -509,6 +509,34 @@ def test_chunk_queries_may_begin_at_any_element(n_q, dim, kv_dtype):
         assert torch.equal(out, seen[0][0]) and np.array_equal(scores.view(np.uint32), seen[0][1].view(np.uint32))
 
 
+@pytest.mark.parametrize("heads,kv_heads,dim,kv_dtype", [(8, 2, 64, "bf16"), (7, 1, 64, "f16"), (16, 2, 64, "bf16"), (10, 2, 128, "f16"), (8, 2, 64, "f32")])
+def test_single_queries_may_begin_at_any_element(heads, kv_heads, dim, kv_dtype):
+    """The same for one query token per sequence, in per-layer calls and in a step over 96 pairs (one workgroup each)."""
+    import paper_2605_09490_amd as tkv
+    from tkv_synth import Workload
+    L = 48 // kv_heads
+    cfg = small_config(name="offset", n_layers=L, batch=2, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=dim, kv_dtype=kv_dtype,
+                       context=333, decode_steps=2, k_window=16, sigma=1.0)
+    print(f"[case] single queries at an offset, {heads}/{kv_heads} heads, {dim}, {kv_dtype}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    k_all, v_all, q_all = wl.decode_inputs(0, 1)
+    q = q_all[0]
+    seen = []
+    for off in (0, 1, 4, 8):
+        kv = tkv.TieredKV(L, cfg.batch, heads, kv_heads, dim, cfg.max_tokens, kv_dtype=kv_dtype, k_window=16, prefetch_mode="lazy")
+        for l in range(L):
+            kv.append(l, *wl.context_kv(l))
+        q_off = torch.empty(q.numel() + 8, dtype=q.dtype, device="cuda")[off:off + q.numel()].view(q.shape)
+        q_off.copy_(q)
+        step = kv.decode_step(k_all[0], v_all[0], q_off).cpu()
+        call = kv.attend_and_score(1, q_off[1]).cpu()
+        seen.append((step, call, kv.get_scores().copy()))
+        kv.close()
+    for step, call, scores in seen[1:]:
+        assert torch.equal(step, seen[0][0]) and torch.equal(call, seen[0][1])
+        assert np.array_equal(scores.view(np.uint32), seen[0][2].view(np.uint32))
+
+
 @pytest.mark.parametrize("kv_dtype,t2", [("bf16", "int8_row"), ("f16", "int4_g32")])
 def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     """A workgroup that walks a whole pair adds far more rows into one binary32 sum than a split one does, T2 codes among
