@@ -26,11 +26,12 @@
 //                 Hq remaining workgroups merge the split outputs of one query head each into out[b, hq].
 //   attn_tiered_mc : the same launch for a chunk of query tokens (tkv_attend_and_score_chunk, 16-bit rows).  The
 //                 tokens ride as extra columns beside the G heads of the group (up to 32 columns per workgroup, as many
-//                 groups of them as there are along grid z): per tile a (64 rows x D) by (D x columns) product and its
+//                 groups of them as there are along grid z): per 8 KB tile a (rows x D) by (D x columns) product and its
 //                 transpose-side twin for the output, which is a dense contraction and runs on the matrix cores
-//                 (16x16x32 instructions; code rows widened to 16-bit values in LDS first).  No logits are written:
-//                 attn_chunk_scores has the products once more and adds the weights to the scores.  binary32 rows: one
-//                 set of attn_tiered's workgroups per token, and attn_finish_chunk.
+//                 (16x16x32 instructions; code rows widened to 16-bit values in LDS first).  Up to 32 columns and 16
+//                 tokens: the logits are written and attn_finish_chunk makes scores and outputs of them.  Beyond, none
+//                 are: attn_chunk_scores has the products once more, adds the weights to the scores and merges the
+//                 outputs.  binary32 rows: one set of attn_tiered's workgroups per token, and attn_finish_chunk.
 // The tile boundaries, the wave assignment and the fp32 summation order depend only on the lists' logical order and
 // lengths, never on whether a row lives in the HBM pool or the staging buffer (both are one slot space), which is
 // what makes T1 placement bit-invisible (Prop. 1).  A decode step (one query token) uses no matrix instructions: the
@@ -1783,9 +1784,10 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
 // The chunk's a.cq * a.G columns go in groups of 16 * NCB along grid z (x batch), whatever token a group begins with, so
 // that one launch serves them all: 13 tokens of seven heads are three groups of 32 columns.  Eight waves per workgroup, two
 // per SIMD, with 8 KB tiles.  A wave's result arrives complete (no row-group partials): [column][D], parked in the LDS.
-// LOG: one group of columns; the logits go to memory and attn_finish_chunk reads them.  Else no logits leave the kernel: a float per row and column
-// is a quarter of the rows' bytes at 32 columns and costs more than that (stores beside the row stream), while the score
-// launch below has the products again for half of the rows' bytes, once for all columns.
+// LOG: one group of columns; the logits go to memory and attn_finish_chunk reads them.  Else no logits leave the kernel: a
+// float per row and column is a quarter of the rows' bytes at 32 columns and costs more than that (stores beside the row
+// stream), while the score launch below has the products again for half of the rows' bytes, once for all columns.
+// Registers with two blocks of columns at head_dim 128: 250-255 of 256 in bfloat16; binary16 spills one (six with LOG).
 constexpr int MC_WAVES = 8;
 constexpr int mc_tile_rows(int D) { return 8192 / (2 * D); }
 constexpr int chunk_blocks(int ncol) { return ncol <= 16 ? 1 : 2; }      // of 16 columns, per workgroup
@@ -1890,7 +1892,8 @@ __global__ __launch_bounds__(MC_WAVES * 64, MC_WAVES / 4) void k_attn_tiered_mc(
 // kv heads and all of the chunk's columns, and adds every entry's weights, summed, to its score: wave w takes kv heads
 // w / nsub, + 8 / nsub, ... and of their columns blocks w % nsub, + nsub, ...; a kv head's blocks, then the kv heads are
 // added in that order.  The weights are exp2 of the same products (same instructions, same operand order) less the merged
-// maximum, times the merged 1 / l, so they sum to one like the ones that went into the output.  The last workgroups of a
+// maximum, times the merged 1 / l: those that went into the output but for one rounding of the scaled logit, which the fma
+// that takes the maximum off does not make.  The last workgroups of a
 // sequence (n_out) merge its splits into out; beside the rows, in the other workgroups, that took 4 us more.
 // Bound by rows arriving, half of what the launch before fetched.  Two tiles per wave are in flight (64-128 KB per compute
 // unit); nothing else goes through the vector memory pipe in the loop, because waiting for it would mean waiting for the
@@ -2701,8 +2704,8 @@ static hipError_t run_tiered(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, 
 }
 // Several query tokens as columns of one workgroup (16-bit rows): a (rows x D) by (D x columns) contraction, on the matrix
 // cores; then the scores and the outputs.
-// Tiles per workgroup of the score launch: one workgroup for every compute unit but some for the outputs, as far as the LDS
-// has room.
+// Tiles per workgroup of the score launch: one workgroup for every compute unit (of 256) but some 32 for the outputs, as far
+// as the LDS has room.
 static int chunk_tiles_per_wg(const AttnArgs& a, int D, int tiles) {
   int tpw = (int)std::min<int64_t>(CS_THREADS / CS_ROWS, ((int64_t)(tiles + 1) * a.B + 223) / 224);
   while (tpw > 1 && chunk_scores_lds(a.Hq, a.Hkv, a.cq, a.G, tpw) > cs_lds(D)) --tpw;

@@ -550,7 +550,8 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   ok = ok && dalloc(c, v.c2K, rows * v.cap2 * v.cb) && dalloc(c, v.c2V, rows * v.cap2 * v.cb);
   ok = ok && dalloc(c, v.s2K, rows * v.cap2 * v.sb) && dalloc(c, v.s2V, rows * v.cap2 * v.sb);
   // The bookkeeping arrays, a few integers a position each, share one allocation: apart they are 29 of the 45 allocations of a
-  // cache, whose callbacks and frees a short request waits for (28 layers, 1422 tokens, 32 steps: 2695 us, 2624 this way).
+  // cache, each with its callback and its free.  (A request of 28 layers, 1422 tokens and 32 steps takes the same time either
+  // way, as far as its runs, which differ by 3 % and more, can tell.)
   {
     char* base = nullptr;
     size_t used = 0;
@@ -805,7 +806,10 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   }
   // Four tiles per workgroup, one per SIMD, until the pairs have all compute units; two waves of a SIMD that have one tile
   // each take nearly twice as long as one.  A chunk's workgroups leave more behind (every token's partials and logits), so
-  // from 512 entries on theirs have a tile for every wave, and 64 entries for every wave where they have one block of columns.
+  // theirs have a tile for every wave (16-bit rows at head_dim 64 from nine tiles on; four or eight are the same below), and
+  // two where a wave has one block of columns, 32-row tiles and a pair more than 16 of them.  us a call with 4 / 8 / 16 tiles a
+  // workgroup: head_dim 128, 12/2 heads, two tokens: one sequence of 16384 31.0 / 21.8 / 18.9, of 4000 13.9 / 13.6 / 13.4
+  // (eight of 2000: 15.9 / 14.1 / 16.2); 28/4, four tokens, 8000: 29.9 / 21.7 / 23.6; head_dim 64, 16/2, two, 9000: 14.2 / 12.3 / 15.0.
   int per_wg = 4;
   if (cols) per_wg = tr == 32 ? (n_wt > 16 && attn_chunk_blocks(m * c->G) == 1 ? 16 : 8) : n_wt > 8 ? 8 : 4;
   else if (m > 1 && n_wt > 8) per_wg = nw;
@@ -924,8 +928,8 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
     return fail(c, TKV_ESTATE, "tkv_attend_and_score_chunk: %d query tokens, but only %d positions were appended since the last tkv_migrate", n_q, c->n_assigned - c->n_at_plan);
   const DevView& v = c->dv;
   const size_t q_tok = (size_t)v.Hq * v.D * c->es, o_tok = (size_t)v.Hq * v.D * (c->cfg.out_dtype == TKV_F32 ? 4 : 2);
-  // The chunk's tokens go in groups of as many as one launch takes.
-  // The streamed mode, whose frame serves one launch pair at a time, takes the tokens one by one.
+  // The chunk's tokens go in groups of as many as one launch takes.  The streamed mode, whose frame serves one launch pair at
+  // a time, takes the tokens one by one.
   const int per = c->streamed ? 1 : chunk_tokens_per_launch(c);
   for (int j = 0; j < n_q; j += per) {
     const int m = std::min(per, n_q - j);

@@ -139,8 +139,8 @@ int attn_step_tile_rows(int D);
 int attn_step_lds_entries(int D, int G);
 hipError_t launch_step_scores(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t st);
-// chunks of 16-bit rows (launch_attn_tiered with groups > 0 and xs_stride == 0 is then the whole call): blocks of 16 columns a workgroup takes,
-// its waves, their tiles, and the query tokens of one launch
+// chunks of 16-bit rows (launch_attn_tiered with groups > 0; with xs_stride == 0 it is the whole call): blocks of 16 columns a
+// workgroup takes, its waves, their tiles, and the query tokens of one launch
 int attn_chunk_blocks(int n_cols);
 bool attn_chunk_logits(int n_tokens, int G);   // whether the logits are written, which launch_attn_finish_chunk then ends the call with
 int attn_chunk_waves();
