@@ -2810,7 +2810,7 @@ bool attn_chunk_logits(int n_tokens, int G) { return chunk_logits(n_tokens, G); 
 int attn_chunk_waves() { return MC_WAVES; }
 int attn_chunk_tile_rows(int D) { return mc_tile_rows(D); }
 // Query tokens of a chunk that one launch serves: as many as grid z and, where the score launch is the second one, its LDS have
-// room for (128 kv heads at head_dim 128: 11 there, 16 with written logits).
+// room for (128 kv heads at head_dim 128: 16, the most with written logits; the score launch would have room for 11).
 int attn_chunk_tokens(int B, int Hq, int Hkv, int D) {
   const int G = Hq / Hkv;
   const auto room = [&](int m) {
