@@ -493,8 +493,8 @@ struct WaveLds {
   char* t; char* sk; char* sv; char* lt;   // tile buffer (K rows, then V rows, in turn), K scales, V scales, slot lists (2 x 64 ints)
   char* p;                                 // probabilities of the current tile (before the first tile: the query block)
   uint32_t ta, ska, sva, lta, pa;          // the same as LDS addresses
-  uint32_t lga; int lcap;                  // a workgroup that walks a whole pair: logits [G][lcap] in LDS; the columns from
-                                           // lcap (whole tiles) on are parked in memory
+  uint32_t lga; int lcap, lim;             // k_attn_step: logits [G][lcap] in LDS; the columns from lim (whole tiles: lcap, or
+  float* sp; int sp_stride;                // none for a part of a pair) on go to memory, column c of head h to sp[h * sp_stride + c]
 };
 
 struct __attribute__((packed, aligned(2))) PackedU32x4 { u32x4 v; };   // 16 bytes at any 16-bit element
@@ -778,15 +778,15 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
       }
       if constexpr (WHOLE) {
         // the logits stay in the LDS as far as it goes; the rest of a longer list is parked in memory for the workgroup
-        if (col0 + tile * TR + TR <= w.lcap) {
+        if (col0 + tile * TR + TR <= w.lim) {
           if (valid) {
 #pragma unroll
             for (int h = 0; h < G; ++h) lds_wr32(w.lga + (uint32_t)(h * w.lcap + col) * 4u, __builtin_bit_cast(uint32_t, x[h]));
           }
         } else if (valid) {
-          float* sp = a.xs + ((size_t)(b * a.Hkv + kvh) * G) * a.xs_stride + (col - w.lcap);
+          float* sp = w.sp + col;
 #pragma unroll
-          for (int h = 0; h < G; ++h) sp[(size_t)h * a.xs_stride] = x[h];
+          for (int h = 0; h < G; ++h) sp[(size_t)h * w.sp_stride] = x[h];
         }
       } else if (valid) {
         const size_t xbase = xs_at(a, b * a.n_q + jq, kvh * G, col);
@@ -1665,6 +1665,8 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
 // The LDS holds eight 8 KB tile buffers (32 rows of 256 bytes; 64 KB in flight per compute unit stream as fast as 128 KB)
 // and the logits of LCAP entries; a longer list parks the rest in memory and reads it back.  The eight waves are divided
 // between the lists as in the split launch (a wave that walked both would need some 90 registers more than it has).
+// The pairs that fill the last round of the chip only in part, those of the (layer, sequence) rows from a.whole_rows on, are cut into a.S parts of eight waves
+// each (the host's rule: step_tail): a part writes its logits and a partial, as in the split launch.
 template <int D, int G>
 struct StepGeo {
   static constexpr int NW = 8, RB = 2 * D, TR = 8192 / RB < 64 ? 8192 / RB : 64, TILE = TR * RB;
@@ -1686,7 +1688,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   __shared__ float sm_lg[G * LCAP];
   __shared__ float sm_ml[NW * 16];
   __shared__ float2 sm_fin[8];
-  const int kvh = blockIdx.x, bl = blockIdx.y, li = bl / a.B, b = bl - li * a.B;
+  const int kvh = blockIdx.x;
+  int bl = blockIdx.y, part = 0;
+  const bool split = bl >= a.whole_rows;
+  if (split) { const int x = bl - a.whole_rows; bl = a.whole_rows + x / a.S; part = x - (bl - a.whole_rows) * a.S; }
+  const int li = bl / a.B, b = bl - li * a.B, pair = bl * a.Hkv + kvh;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int* f_loc = (((a.old_mask >> li) & 1) ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax;
   int nF, nQ;
@@ -1699,6 +1705,9 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   w.sk = sm_sc + wave * 2 * SG::SC; w.sv = w.sk + SG::SC; w.lt = sm_lt + wave * SG::LT;
   w.ta = lds_addr(w.t); w.pa = lds_addr(w.p); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
   w.lga = lds_addr(sm_lg); w.lcap = LCAP;
+  w.lim = split ? 0 : LCAP;
+  w.sp = split ? a.xt + (size_t)(pair + a.tail0) * G * a.sc_stride : a.xs + (size_t)pair * G * a.xs_stride - LCAP;
+  w.sp_stride = split ? a.sc_stride : a.xs_stride;
   float* my_o = (float*)w.t;
 
   float o[G][EV], m_run[G], l_lane[G];
@@ -1708,10 +1717,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
 #pragma unroll
     for (int e = 0; e < EV; ++e) o[h][e] = 0.f;
   }
-  const int nwq = a.B <= ATTN_ARG_SEQS ? a.nWq[b] : q_waves(NW, nft, (nQ + TR - 1) / TR), nwf = NW - nwq;
-  if (wave < nwf) attn_wave<D, G, MF, KT, TR, true>(a, w, bl, 0, kvh, lane, wave, nwf, nF, f_loc, 0, o, m_run, l_lane);
-  else if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, true>(a, w, bl, 0, kvh, lane, wave - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
-  else attn_wave<D, G, Q_INT4, KT, TR, true>(a, w, bl, 0, kvh, lane, wave - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+  const int nwv = split ? NW * a.S : NW, u = part * NW + wave;       // the pair's waves, and which of them this is
+  const int nwq = a.B > ATTN_ARG_SEQS ? q_waves(nwv, nft, (nQ + TR - 1) / TR) : split ? a.nWs[b] : a.nWq[b], nwf = nwv - nwq;
+  if (u < nwf) attn_wave<D, G, MF, KT, TR, true>(a, w, bl, 0, kvh, lane, u, nwf, nF, f_loc, 0, o, m_run, l_lane);
+  else if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, true>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+  else attn_wave<D, G, Q_INT4, KT, TR, true>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
   // ---- merge the waves
 #pragma unroll
   for (int h = 0; h < G; ++h) {
@@ -1726,6 +1736,34 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
     if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
   }
   __syncthreads();
+  if (split) {
+    // a part of a pair: its partial; k_step_scores_parts has the rest of the way
+    const size_t sp = (size_t)(pair + a.tail0) * a.S + part;
+    for (int i = t; i < G * D; i += NW * 64) {
+      const int h = i / D;
+      float mb = sm_ml[h], acc = 0.f;
+#pragma unroll
+      for (int ww = 1; ww < NW; ++ww) mb = fmaxf(mb, sm_ml[ww * 16 + h]);
+      if (mb > -INFINITY) {
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww)
+          acc = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + h] - mb) * LOG2E), ((const float*)(sm_t + ww * TILE))[i], acc);
+      }
+      a.part_o[sp * G * D + i] = acc;
+    }
+    if (t < G) {
+      float mb = sm_ml[t], ll = 0.f;
+#pragma unroll
+      for (int ww = 1; ww < NW; ++ww) mb = fmaxf(mb, sm_ml[ww * 16 + t]);
+      if (mb > -INFINITY) {
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) ll = fmaf(__builtin_amdgcn_exp2f((sm_ml[ww * 16 + t] - mb) * LOG2E), sm_ml[ww * 16 + 8 + t], ll);
+      }
+      a.part_ml[sp * 2 * G + t] = mb;
+      a.part_ml[sp * 2 * G + G + t] = ll;
+    }
+    return;
+  }
   if (t < G) {
     float mb = sm_ml[t], ll = 0.f;
 #pragma unroll
@@ -2640,6 +2678,110 @@ __global__ __launch_bounds__(1024) void k_step_scores(const AttnArgs a, int tr) 
   }
 }
 
+// The same where the last pairs were walked in parts: their weights are made here, from the logits and the merged statistics of
+// the parts, with the arithmetic of k_attn_step, and the last workgroups merge their outputs.  Grid (tiles of COLS columns +
+// output workgroups, B).  Bound by latency: a split pair is G loads a column where a whole one is one, and one sequence of 1422
+// tokens has 23 tiles of 64 columns for 256 compute units.  There a wave's lanes are 16 columns of four kv heads, two layers
+// at a time (6.3 us); where the tiles fill the chip they are 64 columns, four kv heads one after the other with their loads in
+// flight together (8 x 2081, 28 layers, four kv heads: 19.7 us with 16).  Either way the kv heads are added one by one, as
+// k_step_scores and k_call_scores do.
+template <int G, int COLS>
+__global__ __launch_bounds__(1024) void k_step_scores_parts(const AttnArgs a, int tr, int n_ct, int D) {
+  extern __shared__ float2 sm_st[];                      // (m, 1/l) of every head of the layers with a split pair, from layer l0 on
+  __shared__ float tot[MAX_LAYERS_PER_LAUNCH * COLS];
+  const int b = blockIdx.y, t = threadIdx.x;
+  if ((int)blockIdx.x >= n_ct) {
+    const size_t i = ((size_t)(blockIdx.x - n_ct) * gridDim.y + b) * blockDim.x + t, total = (size_t)(a.nl * a.B - a.whole_rows) * a.Hkv * G * D;
+    if (i >= total) return;
+    const int e = (int)(i % ((size_t)G * D)), h = e / D, pair = a.whole_rows * a.Hkv + (int)(i / ((size_t)G * D));
+    const size_t sp = (size_t)(pair + a.tail0) * a.S;
+    const float* pm = a.part_ml + sp * 2 * G + h;
+    float m, il, acc = 0.f;
+    merge_stats<G>(pm, a.S, m, il);
+#pragma unroll 8
+    for (int k = 0; k < a.S; ++k)
+      acc = fmaf(__builtin_amdgcn_exp2f((pm[k * 2 * G] - m) * LOG2E), a.part_o[(sp + k) * G * D + e], acc);
+    acc *= il;
+    const int bl = pair / a.Hkv, kvh = pair - bl * a.Hkv;
+    const size_t oi = ((size_t)bl * a.o_bs + kvh * G) * D + e;
+    if (a.out_kind == KT_BF16) ((uint16_t*)a.out)[oi] = f32_to_bf16(acc);
+    else if (a.out_kind == KT_F16) ((_Float16*)a.out)[oi] = (_Float16)acc;    // round to nearest even
+    else ((float*)a.out)[oi] = acc;
+    return;
+  }
+  int nF, nQ;
+  if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
+  else { nF = a.cnt[b * CNT_N + C_NF]; nQ = a.cnt[b * CNT_N + C_NQ]; }
+  const int colq = (nF + tr - 1) / tr * tr;
+  if ((int)blockIdx.x * COLS >= colq + nQ) return;
+  constexpr int NSG = 64 / COLS, KK = 4 / NSG, LB = NSG == 1 ? 1 : 2;   // kv heads side by side and one after the other, layers at a time
+  const int e = t % COLS, sg = (t % 64) / COLS, wv = __builtin_amdgcn_readfirstlane(t >> 6), nwv = blockDim.x >> 6;
+  const int c = blockIdx.x * COLS + e;
+  const bool live = c < nF || (c >= colq && c < colq + nQ);
+  int pos = 0;
+  float score = 0.f;
+  if (live) pos = c < nF ? a.f_pos[(size_t)b * a.Nmax + c] : a.q_pos[(size_t)b * a.Nmax + (c - colq)];
+  if (live && t < COLS) score = a.score[(size_t)b * a.Nmax + pos];
+  const int l0 = a.whole_rows > b ? (a.whole_rows - b + a.B - 1) / a.B : 0;      // the sequence's first layer whose pairs are split
+  for (int i = t; i < (a.nl - l0) * a.Hq; i += blockDim.x) {
+    const int l = l0 + i / a.Hq, hq = i % a.Hq, k = hq / G, pair = (l * a.B + b) * a.Hkv + k;
+    float m, il;
+    merge_stats<G>(a.part_ml + (size_t)(pair + a.tail0) * a.S * 2 * G + (hq - k * G), a.S, m, il);
+    sm_st[i] = make_float2(m, il);
+  }
+  __syncthreads();
+  const float pen = a.red ? a.red_w * (float)G / (float)(nF + nQ) : 0.f;
+  for (int lb = wv; lb < a.nl; lb += LB * nwv) {
+    float s[LB];
+#pragma unroll
+    for (int q = 0; q < LB; ++q) s[q] = 0.f;
+    for (int k0 = 0; k0 < a.Hkv; k0 += 4) {
+      float x[LB][KK][G], w[LB][KK];
+      bool parts[LB][KK];
+#pragma unroll
+      for (int q = 0; q < LB; ++q)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          const int l = lb + q * nwv, k = k0 + kk + sg, pair = (l * a.B + b) * a.Hkv + k;
+          const bool have = l < a.nl && k < a.Hkv;
+          parts[q][kk] = have && l >= l0;
+          w[q][kk] = 0.f;
+          if (live && have && !parts[q][kk]) w[q][kk] = a.sc[(size_t)pair * a.sc_stride + c];
+          if (live && parts[q][kk]) {
+            const float* src = a.xt + (size_t)(pair + a.tail0) * G * a.sc_stride + c;
+#pragma unroll
+            for (int g = 0; g < G; ++g) x[q][kk][g] = src[(size_t)g * a.sc_stride];
+          }
+        }
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+          if (live && parts[q][kk]) {
+            const int l = lb + q * nwv, k = k0 + kk + sg;
+            const size_t pr = (size_t)(l * a.B + b) * a.Hkv + k;
+            const float2* st = sm_st + (l - l0) * a.Hq + k * G;
+#pragma unroll
+            for (int g = 0; g < G; ++g) w[q][kk] += __builtin_amdgcn_exp2f((x[q][kk][g] - st[g].x) * LOG2E) * st[g].y;
+            if (a.vnorm) w[q][kk] *= a.vnorm[pr * a.Nmax + pos];
+            if (a.red) w[q][kk] = fmaf(-pen, a.red[pr * a.Nmax + pos], w[q][kk]);
+          }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (k0 + j < a.Hkv) s[q] += NSG == 1 ? w[q][j % KK] : __shfl(w[q][0], COLS * j + e);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < LB; ++q)
+      if (sg == 0 && lb + q * nwv < a.nl) tot[(lb + q * nwv) * COLS + e] = s[q];
+  }
+  __syncthreads();
+  if (t < COLS && live) {
+    for (int l = 0; l < a.nl; ++l) score = score + a.score_scale * tot[l * COLS + e];
+    a.score[(size_t)b * a.Nmax + pos] = score;
+  }
+}
+
 // The same for one layer: nothing to add up but the kv heads, so a thread takes two columns and has all their loads in
 // flight (64 sequences of 16384 tokens, 17 MB: 22 us with a wave per 64 columns as above).
 __global__ __launch_bounds__(256) void k_call_scores(const AttnArgs a, int tr) {
@@ -2735,7 +2877,7 @@ static hipError_t run_step(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hi
   if constexpr (KT == KT_F32) {
     return hipErrorInvalidValue;
   } else {
-    const dim3 grid(a.Hkv, a.B * a.nl);
+    const dim3 grid(a.Hkv, a.whole_rows + (a.nl * a.B - a.whole_rows) * a.S);
     if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_step<D, G, KT>), grid, dim3(512), 0, st, ev0, ev1, 0, a);
     else hipLaunchKernelGGL((k_attn_step<D, G, KT>), grid, dim3(512), 0, st, a);
     return hipGetLastError();
@@ -2864,8 +3006,27 @@ int attn_step_lds_entries(int D, int G) {
     case 4: return step_cap<64, 4, 1>(); case 5: return step_cap<64, 5, 1>(); case 6: return step_cap<64, 6, 1>(); case 7: return step_cap<64, 7, 1>(); default: return step_cap<64, 8, 1>(); } };
   return D == 128 ? of_d128() : of_d64();
 }
+template <int G, int COLS>
+static hipError_t run_scores_parts_n(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  const int tr = attn_step_tile_rows(D), threads = 64 * (a.nl < 16 ? a.nl : 16), n_ct = a.n_tiles * (64 / COLS);
+  const int rows = a.nl * a.B - a.whole_rows, layers = (rows + a.B - 1) / a.B;    // split rows, layers that have some
+  const int64_t per_y = (int64_t)threads * a.B;
+  const dim3 grid((unsigned)(n_ct + ((int64_t)rows * a.Hkv * G * D + per_y - 1) / per_y), a.B);
+  const size_t lds = (size_t)layers * a.Hq * sizeof(float2);
+  if (ev0 && ev1) hipExtLaunchKernelGGL((k_step_scores_parts<G, COLS>), grid, dim3(threads), lds, st, ev0, ev1, 0, a, tr, n_ct, D);
+  else hipLaunchKernelGGL((k_step_scores_parts<G, COLS>), grid, dim3(threads), lds, st, a, tr, n_ct, D);
+  return hipGetLastError();
+}
+template <int, int G, int>
+static hipError_t run_scores_parts(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  return a.n_tiles * a.B < 128 ? run_scores_parts_n<G, 16>(a, D, st, ev0, ev1) : run_scores_parts_n<G, 64>(a, D, st, ev0, ev1);
+}
 hipError_t launch_step_scores(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (a.nl < 1 || a.nl > MAX_LAYERS_PER_LAUNCH) return hipErrorInvalidValue;
+  if (a.whole_rows < a.nl * a.B) {
+    const int G = a.Hq / a.Hkv;
+    TKV_DISPATCH_G(run_scores_parts, 0, 0, a, D, st, ev0, ev1)
+  }
   if (a.nl == 1) {
     const dim3 grid((a.n_tiles + 7) / 8, a.B);
     if (ev0 && ev1) hipExtLaunchKernelGGL(k_call_scores, grid, dim3(256), 0, st, ev0, ev1, 0, a, attn_step_tile_rows(D));

@@ -79,6 +79,8 @@ struct tkv_cache {
   bool step_whole = false;
   bool call_whole = false;         // single calls too take one workgroup per pair (sc, then the spill, in xs)
   int sc_stride = 0, spill_stride = 0;
+  int tail_pairs = 0, tail_parts = 1;   // of a whole-pair step the last tail_pairs (layer, sequence, kv head) pairs go in tail_parts parts each
+  float* xt_tail = nullptr; float* ml_tail = nullptr; float* po_tail = nullptr;
   int S_alloc = 0, xs_stride = 0;
   int cus = 0;                     // compute units of the device
   char* static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (tkv_attend_and_score_noalloc)
@@ -410,6 +412,7 @@ tkv_status rehome_store(tkv_cache* c, int n, hipStream_t st) {
 // kinds of launch add in different orders, and neither T1 placement nor prefetch mode nor memory nor timing may change a bit.
 //  - one workgroup per (layer, sequence, kv head) pair (k_attn_step; 16-bit rows) if a launch has STEP_WHOLE_PAIRS pairs or
 //    more: the logits stay on the chip, one float per row leaves it.  With fewer pairs most compute units would idle.
+//    (The pairs of an incomplete round may go in parts: step_tail.)
 //    With long lists the idle units of a partly filled round cost more than splitting does: beyond STEP_LONG_LIST tokens
 //    pairs are split if fewer than 60 % of a launch's units, round by round, would have one, and a layer has eight pairs
 //    or more (with fewer every layer takes its share of workgroups that leave a partial and little else).
@@ -427,12 +430,15 @@ tkv_status rehome_store(tkv_cache* c, int n, hipStream_t st) {
 //   128 x 7, four pairs a layer                           558 / 692                   1105 / 1196
 // Either way several layers per launch, as many as fit a scratch (step_scratch).
 constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
-constexpr int STEP_WHOLE_PAIRS = 96, STEP_LONG_LIST = 20480;
+constexpr int STEP_WHOLE_PAIRS = 96, STEP_LONG_LIST = 20480, STEP_MAX_PARTS = 8;
 size_t step_floats_per_layer(const tkv_cache* c) {
   const DevView& v = c->dv;
   const size_t pairs = (size_t)v.B * v.Hkv;
   if (c->step_whole) return pairs * ((size_t)c->sc_stride + (size_t)c->G * c->spill_stride);
   return (size_t)v.B * v.Hq * c->xs_stride + pairs * c->S_alloc * c->G * (2 + v.D);
+}
+size_t tail_floats(const tkv_cache* c, int64_t pairs, int parts) {
+  return (size_t)pairs * c->G * ((size_t)c->sc_stride + (size_t)parts * (2 + c->dv.D));
 }
 int step_layers(const tkv_cache* c) {
   const DevView& v = c->dv;
@@ -454,6 +460,27 @@ void step_route(tkv_cache* c) {
       (v.Nmax > STEP_LONG_LIST && v.B * v.Hkv >= 8 && pairs * 10 < units * 6)) {
     c->step_whole = c->call_whole;
     c->step_layers = step_layers(c);
+  }
+}
+// Of a whole-pair step the pairs of the chip's last round (all of them, where there is but one), if that round is so empty that
+// walking its pairs in parts pays: in units of the time in which a workgroup's waves take a tile each, a round of pairs in S
+// parts takes its longest wave's tiles and 1.2 for beginning and end; the parts' logits, which leave the chip, 0.6 once; and an
+// eighth of the launch is to be gained (rounds are not that sharp: 896 pairs of 2081 tokens, 3.5 rounds, gain 6 us of 187 by two
+// parts each in the last and lose them to the scores).  Settled with the kind of launch, from the shape alone (list lengths by
+// max_tokens).  us a step, whole / in parts (28/4 heads, 28 layers): 1 x 1422 tokens 40.1 / 32.9, 4000 79.8 / 63.4, 12000 205 / 165;
+// 3 x 2000 90.5 / 80.2, 5 x 2000 139.8 / 125; 64/8 heads, 12 layers, 1 x 3000 66.5 / 49.2.
+void step_tail(tkv_cache* c) {
+  const DevView& v = c->dv;
+  c->tail_pairs = 0; c->tail_parts = 1;
+  const int64_t pairs = (int64_t)v.L * v.B * v.Hkv, rem = (pairs % c->cus + v.Hkv - 1) / v.Hkv * v.Hkv;   // whole rows of kv heads
+  if (!c->step_whole || c->call_whole || c->step_layers < v.L || rem == 0) return;   // (call_whole: steps have the single calls' bits)
+  const int tr = attn_step_tile_rows(v.D), tiles = (v.Nmax + tr - 1) / tr;
+  const double round = (tiles + 7) / 8 + 1.2, full = (double)(pairs / c->cus) * round;
+  double best = 0.88 * (full + round);
+  for (int S = 2; S <= STEP_MAX_PARTS; ++S) {
+    const int64_t rounds = (rem * S + c->cus - 1) / c->cus;
+    const double cost = full + (double)rounds * ((tiles + 8 * S - 1) / (8 * S) + 1.2) + 0.6;
+    if (cost < best && tail_floats(c, rem, S) * sizeof(float) <= STEP_SCRATCH_BYTES) { best = cost; c->tail_pairs = (int)rem; c->tail_parts = S; }
   }
 }
 // The scratch of a launch that serves several layers, taken when the cache is created: a call that runs must not take device
@@ -599,6 +626,12 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
                     (size_t)cols + (size_t)G * c->spill_stride <= (size_t)G * c->xs_stride;
   }
   step_route(c);
+  step_tail(c);
+  if (c->tail_pairs > 0) {
+    ok = ok && dalloc(c, c->xt_tail, tail_floats(c, c->tail_pairs, c->tail_parts));
+    c->ml_tail = c->xt_tail + (size_t)c->tail_pairs * G * c->sc_stride;
+    c->po_tail = c->ml_tail + (size_t)c->tail_pairs * c->tail_parts * 2 * G;
+  }
   // (a whole-pair launch of one layer may need a little more than a split one: lists beyond some 20000 tokens)
   ok = ok && dalloc(c, c->xs, std::max((size_t)B * v.Hq * c->xs_stride, c->step_whole ? step_floats_per_layer(c) : 0));
   const int launches = c->streamed ? 2 : 1;   // streamed T1: a second attention launch serves the frame
@@ -831,6 +864,12 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (whole) { a.sc_stride = c->sc_stride; a.xs_stride = c->spill_stride; }
   if (whole && step_launch && c->sc_step) { a.xs = c->spill_step; a.sc = c->sc_step; }
   else if (whole) { a.sc = c->xs; a.xs = c->xs + (size_t)v.B * v.Hkv * c->sc_stride; }
+  a.whole_rows = nl * v.B;                               // no pair in parts
+  if (step_launch && c->tail_pairs > 0) {
+    a.tail0 = layer * v.B * v.Hkv - (v.L * v.B * v.Hkv - c->tail_pairs);
+    a.whole_rows = std::min(a.whole_rows, std::max(0, -a.tail0 / v.Hkv));
+    a.xt = c->xt_tail; a.part_ml = c->ml_tail; a.part_o = c->po_tail;
+  }
   if (m > 1) { a.xs = c->xs_chunk; a.part_ml = c->ml_chunk; a.part_o = c->po_chunk; }
   if (noalloc) {
     // the same three arrays, carved out of the fixed scratch array (256-byte aligned each)
@@ -848,10 +887,11 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (v.B <= ATTN_ARG_SEQS)
     for (int b = 0; b < v.B; ++b) {
       a.nF[b] = c->nF[b] - trim; a.nQ[b] = c->nQ[b];
+      if (step_launch && c->tail_pairs > 0) a.nWs[b] = (uint8_t)attn_q_waves(8 * c->tail_parts, wave_tiles(c->nF[b]), wave_tiles(c->nQ[b]));
       a.nWq[b] = attn_q_waves(whole ? 8 : S * nw, wave_tiles(c->nF[b] - trim), wave_tiles(c->nQ[b]));
     }
   a.B = v.B; a.Hq = v.Hq; a.Hkv = v.Hkv; a.Nmax = v.Nmax; a.capF = v.capP; a.cap2 = v.cap2;
-  a.S = S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;
+  a.S = step_launch && c->tail_pairs > 0 ? c->tail_parts : S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;
   a.softmax_scale = c->softmax_scale; a.score_scale = c->score_scale;
   a.q_bs = q_bs; a.o_bs = o_bs; a.trim = trim;
   if (cols) { a.n_q = 1; a.cq = m; a.groups = chunk_groups(c, m); a.G = c->G; if (!logits) a.xs_stride = 0; }

@@ -120,12 +120,18 @@ struct AttnArgs {
   float* sc;        // whole-pair step launch (else NULL): [layer][B][Hkv][sc_stride] a row's weights summed over its group's
   int sc_stride;    // heads, by column (list F, list Q from the next multiple of the tile's rows); xs then holds only the
                     // logits that do not fit the LDS, [layer][B][Hkv][G][xs_stride] from column LCAP on
+  // whole-pair step launch: the pairs of the (layer, sequence) rows from whole_rows on are walked in S parts each.
+  // Split pair p keeps its logits in xt [p + tail0][G][sc_stride] and the parts' partials in part_ml [p + tail0][S][2][G] and
+  // part_o [p + tail0][S][G][D]; p + tail0 counts the split pairs of the whole step, however its layers are grouped.
+  int whole_rows, tail0;
+  float* xt;
   const int* f_loc_old;   // slots of list F for the layers whose bit is set in old_mask (lazy prefetch: the copies are in flight)
   uint64_t old_mask;
   int B, Hq, Hkv, Nmax, capF, cap2, xs_stride, cb, sb, t2fmt, out_kind, q_es;   // out_kind: 0 binary32, 1 bfloat16, 2 binary16
   float softmax_scale, score_scale;
   int nF[ATTN_ARG_SEQS], nQ[ATTN_ARG_SEQS];   // list lengths per sequence (host mirror), used when B <= ATTN_ARG_SEQS
   int nWq[ATTN_ARG_SEQS];                     // waves of each (sequence, kv head) pair that serve the Q list (same condition)
+  uint8_t nWs[ATTN_ARG_SEQS];                 // the same for a pair walked in S parts
   // (streamed T1: the second launch and the finishing kernel take the T1 list's length and the first launch's tile
   // counts from the device counters; the argument block stays small, it is read over the host link in some set-ups)
 };

@@ -208,6 +208,19 @@ def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
         c.close()
 
 
+@pytest.mark.parametrize("mode,scorer,shape", [
+    ("lazy", "attention", dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=700)),          # 24 of 280 pairs, eight parts; device counters
+    ("wait", "vatp", dict(n_layers=9, batch=4, n_q_heads=8, n_kv_heads=8, head_dim=64, context=1300)),               # 32 of 288, eight parts
+    ("lazy", "combined", dict(n_layers=25, batch=1, n_q_heads=24, n_kv_heads=4, head_dim=128, context=800, t2_format="int4_g32", kv_dtype="f16")),   # all 100, two
+    ("lazy", "attention", dict(n_layers=28, batch=3, n_q_heads=28, n_kv_heads=4, head_dim=128, context=2900)),        # 80 of 336, three; score tiles of 64 columns
+    ("wait", "redundancy", dict(n_layers=34, batch=1, n_q_heads=6, n_kv_heads=3, head_dim=64, context=1700)),         # all 102, two; three kv heads
+])
+def test_decode_step_whose_last_pairs_go_in_parts(mode, scorer, shape):
+    """The pairs of a round that the chip does not fill are walked in parts and their weights and outputs made by the score
+    launch: the same comparison with per-layer calls, with the same bounds, at numbers of pairs and tokens where that is done."""
+    test_decode_step_serves_several_layers_per_launch(mode, scorer, shape)
+
+
 @pytest.mark.parametrize("shape", [
     dict(n_layers=28, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100),                    # logits beyond the LDS
     dict(n_layers=3, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=150, kv_dtype="f16"),       # list lengths from device counters
