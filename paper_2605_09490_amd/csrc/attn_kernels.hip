@@ -18,7 +18,7 @@
 //                 The waves of a workgroup are merged through LDS into one split partial (m, l, o[G][D]); the scaled
 //                 logits go to a scratch array.
 //   attn_step   : a whole decode step's layers (or a single call over many pairs), one workgroup per (layer, sequence, kv
-//                 head) pair: the same waves, but the logits stay in the LDS, the workgroup writes its output itself and
+//                 head) pair, on the matrix cores: the logits stay in the LDS, the workgroup writes its output itself and
 //                 one float per row (the weights summed over the group) for step_scores / call_scores.
 //   attn_finish : grid (64-entry tiles + Hq, B).  Every workgroup first merges the (m, l) of all splits of its sequence
 //                 into the global (m, 1/l) of every query head.  Tile workgroups then turn the stored logits
@@ -34,8 +34,7 @@
 //                 outputs.  binary32 rows: one set of attn_tiered's workgroups per token, and attn_finish_chunk.
 // The tile boundaries, the wave assignment and the fp32 summation order depend only on the lists' logical order and
 // lengths, never on whether a row lives in the HBM pool or the staging buffer (both are one slot space), which is
-// what makes T1 placement bit-invisible (Prop. 1).  A decode step (one query token) uses no matrix instructions: the
-// launch is bound by HBM, and the per-row work is G dot products.
+// what makes T1 placement bit-invisible (Prop. 1).
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -149,6 +148,12 @@ __device__ __forceinline__ float group_sum(float x) {
   if constexpr (LPR >= 8) x += dpp_f<0x141>(x);   // row_half_mirror
   if constexpr (LPR >= 16) x += dpp_f<0x140>(x);  // row_mirror
   return x;
+}
+// e^d for d <= 0, the rounding of d * log2(e) put back in: exp2 of a product of ten is off by some 2e-7 without.
+// (d = -inf: the remainder is no number and counts as -1, of nothing; no number stays none.)
+__device__ __forceinline__ float exp_le0(float d) {
+  const float e = d * LOG2E, r = __builtin_amdgcn_fmed3f(fmaf(d, LOG2E, -e), -1.0f, 1.0f), p = __builtin_amdgcn_exp2f(e);
+  return fmaf(p, r * LN2, p);
 }
 __device__ __forceinline__ float rdlane(float x, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
@@ -519,7 +524,7 @@ __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t& rs, char* lds,
 //   V scales of t+1 | per V step of t: the K pieces of t+1 on its bytes
 // Accumulates into o, m_run, l_lane (per-lane partial sums of the softmax denominator, relative to m_run); leaves the
 // scaled logits in xs.
-template <int D, int G, Mode M, int KT, int TR, bool WHOLE>
+template <int D, int G, Mode M, int KT, int TR>
 __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, int b, int jq, int kvh, int lane,
                                           int tile0, int tstride, int n_list, const int* loc_list, int col0,
                                           float (&o)[G][Geo<D, M>::EV], float (&m_run)[G], float (&l_lane)[G]) {
@@ -776,19 +781,7 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
         x[h] = valid ? xt[h] * a.softmax_scale : -INFINITY;
         xm[h] = x[h];
       }
-      if constexpr (WHOLE) {
-        // the logits stay in the LDS as far as it goes; the rest of a longer list is parked in memory for the workgroup
-        if (col0 + tile * TR + TR <= w.lim) {
-          if (valid) {
-#pragma unroll
-            for (int h = 0; h < G; ++h) lds_wr32(w.lga + (uint32_t)(h * w.lcap + col) * 4u, __builtin_bit_cast(uint32_t, x[h]));
-          }
-        } else if (valid) {
-          float* sp = w.sp + col;
-#pragma unroll
-          for (int h = 0; h < G; ++h) sp[(size_t)h * w.sp_stride] = x[h];
-        }
-      } else if (valid) {
+      if (valid) {
         const size_t xbase = xs_at(a, b * a.n_q + jq, kvh * G, col);
 #pragma unroll
         for (int h = 0; h < G; ++h) a.xs[xbase + (size_t)h * a.xs_stride] = x[h];
@@ -883,8 +876,8 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
 //             the registers.
 //   softmax : online per column; a quarter of a tile's entries per lane, the maximum completed over the column's 4 lanes.
 //   output  : O[column][d] += P[column][entry] * V[entry][d], 32 entries per instruction; the right operand needs, per
-//             lane, the same column of 4 + 4 rows: a transposing LDS read delivers it.  P is fed as two 16-bit terms
-//             (leading bits and remainder), so the product carries 16 significant bits of every weight.
+//             lane, the same column of 4 + 4 rows: a transposing LDS read delivers it.  P is fed as two or three 16-bit
+//             terms (PSplit).
 // Rows still come in by direct-to-LDS loads of 1 KB (8 rows x 8 pieces of 16 bytes, 128 contiguous bytes per row).
 // Within a row's 128 bytes the pieces are rotated by an amount that depends on the row, so that the 16 lanes of an
 // operand read (16 different rows, same piece) fall on 16 different bank groups; the rotation is undone by the read
@@ -927,11 +920,11 @@ struct PSplit {
   static constexpr float P_SHIFT = KT == KT_BF16 ? 0.f : 14.f;
   static constexpr float SCALE_MAX = 3.75f;   // binary16: what a weight of 1 can be multiplied by and stay in range (65504) with the shift
 };
-template <int KT>
-__device__ __forceinline__ void split_pair(float p0, float p1, uint32_t (&t)[PSplit<KT>::N]) {
+template <int KT, int N>
+__device__ __forceinline__ void split_pair(float p0, float p1, uint32_t (&t)[N]) {
   if constexpr (KT == KT_BF16) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < N; ++i) {
       const uint32_t u0 = __builtin_bit_cast(uint32_t, p0) & 0xffff0000u, u1 = __builtin_bit_cast(uint32_t, p1) & 0xffff0000u;
       t[i] = u1 | (u0 >> 16);
       p0 -= __builtin_bit_cast(float, u0);
@@ -939,7 +932,7 @@ __device__ __forceinline__ void split_pair(float p0, float p1, uint32_t (&t)[PSp
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < N; ++i) {
       const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(p0, p1));
       t[i] = __builtin_bit_cast(uint32_t, h);
       p0 -= (float)h.x;
@@ -977,7 +970,8 @@ __device__ __forceinline__ u32x4 widen_int4(uint32_t w) {
 // a time is widened to 16-bit values into the free upper half of the wave's tile buffer, in the layout the
 // full-precision rows arrive in, where the same operand reads pick it up.  Scales stay outside the products: a K row's
 // scale multiplies its logits (per 32-element group: one product per group), a V row's scale its weights.
-template <int D, int KT, Mode M, int NCB, bool LOG>
+enum Logits : int { LOG_NONE = 0, LOG_XS = 1, LOG_STEP = 2 };   // not kept; scaled, in a.xs; k_attn_step's: unscaled, in the LDS as far as it goes
+template <int D, int KT, Mode M, int NCB, int LOG>
 __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds& w, int b, int c0, int kvh, int lane,
                                                int tile0, int tstride, int n_list, int n_walk, const int* loc_list, int xcol0,
                                                f32x4 (&o)[NCB][D / 16], float (&m_run)[NCB], float (&l_run)[NCB]) {
@@ -1081,7 +1075,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
       const int jq = small_div(col, inv_g);
       live[cb] = col < ncol;
       n_seen[cb] = IS_Q || !live[cb] ? n_list : n_list - (a.cq - 1 - jq);
-      if constexpr (LOG) xrow[cb] = live[cb] ? xs_at(a, b * a.cq + jq, kvh * a.G + (col - jq * a.G), xcol0 + 4 * kb) : 0;
+      if constexpr (LOG == LOG_XS) xrow[cb] = live[cb] ? xs_at(a, b * a.cq + jq, kvh * a.G + (col - jq * a.G), xcol0 + 4 * kb) : 0;
     }
   }
   // list Q: the lane's piece of a code row is widened and stored where the operand reads expect it.  Piece sl of a
@@ -1162,7 +1156,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
 #pragma unroll
   for (int s = 0; s < NP; ++s) issue_k_piece(s);
   // the pair's first wave leaves the operand as it is for the score launch, which then reads it in lane order
-  if (!LOG && !IS_Q && tile0 == 0) {
+  if (LOG == LOG_NONE && !IS_Q && tile0 == 0) {
     const int blocks = (a.cq * a.G + 15) / 16;
     u32x4* pk = (u32x4*)a.xs + ((size_t)(b * a.Hkv + kvh) * blocks + c0 / 16) * (NKS * 64) + lane;
 #pragma unroll
@@ -1215,12 +1209,28 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           c[cb][rb] = acc;
         }
       } else {
+        if constexpr (LOG == LOG_STEP) {
+          // halves of a row by themselves: smaller partial sums to round
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) c[cb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int cb = 0; cb < NCB; ++cb) {
+            f32x4 half[2];
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
+            for (int hf = 0; hf < 2; ++hf) {
+              half[hf] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) c[cb][rb] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], c[cb][rb]);
+              for (int ks = hf * NKS / 2; ks < (hf + 1) * NKS / 2; ++ks) half[hf] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], half[hf]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c[cb][rb][j] = half[0][j] + half[1][j];
+          }
+        } else {
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) c[cb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) c[cb][rb] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], c[cb][rb]);
+        }
         if constexpr (M == Q_INT8) {
           u32x4 sc = lds_rd128<rb * 64>(w.ska + (uint32_t)kb * 16u);
           lds_wait(); tie(sc);
@@ -1330,7 +1340,25 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
               }
             });
         }
-        if constexpr (LOG) {
+        if constexpr (LOG == LOG_STEP) {
+          const int col = xcol0 + tile * TR + 4 * kb;
+          if (live[cb]) {
+            if (xcol0 + tile * TR + TR <= w.lim) {
+              static_for<NRB>([&](auto rc) {
+                constexpr int rb = decltype(rc)::value;
+                u32x4 t;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { const float x = c[cb][rb][j]; t[j] = __builtin_bit_cast(uint32_t, x); }
+                lds_wr128<rb * 64>(w.lga + (uint32_t)(n * w.lcap + col) * 4u, t);
+              });
+            } else {
+              float* sp = w.sp + (size_t)n * w.sp_stride + col;
+#pragma unroll
+              for (int rb = 0; rb < NRB; ++rb) *(f32x4*)(sp + 16 * rb) = c[cb][rb];
+            }
+          }
+        }
+        if constexpr (LOG == LOG_XS) {
           if (live[cb]) {
 #pragma unroll
             for (int rb = 0; rb < NRB; ++rb)
@@ -1347,7 +1375,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(p[cb][rb][j] - ms, LOG2E, PSplit<KT>::P_SHIFT));
+            // (LOG_STEP: the product's rounding is left out of the distance to the reference; a masked entry stays one)
+            const float d = LOG == LOG_STEP ? (p[cb][rb][j] > -INFINITY ? fmaf(c[cb][rb][j], a.softmax_scale, -ms) : -INFINITY) : p[cb][rb][j] - ms;
+            p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(d, LOG2E, PSplit<KT>::P_SHIFT));
             ps += p[cb][rb][j];
           }
         l_run[cb] = fmaf(l_run[cb], corr, ps);
@@ -1368,7 +1398,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     }
     // -- output: 32 entries per instruction; V rows that have been read are replaced by K pieces
     __builtin_amdgcn_s_setprio(MORE ? 2 : 0);
-    constexpr int NT = PSplit<KT>::N;
+    constexpr int NT = LOG == LOG_STEP ? 3 : PSplit<KT>::N;
     // V scales of the tile: the 4 entries' of each 16-entry block (all older than the K pieces: they are in)
     u32x4 vsc[IS_Q ? SCD : 1][NRB];
     if constexpr (IS_Q) {
@@ -1395,10 +1425,10 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           pw[r2][j] = v;
         }
       uint32_t s0[NT], s1[NT], s2[NT], s3[NT];
-      split_pair<KT>(pw[0][0], pw[0][1], s0);
-      split_pair<KT>(pw[0][2], pw[0][3], s1);
-      split_pair<KT>(pw[1][0], pw[1][1], s2);
-      split_pair<KT>(pw[1][2], pw[1][3], s3);
+      split_pair<KT, NT>(pw[0][0], pw[0][1], s0);
+      split_pair<KT, NT>(pw[0][2], pw[0][3], s1);
+      split_pair<KT, NT>(pw[1][0], pw[1][1], s2);
+      split_pair<KT, NT>(pw[1][2], pw[1][3], s3);
 #pragma unroll
       for (int i = 0; i < NT; ++i) pt[i] = u32x4{s0[i], s1[i], s2[i], s3[i]};
     };
@@ -1460,8 +1490,17 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int db = 0; db < NDB; ++db) {
           if constexpr (M == Q_INT4) { if (db % 2 == 0) weights(tc, cb, db / 2, pt); }
           const u32x4 vb = u32x4{vv[0][db].x, vv[0][db].y, vv[1][db].x, vv[1][db].y};
+          if constexpr (LOG == LOG_STEP) {
+            // many tiles per wave: the 32 entries' sum by itself, small terms first, and one addition to the running one
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int i = NT - 1; i >= 0; --i) o[cb][db] = mfma_16x16x32<KT>(pt[i], vb, o[cb][db]);
+            for (int i = NT - 1; i >= 0; --i) sum = mfma_16x16x32<KT>(pt[i], vb, sum);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[cb][db][j] += sum[j];
+          } else {
+#pragma unroll
+            for (int i = NT - 1; i >= 0; --i) o[cb][db] = mfma_16x16x32<KT>(pt[i], vb, o[cb][db]);
+          }
         }
       }
     });
@@ -1580,11 +1619,11 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
   }
   bool o_written = false;
   if (u < nwf) {
-    attn_wave<D, G, KG::MF, KT, TR, false>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
+    attn_wave<D, G, KG::MF, KT, TR>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
   } else {
     if constexpr (EV == 8) {
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
     } else {
       // binary32 rows use 4 elements per lane, code rows 8: separate accumulators, parked directly
       float o8[G][8];
@@ -1592,8 +1631,8 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
       for (int h = 0; h < G; ++h)
 #pragma unroll
         for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT, TR, false>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
+      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
+      else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
 #pragma unroll
       for (int h = 0; h < G; ++h) {
         constexpr int L8 = D / 8;
@@ -1657,21 +1696,30 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
 // With the pairs of all layers of a step in one launch there are enough of them to fill the chip without splitting any,
 // and a workgroup that has walked a pair's lists to their end knows the final softmax statistics of its heads.  So it
 // writes its output itself, and of the logits, which stay in the LDS, one float per row: the row's weights summed over
-// the group's heads.  That is what this kernel is for: it is bound by HBM, and written logits (G floats per row, 4-6 % of
-// the bytes) add a third to its time and their reading back another tenth (1.6 GB of rows stream in 237 us alone, in 317 us
-// with 90 MB of logits written beside them, whatever the shape of the stores).
-// Measured (14B shape, 48 layers, batch 8, 4112 tokens all at full precision): 960-1140 us a step, 6.0 TB/s, against
-// 5 x (243 + 23) us with split pairs, written logits and ten layers per launch.
+// the group's heads.  That is what this kernel is for: written logits (G floats per row, 4-6 % of the bytes) cost far more
+// than their bytes beside the row stream (1.6 GB of rows stream in 233 us alone, in 284 us with 25 MB of stores beside them and
+// 316 us with 101 MB, in 257 us if all of those come at once at the end).
+// The rows' arithmetic runs on the matrix cores, with the G heads as columns of which 16 - G are padding: G dot products and
+// G scaled additions per row on the vector ALUs kept these busy for 76 % of the time at seven heads.  us a step with vector /
+// matrix instructions, 28 layers, 28/4 heads: 8 x 600 tokens 82 / 68, 5 x 2000 119 / 109, 1 x 1422 33.3 / 30.0; 12 layers, 64/8,
+// 1 x 3000 48.9 / 45.0; ten layers, 10/2, 10 x 1500 37.3 / 35.6; 27 layers, 8/8 at head_dim 64, 6 x 1200 88.2 / 87.2.  What the
+// stream of rows bounds (14B shape, 48 layers, batch 8, 4112 tokens: 960-1140 us, 6.0 TB/s) is within 1 %.
+// Precision: weights enter the product as exact sums of three 16-bit terms, a tile's 32 entries are summed by themselves and
+// added to the running output once, a row's halves are summed by themselves, and logits stay unscaled until the distance to the
+// maximum is taken (one rounding less).  Outputs against 64 bits, vector / matrix instructions, relative 2-norm: 28/4 heads,
+// 8 x 2081, 10 % int8 2.9e-7 / 2.6e-7; 40/8, 8 x 4096, 15 % int8 3.2e-7 / 2.7e-7; 16/4, 1 x 16000 4.8e-7 / 3.1e-7; binary16,
+// 40/8, 1 x 8000, int4 4.1e-7 / 3.5e-7; 8/8 at head_dim 64, 2 x 3000 2.44e-7 / 2.33e-7; 10/2, 4 x 700 2.42e-7 / 2.32e-7.
 // The LDS holds eight 8 KB tile buffers (32 rows of 256 bytes; 64 KB in flight per compute unit stream as fast as 128 KB)
 // and the logits of LCAP entries; a longer list parks the rest in memory and reads it back.  The eight waves are divided
-// between the lists as in the split launch (a wave that walked both would need some 90 registers more than it has).
-// The pairs that fill the last round of the chip only in part, those of the (layer, sequence) rows from a.whole_rows on, are cut into a.S parts of eight waves
-// each (the host's rule: step_tail): a part writes its logits and a partial, as in the split launch.
+// between the lists as in the split launch.
+// The pairs that fill the last round of the chip only in part, those of the (layer, sequence) rows from a.whole_rows on, are
+// cut into a.S parts of eight waves each (the host's rule: step_tail): a part writes its logits and a partial, as in the
+// split launch.
 template <int D, int G>
 struct StepGeo {
   static constexpr int NW = 8, RB = 2 * D, TR = 8192 / RB < 64 ? 8192 / RB : 64, TILE = TR * RB;
-  static constexpr int P = TR * GPad<G>::v * 4, SC = (D / 64) * TR * 4, LT = 2 * TR * 4;   // per wave: weights, K or V scales, slot lists
-  static constexpr int LDS = 163840, FIXED = NW * (TILE + P + 2 * SC + LT) + NW * 16 * 4 + 8 * 8 + 256;
+  static constexpr int SC = (D / 64) * TR * 4, LT = 2 * TR * 4;   // per wave: K or V scales, slot lists
+  static constexpr int LDS = 163840, FIXED = NW * (TILE + 2 * SC + LT) + NW * 16 * 4 + 8 * 8 + 256;
   static constexpr int LCAP = (LDS - FIXED) / 4 / G / TR * TR;
 };
 template <int D, int G, int KT>
@@ -1679,13 +1727,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   using SG = StepGeo<D, G>;
   constexpr Mode MF = KT == KT_BF16 ? F_BF16 : F_F16;
   constexpr int NW = SG::NW, TR = SG::TR, TILE = SG::TILE, LCAP = SG::LCAP;
-  constexpr int EV = Geo<D, MF, TR>::EV, LPRV = Geo<D, MF, TR>::LPRV;
   static_assert(G * D * 4 <= TILE, "a wave's output partial is parked in its tile buffer");
   __shared__ __attribute__((aligned(16))) char sm_t[NW * TILE];
-  __shared__ __attribute__((aligned(16))) char sm_p[NW * SG::P];
   __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * SG::SC];
   __shared__ __attribute__((aligned(16))) char sm_lt[NW * SG::LT];
-  __shared__ float sm_lg[G * LCAP];
+  __shared__ __attribute__((aligned(16))) float sm_lg[G * LCAP];
   __shared__ float sm_ml[NW * 16];
   __shared__ float2 sm_fin[8];
   const int kvh = blockIdx.x;
@@ -1701,40 +1747,35 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   const int nft = (nF + TR - 1) / TR, colq = nft * TR;
 
   WaveLds w;
-  w.t = sm_t + wave * TILE; w.p = sm_p + wave * SG::P;
+  w.t = sm_t + wave * TILE; w.p = nullptr; w.pa = 0;
   w.sk = sm_sc + wave * 2 * SG::SC; w.sv = w.sk + SG::SC; w.lt = sm_lt + wave * SG::LT;
-  w.ta = lds_addr(w.t); w.pa = lds_addr(w.p); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
+  w.ta = lds_addr(w.t); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
   w.lga = lds_addr(sm_lg); w.lcap = LCAP;
   w.lim = split ? 0 : LCAP;
   w.sp = split ? a.xt + (size_t)(pair + a.tail0) * G * a.sc_stride : a.xs + (size_t)pair * G * a.xs_stride - LCAP;
   w.sp_stride = split ? a.sc_stride : a.xs_stride;
   float* my_o = (float*)w.t;
 
-  float o[G][EV], m_run[G], l_lane[G];
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    m_run[h] = -INFINITY; l_lane[h] = 0.f;
-#pragma unroll
-    for (int e = 0; e < EV; ++e) o[h][e] = 0.f;
-  }
   const int nwv = split ? NW * a.S : NW, u = part * NW + wave;       // the pair's waves, and which of them this is
   const int nwq = a.B > ATTN_ARG_SEQS ? q_waves(nwv, nft, (nQ + TR - 1) / TR) : split ? a.nWs[b] : a.nWq[b], nwf = nwv - nwq;
-  if (u < nwf) attn_wave<D, G, MF, KT, TR, true>(a, w, bl, 0, kvh, lane, u, nwf, nF, f_loc, 0, o, m_run, l_lane);
-  else if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, true>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
-  else attn_wave<D, G, Q_INT4, KT, TR, true>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+  f32x4 om[1][D / 16];
+  float mr[1] = {-INFINITY}, lr[1] = {0.f};
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) om[0][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (u < nwf) attn_wave_mfma<D, KT, MF, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u, nwf, nF, nF, f_loc, 0, om, mr, lr);
+  else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
+  else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
+  // the wave's partial: lane (n, kb) has the statistics of head n and the outputs of heads 4*kb + j, element 16*db + n
+  const float ls = quad_sum(lr[0]);
+  if (lane < G) { sm_ml[wave * 16 + lane] = mr[0]; sm_ml[wave * 16 + 8 + lane] = ls; }
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int h = 4 * (lane >> 4) + j;
+      if (h < G) my_o[h * D + 16 * db + (lane & 15)] = om[0][db][j];
+    }
   // ---- merge the waves
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float t1[RowSum<EV, LPRV>::N];
-    row_sum<EV, LPRV>(o[h], lane, t1);
-#pragma unroll
-    for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t1[k];
-  }
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float ls = wave_sum(l_lane[h]);
-    if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
-  }
   __syncthreads();
   if (split) {
     // a part of a pair: its partial; k_step_scores_parts has the rest of the way
@@ -1808,7 +1849,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
       for (int h = 0; h < G; ++h) x[h] = a.xs[(pr * G + h) * a.xs_stride + (c - LCAP)];
     }
 #pragma unroll
-    for (int h = 0; h < G; ++h) s += __builtin_amdgcn_exp2f((x[h] - fin[h].x) * LOG2E) * fin[h].y;
+    for (int h = 0; h < G; ++h) s += exp_le0(fmaf(x[h], a.softmax_scale, -fin[h].x)) * fin[h].y;
     if (a.vnorm || a.red) {
       const int pos = c < nF ? a.f_pos[(size_t)b * a.Nmax + c] : a.q_pos[(size_t)b * a.Nmax + (c - colq)];
       if (a.vnorm) s *= a.vnorm[pr * a.Nmax + pos];         // value-aware scorer: times the norm of the value row the group reads
@@ -1872,9 +1913,9 @@ __global__ __launch_bounds__(MC_WAVES * 64, MC_WAVES / 4) void k_attn_tiered_mc(
 #pragma unroll
     for (int db = 0; db < D / 16; ++db) om[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (u < nwf) attn_wave_mfma<D, KT, MF, NCB, LOG>(a, w, b, c0, kvh, lane, u, nwf, nF, nFw, (a.old_mask ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax, 0, om, mr, lr);
-  else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, NCB, LOG>(a, w, b, c0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, ((nF + 63) >> 6) * TB, om, mr, lr);
-  else attn_wave_mfma<D, KT, Q_INT4, NCB, LOG>(a, w, b, c0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, ((nF + 63) >> 6) * TB, om, mr, lr);
+  if (u < nwf) attn_wave_mfma<D, KT, MF, NCB, LOG ? LOG_XS : LOG_NONE>(a, w, b, c0, kvh, lane, u, nwf, nF, nFw, (a.old_mask ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax, 0, om, mr, lr);
+  else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, NCB, LOG ? LOG_XS : LOG_NONE>(a, w, b, c0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, ((nF + 63) >> 6) * TB, om, mr, lr);
+  else attn_wave_mfma<D, KT, Q_INT4, NCB, LOG ? LOG_XS : LOG_NONE>(a, w, b, c0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, ((nF + 63) >> 6) * TB, om, mr, lr);
   // ---- wave partial into LDS: lane (n, kb) has the statistics of column 16*cb + n and the outputs of columns
   // 16*cb + 4*kb + j, element 16*db + n
 #pragma unroll
@@ -2762,7 +2803,7 @@ __global__ __launch_bounds__(1024) void k_step_scores_parts(const AttnArgs a, in
             const size_t pr = (size_t)(l * a.B + b) * a.Hkv + k;
             const float2* st = sm_st + (l - l0) * a.Hq + k * G;
 #pragma unroll
-            for (int g = 0; g < G; ++g) w[q][kk] += __builtin_amdgcn_exp2f((x[q][kk][g] - st[g].x) * LOG2E) * st[g].y;
+            for (int g = 0; g < G; ++g) w[q][kk] += exp_le0(fmaf(x[q][kk][g], a.softmax_scale, -st[g].x)) * st[g].y;
             if (a.vnorm) w[q][kk] *= a.vnorm[pr * a.Nmax + pos];
             if (a.red) w[q][kk] = fmaf(-pen, a.red[pr * a.Nmax + pos], w[q][kk]);
           }

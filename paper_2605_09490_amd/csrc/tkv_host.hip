@@ -895,7 +895,7 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   a.softmax_scale = c->softmax_scale; a.score_scale = c->score_scale;
   a.q_bs = q_bs; a.o_bs = o_bs; a.trim = trim;
   if (cols) { a.n_q = 1; a.cq = m; a.groups = chunk_groups(c, m); a.G = c->G; if (!logits) a.xs_stride = 0; }
-  else { a.n_q = m; a.cq = 1; }
+  else { a.n_q = m; a.cq = 1; a.G = c->G; }
   EvPair* pe = nullptr;
   EvPair* pe2 = nullptr;
   EvPair* pf = nullptr;
