@@ -15,8 +15,9 @@
 //                             by the lane whose index equals the entry's index in the tile;
 //                   softmax - online, one entry per lane (exact tile maximum, exp2, running m and l);
 //                   V rows  - D/EV lanes per row, probabilities broadcast from LDS, per-lane fp32 output slices.
-//                 The waves of a workgroup are merged through LDS into one split partial (m, l, o[G][D]); the scaled
-//                 logits go to a scratch array.
+//                 The waves of a workgroup are merged through LDS into one split partial (m, l, o[G][D]); the
+//                 logits go to a scratch array.  16-bit rows of 256 bytes under four and more heads: the same launch with
+//                 its waves on the matrix cores, as in attn_step.
 //   attn_step   : a whole decode step's layers (or a single call over many pairs), one workgroup per (layer, sequence, kv
 //                 head) pair, on the matrix cores: the logits stay in the LDS, the workgroup writes its output itself and
 //                 one float per row (the weights summed over the group) for step_scores / call_scores.
@@ -970,7 +971,9 @@ __device__ __forceinline__ u32x4 widen_int4(uint32_t w) {
 // a time is widened to 16-bit values into the free upper half of the wave's tile buffer, in the layout the
 // full-precision rows arrive in, where the same operand reads pick it up.  Scales stay outside the products: a K row's
 // scale multiplies its logits (per 32-element group: one product per group), a V row's scale its weights.
-enum Logits : int { LOG_NONE = 0, LOG_XS = 1, LOG_STEP = 2 };   // not kept; scaled, in a.xs; k_attn_step's: unscaled, in the LDS as far as it goes
+// What becomes of the logits: not kept; scaled, in a.xs by query token; one token's, unscaled, in the LDS as far as it goes
+// (k_attn_step); one token's, unscaled, in memory (k_attn_tiered)
+enum Logits : int { LOG_NONE = 0, LOG_XS = 1, LOG_STEP = 2, LOG_CALL = 3 };
 template <int D, int KT, Mode M, int NCB, int LOG>
 __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds& w, int b, int c0, int kvh, int lane,
                                                int tile0, int tstride, int n_list, int n_walk, const int* loc_list, int xcol0,
@@ -978,6 +981,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   static_assert(KT == KT_BF16 || KT == KT_F16, "16-bit operands");
   static_assert(D % 64 == 0, "head_dim in whole 128-byte row halves");
   constexpr bool IS_Q = (M == Q_INT8 || M == Q_INT4);
+  constexpr bool ONE = LOG == LOG_STEP || LOG == LOG_CALL;      // one query token: many tiles per wave, few columns
   constexpr int RB = 2 * D;                    // bytes per row as the matrix cores read it
   constexpr int TR = 8192 / RB;                // rows per tile: 8 KB
   constexpr int NRB = TR / 16, NTV = TR / 32;  // 16-entry blocks (logits), 32-entry steps (output)
@@ -1209,19 +1213,16 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           c[cb][rb] = acc;
         }
       } else {
-        if constexpr (LOG == LOG_STEP) {
-          // halves of a row by themselves: smaller partial sums to round
+        if constexpr (ONE) {
+          // 32 elements at a time by themselves, then added in pairs (a chain of four is 1.5 times as far off, dot products on the
+          // vector ALUs about as far; 128 elements, one of them large: rms 3.3e-6, 2.2e-6, 2.2e-6)
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) {
-            f32x4 half[2];
+            f32x4 part[NKS];
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-              half[hf] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < NKS; ++ks) part[ks] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-              for (int ks = hf * NKS / 2; ks < (hf + 1) * NKS / 2; ++ks) half[hf] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], half[hf]);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) c[cb][rb][j] = half[0][j] + half[1][j];
+            for (int j = 0; j < 4; ++j) c[cb][rb][j] = NKS == 2 ? part[0][j] + part[1][j] : (part[0][j] + part[1][j]) + (part[NKS - 2][j] + part[NKS - 1][j]);
           }
         } else {
 #pragma unroll
@@ -1358,6 +1359,13 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
             }
           }
         }
+        if constexpr (LOG == LOG_CALL) {
+          if (live[cb]) {
+            float* sp = w.sp + (size_t)n * w.sp_stride + (xcol0 + tile * TR + 4 * kb);
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) *(f32x4*)(sp + 16 * rb) = c[cb][rb];
+          }
+        }
         if constexpr (LOG == LOG_XS) {
           if (live[cb]) {
 #pragma unroll
@@ -1375,9 +1383,10 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            // (LOG_STEP: the product's rounding is left out of the distance to the reference; a masked entry stays one)
-            const float d = LOG == LOG_STEP ? (p[cb][rb][j] > -INFINITY ? fmaf(c[cb][rb][j], a.softmax_scale, -ms) : -INFINITY) : p[cb][rb][j] - ms;
-            p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(d, LOG2E, PSplit<KT>::P_SHIFT));
+            // (one token: the product's rounding is left out of the distance to the reference; a masked entry stays one)
+            const float d = ONE ? (p[cb][rb][j] > -INFINITY ? fmaf(c[cb][rb][j], a.softmax_scale, -ms) : -INFINITY) : p[cb][rb][j] - ms;
+            if constexpr (ONE) p[cb][rb][j] = exp_le0(d) * (float)(1 << (int)PSplit<KT>::P_SHIFT);
+            else p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(d, LOG2E, PSplit<KT>::P_SHIFT));
             ps += p[cb][rb][j];
           }
         l_run[cb] = fmaf(l_run[cb], corr, ps);
@@ -1398,7 +1407,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     }
     // -- output: 32 entries per instruction; V rows that have been read are replaced by K pieces
     __builtin_amdgcn_s_setprio(MORE ? 2 : 0);
-    constexpr int NT = LOG == LOG_STEP ? 3 : PSplit<KT>::N;
+    constexpr int NT = ONE ? 3 : PSplit<KT>::N;
     // V scales of the tile: the 4 entries' of each 16-entry block (all older than the K pieces: they are in)
     u32x4 vsc[IS_Q ? SCD : 1][NRB];
     if constexpr (IS_Q) {
@@ -1490,7 +1499,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int db = 0; db < NDB; ++db) {
           if constexpr (M == Q_INT4) { if (db % 2 == 0) weights(tc, cb, db / 2, pt); }
           const u32x4 vb = u32x4{vv[0][db].x, vv[0][db].y, vv[1][db].x, vv[1][db].y};
-          if constexpr (LOG == LOG_STEP) {
+          if constexpr (ONE) {
             // many tiles per wave: the 32 entries' sum by itself, small terms first, and one addition to the running one
             f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1524,13 +1533,36 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   }
 }
 
+// One token's result of a wave into LDS: lane (n, kb) has the statistics of head n and the outputs of heads 4*kb + j, element 16*db + n
+template <int D, int G>
+__device__ __forceinline__ void park_one(const f32x4 (&om)[D / 16], float m, float l, int lane, float* o, float* ml) {
+  const float ls = quad_sum(l);
+  if (lane < G) { ml[lane] = m; ml[8 + lane] = ls; }
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int h = 4 * (lane >> 4) + j;
+      if (h < G) o[h * D + 16 * db + (lane & 15)] = om[db][j];
+    }
+}
+
 // Geometry of the split launch: rows per tile and waves per workgroup (one workgroup per compute unit).  16-bit rows: 8 KB
 // tiles (32 rows of 256 bytes, 64 of 128) and eight waves, two per SIMD; 64 KB in flight per compute unit stream as fast
 // as 128 KB do, and the finer tiles keep more waves busy on short lists and end closer together on long ones.  binary32
 // rows: 32 rows of 256 bytes; 64 rows of 512 bytes with four waves, which large groups take in any case (their waves need
 // more than half a SIMD's registers).
+// Whether a split launch's waves run on the matrix cores.  us a call, vector / matrix instructions, 12 % int8 T2, head_dim 128: 28/4
+// heads, 1 x 300 tokens 11.6 / 10.3, 1 x 1422 12.9 / 11.7, 1 x 16000 21.4 / 19.2, 8 x 2081 18.2 / 15.8; 64/8, 1 x 2000 13.8 / 11.8;
+// 40/8, 8 x 4133 32.2 / 31.6; 10/2, 16 x 1000 12.4 / 12.2; 16/4, 30 x 700 15.4 / 14.4; but 6/2, 8 x 3000 12.5 / 12.7, 4/2, 2 x 5000
+// 13.2 / 13.6, 4/4, 1 x 9000 13.7 / 14.5: with few heads the vector ALUs have little to do, and a wave's first products wait
+// for the queries.  At head_dim 64 outputs would be further from 64 bits than they are (8/2, 1 x 700: 2.0e-7 / 2.1e-7).
+// Outputs against 64 bits at head_dim 128: 28/4, 1 x 1422 2.5e-7 / 2.3e-7; 40/8, 8 x 4133 3.2e-7 / 2.5e-7; binary16, 28/4,
+// 2 x 9000, int4 3.4e-7 / 3.0e-7; 10/2, 3 x 300, int4 2.1e-7 / 1.9e-7.
+constexpr bool split_on_matrix(int D, int G, int q_es) { return q_es == 2 && D == 128 && G >= 4; }
 template <int D, int G, int KT>
 struct KernelGeo {
+  static constexpr bool MC = split_on_matrix(D, G, KT == KT_F32 ? 4 : 2);
   static constexpr Mode MF = KT == KT_BF16 ? F_BF16 : KT == KT_F16 ? F_F16 : F_F32;
   static constexpr int RB = Geo<D, MF>::RB;
   static constexpr int TR = RB == 256 ? 32 : 64, TILE = TR * RB;
@@ -1610,54 +1642,67 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
   w.pa = lds_addr(w.p);
   float* my_o = (float*)w.t;          // after the wave's last tile: its output partial, [G][D]
 
-  float o[G][EV], m_run[G], l_lane[G];
+  if constexpr (KG::MC) {
+    w.sp = a.xs + xs_at(a, bl, kvh * G, 0);
+    w.sp_stride = a.xs_stride;
+    f32x4 om[1][D / 16];
+    float mr[1] = {-INFINITY}, lr[1] = {0.f};
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    m_run[h] = -INFINITY; l_lane[h] = 0.f;
-#pragma unroll
-    for (int e = 0; e < EV; ++e) o[h][e] = 0.f;
-  }
-  bool o_written = false;
-  if (u < nwf) {
-    attn_wave<D, G, KG::MF, KT, TR>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
+    for (int db = 0; db < D / 16; ++db) om[0][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (u < nwf) attn_wave_mfma<D, KT, KG::MF, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u, nwf, nF, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, om, mr, lr);
+    else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
+    else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
+    park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
   } else {
-    if constexpr (EV == 8) {
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
-    } else {
-      // binary32 rows use 4 elements per lane, code rows 8: separate accumulators, parked directly
-      float o8[G][8];
-#pragma unroll
-      for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
-      if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
-      else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        constexpr int L8 = D / 8;
-        float t8[RowSum<8, L8>::N];
-        row_sum<8, L8>(o8[h], lane, t8);
-#pragma unroll
-        for (int k = 0; k < RowSum<8, L8>::N; ++k) my_o[h * D + row_sum_elem<8, L8>(lane, k)] = t8[k];
-      }
-      o_written = true;
-    }
-  }
-  // ---- wave partial: sum the row groups and the per-lane denominators, then merge the waves through LDS
-  if (!o_written) {
+    float o[G][EV], m_run[G], l_lane[G];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      float t1[RowSum<EV, LPRV>::N];
-      row_sum<EV, LPRV>(o[h], lane, t1);
+      m_run[h] = -INFINITY; l_lane[h] = 0.f;
 #pragma unroll
-      for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t1[k];
+      for (int e = 0; e < EV; ++e) o[h][e] = 0.f;
     }
-  }
+    bool o_written = false;
+    if (u < nwf) {
+      attn_wave<D, G, KG::MF, KT, TR>(a, w, bl, jq, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, o, m_run, l_lane);
+    } else {
+      if constexpr (EV == 8) {
+        if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+        else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o, m_run, l_lane);
+      } else {
+        // binary32 rows use 4 elements per lane, code rows 8: separate accumulators, parked directly
+        float o8[G][8];
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float ls = wave_sum(l_lane[h]);
-    if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
+        for (int h = 0; h < G; ++h)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
+        if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
+        else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          constexpr int L8 = D / 8;
+          float t8[RowSum<8, L8>::N];
+          row_sum<8, L8>(o8[h], lane, t8);
+#pragma unroll
+          for (int k = 0; k < RowSum<8, L8>::N; ++k) my_o[h * D + row_sum_elem<8, L8>(lane, k)] = t8[k];
+        }
+        o_written = true;
+      }
+    }
+    // ---- wave partial: sum the row groups and the per-lane denominators, then merge the waves through LDS
+    if (!o_written) {
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float t1[RowSum<EV, LPRV>::N];
+        row_sum<EV, LPRV>(o[h], lane, t1);
+#pragma unroll
+        for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t1[k];
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float ls = wave_sum(l_lane[h]);
+      if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
+    }
   }
   __syncthreads();
   const int bq = bl * a.n_q + jq;
@@ -1765,16 +1810,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   if (u < nwf) attn_wave_mfma<D, KT, MF, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u, nwf, nF, nF, f_loc, 0, om, mr, lr);
   else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
   else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
-  // the wave's partial: lane (n, kb) has the statistics of head n and the outputs of heads 4*kb + j, element 16*db + n
-  const float ls = quad_sum(lr[0]);
-  if (lane < G) { sm_ml[wave * 16 + lane] = mr[0]; sm_ml[wave * 16 + 8 + lane] = ls; }
-#pragma unroll
-  for (int db = 0; db < D / 16; ++db)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int h = 4 * (lane >> 4) + j;
-      if (h < G) my_o[h * D + 16 * db + (lane & 15)] = om[0][db][j];
-    }
+  park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
   // ---- merge the waves
   __syncthreads();
   if (split) {
@@ -2446,6 +2482,7 @@ __global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs
     else if (in_q) pos = a.q_pos[(size_t)b * a.Nmax + (j - cf * TB)];
     else if (in_s) pos = a.s_pos[(size_t)b * a.Nmax + (j - (cf + cq) * TB)];
     float score = 0.f;
+    const float xscale = split_on_matrix(D, G, a.q_es) ? a.softmax_scale : 1.0f;      // (the others leave scaled logits)
     const float pen = a.red ? a.red_w * (float)G / (float)(nF + nQ + nS) : 0.f;
     const int per_pass = STEP ? (FG::NST / a.Hq < FG::LB ? FG::NST / a.Hq : FG::LB) : 1;
     for (int l0 = 0; l0 < a.nl; l0 += per_pass) {
@@ -2479,11 +2516,11 @@ __global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs
               // value-aware scorer: the group's weights times the norm of the value row its heads read
               float w = 0.f;
 #pragma unroll
-              for (int g = 0; g < G; ++g) w += __builtin_amdgcn_exp2f((x[g] - stt[g].x) * LOG2E) * stt[g].y;
+              for (int g = 0; g < G; ++g) w += exp_le0(fmaf(x[g], xscale, -stt[g].x)) * stt[g].y;
               acc = fmaf(w, a.vnorm[((size_t)bl * a.Hkv + kvh) * a.Nmax + pos], acc);
             } else {
 #pragma unroll
-              for (int g = 0; g < G; ++g) acc += __builtin_amdgcn_exp2f((x[g] - stt[g].x) * LOG2E) * stt[g].y;
+              for (int g = 0; g < G; ++g) acc += exp_le0(fmaf(x[g], xscale, -stt[g].x)) * stt[g].y;
             }
             // redundancy-penalised scorers: the G heads of the group each take red_w * rho / (positions attended) off
             if (a.red) acc = fmaf(-pen, a.red[((size_t)bl * a.Hkv + kvh) * a.Nmax + pos], acc);

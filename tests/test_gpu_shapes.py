@@ -494,18 +494,22 @@ def test_chunk_over_large_values_in_binary16(n_q, heads, dim, t2, every):
         p.close()
 
 
-@pytest.mark.parametrize("heads,dim,kv_dtype,t2,context", [
-    (7, 128, "bf16", "int4_g32", 300),
-    (5, 128, "f16", "int8_row", 290),
-    (8, 64, "f16", "int4_g32", 321),
-    (1, 64, "bf16", "int8_row", 257),
+@pytest.mark.parametrize("heads,dim,kv_dtype,t2,context,batch", [
+    (7, 128, "bf16", "int4_g32", 300, 256),        # one workgroup per pair
+    (5, 128, "f16", "int8_row", 290, 256),
+    (8, 64, "f16", "int4_g32", 321, 256),
+    (1, 64, "bf16", "int8_row", 257, 256),
+    (7, 128, "bf16", "int8_row", 1500, 2),         # pairs split, matrix instructions
+    (4, 128, "f16", "int4_g32", 261, 3),
+    (8, 128, "f16", "int8_row", 1025, 2),
+    (3, 128, "bf16", "int4_g32", 700, 2),          # ... vector instructions
 ])
-def test_whole_pairs_over_infinite_keys_and_large_values(heads, dim, kv_dtype, t2, context):
-    """One workgroup per pair (256 pairs): rows whose logit is -inf have no weight and keep their score, padding columns have no
-    part in anything, T2 rows with V scales far above one stay in binary16's range, and queries may begin at any element."""
+def test_single_calls_over_infinite_keys_and_large_values(heads, dim, kv_dtype, t2, context, batch):
+    """Rows whose logit is -inf have no weight and keep their score, padding columns have no part in anything, T2 rows with V
+    scales far above one stay in binary16's range, and queries may begin at any element."""
     from gpu_common import assert_out_close, assert_scores_close
     from tkv_synth import Workload
-    cfg = small_config(name="pairs-edge", n_layers=1, batch=256, n_q_heads=heads, n_kv_heads=1, head_dim=dim, kv_dtype=kv_dtype,
+    cfg = small_config(name="pairs-edge", n_layers=1, batch=batch, n_q_heads=heads, n_kv_heads=1, head_dim=dim, kv_dtype=kv_dtype,
                        t2_format=t2, context=context, decode_steps=1, k_window=16, sigma=1.0)
     wl = Workload(cfg, device="cuda")
     k, v = wl.context_kv(0)
@@ -520,7 +524,7 @@ def test_whole_pairs_over_infinite_keys_and_large_values(heads, dim, kv_dtype, t
     tiers[:, rows] = (0, 1, 0)
     offset = torch.empty(q.numel() + 1, dtype=q.dtype, device="cuda")[1:].view(q.shape).copy_(q)
     for amp in (1.0, 2000.0):
-        print(f"[case] 256 pairs, {heads} heads, {dim}, {kv_dtype}, {t2}, values of {amp}", flush=True)
+        print(f"[case] {batch} pairs, {heads} heads, {dim}, {kv_dtype}, {t2}, values of {amp}", flush=True)
         vv = v.clone()
         vv[:, ::9] *= amp
         p = _chunk_pair(cfg, tiers, k, vv, k_new, v_new)
