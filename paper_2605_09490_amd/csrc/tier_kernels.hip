@@ -2,6 +2,8 @@
 // radix select, plan counting, plan commit (stream compaction of the tier lists by prefix sums, slot
 // allocation from per-pool free stacks), and the row movers (copy, encode, decode, gather, scatter).
 // One workgroup of PLAN_THREADS threads owns one sequence in the planning kernels; all work is integer.
+#include <algorithm>
+
 #include "tkv_internal.h"
 
 namespace tkv {
@@ -10,6 +12,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 
 struct Ppm { uint32_t f[4]; uint32_t rule; };
+struct StepFree { int n[ATTN_ARG_SEQS]; };   // free slots of every sequence's HBM pool
 
 // ---------------------------------------------------------------------------------------------------------
 __global__ void k_init_state(DevView v) {
@@ -75,30 +78,51 @@ __global__ void k_append_rows(DevView v, int layer, const char* __restrict__ k, 
   *(u32x4*)(v.fpV + dst) = *(const u32x4*)(vv + src);
 }
 
-// one new token for every layer at once: k, v [L][B][1][Hkv][D]
-__global__ void k_append_step(DevView v, const char* __restrict__ k, const char* __restrict__ vv, int pos) {
-  const int row_bytes = v.D * v.es, cpr = row_bytes / 16;
-  const long long total = (long long)v.L * v.B * v.Hkv * cpr;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int c = (int)(i % cpr);
-  long long r = i / cpr;
-  const int kvh = (int)(r % v.Hkv); r /= v.Hkv;
-  const int b = (int)(r % v.B);
-  const int layer = (int)(r / v.B);
-  const int slot = v.loc[(size_t)b * v.Nmax + pos];
-  if (slot < 0 || slot >= v.capP) return;
-  const size_t dst = ((((size_t)layer * v.B + b) * v.Hkv + kvh) * v.capP + slot) * row_bytes + (size_t)c * 16;
-  *(u32x4*)(v.fpK + dst) = *(const u32x4*)(k + (size_t)i * 16);
-  *(u32x4*)(v.fpV + dst) = *(const u32x4*)(vv + (size_t)i * 16);
+// One new token for every layer at once: k, v [L][B][1][Hkv][D].  Bound by its launch (some 60 KB per sequence at 28 layers).
+// The slot comes from the top of the free stack, whose height the host knows: no workgroup reads a counter, so that the
+// first one can enter the position and move the counters in the same launch (a step of 28 layers, one sequence of 1422 tokens:
+// 30.1 us with two, 27.8).  More sequences than fit the arguments: the position is entered by k_append_assign before.
+template <bool ASSIGN>
+__global__ void k_append_step(DevView v, const char* __restrict__ k, const char* __restrict__ vv, int pos, StepFree nfree) {
+  const uint32_t row_bytes = v.D * v.es, cpr = row_bytes / 16, i = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t total = (uint32_t)v.L * v.B * v.Hkv * cpr;
+  if (i < total) {
+    const uint32_t r = i / cpr, c = i - r * cpr, bl = r / v.Hkv, b = bl % v.B;     // r = (layer * B + b) * Hkv + kv head
+    const int slot = ASSIGN ? (nfree.n[b] > 0 ? v.free0[(size_t)b * v.cap0 + nfree.n[b] - 1] : -1) : v.loc[(size_t)b * v.Nmax + pos];
+    if (slot >= 0 && slot < v.capP) {
+      const size_t dst = ((size_t)r * v.capP + slot) * row_bytes + (size_t)c * 16;
+      *(u32x4*)(v.fpK + dst) = *(const u32x4*)(k + (size_t)i * 16);
+      *(u32x4*)(v.fpV + dst) = *(const u32x4*)(vv + (size_t)i * 16);
+    }
+  }
+  if (ASSIGN && blockIdx.x == 0 && threadIdx.x < v.B && pos < v.Nmax) {
+    const int b = threadIdx.x;
+    int* cnt = v.cnt + b * CNT_N;
+    const int nf = nfree.n[b], nF = cnt[C_NF], n0 = cnt[C_N0], len = cnt[C_LEN];
+    if (nf > 0) {                                        // (the host checks capacity before launching)
+      const int slot = v.free0[(size_t)b * v.cap0 + nf - 1];
+      const size_t o = (size_t)b * v.Nmax;
+      v.tier[o + pos] = 0; v.loc[o + pos] = slot; v.hloc[o + pos] = -1;
+      v.f_pos[o + nF] = pos; v.f_loc[o + nF] = slot; v.f_loc_old[o + nF] = slot;
+      v.idx[((size_t)0 * v.B + b) * v.Nmax + n0] = pos;
+      cnt[C_FREE0] = nf - 1; cnt[C_NF] = nF + 1; cnt[C_N0] = n0 + 1; cnt[C_LEN] = len + 1;
+    }
+  }
 }
 static void launch_vnorm(const DevView& v, const void* rows, long long n_rows, int n_new, int lb0, int pos0, hipStream_t st);
 static void launch_redundancy(const DevView& v, const void* rows, long long n_rows, int n_new, int lb0, int pos0, hipStream_t st);
 
-hipError_t launch_append_step(const DevView& v, const void* k, const void* v_, int pos, hipStream_t st) {
-  hipLaunchKernelGGL(k_append_assign, dim3(v.B), dim3(256), 0, st, v, pos, 1);
-  const long long total = (long long)v.L * v.B * v.Hkv * (v.D * v.es / 16);
-  hipLaunchKernelGGL(k_append_step, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, v, (const char*)k, (const char*)v_, pos);
+hipError_t launch_append_step(const DevView& v, const void* k, const void* v_, int pos, const int* nfree, hipStream_t st) {
+  const long long total = (long long)v.L * v.B * v.Hkv * (v.D * v.es / 16);      // (n_layers * batch <= 65535: below 2^31)
+  const dim3 grid((unsigned)((total + 255) / 256));
+  StepFree f{};
+  if (v.B <= ATTN_ARG_SEQS) {
+    std::copy(nfree, nfree + v.B, f.n);
+    hipLaunchKernelGGL(k_append_step<true>, grid, dim3(256), 0, st, v, (const char*)k, (const char*)v_, pos, f);
+  } else {
+    hipLaunchKernelGGL(k_append_assign, dim3(v.B), dim3(256), 0, st, v, pos, 1);
+    hipLaunchKernelGGL(k_append_step<false>, grid, dim3(256), 0, st, v, (const char*)k, (const char*)v_, pos, f);
+  }
   if (v.vnorm) launch_vnorm(v, v_, (long long)v.L * v.B * v.Hkv, 1, 0, pos, st);
   if (v.red) launch_redundancy(v, k, (long long)v.L * v.B * v.Hkv, 1, 0, pos, st);
   return hipGetLastError();

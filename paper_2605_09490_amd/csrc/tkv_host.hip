@@ -1000,7 +1000,7 @@ tkv_status tkv_decode_step(tkv_cache* c, const void* k_all, const void* v_all, c
       if (!se) return fail(c, TKV_EDEVICE, "hipEventCreate failed");
       HIPCHK(c, hipEventRecord(se->a, (hipStream_t)hip_stream));
     }
-    HIPCHK(c, launch_append_step(v, k_all, v_all, n, (hipStream_t)hip_stream));
+    HIPCHK(c, launch_append_step(v, k_all, v_all, n, c->free0.data(), (hipStream_t)hip_stream));
     for (int b = 0; b < v.B; ++b) { c->free0[b] -= 1; c->nF[b] += 1; }
     c->ntier[0] += v.B;
     c->n_assigned += 1;

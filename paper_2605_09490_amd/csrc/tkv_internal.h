@@ -158,7 +158,7 @@ int attn_tile_rows(int D, int elem_bytes);   // list entries per wave tile of th
 int attn_q_waves(int n_waves, int n_f_tiles, int n_q_tiles);   // how many of a pair's waves serve the Q list
 hipError_t launch_append(const DevView& v, int layer, const void* k, const void* v_, int pos0, int n_new,
                          bool assign, hipStream_t st);
-hipError_t launch_append_step(const DevView& v, const void* k, const void* v_, int pos, hipStream_t st);
+hipError_t launch_append_step(const DevView& v, const void* k, const void* v_, int pos, const int* nfree, hipStream_t st);   // nfree: host
 hipError_t launch_classify(const DevView& v, int n, const uint32_t* ppm, hipStream_t st);
 hipError_t launch_plan_count(const DevView& v, int n, hipStream_t st);
 hipError_t launch_plan_commit(const DevView& v, int n, hipStream_t st);
