@@ -214,14 +214,13 @@ class TieredKV:
 
     @staticmethod
     def _stream(stream):
-        if stream is None:
-            stream = torch.cuda.current_stream()
-        return C.c_void_p(stream.cuda_stream)
+        # (the raw handle: a Stream object for every layer's call takes longer than the call's checks)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
     def _dev_tensor(self, t, shape, dtype=None):
-        assert t.is_cuda and t.dtype == (dtype or self.torch_dtype) and t.is_contiguous() and tuple(t.shape) == tuple(shape), \
+        assert t.is_cuda and t.dtype == (dtype or self.torch_dtype) and t.is_contiguous() and t.shape == shape, \
             (t.device, t.dtype, t.shape, shape)
-        return C.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     def close(self):
         if getattr(self, "_h", None):
