@@ -895,6 +895,16 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(const u32x4& x, const u32x4& y, f
   else
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), c, 0, 0, 0);
 }
+// the same, 16 deep: operands of 8 bytes a lane
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+template <int KT>
+__device__ __forceinline__ f32x4 mfma_16x16x16(const u32x2& x, const u32x2& y, f32x4 c) {
+  if constexpr (KT == KT_BF16)
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, x), __builtin_bit_cast(s16x4, y), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, x), __builtin_bit_cast(f16x4, y), c, 0, 0, 0);
+}
 // maximum / sum over the four lanes n, n + 16, n + 32, n + 48, in all of them
 __device__ __forceinline__ float quad_max(float x) {
   const uint32_t u = __builtin_bit_cast(uint32_t, x);
@@ -1206,7 +1216,13 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int ks = 0; ks < NKS; ++ks) {
-            const f32x4 part = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], f32x4{0.f, 0.f, 0.f, 0.f});
+            f32x4 part = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (ONE) {
+              const u32x4 x = ka[ks], y = qreg[cb][ks];
+              const f32x4 lo = mfma_16x16x16<KT>(u32x2{x.x, x.y}, u32x2{y.x, y.y}, part), hi = mfma_16x16x16<KT>(u32x2{x.z, x.w}, u32x2{y.z, y.w}, part);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) part[j] = lo[j] + hi[j];
+            } else part = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], part);
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[j] = fmaf(half_of(elem(sc[ks >> 1], j), ks & 1), part[j], acc[j]);
           }
@@ -1214,15 +1230,22 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         }
       } else {
         if constexpr (ONE) {
-          // 32 elements at a time by themselves, then added in pairs (a chain of four is 1.5 times as far off, dot products on the
+          // A quarter of the elements at a time, then added in pairs (a chain of four is 1.5 times as far off, dot products on the
           // vector ALUs about as far; 128 elements, one of them large: rms 3.3e-6, 2.2e-6, 2.2e-6)
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) {
-            f32x4 part[NKS];
+            f32x4 part[4];
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) part[ks] = mfma_16x16x32<KT>(ka[ks], qreg[cb][ks], f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int i = 0; i < 4; ++i) {
+              const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+              if constexpr (NKS == 4) part[i] = mfma_16x16x32<KT>(ka[i], qreg[cb][i], zero);
+              else {                                     // the first or last four of every lane's eight elements
+                const u32x4 x = ka[i >> 1], y = qreg[cb][i >> 1];
+                part[i] = (i & 1) ? mfma_16x16x16<KT>(u32x2{x.z, x.w}, u32x2{y.z, y.w}, zero) : mfma_16x16x16<KT>(u32x2{x.x, x.y}, u32x2{y.x, y.y}, zero);
+              }
+            }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) c[cb][rb][j] = NKS == 2 ? part[0][j] + part[1][j] : (part[0][j] + part[1][j]) + (part[NKS - 2][j] + part[NKS - 1][j]);
+            for (int j = 0; j < 4; ++j) c[cb][rb][j] = (part[0][j] + part[1][j]) + (part[2][j] + part[3][j]);
           }
         } else {
 #pragma unroll
@@ -1455,6 +1478,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
       }
       widen(cu, true);
     };
+    f32x4 sum[ONE ? NDB : 1];                            // one token: the tile's own sum, of many tiles per wave
+#pragma unroll
+    for (int db = 0; db < (ONE ? NDB : 1); ++db) sum[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     static_for<NTV>([&](auto tc) {
       constexpr int t = decltype(tc)::value;
       constexpr int NPV = NP / NTV;                      // V pieces of this step
@@ -1500,12 +1526,13 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           if constexpr (M == Q_INT4) { if (db % 2 == 0) weights(tc, cb, db / 2, pt); }
           const u32x4 vb = u32x4{vv[0][db].x, vv[0][db].y, vv[1][db].x, vv[1][db].y};
           if constexpr (ONE) {
-            // many tiles per wave: the 32 entries' sum by itself, small terms first, and one addition to the running one
-            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+            // small terms first, and one addition to the running output per tile
 #pragma unroll
-            for (int i = NT - 1; i >= 0; --i) sum = mfma_16x16x32<KT>(pt[i], vb, sum);
+            for (int i = NT - 1; i >= 0; --i) sum[db] = mfma_16x16x32<KT>(pt[i], vb, sum[db]);
+            if constexpr (t + 1 == NTV) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[cb][db][j] += sum[j];
+              for (int j = 0; j < 4; ++j) o[cb][db][j] += sum[db][j];
+            }
           } else {
 #pragma unroll
             for (int i = NT - 1; i >= 0; --i) o[cb][db] = mfma_16x16x32<KT>(pt[i], vb, o[cb][db]);
@@ -1556,7 +1583,8 @@ __device__ __forceinline__ void park_one(const f32x4 (&om)[D / 16], float m, flo
 // heads, 1 x 300 tokens 11.6 / 10.3, 1 x 1422 12.9 / 11.7, 1 x 16000 21.4 / 19.2, 8 x 2081 18.2 / 15.8; 64/8, 1 x 2000 13.8 / 11.8;
 // 40/8, 8 x 4133 32.2 / 31.6; 10/2, 16 x 1000 12.4 / 12.2; 16/4, 30 x 700 15.4 / 14.4; but 6/2, 8 x 3000 12.5 / 12.7, 4/2, 2 x 5000
 // 13.2 / 13.6, 4/4, 1 x 9000 13.7 / 14.5: with few heads the vector ALUs have little to do, and a wave's first products wait
-// for the queries.  At head_dim 64 outputs would be further from 64 bits than they are (8/2, 1 x 700: 2.0e-7 / 2.1e-7).
+// for the queries.  At head_dim 64 calls would be faster (28/4, 1 x 1422 12.8 / 10.8, 64/8, 4 x 4000 18.6 / 15.5), but outputs
+// further from 64 bits (16/4, 1 x 2500 2.0e-7 / 2.1e-7; 12/2, 2 x 5000, int4 2.6e-7 / 2.75e-7; 64/8, 2 x 3000 2.2e-7 / 2.25e-7).
 // Outputs against 64 bits at head_dim 128: 28/4, 1 x 1422 2.5e-7 / 2.3e-7; 40/8, 8 x 4133 3.2e-7 / 2.5e-7; binary16, 28/4,
 // 2 x 9000, int4 3.4e-7 / 3.0e-7; 10/2, 3 x 300, int4 2.1e-7 / 1.9e-7.
 constexpr bool split_on_matrix(int D, int G, int q_es) { return q_es == 2 && D == 128 && G >= 4; }
@@ -1750,10 +1778,11 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
 // 1 x 3000 48.9 / 45.0; ten layers, 10/2, 10 x 1500 37.3 / 35.6; 27 layers, 8/8 at head_dim 64, 6 x 1200 88.2 / 87.2.  What the
 // stream of rows bounds (14B shape, 48 layers, batch 8, 4112 tokens: 960-1140 us, 6.0 TB/s) is within 1 %.
 // Precision: weights enter the product as exact sums of three 16-bit terms, a tile's 32 entries are summed by themselves and
-// added to the running output once, a row's halves are summed by themselves, and logits stay unscaled until the distance to the
-// maximum is taken (one rounding less).  Outputs against 64 bits, vector / matrix instructions, relative 2-norm: 28/4 heads,
-// 8 x 2081, 10 % int8 2.9e-7 / 2.6e-7; 40/8, 8 x 4096, 15 % int8 3.2e-7 / 2.7e-7; 16/4, 1 x 16000 4.8e-7 / 3.1e-7; binary16,
-// 40/8, 1 x 8000, int4 4.1e-7 / 3.5e-7; 8/8 at head_dim 64, 2 x 3000 2.44e-7 / 2.33e-7; 10/2, 4 x 700 2.42e-7 / 2.32e-7.
+// added to the running output once, quarters of a row's elements are summed by themselves, logits stay unscaled until the
+// distance to the maximum is taken, and the exponent's product keeps its remainder.  Outputs against 64 bits, vector / matrix
+// instructions, relative 2-norm: 28/4 heads, 8 x 2081, 10 % int8 2.9e-7 / 2.4e-7; 40/8, 8 x 4096, 15 % int8 3.2e-7 / 2.5e-7; 16/4, 1 x
+// 16000 4.9e-7 / 2.9e-7; binary16, 40/8, 1 x 8000, int4 4.2e-7 / 2.9e-7; 8/8 at head_dim 64, 2 x 3000 2.45e-7 / 2.25e-7; 10/2, 4 x 700
+// 2.4e-7 / 2.1e-7.
 // The LDS holds eight 8 KB tile buffers (32 rows of 256 bytes; 64 KB in flight per compute unit stream as fast as 128 KB)
 // and the logits of LCAP entries; a longer list parks the rest in memory and reads it back.  The eight waves are divided
 // between the lists as in the split launch.
