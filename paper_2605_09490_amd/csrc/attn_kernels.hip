@@ -1406,8 +1406,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            // (one token: the product's rounding is left out of the distance to the reference; a masked entry stays one)
-            const float d = ONE ? (p[cb][rb][j] > -INFINITY ? fmaf(c[cb][rb][j], a.softmax_scale, -ms) : -INFINITY) : p[cb][rb][j] - ms;
+            // (one token: the product's rounding is left out of the distance to the reference; a masked entry stays one, and a
+            // logit that is no number stays none)
+            const float d = ONE ? (p[cb][rb][j] == -INFINITY ? -INFINITY : fmaf(c[cb][rb][j], a.softmax_scale, -ms)) : p[cb][rb][j] - ms;
             if constexpr (ONE) p[cb][rb][j] = exp_le0(d) * (float)(1 << (int)PSplit<KT>::P_SHIFT);
             else p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(d, LOG2E, PSplit<KT>::P_SHIFT));
             ps += p[cb][rb][j];

@@ -536,6 +536,75 @@ def test_single_calls_over_infinite_keys_and_large_values(heads, dim, kv_dtype, 
         p.close()
 
 
+def _one_token_outputs(kind, cfg, k, v, k_new, v_new, q, tiers=None):
+    """Outputs [layers, sequences, heads, head_dim] and scores of one decode step by whole steps ("step"), per-layer calls
+    ("call") or chunks of two query tokens ("chunk": the last one's) over the context rows k[l], v[l] and the new row."""
+    import paper_2605_09490_amd as tkv
+    kv = tkv.TieredKV(cfg.n_layers, cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.max_tokens, kv_dtype=cfg.kv_dtype,
+                      t2_format=cfg.t2_format, k_window=16, prefetch_mode="lazy")
+    last = 1 if kind == "chunk" else 0        # a chunk's first query token stands before the new row
+    for l in range(cfg.n_layers):
+        kv.append(l, k[l], v[l])
+    if tiers is not None:
+        kv.set_tiers(tiers)
+        kv.migrate()
+    if kind == "step":
+        out = kv.decode_step(k_new, v_new, q)
+    else:
+        outs = []
+        for l in range(cfg.n_layers):
+            kn, vn = k_new[l], v_new[l]
+            if last:
+                kn, vn = torch.cat([kn, kn], dim=1), torch.cat([vn, vn], dim=1)
+            kv.append(l, kn, vn)
+            if last:
+                outs.append(kv.attend_and_score_chunk(l, torch.stack([q[l], q[l]], dim=1).contiguous())[:, 1])
+            else:
+                outs.append(kv.attend_and_score(l, q[l]))
+        out = torch.stack(outs)
+    scores = kv.get_scores()
+    kv.close()
+    return out, scores
+
+
+ONE_TOKEN_LAUNCHES = [
+    ("call", dict(n_layers=1, batch=256, n_q_heads=7, n_kv_heads=1, head_dim=128, context=300)),                      # one workgroup per pair
+    ("call", dict(n_layers=1, batch=128, n_q_heads=16, n_kv_heads=2, head_dim=64, context=321, kv_dtype="f16")),
+    ("step", dict(n_layers=64, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=200, kv_dtype="f16")),      # ... of whole steps
+    ("step", dict(n_layers=25, batch=2, n_q_heads=14, n_kv_heads=2, head_dim=128, context=1500)),                     # pairs in parts
+    ("call", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700)),                       # pairs split, matrix instructions
+    ("call", dict(n_layers=2, batch=2, n_q_heads=8, n_kv_heads=2, head_dim=128, context=1100, kv_dtype="f16")),
+    ("call", dict(n_layers=2, batch=2, n_q_heads=6, n_kv_heads=2, head_dim=128, context=700)),                        # ... vector instructions
+    ("call", dict(n_layers=2, batch=2, n_q_heads=16, n_kv_heads=2, head_dim=64, context=900, kv_dtype="f16")),
+]
+
+
+@pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES + [("chunk", ONE_TOKEN_LAUNCHES[4][1])])
+def test_logits_that_are_no_numbers_reach_the_output(kind, shape):
+    """A NaN in a key row, and an infinite key element under a query element of zero: the heads that read the row have no
+    number for an output, whichever launch serves the call.  All others have the bits they have without."""
+    from tkv_synth import Workload
+    cfg = small_config(name="nan", **{**dict(kv_dtype="bf16", decode_steps=2, k_window=16, sigma=1.0), **shape})
+    print(f"[case] {kind} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    k, v = (list(x) for x in zip(*(wl.context_kv(l) for l in range(cfg.n_layers))))
+    k_all, v_all, q_all = wl.decode_inputs(0, 1)
+    q, G = q_all[0].clone(), cfg.n_q_heads // cfg.n_kv_heads
+    q[-1, -1, -G:, 5] = 0
+    clean, _ = _one_token_outputs(kind, cfg, k, v, k_all[0], v_all[0], q)
+    k[0], k[-1] = k[0].clone(), k[-1].clone()
+    k[0][0, 17, 0, 3] = float("nan")                    # first layer, sequence and kv head
+    k[-1][-1, 130, -1, 5] = float("inf")                # last ones
+    out, scores = _one_token_outputs(kind, cfg, k, v, k_all[0], v_all[0], q)
+    hit = torch.zeros(clean.shape[:3], dtype=torch.bool, device="cuda")
+    hit[0, 0, :G] = True
+    hit[-1, -1, -G:] = True
+    assert torch.isfinite(clean).all()
+    assert out[hit].isnan().all(), int(out[hit].isfinite().sum())
+    assert torch.equal(out[~hit], clean[~hit])
+    assert np.isnan(scores[0, 17]) and np.isnan(scores[-1, 130])
+
+
 @pytest.mark.parametrize("n_q,dim,kv_dtype", [
     (3, 128, "bf16"),                      # 15 columns, logits written
     (6, 64, "f16"),                        # 30 columns, logits written
