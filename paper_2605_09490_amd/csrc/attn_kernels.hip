@@ -48,6 +48,7 @@ namespace tkv {
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) char lds_char;
 
@@ -924,15 +925,17 @@ __device__ __forceinline__ int small_div(int n, float inv) { return (int)(((floa
 // A binary32 weight as a sum of 16-bit terms, each the leading bits (by truncation) of what the terms before it left.
 // bfloat16: three terms of 8 significant bits are the weight exactly.  binary16: two terms of 11 bits (22 of the 24);
 // the weights are taken times 2^P_SHIFT there, so that small ones stay clear of binary16's narrow exponent range
-// (the factor is taken out of the accumulators at the end).
+// (the factor is taken out of the accumulators at the end).  One query token: three terms in either type, and binary16's
+// weights relative to the tile's largest (attn_wave_mfma).
 template <int KT>
 struct PSplit {
   static constexpr int N = KT == KT_BF16 ? 3 : 2;
   static constexpr float P_SHIFT = KT == KT_BF16 ? 0.f : 14.f;
   static constexpr float SCALE_MAX = 3.75f;   // binary16: what a weight of 1 can be multiplied by and stay in range (65504) with the shift
 };
+// (p0, p1: left with what the terms do not hold)
 template <int KT, int N>
-__device__ __forceinline__ void split_pair(float p0, float p1, uint32_t (&t)[N]) {
+__device__ __forceinline__ void split_pair(float& p0, float& p1, uint32_t (&t)[N]) {
   if constexpr (KT == KT_BF16) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -1311,15 +1314,24 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
       });
     }
     // -- online softmax: the lane has entries 16*rb + 4*kb + j of its column
+    // One token in binary16, whose terms end at 2^-24: the tile's weights enter the product relative to the column's largest
+    // (the power of two above it), and list Q's V scales relative to the tile's largest, and the tile's sum gets both back:
+    // weights down to 1 / 8192 of the tile's largest are whole in the three terms, whatever the values' magnitude and wherever
+    // the tile lies below the running maximum.  A tile that has smaller ones adds what the terms leave of them by itself.
+    // (All times 2^14, as a chunk's: values of 1e-4 in int8 rows were 3.4e-6 from 64 bits, as any others now 3.0e-7, and beside a
+    // first row with all of the attention but e^-24 and a value of zero outputs were 1.2e-3 off.)
+    constexpr bool REL = ONE && KT == KT_F16;
+    uint32_t rel = 0;                                    // REL: that power of two, as bits
+    bool wide = false;                                   // ... wave-uniform: smaller weights
     float p[NCB][NRB][4];
     {
       const int e0 = tile * TR + 4 * kb;
       const bool edge = (tile + 1) * TR > n_list - (IS_Q ? 0 : a.cq - 1);   // wave-uniform: some column does not see the whole tile
-      // binary16 code rows: a weight times its V row's scale has to stay in binary16's range.  Where the tile has a scale
-      // beyond what the shift leaves room for (V of some 26 and more in an int4 group, 480 in an int8 row), such an entry counts
-      // with the logit of its scaled weight in the running reference, which is then above the largest logit: any reference
-      // does, the statistics are merged relative to it.
-      constexpr bool BOUND = IS_Q && KT == KT_F16;
+      // A chunk's binary16 code rows: a weight times its V row's scale has to stay in binary16's range.  Where the tile has a
+      // scale beyond what the shift leaves room for (V of some 26 and more in an int4 group, 480 in an int8 row), such an entry
+      // counts with the logit of its scaled weight in the running reference, which is then above the largest logit: any
+      // reference does, the statistics are merged relative to it.
+      constexpr bool BOUND = IS_Q && KT == KT_F16 && !ONE;
       bool big = false;                                  // wave-uniform
       if constexpr (BOUND) {
         uint32_t sv[SCD];
@@ -1337,11 +1349,21 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
           for (int j = 0; j < 4; ++j) p[cb][rb][j] = c[cb][rb][j] * a.softmax_scale;
+        float least = INFINITY;                          // REL: the lane's smallest logit but masked ones
         if (edge) {
 #pragma unroll
           for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) p[cb][rb][j] = (e0 + 16 * rb + j < n_seen[cb]) ? p[cb][rb][j] : -INFINITY;
+            for (int j = 0; j < 4; ++j) {
+              const bool seen = e0 + 16 * rb + j < n_seen[cb];
+              if constexpr (REL) least = fminf(least, seen ? p[cb][rb][j] : INFINITY);
+              p[cb][rb][j] = seen ? p[cb][rb][j] : -INFINITY;
+            }
+        } else if constexpr (REL) {
+#pragma unroll
+          for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) least = fminf(least, p[cb][rb][j]);
         }
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb)
@@ -1398,7 +1420,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         }
         // m_run starts at -inf: corr = exp2(-inf) = 0 against zero accumulators.  A tile of which the column sees
         // nothing (an early token of a chunk, the list's last tile) leaves mn at -inf: nothing to add, nothing to rescale.
-        const float mn = fmaxf(m_run[cb], quad_max(mx));
+        const float mt = quad_max(mx), mn = fmaxf(m_run[cb], mt);
         const float corr = mn > -INFINITY ? __builtin_amdgcn_exp2f((m_run[cb] - mn) * LOG2E) : 1.0f;
         const float ms = mn > -INFINITY ? mn : 0.f;      // (all weights are exp2(-inf) = 0 then)
         float ps = 0.f;
@@ -1409,12 +1431,17 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
             // (one token: the product's rounding is left out of the distance to the reference; a masked entry stays one, and a
             // logit that is no number stays none)
             const float d = ONE ? (p[cb][rb][j] == -INFINITY ? -INFINITY : fmaf(c[cb][rb][j], a.softmax_scale, -ms)) : p[cb][rb][j] - ms;
-            if constexpr (ONE) p[cb][rb][j] = exp_le0(d) * (float)(1 << (int)PSplit<KT>::P_SHIFT);
+            if constexpr (ONE) p[cb][rb][j] = exp_le0(d);
             else p[cb][rb][j] = __builtin_amdgcn_exp2f(fmaf(d, LOG2E, PSplit<KT>::P_SHIFT));
             ps += p[cb][rb][j];
           }
         l_run[cb] = fmaf(l_run[cb], corr, ps);
         m_run[cb] = mn;
+        if constexpr (REL) {
+          // (2^-64 of the running maximum: nothing the outputs could hold)
+          rel = (__builtin_bit_cast(uint32_t, fmaxf(__builtin_amdgcn_exp2f((mt - ms) * LOG2E), 0x1p-64f)) & 0x7f800000u) + 0x800000u;
+          wide = __builtin_amdgcn_ballot_w64(mt - least > 9.0f) != 0;      // (e^9 is just below 8192)
+        }
         // the output accumulators of this lane belong to columns 4*kb + j: their factors come from those columns'
         // lanes; once the maxima have settled nothing needs rescaling (x * 1.0f is exact)
         if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {
@@ -1444,10 +1471,43 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
       for (int j = 0; j < SCD; ++j) tie(vsc[j]);
       if constexpr (MORE) issue_scales();                // both scale regions are free: the next tile's
     }
-    // weights of 32 entries as operand terms; list Q: times the V row's scale (of scale group gd)
-    auto weights = [&](auto tc, int cb, int gd, u32x4 (&pt)[NT]) {
+    float unit[4] = {1.f, 1.f, 1.f, 1.f};                // what the tile's sums of columns 4*kb + j are in units of
+    if constexpr (REL) {
+      // 2^14 / rel, and unit its inverse; list Q: over the power of two at or below the tile's largest scale as well
+      float up = __builtin_bit_cast(float, 0x7f000000u + (14u << 23) - rel), down = __builtin_bit_cast(float, rel - (14u << 23));
+      if constexpr (IS_Q) {
+        float s = 0.f;
+        if constexpr (M == Q_INT8) {
+#pragma unroll
+          for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s = fmaxf(s, elem_f(vsc[0][rb], j));
+        } else {
+          u16x2 t = {0, 0};                              // (no scale is negative: their order is that of their bits)
+#pragma unroll
+          for (int i = 0; i < SCD; ++i)
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) t = __builtin_elementwise_max(t, __builtin_bit_cast(u16x2, elem(vsc[i][rb], j)));
+          s = fmaxf(half_of(t.x, 0), half_of(t.y, 0));
+        }
+        // (no scale of a binary16 row but zero and infinity lies outside; an infinite one stays infinite in the product)
+        const uint32_t e = __builtin_bit_cast(uint32_t, fminf(fmaxf(quad_max(s), 0x1p-40f), 0x1p20f)) & 0x7f800000u;
+        up *= __builtin_bit_cast(float, 0x7f000000u - e);
+        down *= __builtin_bit_cast(float, e);
+      }
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[0][rb][j] *= up;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        unit[j] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((4 * kb + j) << 2, __builtin_bit_cast(int, down)));
+    }
+    // weights of 32 entries; list Q: times the V row's scale (of scale group gd)
+    auto products = [&](auto tc, int cb, int gd, float (&pw)[2][4]) {
       constexpr int t = decltype(tc)::value;
-      float pw[2][4];
 #pragma unroll
       for (int r2 = 0; r2 < 2; ++r2)
 #pragma unroll
@@ -1457,6 +1517,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           if constexpr (M == Q_INT4) v *= half_of(elem(vsc[gd >> 1][2 * t + r2], j), gd & 1);
           pw[r2][j] = v;
         }
+    };
+    // ... as operand terms
+    auto terms = [&](float (&pw)[2][4], u32x4 (&pt)[NT]) {
       uint32_t s0[NT], s1[NT], s2[NT], s3[NT];
       split_pair<KT, NT>(pw[0][0], pw[0][1], s0);
       split_pair<KT, NT>(pw[0][2], pw[0][3], s1);
@@ -1521,10 +1584,11 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
         u32x4 pt[NT];
-        if constexpr (M != Q_INT4) weights(tc, cb, 0, pt);
+        float pw[2][4];
+        if constexpr (M != Q_INT4) { products(tc, cb, 0, pw); terms(pw, pt); }
 #pragma unroll
         for (int db = 0; db < NDB; ++db) {
-          if constexpr (M == Q_INT4) { if (db % 2 == 0) weights(tc, cb, db / 2, pt); }
+          if constexpr (M == Q_INT4) { if (db % 2 == 0) { products(tc, cb, db / 2, pw); terms(pw, pt); } }
           const u32x4 vb = u32x4{vv[0][db].x, vv[0][db].y, vv[1][db].x, vv[1][db].y};
           if constexpr (ONE) {
             // small terms first, and one addition to the running output per tile
@@ -1532,11 +1596,40 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
             for (int i = NT - 1; i >= 0; --i) sum[db] = mfma_16x16x32<KT>(pt[i], vb, sum[db]);
             if constexpr (t + 1 == NTV) {
 #pragma unroll
-              for (int j = 0; j < 4; ++j) o[cb][db][j] += sum[db][j];
+              for (int j = 0; j < 4; ++j) o[cb][db][j] = fmaf(sum[db][j], unit[j], o[cb][db][j]);
             }
           } else {
 #pragma unroll
             for (int i = NT - 1; i >= 0; --i) o[cb][db] = mfma_16x16x32<KT>(pt[i], vb, o[cb][db]);
+          }
+        }
+        if constexpr (REL) {
+          if (wide) {
+            // what the terms leave (below 2^-24), times 2^38, and what that leaves once more: 2^-86 of the tile's largest
+            constexpr int GDB = M == Q_INT4 ? 2 : NDB;   // columns of output with the same weights
+#pragma unroll
+            for (int g0 = 0; g0 < NDB; g0 += GDB) {
+              float f = 1.0f;
+              products(tc, cb, g0 / 2, pw);
+              terms(pw, pt);
+              for (int k = 0; k < 2; ++k) {
+                f *= 0x1p-38f;
+#pragma unroll
+                for (int r2 = 0; r2 < 2; ++r2)
+#pragma unroll
+                  for (int j = 0; j < 4; ++j) pw[r2][j] *= 0x1p38f;
+                terms(pw, pt);
+#pragma unroll
+                for (int db = g0; db < g0 + GDB; ++db) {
+                  const u32x4 vb = u32x4{vv[0][db].x, vv[0][db].y, vv[1][db].x, vv[1][db].y};
+                  f32x4 rest = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                  for (int i = NT - 1; i >= 0; --i) rest = mfma_16x16x32<KT>(pt[i], vb, rest);
+#pragma unroll
+                  for (int j = 0; j < 4; ++j) o[cb][db][j] = fmaf(rest[j], unit[j] * f, o[cb][db][j]);
+                }
+              }
+            }
           }
         }
       }
@@ -1548,7 +1641,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   for (; (tile + tstride) * TR < n_walk; tile += tstride) tile_body(tile, std::true_type{});
   tile_body(tile, std::false_type{});
 
-  if constexpr (PSplit<KT>::P_SHIFT != 0.f) {
+  if constexpr (PSplit<KT>::P_SHIFT != 0.f && !ONE) {
     const float back = __builtin_amdgcn_exp2f(-PSplit<KT>::P_SHIFT);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {

@@ -605,6 +605,72 @@ def test_logits_that_are_no_numbers_reach_the_output(kind, shape):
     assert np.isnan(scores[0, 17]) and np.isnan(scores[-1, 130])
 
 
+@pytest.mark.parametrize("t2", ["int8_row", "int4_g32"])
+@pytest.mark.parametrize("kind,shape", [
+    ("call", dict(n_layers=1, batch=256, n_q_heads=5, n_kv_heads=1, head_dim=128, context=400)),
+    ("call", dict(n_layers=1, batch=256, n_q_heads=8, n_kv_heads=1, head_dim=64, context=500)),
+    ("call", dict(n_layers=2, batch=2, n_q_heads=14, n_kv_heads=2, head_dim=128, context=1500)),
+    ("call", dict(n_layers=2, batch=2, n_q_heads=6, n_kv_heads=2, head_dim=128, context=1500)),      # vector instructions
+])
+def test_binary16_outputs_are_as_exact_whatever_the_values_magnitude(kind, t2, shape):
+    """T2 rows of a binary16 cache whose values are far from one either way.  Outputs are linear in the values, so their error
+    against 64 bits, relative to the outputs, is that of values of order one: a factor of two is left for another draw of the
+    roundings (values of 1e-4 are rounded to fewer bits by binary16 itself, which the reference sees too)."""
+    from gpu_common import to_f64
+    from tkv_synth import Workload
+    cfg = small_config(name="magnitude", **{**dict(kv_dtype="f16", decode_steps=2, k_window=16, t2_format=t2), **shape})
+    cfg = dataclasses.replace(cfg, recipe="bias", sigma=1.5)
+    print(f"[case] {kind} {t2} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    tiers = np.random.default_rng(5).choice(4, size=(cfg.batch, cfg.context), p=(0.1, 0.05, 0.8, 0.05)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    k, v = (list(x) for x in zip(*(wl.context_kv(l) for l in range(cfg.n_layers))))
+    k_new, v_new, _ = _step_rows(wl, 1)
+    q = wl.step_q(0, 0)
+    errs = []
+    for amp in (1.0, 2.0 ** 11, 2.0 ** -7, 2.0 ** -13):
+        p = _chunk_pair(dataclasses.replace(cfg, n_layers=1), tiers, k[0], v[0] * amp, k_new, v_new * amp)
+        got, ref = p.attend(0, q)
+        errs.append(float(np.linalg.norm(got - ref) / np.linalg.norm(ref)))
+        print(f"[case] values of {amp}: error {errs[-1]:.2e}", flush=True)
+        p.close()
+    assert max(errs) <= 2 * errs[0], errs
+
+
+@pytest.mark.parametrize("kind,shape", [
+    ("call", dict(n_layers=1, batch=256, n_q_heads=5, n_kv_heads=1, head_dim=128, context=400)),
+    ("call", dict(n_layers=1, batch=256, n_q_heads=8, n_kv_heads=1, head_dim=64, context=500)),
+    ("call", dict(n_layers=2, batch=2, n_q_heads=14, n_kv_heads=2, head_dim=128, context=1500)),
+    ("call", dict(n_layers=2, batch=2, n_q_heads=6, n_kv_heads=2, head_dim=128, context=1500)),      # vector instructions
+])
+def test_binary16_outputs_beside_a_row_with_nearly_all_the_attention(kind, shape):
+    """A row that takes all of the attention but some 1e-3 to 1e-8 and has a value of zero, as first tokens often have: the
+    outputs are made of weights far below the largest.  A logit's distance to that row's is rounded in binary32, and so is what
+    it is the distance of: 2^-24 of it either time, beyond what the outputs are off without such a row."""
+    from gpu_common import to_f64
+    from tkv_synth import Workload
+    cfg = small_config(name="sink", **{**dict(kv_dtype="f16", decode_steps=2, k_window=16), **shape})
+    cfg = dataclasses.replace(cfg, recipe="bias", sigma=1.0)
+    print(f"[case] {kind} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    tiers = np.random.default_rng(5).choice(4, size=(cfg.batch, cfg.context), p=(0.4, 0.15, 0.4, 0.05)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    k, v = wl.context_kv(0)
+    k_new, v_new, _ = _step_rows(wl, 1)
+    q = wl.step_q(0, 0)
+    errs = []
+    for logit in (0, 12, 18, 24):
+        k[:, 2, :, 0], v[:, 2] = logit, 0
+        p = _chunk_pair(dataclasses.replace(cfg, n_layers=1), tiers, k, v, k_new, v_new)
+        got, ref = p.attend(0, q)
+        errs.append(float(np.linalg.norm(got - ref) / np.linalg.norm(ref)))
+        print(f"[case] logit {logit}: error {errs[-1]:.2e}", flush=True)
+        p.close()
+        assert errs[-1] <= 2 * errs[0] + 2 * logit * 2.0 ** -24, errs
+
+
 @pytest.mark.parametrize("n_q,dim,kv_dtype", [
     (3, 128, "bf16"),                      # 15 columns, logits written
     (6, 64, "f16"),                        # 30 columns, logits written
