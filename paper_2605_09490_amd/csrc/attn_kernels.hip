@@ -1668,6 +1668,79 @@ __device__ __forceinline__ void park_one(const f32x4 (&om)[D / 16], float m, flo
     }
 }
 
+// Whether a wave's outputs of live columns are all numbers, in every lane
+template <int D, int G>
+__device__ __forceinline__ bool finite_one(const f32x4 (&om)[D / 16], int lane) {
+  float z = 0.f;                                         // (no number times zero is none, and neither is infinity)
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z = 4 * (lane >> 4) + j < G ? fmaf(om[db][j], 0.f, z) : z;
+  return __builtin_amdgcn_ballot_w64(z != 0.f) == 0;
+}
+
+// One token's outputs of a wave once more, a product at a time: on the matrix cores an infinite value has no number for its
+// output wherever a term of its weight is zero (the largest weight's second, for one), where weight times value is infinite.
+// From the logits that the wave has left behind, its final maxima and the rows, all of it plain: a lane has D / 64 elements of
+// every head, the wave its rows one after the other.  Only for waves of which some output is no finite number.
+template <int D, int G, int KT, Mode M, int LOG>
+__device__ __forceinline__ void outputs_plain(const AttnArgs& a, const WaveLds& w, int b, int kvh, int lane, int tile0, int tstride,
+                                              int n_list, const int* loc_list, int xcol0, float m, float* o) {
+  constexpr bool IS_Q = (M == Q_INT8 || M == Q_INT4);
+  constexpr int TR = 4096 / D, EPL = D / 64;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // the logits, which other lanes have stored
+  lds_wait();
+  const size_t pair = (size_t)b * a.Hkv + kvh;
+  const int el = lane * EPL;
+  float acc[G][EPL], ms[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float mh = rdlane(m, h);
+    ms[h] = mh > -INFINITY ? mh : 0.f;
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) acc[h][k] = 0.f;
+  }
+  for (int tile = tile0; tile * TR < n_list; tile += tstride) {
+    const bool in_lds = LOG == LOG_STEP && xcol0 + tile * TR + TR <= w.lim;
+    for (int i = tile * TR; i < tile * TR + TR && i < n_list; ++i) {
+      const int slot = loc_list[i], col = xcol0 + i;
+      float v[EPL], sc = 1.f;
+#pragma unroll
+      for (int k = 0; k < EPL; ++k) v[k] = 0.f;          // (no row: zeros, as fetched by the tile)
+      if ((uint32_t)slot < (uint32_t)(IS_Q ? a.cap2 : a.capF)) {
+        if constexpr (!IS_Q) {
+          const uint16_t* row = (const uint16_t*)(a.fpV + (pair * a.capF + slot) * (2 * D)) + el;
+#pragma unroll
+          for (int k = 0; k < EPL; ++k) v[k] = KT == KT_BF16 ? bf_lo(row[k]) : half_of(row[k], 0);
+        } else {
+          const size_t r = pair * a.cap2 + slot;
+          const uint8_t* codes = (const uint8_t*)a.c2V + r * a.cb;
+#pragma unroll
+          for (int k = 0; k < EPL; ++k) v[k] = M == Q_INT8 ? sbyte_f(codes[el + k], 0) : snib_f(codes[(el + k) / 2], (el + k) & 1);
+          sc = M == Q_INT8 ? *(const float*)(a.s2V + r * a.sb) : half_of(((const uint16_t*)(a.s2V + r * a.sb))[el / 32], 0);
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float x;
+        if (in_lds) {
+          uint32_t t = lds_rd32<0>(w.lga + (uint32_t)(h * w.lcap + col) * 4u);
+          lds_wait(); tie(t);
+          x = __builtin_bit_cast(float, t);
+        } else x = w.sp[(size_t)h * w.sp_stride + col];
+        float p = exp_le0(fmaf(x, a.softmax_scale, -ms[h]));
+        if constexpr (IS_Q) p *= sc;
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) acc[h][k] = fmaf(p, v[k], acc[h][k]);
+      }
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < G; ++h)
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) o[h * D + el + k] = acc[h][k];
+}
+
 // Geometry of the split launch: rows per tile and waves per workgroup (one workgroup per compute unit).  16-bit rows: 8 KB
 // tiles (32 rows of 256 bytes, 64 of 128) and eight waves, two per SIMD; 64 KB in flight per compute unit stream as fast
 // as 128 KB do, and the finer tiles keep more waves busy on short lists and end closer together on long ones.  binary32
@@ -1775,6 +1848,11 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
     else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
     else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
     park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
+    if (!finite_one<D, G>(om[0], lane)) {
+      if (u < nwf) outputs_plain<D, G, KT, KG::MF, LOG_CALL>(a, w, bl, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, mr[0], my_o);
+      else if (a.t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_CALL>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
+      else outputs_plain<D, G, KT, Q_INT4, LOG_CALL>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
+    }
   } else {
     float o[G][EV], m_run[G], l_lane[G];
 #pragma unroll
@@ -1934,6 +2012,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
   else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
   park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
+  if (!finite_one<D, G>(om[0], lane)) {
+    if (u < nwf) outputs_plain<D, G, KT, MF, LOG_STEP>(a, w, bl, kvh, lane, u, nwf, nF, f_loc, 0, mr[0], my_o);
+    else if (a.t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
+    else outputs_plain<D, G, KT, Q_INT4, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
+  }
   // ---- merge the waves
   __syncthreads();
   if (split) {

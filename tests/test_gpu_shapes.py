@@ -605,6 +605,77 @@ def test_logits_that_are_no_numbers_reach_the_output(kind, shape):
     assert np.isnan(scores[0, 17]) and np.isnan(scores[-1, 130])
 
 
+@pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES)
+def test_infinite_values_reach_the_output(kind, shape):
+    """A value row with infinite elements at full precision: those elements of the outputs are infinite, whatever the row's
+    weight (the largest one's, exactly 1 before it is normalised, or any other), the others what they are in 64 bits."""
+    from gpu_common import assert_out_close, to_f64
+    from tkv_synth import Workload
+    cfg = small_config(name="infinite", **{**dict(kv_dtype="bf16", decode_steps=2, k_window=16, sigma=1.0), **shape})
+    cfg = dataclasses.replace(cfg, recipe="bias")       # (no weight underflows)
+    print(f"[case] {kind} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    k, v = (list(x) for x in zip(*(wl.context_kv(l) for l in range(cfg.n_layers))))
+    k_all, v_all, q_all = wl.decode_inputs(0, 1)
+    q, G = q_all[0], cfg.n_q_heads // cfg.n_kv_heads
+    for l, b, kvh in ((0, 0, 0), (cfg.n_layers - 1, cfg.batch - 1, cfg.n_kv_heads - 1)):
+        v[l] = v[l].clone()
+        x = to_f64(k[l][b, :, kvh]) @ to_f64(q[l, b, kvh * G:(kvh + 1) * G]).T
+        for i, row in enumerate([*np.unique(x.argmax(0)), 7, 64, 101, cfg.context - 1]):
+            v[l][b, row, kvh, 3 * i] = float("inf") if i % 2 else float("-inf")
+    out, _ = _one_token_outputs(kind, cfg, k, v, k_all[0], v_all[0], q)
+    for l, b, kvh in ((0, 0, 0), (cfg.n_layers - 1, cfg.batch - 1, cfg.n_kv_heads - 1)):
+        kk, vv = (np.concatenate([to_f64(c[l][b, :, kvh]), to_f64(n[0, l, b, :, kvh])]) for c, n in ((k, k_all), (v, v_all)))
+        x = to_f64(q[l, b, kvh * G:(kvh + 1) * G]) @ kk.T / np.sqrt(cfg.head_dim)
+        w = np.exp(x - x.max(1, keepdims=True))
+        w /= w.sum(1, keepdims=True)
+        ref, inf = w @ np.where(np.isinf(vv), 0, vv), np.where(np.isinf(vv), vv, 0).sum(0)
+        got = to_f64(out[l, b, kvh * G:(kvh + 1) * G])
+        assert (got[:, inf != 0] == inf[inf != 0]).all(), got[:, inf != 0]
+        assert_out_close(got[:, inf == 0], ref[:, inf == 0], cfg.kv_dtype)
+
+
+@pytest.mark.parametrize("kind,t2,shape", [
+    ("call", "int8_row", dict(n_layers=1, batch=256, n_q_heads=7, n_kv_heads=1, head_dim=128, context=300)),
+    ("call", "int4_g32", dict(n_layers=1, batch=256, n_q_heads=5, n_kv_heads=1, head_dim=128, context=300, kv_dtype="f16")),
+    ("call", "int4_g32", dict(n_layers=1, batch=256, n_q_heads=8, n_kv_heads=1, head_dim=64, context=300)),
+    ("step", "int8_row", dict(n_layers=25, batch=2, n_q_heads=14, n_kv_heads=2, head_dim=128, context=1500, kv_dtype="f16")),
+    ("call", "int8_row", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700, kv_dtype="f16")),
+    ("call", "int4_g32", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700)),
+    ("call", "int4_g32", dict(n_layers=2, batch=2, n_q_heads=6, n_kv_heads=2, head_dim=128, context=700)),       # vector instructions
+])
+def test_infinite_values_in_t2(kind, t2, shape):
+    """A value row that is compressed with an element of -inf: its scale (int4: its group's) is infinite, the element's code the
+    lowest, all others zero.  Code times scale is -inf there and no number in the rest of the row (group); elements of other
+    groups have the bits that a finite row of the same codes gives them."""
+    from tkv_synth import Workload
+    cfg = small_config(name="infinite", **{**dict(kv_dtype="bf16", decode_steps=2, k_window=16, sigma=1.0, t2_format=t2), **shape})
+    cfg = dataclasses.replace(cfg, recipe="bias")
+    print(f"[case] {kind} {t2} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    k, v = (list(x) for x in zip(*(wl.context_kv(l) for l in range(cfg.n_layers))))
+    k_all, v_all, q_all = wl.decode_inputs(0, 1)
+    G = cfg.n_q_heads // cfg.n_kv_heads
+    v[0] = v[0].clone()
+    v[0][0, 33, 0, 40] = float("-inf")
+    tiers = np.random.default_rng(3).choice((0, 2), size=(cfg.batch, cfg.context)).astype(np.uint8)
+    tiers[:, :4] = 0
+    tiers[:, -16:] = 0
+    tiers[:, 33] = 2
+    out, _ = _one_token_outputs(kind, cfg, k, v, k_all[0], v_all[0], q_all[0], tiers)
+    got = out[0, 0, :G]
+    lo, hi = (32, 64) if t2 == "int4_g32" else (0, cfg.head_dim)
+    assert (got[:, 40] == float("-inf")).all(), got[:, 40]
+    rest = torch.ones(cfg.head_dim, dtype=torch.bool, device="cuda")
+    rest[lo:hi] = False
+    assert got[:, rest].isfinite().all()
+    rest = ~rest
+    rest[40] = False
+    assert got[:, rest].isnan().all()
+    out[0, 0, :G] = 0
+    assert out.isfinite().all()
+
+
 @pytest.mark.parametrize("t2", ["int8_row", "int4_g32"])
 @pytest.mark.parametrize("kind,shape", [
     ("call", dict(n_layers=1, batch=256, n_q_heads=5, n_kv_heads=1, head_dim=128, context=400)),
