@@ -80,7 +80,7 @@ struct tkv_cache {
   bool call_whole = false;         // single calls too take one workgroup per pair (sc, then the spill, in xs)
   int sc_stride = 0, spill_stride = 0;
   int tail_pairs = 0, tail_parts = 1;   // of a whole-pair step the last tail_pairs (layer, sequence, kv head) pairs go in tail_parts parts each
-  float* xt_tail = nullptr; float* ml_tail = nullptr; float* po_tail = nullptr;
+  float* xt_tail = nullptr; float* ml_tail = nullptr; float* po_tail = nullptr;   // (none: a layer's in the scratch of the single calls)
   int S_alloc = 0, xs_stride = 0;
   int cus = 0;                     // compute units of the device
   char* static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (tkv_attend_and_score_noalloc)
@@ -485,9 +485,16 @@ void step_tail(tkv_cache* c) {
 }
 // The scratch of a launch that serves several layers, taken when the cache is created: a call that runs must not take device
 // memory, an allocator may hand out a block that work on another stream still uses, and a step may be captured into a
-// graph.  With less memory than that the launches serve fewer layers, down to one in the scratch of the single calls.
+// graph.  With less memory than that the launches serve fewer layers, down to one in the scratch of the single calls, which
+// has room for a layer's pairs in parts too: which pairs go in parts is settled, and a launch cannot do without their logits.
 void step_scratch(tkv_cache* c) {
   const DevView& v = c->dv;
+  if (c->tail_pairs > 0) {
+    c->xt_tail = (float*)dev_alloc(c, tail_floats(c, c->tail_pairs, c->tail_parts) * sizeof(float));
+    if (!c->xt_tail) { c->step_layers = 1; return; }
+    c->ml_tail = c->xt_tail + (size_t)c->tail_pairs * c->G * c->sc_stride;
+    c->po_tail = c->ml_tail + (size_t)c->tail_pairs * c->tail_parts * 2 * c->G;
+  }
   for (; c->step_layers > 1; c->step_layers /= 2) {
     const size_t nl = c->step_layers, pairs = (size_t)v.B * v.Hkv;
     float* p = (float*)dev_alloc(c, nl * step_floats_per_layer(c) * sizeof(float));
@@ -627,16 +634,12 @@ tkv_status tkv_create(const tkv_config* cfg, tkv_cache** out) {
   }
   step_route(c);
   step_tail(c);
-  if (c->tail_pairs > 0) {
-    ok = ok && dalloc(c, c->xt_tail, tail_floats(c, c->tail_pairs, c->tail_parts));
-    c->ml_tail = c->xt_tail + (size_t)c->tail_pairs * G * c->sc_stride;
-    c->po_tail = c->ml_tail + (size_t)c->tail_pairs * c->tail_parts * 2 * G;
-  }
   // (a whole-pair launch of one layer may need a little more than a split one: lists beyond some 20000 tokens)
   ok = ok && dalloc(c, c->xs, std::max((size_t)B * v.Hq * c->xs_stride, c->step_whole ? step_floats_per_layer(c) : 0));
-  const int launches = c->streamed ? 2 : 1;   // streamed T1: a second attention launch serves the frame
-  ok = ok && dalloc(c, c->part_ml, (size_t)B * Hkv * c->S_alloc * launches * 2 * G);
-  ok = ok && dalloc(c, c->part_o, (size_t)B * Hkv * c->S_alloc * launches * G * D);
+  // (streamed T1: a second attention launch serves the frame; parts of a step's pairs may be more than a single call's splits)
+  const size_t partials = (size_t)B * Hkv * std::max(c->S_alloc * (c->streamed ? 2 : 1), c->tail_parts);
+  ok = ok && dalloc(c, c->part_ml, partials * 2 * G);
+  ok = ok && dalloc(c, c->part_o, partials * G * D);
   c->tok_bytes = (size_t)Hkv * 2 * D * c->es;
   c->bounce_bytes = cfg->bounce_bytes ? (size_t)cfg->bounce_bytes : ((size_t)64 << 20);
   if (c->bounce_bytes < RING * c->tok_bytes) c->bounce_bytes = RING * c->tok_bytes;
@@ -868,7 +871,14 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (step_launch && c->tail_pairs > 0) {
     a.tail0 = layer * v.B * v.Hkv - (v.L * v.B * v.Hkv - c->tail_pairs);
     a.whole_rows = std::min(a.whole_rows, std::max(0, -a.tail0 / v.Hkv));
-    a.xt = c->xt_tail; a.part_ml = c->ml_tail; a.part_o = c->po_tail;
+    if (c->xt_tail) { a.xt = c->xt_tail; a.part_ml = c->ml_tail; a.part_o = c->po_tail; }
+    else {
+      // one layer: its whole pairs' row weights and spilled logits, then the logits of those in parts (a pair of either kind
+      // takes no more than it has in xs: sc_stride <= xs_stride)
+      a.tail0 = -a.whole_rows * v.Hkv;
+      a.xs = a.sc + (size_t)a.whole_rows * v.Hkv * c->sc_stride;
+      a.xt = a.xs + (size_t)a.whole_rows * v.Hq * c->spill_stride;
+    }
   }
   if (m > 1) { a.xs = c->xs_chunk; a.part_ml = c->ml_chunk; a.part_o = c->po_chunk; }
   if (noalloc) {

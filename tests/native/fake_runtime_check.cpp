@@ -35,7 +35,8 @@ static hipError_t g_last = hipSuccess;
 static std::vector<Launch> g_launches;
 static std::string g_log;                           // A: device allocation, S: device synchronised, M: memset, L: launch
 static int g_allocs = 0, g_fail_at = -1, g_fail_from = 1 << 30, g_cus = 256;
-static size_t g_fail_above = SIZE_MAX;
+static int g_last_host_alloc = 0;                   // the number of the last pinned one
+static size_t g_fail_above = SIZE_MAX, g_fail_size = SIZE_MAX;
 static hipStream_t g_capturing = nullptr;
 static std::set<hipEvent_t> g_recorded;
 static dim3 g_cfg_grid, g_cfg_block;
@@ -50,7 +51,7 @@ static bool inside(const void* p, size_t n) {
   --it;
   return (uintptr_t)p + n <= it->first + it->second;
 }
-static bool refused(size_t n) { const int k = g_allocs++; return k == g_fail_at || k >= g_fail_from || n > g_fail_above; }
+static bool refused(size_t n) { const int k = g_allocs++; return k == g_fail_at || k >= g_fail_from || n > g_fail_above || n == g_fail_size; }
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
@@ -61,6 +62,7 @@ hipError_t hipMalloc(void** p, size_t n) {
 }
 hipError_t hipFree(void* p) { CHECK(g_mem.erase((uintptr_t)p) == 1); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  g_last_host_alloc = g_allocs;
   if (refused(n)) return err(hipErrorOutOfMemory);
   *p = std::calloc(n, 1);
   return hipSuccess;
@@ -117,13 +119,22 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t l
     CHECK(grid.x >= 1 && grid.y >= 1 && grid.y <= 65535 && grid.z >= 1 && grid.z <= 65535);
     const size_t seqs = (size_t)a.nl * a.B * a.n_q * a.cq, G = a.Hq / a.Hkv;
     const size_t D = l.kernel.find("ILi128E") != std::string::npos ? 128 : 64;
-    CHECK(a.xs_stride == 0 || inside(a.xs, seqs * a.Hq * a.xs_stride * 4));
+    CHECK(a.xs_stride == 0 || a.sc || inside(a.xs, seqs * a.Hq * a.xs_stride * 4));
     // a chunk whose logits are not written keeps its packed query vectors there
     if (a.groups && a.xs_stride == 0) CHECK(inside(a.xs, (size_t)a.B * a.Hkv * ((a.cq * G + 15) / 16) * (D / 32) * 64 * 16));
     if (a.sc) {
-      const size_t sc = seqs * a.Hkv * a.sc_stride * 4;
-      CHECK(inside(a.sc, sc));
-      CHECK(a.xs_stride == 0 || (char*)a.xs >= (char*)a.sc + sc || (char*)a.xs + seqs * a.Hq * a.xs_stride * 4 <= (char*)a.sc);
+      // whole pairs: a row's weights, and the logits beyond the LDS; pairs in parts: their logits and the parts' partials
+      const size_t rows = a.whole_rows, split = seqs - rows, first = (size_t)(a.whole_rows * a.Hkv + a.tail0);
+      const size_t sc = rows * a.Hkv * a.sc_stride * 4, xs = rows * a.Hq * a.xs_stride * 4, xt = split * a.Hq * a.sc_stride * 4;
+      const char *sc0 = (char*)a.sc, *xs0 = (char*)a.xs, *xt0 = (char*)(a.xt + first * G * a.sc_stride);
+      CHECK(a.whole_rows >= 0 && rows <= seqs && inside(sc0, sc) && inside(xs0, xs));
+      CHECK(xs == 0 || xs0 >= sc0 + sc || xs0 + xs <= sc0);
+      if (split > 0) {
+        CHECK(a.whole_rows * a.Hkv + a.tail0 >= 0 && a.S >= 2 && a.S <= 8 && inside(xt0, xt));
+        CHECK(inside(a.part_ml + first * a.S * 2 * G, split * a.Hkv * a.S * 2 * G * 4) && inside(a.part_o + first * a.S * G * D, split * a.Hkv * a.S * G * D * 4));
+        CHECK((xt0 >= sc0 + sc || xt0 + xt <= sc0) && (xs == 0 || xt0 >= xs0 + xs || xt0 + xt <= xs0));
+        if (is("k_attn_step")) CHECK(grid.y == rows + split * a.S);
+      }
     } else {
       CHECK(inside(a.part_ml, seqs * a.Hkv * a.S_total * 2 * G * 4) && inside(a.part_o, seqs * a.Hkv * a.S_total * G * D * 4));
     }
@@ -270,6 +281,44 @@ static void route_follows_from_the_shape() {
   }
 }
 
+// Pairs in parts: which, and in how many, follows from the shape as well, whatever groups the layers go in.  A cache is created
+// with the memory it needs without parts but for their partials: with no more than that its steps go layer by layer.
+static const int PARTS[][8] = {   // layers, sequences, query heads, kv heads, head_dim, max_tokens; parts, pairs that go in parts
+    {4, 70, 5, 1, 128, 2048, 8, 24}, {4, 70, 5, 1, 128, 1792, 7, 24}, {20, 7, 8, 2, 64, 3072, 6, 24}, {28, 5, 28, 4, 128, 2500, 5, 48},
+    {9, 4, 8, 8, 64, 2048, 4, 32}, {28, 3, 28, 4, 128, 2904, 3, 80}, {28, 1, 28, 4, 128, 1500, 2, 112}, {48, 8, 40, 8, 128, 4200, 1, 0}};
+static void parts_of_pairs() {
+  for (auto& s : PARTS)
+    for (int mode : {TKV_PREFETCH_WAIT, TKV_PREFETCH_LAZY}) {
+      tkv_config cfg = config(s[0], s[1], s[2], s[3], s[4], s[5]);
+      cfg.prefetch_mode = mode;
+      const size_t columns = (s[5] + 127) / 64 * 64, G = s[2] / s[3], scratch = (size_t)s[7] * G * (columns + s[6] * (2 + s[4])) * 4;
+      int nl[3];                                    // layers of the first launch
+      for (int refuse = 0; refuse < 3; ++refuse) {  // nothing, the parts' scratch, everything behind the pinned store
+        tkv_cache* c = nullptr;
+        g_allocs = 0;
+        if (refuse == 1) g_fail_size = scratch;
+        if (refuse == 2) g_fail_from = g_last_host_alloc + 1;
+        CHECK(tkv_create(&cfg, &c) == TKV_OK);
+        CHECK(refuse != 2 || g_allocs > g_fail_from);
+        g_fail_from = 1 << 30; g_fail_size = SIZE_MAX;
+        fill(c, cfg, 60);
+        const auto launches = step(c, cfg);
+        int pairs = 0;
+        for (auto& l : launches) {
+          const int split = (l.a.nl * s[1] - l.a.whole_rows) * s[3];
+          CHECK(l.kernel.find("k_attn_step") != std::string::npos);
+          CHECK(split == 0 || l.a.S == s[6]);
+          CHECK(pairs == 0 || split == l.a.nl * s[1] * s[3]);     // the last ones of the step
+          pairs += split;
+        }
+        CHECK(pairs == s[7]);
+        nl[refuse] = launches[0].a.nl;
+        tkv_destroy(c);
+      }
+      CHECK(nl[0] > 1 && nl[1] == (s[7] ? 1 : nl[0]) && nl[2] == 1);
+    }
+}
+
 // Whole pairs where they fill the chip, their lists are short or a layer has few; with other compute unit counts too.
 static void long_lists_fill_the_chip() {
   const struct { int L, Hq, Hkv, n, cus; bool whole; } cases[] = {
@@ -363,6 +412,7 @@ int main(int argc, char** argv) {
   if (what == "refused_allocations") refused_allocations();
   else if (what == "allocations_before_use") allocations_before_use();
   else if (what == "route_follows_from_the_shape") route_follows_from_the_shape();
+  else if (what == "parts_of_pairs") parts_of_pairs();
   else if (what == "long_lists_fill_the_chip") long_lists_fill_the_chip();
   else if (what == "chunk_splits") chunk_splits();
   else if (what == "chunk_tokens_per_launch") chunk_tokens_per_launch();

@@ -226,12 +226,14 @@ def test_decode_step_whose_last_pairs_go_in_parts(mode, scorer, shape):
     dict(n_layers=3, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=150, kv_dtype="f16"),       # list lengths from device counters
     dict(n_layers=4, batch=64, n_q_heads=24, n_kv_heads=4, head_dim=128, context=90, t2_format="int4_g32"),   # WAIT: layers one by one
     dict(n_layers=5, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700),                      # split pairs
+    dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=2040),                     # 24 of the last layer's 70 pairs in eight parts
+    dict(n_layers=11, batch=3, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2900),                     # 8 of its 24 in six, logits beyond the LDS
 ])
 def test_prop1_of_whole_steps(shape, monkeypatch):
     """T1 placement, prefetch mode and the memory there is for a step's scratch change no bit of a decode step: the same rows
     in T1 with attention reading old slots while the copies are in flight (LAZY), behind them (WAIT: small groups of
     layers), with the rows in T0 all along, and with every allocation refused that the cache can do without (one layer per
-    launch).  Steps straddle two plans."""
+    launch, parts of pairs among them).  Steps straddle two plans."""
     import paper_2605_09490_amd as tkv
     from tkv_synth import Workload
     cfg = small_config(name="prop1", **{**dict(kv_dtype="bf16", decode_steps=6, k_window=16, sigma=1.0), **shape})
