@@ -791,11 +791,11 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
       wave_max_all<G>(xm);
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        // m_run starts at -inf and every tile has a live entry, so the first tile needs no special case:
-        // corr = exp2(-inf) = 0 there, against zero accumulators
-        const float mn = fmaxf(m_run[h], rdlane(xm[h], 63));
-        corr[h] = __builtin_amdgcn_exp2f((m_run[h] - mn) * LOG2E);
-        const float p = valid ? __builtin_amdgcn_exp2f((x[h] - mn) * LOG2E) : 0.f;
+        // m_run starts at -inf: corr = exp2(-inf) = 0 there, against zero accumulators.  Tiles whose logits are all -inf
+        // leave it there: their weights are exp2(-inf) = 0 too.
+        const float mn = fmaxf(m_run[h], rdlane(xm[h], 63)), ms = mn > -INFINITY ? mn : 0.f;
+        corr[h] = __builtin_amdgcn_exp2f((m_run[h] - ms) * LOG2E);
+        const float p = valid ? __builtin_amdgcn_exp2f((x[h] - ms) * LOG2E) : 0.f;
         l_lane[h] = fmaf(l_lane[h], corr[h], p);
         m_run[h] = mn;
         pv[h] = p;

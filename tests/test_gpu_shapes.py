@@ -607,6 +607,35 @@ def test_logits_that_are_no_numbers_reach_the_output(kind, shape):
     assert np.isnan(scores[0, 17]) and np.isnan(scores[-1, 130])
 
 
+@pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES + [
+    ("call", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=64, context=700, kv_dtype="f32")),
+    ("call", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=900, kv_dtype="f32")),
+    ("chunk", ONE_TOKEN_LAUNCHES[4][1]),
+])
+def test_whole_tiles_of_keys_without_weight(kind, shape):
+    """Rows whose logit is -inf, whole tiles of them, a list's first and others: no weight, whatever else a wave walks."""
+    from gpu_common import assert_out_close, to_f64
+    from tkv_synth import Workload
+    cfg = small_config(name="tiles", **{**dict(kv_dtype="bf16", decode_steps=2, k_window=16, sigma=1.0), **shape})
+    cfg = dataclasses.replace(cfg, recipe="bias")
+    print(f"[case] {kind} {shape}", flush=True)
+    wl = Workload(cfg, device="cuda")
+    k, v = (list(x) for x in zip(*(wl.context_kv(l) for l in range(cfg.n_layers))))
+    k_all, v_all, q_all = wl.decode_inputs(0, 1)
+    q, G = q_all[0].clone(), cfg.n_q_heads // cfg.n_kv_heads
+    q[..., 3] = q[..., 3].abs() + 0.5
+    k[0] = k[0].clone()
+    k[0][0, :192, :, 3] = float("-inf")
+    out, scores = _one_token_outputs(kind, cfg, k, v, k_all[0], v_all[0], q)
+    for kvh in range(cfg.n_kv_heads):
+        kk, vv = (np.concatenate([to_f64(c[0][0, 192:, kvh]), to_f64(n[0, 0, 0, :, kvh])] + [to_f64(n[0, 0, 0, :, kvh])] * (kind == "chunk"))
+                  for c, n in ((k, k_all), (v, v_all)))
+        x = to_f64(q[0, 0, kvh * G:(kvh + 1) * G]) @ kk.T / np.sqrt(cfg.head_dim)
+        w = np.exp(x - x.max(1, keepdims=True))
+        assert_out_close(to_f64(out[0, 0, kvh * G:(kvh + 1) * G]), (w / w.sum(1, keepdims=True)) @ vv, cfg.kv_dtype)
+    assert out.isfinite().all() and np.isfinite(scores).all()
+
+
 @pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES)
 def test_infinite_values_reach_the_output(kind, shape):
     """A value row with infinite elements at full precision: those elements of the outputs are infinite, whatever the row's
