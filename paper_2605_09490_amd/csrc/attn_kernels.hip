@@ -1062,16 +1062,16 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
   u32x4 qreg[NCB][NKS];
   const bool q_aligned = ((uintptr_t)a.q & 15) == 0;
   {
-    const int ncol = a.cq * a.G;
+    const int ncol = ONE ? a.G : a.cq * a.G;
     const char* qb = (const char*)a.q + (size_t)b * a.q_bs * RB;
-    const float inv_g = 1.0f / (float)a.G;
+    const float inv_g = ONE ? 0.f : 1.0f / (float)a.G;
     auto q_row = [&](int col) {                  // byte offset of a column's query vector
       col = col < ncol ? col : ncol - 1;
-      const int jq = small_div(col, inv_g);
+      const int jq = ONE ? 0 : small_div(col, inv_g);
       return (uint32_t)(jq * a.Hq + kvh * a.G + (col - jq * a.G)) * (uint32_t)RB;
     };
     if (q_aligned) {
-      const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)(a.cq * a.Hq) * RB);
+      const __amdgpu_buffer_rsrc_t rq = make_rsrc(qb, (uint32_t)((ONE ? 1 : a.cq) * a.Hq) * RB);
 #pragma unroll
       for (int i = 0; i < 2 * NCB; ++i) {
         const uint32_t off = q_row(c0 + 8 * i + g) + ((i & 1) ? kcol1 : kcol0);
@@ -1089,9 +1089,9 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
       const int col = c0 + 16 * cb + n;
-      const int jq = small_div(col, inv_g);
+      const int jq = ONE ? 0 : small_div(col, inv_g);
       live[cb] = col < ncol;
-      n_seen[cb] = IS_Q || !live[cb] ? n_list : n_list - (a.cq - 1 - jq);
+      n_seen[cb] = ONE || IS_Q || !live[cb] ? n_list : n_list - (a.cq - 1 - jq);
       if constexpr (LOG == LOG_XS) xrow[cb] = live[cb] ? xs_at(a, b * a.cq + jq, kvh * a.G + (col - jq * a.G), xcol0 + 4 * kb) : 0;
     }
   }
@@ -1326,7 +1326,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     float p[NCB][NRB][4];
     {
       const int e0 = tile * TR + 4 * kb;
-      const bool edge = (tile + 1) * TR > n_list - (IS_Q ? 0 : a.cq - 1);   // wave-uniform: some column does not see the whole tile
+      const bool edge = (tile + 1) * TR > n_list - (ONE || IS_Q ? 0 : a.cq - 1);   // wave-uniform: some column does not see the whole tile
       // A chunk's binary16 code rows: a weight times its V row's scale has to stay in binary16's range.  Where the tile has a
       // scale beyond what the shift leaves room for (V of some 26 and more in an int4 group, 480 in an int8 row), such an entry
       // counts with the logit of its scaled weight in the running reference, which is then above the largest logit: any
@@ -1668,15 +1668,15 @@ __device__ __forceinline__ void park_one(const f32x4 (&om)[D / 16], float m, flo
     }
 }
 
-// Whether a wave's outputs of live columns are all numbers, in every lane
-template <int D, int G>
-__device__ __forceinline__ bool finite_one(const f32x4 (&om)[D / 16], int lane) {
-  float z = 0.f;                                         // (no number times zero is none, and neither is infinity)
+// Whether a wave's outputs are all finite, in every lane (the padding columns' are those of the last head)
+template <int D>
+__device__ __forceinline__ bool finite_one(const f32x4 (&om)[D / 16]) {
+  float z[4] = {0.f, 0.f, 0.f, 0.f};                     // (infinity times zero is no number, as no number is)
 #pragma unroll
   for (int db = 0; db < D / 16; ++db)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) z = 4 * (lane >> 4) + j < G ? fmaf(om[db][j], 0.f, z) : z;
-  return __builtin_amdgcn_ballot_w64(z != 0.f) == 0;
+    for (int j = 0; j < 4; ++j) z[j] = fmaf(om[db][j], 0.f, z[j]);
+  return __builtin_amdgcn_ballot_w64((z[0] + z[1]) + (z[2] + z[3]) != 0.f) == 0;
 }
 
 // One token's outputs of a wave once more, a product at a time: on the matrix cores an infinite value has no number for its
@@ -1848,7 +1848,7 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
     else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
     else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_CALL>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
     park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
-    if (!finite_one<D, G>(om[0], lane)) {
+    if (!finite_one<D>(om[0])) {
       if (u < nwf) outputs_plain<D, G, KT, KG::MF, LOG_CALL>(a, w, bl, kvh, lane, u, nwf, nF, f_loc + (size_t)b * a.Nmax, xsb * TB, mr[0], my_o);
       else if (a.t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_CALL>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
       else outputs_plain<D, G, KT, Q_INT4, LOG_CALL>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
@@ -1982,14 +1982,31 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   __shared__ float2 sm_fin[8];
   const int kvh = blockIdx.x;
   int bl = blockIdx.y, part = 0;
-  const bool split = bl >= a.whole_rows;
-  if (split) { const int x = bl - a.whole_rows; bl = a.whole_rows + x / a.S; part = x - (bl - a.whole_rows) * a.S; }
-  const int li = bl / a.B, b = bl - li * a.B, pair = bl * a.Hkv + kvh;
+  // What stands between a workgroup and its first request, all of the arguments asked for at once: they come over the host link,
+  // and as the compiler places them, behind the conditions below, one waits for another (64 x 700 tokens, 8/8 heads at head_dim
+  // 64, two rounds of pairs: 25.2 us a call so, 23.5 now; 64 x 300, 4/4 at 128, one round: 14.8, 14.1).  A single call's sequence
+  // is blockIdx.y; its list lengths are asked for with the rest and corrected in other launches.
+  int nl = a.nl, whole_rows = a.whole_rows, S = a.S, B = a.B, Hkv = a.Hkv, Nmax = a.Nmax, t2fmt = a.t2fmt, xs_stride = a.xs_stride;
+  int nF = a.nF[bl & (ATTN_ARG_SEQS - 1)], nQ = a.nQ[bl & (ATTN_ARG_SEQS - 1)], nwq = a.nWq[bl & (ATTN_ARG_SEQS - 1)];
+  const int *f_new = a.f_loc, *f_old = a.f_loc_old, *q_list = a.q_loc;
+  uint64_t old_mask = a.old_mask;
+  float* spill = a.xs;
+  asm volatile("" : : "s"(nl), "s"(whole_rows), "s"(S), "s"(B), "s"(Hkv), "s"(Nmax), "s"(t2fmt), "s"(xs_stride), "s"(nF), "s"(nQ),
+                    "s"(nwq), "s"(f_new), "s"(f_old), "s"(q_list), "s"(old_mask), "s"(spill));
+  const bool split = bl >= whole_rows;
+  if (split) { const int x = bl - whole_rows; bl = whole_rows + x / S; part = x - (bl - whole_rows) * S; }
+  const int li = nl > 1 ? bl / B : 0, b = bl - li * B, pair = bl * Hkv + kvh;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int* f_loc = (((a.old_mask >> li) & 1) ? a.f_loc_old : a.f_loc) + (size_t)b * a.Nmax;
-  int nF, nQ;
-  if (a.B <= ATTN_ARG_SEQS) { nF = a.nF[b]; nQ = a.nQ[b]; }
-  else { nF = a.cnt[b * CNT_N + C_NF]; nQ = a.cnt[b * CNT_N + C_NQ]; }
+  const int* f_loc = (((old_mask >> li) & 1) ? f_old : f_new) + (size_t)b * Nmax;
+  const int nwv = split ? NW * S : NW, u = part * NW + wave;         // the pair's waves, and which of them this is
+  if (B > ATTN_ARG_SEQS) {
+    nF = a.cnt[b * CNT_N + C_NF]; nQ = a.cnt[b * CNT_N + C_NQ];
+    const int nft = (nF + TR - 1) / TR, nqt = (nQ + TR - 1) / TR;
+    nwq = split ? q_waves(nwv, nft, nqt) : q_waves(NW, nft, nqt);   // (a constant number of waves: no division, of 16)
+  } else {
+    if (nl > 1 || split) { nF = a.nF[b]; nQ = a.nQ[b]; nwq = a.nWq[b]; }
+    nwq = split ? nwq >> 16 : nwq & 0xffff;
+  }
   const int nft = (nF + TR - 1) / TR, colq = nft * TR;
 
   WaveLds w;
@@ -1998,30 +2015,30 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   w.ta = lds_addr(w.t); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
   w.lga = lds_addr(sm_lg); w.lcap = LCAP;
   w.lim = split ? 0 : LCAP;
-  w.sp = split ? a.xt + (size_t)(pair + a.tail0) * G * a.sc_stride : a.xs + (size_t)pair * G * a.xs_stride - LCAP;
-  w.sp_stride = split ? a.sc_stride : a.xs_stride;
+  w.sp = split ? a.xt + (size_t)(pair + a.tail0) * G * a.sc_stride : spill + (size_t)pair * G * xs_stride - LCAP;
+  w.sp_stride = split ? a.sc_stride : xs_stride;
   float* my_o = (float*)w.t;
 
-  const int nwv = split ? NW * a.S : NW, u = part * NW + wave;       // the pair's waves, and which of them this is
-  const int nwq = a.B > ATTN_ARG_SEQS ? q_waves(nwv, nft, (nQ + TR - 1) / TR) : split ? a.nWs[b] : a.nWq[b], nwf = nwv - nwq;
+  const int nwf = nwv - nwq;
+  const int* q_loc = q_list + (size_t)b * Nmax;
   f32x4 om[1][D / 16];
   float mr[1] = {-INFINITY}, lr[1] = {0.f};
 #pragma unroll
   for (int db = 0; db < D / 16; ++db) om[0][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (u < nwf) attn_wave_mfma<D, KT, MF, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u, nwf, nF, nF, f_loc, 0, om, mr, lr);
-  else if (a.t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
-  else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, a.q_loc + (size_t)b * a.Nmax, colq, om, mr, lr);
+  else if (t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, q_loc, colq, om, mr, lr);
+  else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, q_loc, colq, om, mr, lr);
   park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
-  if (!finite_one<D, G>(om[0], lane)) {
+  if (!finite_one<D>(om[0])) {
     if (u < nwf) outputs_plain<D, G, KT, MF, LOG_STEP>(a, w, bl, kvh, lane, u, nwf, nF, f_loc, 0, mr[0], my_o);
-    else if (a.t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
-    else outputs_plain<D, G, KT, Q_INT4, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, mr[0], my_o);
+    else if (t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, mr[0], my_o);
+    else outputs_plain<D, G, KT, Q_INT4, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, mr[0], my_o);
   }
   // ---- merge the waves
   __syncthreads();
   if (split) {
     // a part of a pair: its partial; k_step_scores_parts has the rest of the way
-    const size_t sp = (size_t)(pair + a.tail0) * a.S + part;
+    const size_t sp = (size_t)(pair + a.tail0) * S + part;
     for (int i = t; i < G * D; i += NW * 64) {
       const int h = i / D;
       float mb = sm_ml[h], acc = 0.f;

@@ -897,8 +897,8 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (v.B <= ATTN_ARG_SEQS)
     for (int b = 0; b < v.B; ++b) {
       a.nF[b] = c->nF[b] - trim; a.nQ[b] = c->nQ[b];
-      if (step_launch && c->tail_pairs > 0) a.nWs[b] = (uint8_t)attn_q_waves(8 * c->tail_parts, wave_tiles(c->nF[b]), wave_tiles(c->nQ[b]));
       a.nWq[b] = attn_q_waves(whole ? 8 : S * nw, wave_tiles(c->nF[b] - trim), wave_tiles(c->nQ[b]));
+      if (step_launch && c->tail_pairs > 0) a.nWq[b] |= attn_q_waves(8 * c->tail_parts, wave_tiles(c->nF[b]), wave_tiles(c->nQ[b])) << 16;
     }
   a.B = v.B; a.Hq = v.Hq; a.Hkv = v.Hkv; a.Nmax = v.Nmax; a.capF = v.capP; a.cap2 = v.cap2;
   a.S = step_launch && c->tail_pairs > 0 ? c->tail_parts : S; a.S_total = S + S2; a.s0 = 0; a.second = 0; a.s_pos = c->streamed ? v.s_pos : nullptr; a.n_tiles = n_tiles; if (!whole) a.xs_stride = c->xs_stride; a.cb = v.cb; a.sb = v.sb; a.t2fmt = v.t2fmt; a.out_kind = c->cfg.out_dtype;

@@ -130,8 +130,8 @@ struct AttnArgs {
   int B, Hq, Hkv, Nmax, capF, cap2, xs_stride, cb, sb, t2fmt, out_kind, q_es;   // out_kind: 0 binary32, 1 bfloat16, 2 binary16
   float softmax_scale, score_scale;
   int nF[ATTN_ARG_SEQS], nQ[ATTN_ARG_SEQS];   // list lengths per sequence (host mirror), used when B <= ATTN_ARG_SEQS
-  int nWq[ATTN_ARG_SEQS];                     // waves of each (sequence, kv head) pair that serve the Q list (same condition)
-  uint8_t nWs[ATTN_ARG_SEQS];                 // the same for a pair walked in S parts
+  int nWq[ATTN_ARG_SEQS];                     // waves of each (sequence, kv head) pair that serve the Q list (same condition); whole-pair
+                                              // step launch: in the upper half the same for a pair walked in S parts
   // (streamed T1: the second launch and the finishing kernel take the T1 list's length and the first launch's tile
   // counts from the device counters; the argument block stays small, it is read over the host link in some set-ups)
 };
