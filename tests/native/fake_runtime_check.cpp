@@ -407,7 +407,32 @@ static void kernel_times() {
   tkv_destroy(c);
 }
 
+// What a decode step of a cache of the given shape (layers, sequences, query heads, kv heads, head_dim, max_tokens; 16-bit rows) does:
+// the pairs that go whole, those in parts and in how many, and the entries of a whole pair whose logits the LDS holds; the same
+// of a single call.
+static void print_route(char** v) {
+  int s[6];
+  for (int i = 0; i < 6; ++i) s[i] = std::atoi(v[i]);
+  tkv_config cfg = config(s[0], s[1], s[2], s[3], s[4], s[5]);
+  tkv_cache* c = nullptr;
+  CHECK(tkv_create(&cfg, &c) == TKV_OK);
+  fill(c, cfg, 1);
+  const auto launches = step(c, cfg);
+  int whole = 0, parts = 0, S = 1;
+  for (auto& l : launches)
+    if (l.a.sc) {
+      whole += l.a.whole_rows * s[3];
+      parts += (l.a.nl * s[1] - l.a.whole_rows) * s[3];
+      if (l.a.whole_rows < l.a.nl * s[1]) S = l.a.S;
+    }
+  g_launches.clear();
+  OK(tkv_attend_and_score(c, 0, DATA, DATA, STREAM));
+  std::printf("step %d whole %d in %d parts; call %d whole; lds %d\n", whole, parts, S, g_launches[0].a.sc ? s[1] * s[3] : 0, tkv::attn_step_lds_entries(s[4], s[2] / s[3]));
+  tkv_destroy(c);
+}
+
 int main(int argc, char** argv) {
+  if (argc == 8 && std::string(argv[1]) == "route") { print_route(argv + 2); return 0; }
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused_allocations") refused_allocations();
   else if (what == "allocations_before_use") allocations_before_use();

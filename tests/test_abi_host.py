@@ -137,6 +137,39 @@ def test_host_code_on_a_runtime_that_launches_nothing(scenario):
     assert r.returncode == 0 and f"{scenario}: ok" in r.stdout, r.stdout + r.stderr
 
 
+def test_launches_that_the_gpu_tests_mean():
+    """Shapes of tests/test_gpu_shapes.py that are there for what a launch does with them: pairs in so many parts, whole pairs whose
+    logits do not fit the LDS.  Both follow from rules on the shape, which may move."""
+    import re
+    import subprocess
+
+    import test_gpu_shapes as shapes
+    from paper_2605_09490_amd import build
+    exe = build.build_fake_check()
+
+    def route(s):
+        tokens = s["context"] + s.get("decode_steps", 4)
+        args = [str(s[k]) for k in ("n_layers", "batch", "n_q_heads", "n_kv_heads", "head_dim")] + [str(tokens)]
+        r = subprocess.run([exe, "route", *args], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return [int(x) for x in re.fullmatch(r"step (\d+) whole (\d+) in (\d+) parts; call (\d+) whole; lds (\d+)\n", r.stdout).groups()]
+
+    seen = set()
+    for n, pairs, _, _, s in shapes.STEPS_IN_PARTS:
+        whole, in_parts, parts, _, _ = route(s)
+        assert (parts, in_parts) == (n, pairs), (s, whole, in_parts, parts)
+        seen.add(parts)
+    assert seen == set(range(2, 9))
+    for s in shapes.STEPS_BEYOND_THE_LDS:
+        whole, _, _, _, lds = route(s)
+        assert whole > 0 and s["context"] > lds, (s, whole, lds)
+    for s in shapes.CALLS_BEYOND_THE_LDS:
+        _, _, _, whole, lds = route(dict(s, n_layers=1))
+        assert whole > 0 and s["context"] > lds, (s, whole, lds)
+    whole, in_parts, _, call, _ = route(shapes.PRECISION)
+    assert whole > 0 and in_parts == 0 and call == 0
+
+
 def test_chunk_scratch_comes_from_the_calls_own_stream(monkeypatch):
     """PyTorch's allocator keeps a pool per stream.  The scratch of a handle's first chunk is written on the stream that the
     call names, so it has to come from that stream's pool, not from the one of whatever stream is current."""

@@ -147,19 +147,48 @@ def test_decode_step_equals_per_layer_calls():
     a.close(); b.close()
 
 
+# Whole steps of which some pairs go in parts (how many parts, pairs in parts, mode, scorer, shape) and steps and single calls of
+# whole pairs with logits beyond the LDS: test_abi_host.py holds the launches to it.
+STEPS_IN_PARTS = [
+    (3, 24, "lazy", "attention", dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=700)),          # list lengths from device counters
+    (3, 32, "wait", "vatp", dict(n_layers=9, batch=4, n_q_heads=8, n_kv_heads=8, head_dim=64, context=1300)),
+    (2, 100, "lazy", "combined", dict(n_layers=25, batch=1, n_q_heads=24, n_kv_heads=4, head_dim=128, context=800, t2_format="int4_g32", kv_dtype="f16")),   # all pairs
+    (3, 80, "lazy", "attention", dict(n_layers=28, batch=3, n_q_heads=28, n_kv_heads=4, head_dim=128, context=2900)),        # score tiles of 64 columns
+    (2, 102, "wait", "redundancy", dict(n_layers=34, batch=1, n_q_heads=6, n_kv_heads=3, head_dim=64, context=1700)),        # three kv heads
+    (4, 32, "lazy", "vatp", dict(n_layers=9, batch=4, n_q_heads=8, n_kv_heads=8, head_dim=64, context=2040, t2_format="int4_g32")),
+    (5, 48, "lazy", "attention", dict(n_layers=28, batch=5, n_q_heads=28, n_kv_heads=4, head_dim=128, context=2490)),
+    (6, 24, "wait", "combined", dict(n_layers=20, batch=7, n_q_heads=8, n_kv_heads=2, head_dim=64, context=3060, kv_dtype="f16")),
+    (7, 24, "lazy", "attention", dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=1780, t2_format="int4_g32", kv_dtype="f16")),
+    (8, 24, "lazy", "redundancy", dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=2040)),
+    (8, 24, "lazy", "vatp", dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=90, decode_steps=1950)),   # fewer tiles than parts
+    (4, 32, "lazy", "attention", dict(n_layers=9, batch=4, n_q_heads=8, n_kv_heads=8, head_dim=64, context=40, decode_steps=2000)),   # ... of list lengths from the arguments
+]
+STEPS_BEYOND_THE_LDS = [
+    dict(n_layers=7, batch=24, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2900),
+    dict(n_layers=64, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3500, t2_format="int4_g32"),
+    dict(n_layers=32, batch=1, n_q_heads=48, n_kv_heads=8, head_dim=128, context=4000),
+    dict(n_layers=11, batch=3, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2900),
+]
+CALLS_BEYOND_THE_LDS = [
+    dict(batch=32, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2900, sequences=2),
+    dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3500, t2_format="int4_g32", sequences=2),
+]
+PRECISION = dict(n_layers=32, batch=1, n_q_heads=40, n_kv_heads=8, head_dim=128, context=6001, decode_steps=2)
+
+
 @pytest.mark.parametrize("mode,scorer,shape", [
     # split pairs (fewer than 96 pairs in the step)
     ("wait", "combined", dict(n_layers=5, batch=3, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700)),
     ("lazy", "attention", dict(n_layers=40, batch=1, n_q_heads=5, n_kv_heads=1, head_dim=128, context=333)),    # two passes of the finishing kernel
     ("lazy", "vatp", dict(n_layers=2, batch=8, n_q_heads=24, n_kv_heads=4, head_dim=64, context=129, kv_dtype="f32")),
     # one workgroup per pair
-    ("lazy", "attention", dict(n_layers=7, batch=24, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2600)),   # logits beyond the LDS
+    ("lazy", "attention", STEPS_BEYOND_THE_LDS[0]),
     ("wait", "vatp", dict(n_layers=40, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=333, t2_format="int4_g32")),
     ("wait", "attention", dict(n_layers=4, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=200)),
     ("lazy", "redundancy", dict(n_layers=3, batch=9, n_q_heads=40, n_kv_heads=8, head_dim=128, context=31, kv_dtype="f16")),
     ("lazy", "attention", dict(n_layers=70, batch=1, n_q_heads=6, n_kv_heads=2, head_dim=64, context=65, t2_format="int4_g32")),   # two groups of layers
-    ("lazy", "vatp", dict(n_layers=25, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100, t2_format="int4_g32")),   # beyond the LDS: value norms
-    ("wait", "redundancy", dict(n_layers=13, batch=1, n_q_heads=48, n_kv_heads=8, head_dim=128, context=3700)),                  # ... the penalty
+    ("lazy", "vatp", STEPS_BEYOND_THE_LDS[1]),                                                                       # ... value norms
+    ("wait", "redundancy", STEPS_BEYOND_THE_LDS[2]),                                                                 # ... the penalty
     ("lazy", "combined", dict(n_layers=12, batch=1, n_q_heads=8, n_kv_heads=8, head_dim=128, context=300)),
     ("lazy", "attention", dict(n_layers=6, batch=2, n_q_heads=32, n_kv_heads=8, head_dim=128, context=300, t2_format="int4_g32", kv_dtype="f16")),
 ])
@@ -208,13 +237,7 @@ def test_decode_step_serves_several_layers_per_launch(mode, scorer, shape):
         c.close()
 
 
-@pytest.mark.parametrize("mode,scorer,shape", [
-    ("lazy", "attention", dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=700)),          # 24 of 280 pairs, eight parts; device counters
-    ("wait", "vatp", dict(n_layers=9, batch=4, n_q_heads=8, n_kv_heads=8, head_dim=64, context=1300)),               # 32 of 288, eight parts
-    ("lazy", "combined", dict(n_layers=25, batch=1, n_q_heads=24, n_kv_heads=4, head_dim=128, context=800, t2_format="int4_g32", kv_dtype="f16")),   # all 100, two
-    ("lazy", "attention", dict(n_layers=28, batch=3, n_q_heads=28, n_kv_heads=4, head_dim=128, context=2900)),        # 80 of 336, three; score tiles of 64 columns
-    ("wait", "redundancy", dict(n_layers=34, batch=1, n_q_heads=6, n_kv_heads=3, head_dim=64, context=1700)),         # all 102, two; three kv heads
-])
+@pytest.mark.parametrize("mode,scorer,shape", [t[2:] for t in STEPS_IN_PARTS])
 def test_decode_step_whose_last_pairs_go_in_parts(mode, scorer, shape):
     """The pairs of a round that the chip does not fill are walked in parts and their weights and outputs made by the score
     launch: the same comparison with per-layer calls, with the same bounds, at numbers of pairs and tokens where that is done."""
@@ -222,12 +245,12 @@ def test_decode_step_whose_last_pairs_go_in_parts(mode, scorer, shape):
 
 
 @pytest.mark.parametrize("shape", [
-    dict(n_layers=28, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100),                    # logits beyond the LDS
+    dict(n_layers=28, batch=1, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100),                    # pairs in two parts
     dict(n_layers=3, batch=70, n_q_heads=4, n_kv_heads=2, head_dim=64, context=150, kv_dtype="f16"),       # list lengths from device counters
     dict(n_layers=4, batch=64, n_q_heads=24, n_kv_heads=4, head_dim=128, context=90, t2_format="int4_g32"),   # WAIT: layers one by one
     dict(n_layers=5, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700),                      # split pairs
     dict(n_layers=4, batch=70, n_q_heads=5, n_kv_heads=1, head_dim=128, context=2040),                     # 24 of the last layer's 70 pairs in eight parts
-    dict(n_layers=11, batch=3, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2900),                     # 8 of its 24 in six, logits beyond the LDS
+    STEPS_BEYOND_THE_LDS[3],                                                                               # 8 of its 24 in six
 ])
 def test_prop1_of_whole_steps(shape, monkeypatch):
     """T1 placement, prefetch mode and the memory there is for a step's scratch change no bit of a decode step: the same rows
@@ -289,8 +312,7 @@ def test_prop1_of_whole_steps(shape, monkeypatch):
 @pytest.mark.parametrize("shape", [
     dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=97),
     dict(batch=130, n_q_heads=4, n_kv_heads=2, head_dim=64, context=129, t2_format="int4_g32", kv_dtype="f16"),   # list lengths from device counters
-    dict(batch=32, n_q_heads=64, n_kv_heads=8, head_dim=64, context=2600, sequences=2),                            # logits beyond the LDS
-    dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=3100, t2_format="int4_g32", sequences=2),    # ... the production batch's kernel
+    *CALLS_BEYOND_THE_LDS,                                                                                         # the second: the production batch's kernel
 ])
 def test_single_calls_with_a_pair_for_every_compute_unit(shape):
     """256 or more pairs: single calls take one workgroup per pair as a whole step does.  Outputs and scores against the
@@ -839,8 +861,7 @@ def test_whole_pairs_keep_the_precision_of_split_ones(kv_dtype, t2):
     import paper_2605_09490_amd as tkv
     from oracle import tkv_oracle as O
     from tkv_synth import Workload
-    cfg = small_config(name="precision", n_layers=12, batch=1, n_q_heads=40, n_kv_heads=8, head_dim=128, kv_dtype=kv_dtype,
-                       t2_format=t2, context=6001, decode_steps=2, k_window=16, sigma=1.0)
+    cfg = small_config(name="precision", kv_dtype=kv_dtype, t2_format=t2, k_window=16, sigma=1.0, **PRECISION)
     cfg = dataclasses.replace(cfg, recipe="bias")
     print(f"[case] {kv_dtype} {t2}", flush=True)
     wl = Workload(cfg, device="cuda")
