@@ -285,7 +285,8 @@ __device__ __forceinline__ float half_of(uint32_t w, int hi) {
   return (float)__builtin_bit_cast(_Float16, (uint16_t)(hi ? (w >> 16) : (w & 0xffffu)));
 }
 
-// Scaled logits of one call: [sequence entry][query head][xs_stride], by list index
+// Logits of one call: [sequence entry][query head][xs_stride], by list index; scaled, but of one token on the matrix cores
+// (split_on_matrix), whose readers scale them
 __device__ __forceinline__ size_t xs_at(const AttnArgs& a, int seq, int hq, int col) {
   return ((size_t)seq * a.Hq + hq) * a.xs_stride + col;
 }
@@ -2706,7 +2707,8 @@ __global__ __launch_bounds__(FinGeo<STEP>::NT) void k_attn_finish(const AttnArgs
     else if (in_s) pos = a.s_pos[(size_t)b * a.Nmax + (j - (cf + cq) * TB)];
     float score = 0.f;
     // A logit's weight: the matrix cores' waves leave unscaled logits, the others scaled ones.  (A branch on the rows' type in
-    // its place costs a call 0.4 us.)
+    // its place costs a call 0.4 us: binary32 rows at a head_dim and group size of the matrix cores' have the exponent's
+    // remainder put back in too, for 0.1 us.)
     const float xscale = split_on_matrix(D, G, a.q_es) ? a.softmax_scale : 1.0f;
     const auto weight = [&](float x, const float2& st) {
       if constexpr (split_on_matrix(D, G, 2)) return exp_le0(fmaf(x, xscale, -st.x)) * st.y;

@@ -417,17 +417,19 @@ tkv_status rehome_store(tkv_cache* c, int n, hipStream_t st) {
 //    pairs are split if fewer than 60 % of a launch's units, round by round, would have one, and a layer has eight pairs
 //    or more (with fewer every layer takes its share of workgroups that leave a partial and little else).
 //  - else pairs are split as in a single call.
-// us a step with whole / split pairs (15 % int8 T2; the split launch also several layers at a time):
+// us a step with whole / split pairs (15 % int8 T2; the split launch also several layers at a time; whole pairs with the parts that
+// step_tail gives them, which the line was drawn without: up to some 40000 tokens it is now on the slow side for 96 x 5, and for
+// 96 x 1 and 264 x 4 beyond):
 //   pairs x heads   1500 tokens   4096        16384       32768         49152         65536
-//   96 x 1                                    187 / 160   404 / 288                   817 / 553
-//   96 x 5          35 / 55       68 / 124    225 / 220   445 / 400     672 / 551     887 / 742
-//   128 x 5                                               510 / 497
-//   160 x 5         38 / 77       75 / 186    281 / 344   578 / 617                   1168 / 1213
-//   264 x 4         61 / 97       131 / 240   530 / 518   1084 / 945    1639 / 1371   2019 / 1805
-//   384 x 5         73 / 156      156 / 426   624 / 815   1289 / 1480
-//   512 x 5         85 / 202      191 / 570   760 / 1086  1575 / 1921
-//   112 x 7, four pairs a layer   43 / 69     83 / 143    275 / 403     538 / 580     795 / 831     1053 / 1086
-//   128 x 7, four pairs a layer                           558 / 692                   1105 / 1196
+//   96 x 1                        41 / 73     133 / 159   263 / 287                   502 / 555
+//   96 x 5          25 / 51       50 / 110    160 / 210   312 / 389     635 / 552     847 / 743
+//   128 x 5                                               495 / 495
+//   160 x 5         30 / 70       79 / 167    268 / 332   563 / 603                   1139 / 1203
+//   264 x 4         46 / 92       103 / 232   397 / 512   812 / 926     1210 / 1376   1976 / 1826
+//   384 x 5         63 / 147      146 / 382   583 / 799   1268 / 1448
+//   512 x 5         73 / 190      174 / 513   751 / 1065  1563 / 1910
+//   112 x 7, four pairs a layer   28 / 58     62 / 119    203 / 364   479 / 547     710 / 789     950 / 1036
+//   128 x 7, four pairs a layer                           517 / 658                   1041 / 1150
 // Either way several layers per launch, as many as fit a scratch (step_scratch).
 constexpr size_t STEP_SCRATCH_BYTES = (size_t)64 << 20, STEP_WHOLE_SCRATCH_BYTES = (size_t)256 << 20;
 constexpr int STEP_WHOLE_PAIRS = 96, STEP_LONG_LIST = 20480, STEP_MAX_PARTS = 8;
@@ -465,10 +467,11 @@ void step_route(tkv_cache* c) {
 // Of a whole-pair step the pairs of the chip's last round (all of them, where there is but one), if that round is so empty that
 // walking its pairs in parts pays: in units of the time in which a workgroup's waves take a tile each, a round of pairs in S
 // parts takes its longest wave's tiles and 1.2 for beginning and end; the parts' logits, which leave the chip, 0.6 once; and an
-// eighth of the launch is to be gained (rounds are not that sharp: 896 pairs of 2081 tokens, 3.5 rounds, gain 6 us of 187 by two
-// parts each in the last and lose them to the scores).  Settled with the kind of launch, from the shape alone (list lengths by
-// max_tokens).  us a step, whole / in parts (28/4 heads, 28 layers): 1 x 1422 tokens 40.1 / 32.9, 4000 79.8 / 63.4, 12000 205 / 165;
-// 3 x 2000 90.5 / 80.2, 5 x 2000 139.8 / 125; 64/8 heads, 12 layers, 1 x 3000 66.5 / 49.2.
+// eighth of the launch is to be gained (rounds are not that sharp: 896 pairs of 2081 tokens, 3.5 rounds, 174 us a step, take 178 with
+// two parts each in the last).  Settled with the kind of launch, from the shape alone (list lengths by max_tokens).  The constants
+// are those of waves on the vector ALUs; with the present ones, us a step, whole / in parts (28/4 heads, 28 layers): 1 x 1422 tokens
+// 29.4 / 27.4, 4000 57.8 / 59.5, 12000 173 / 147; 3 x 2000 73.7 / 70.5, 5 x 2000 115.5 / 107.0; 64/8 heads, 12 layers, 1 x 3000 43.5 /
+// 42.9.  Of two to eight parts the rule's number is the best or within 1 % of it in each of these.
 void step_tail(tkv_cache* c) {
   const DevView& v = c->dv;
   c->tail_pairs = 0; c->tail_parts = 1;

@@ -91,7 +91,8 @@ struct AttnArgs {
   const int* f_loc; const int* f_pos; const int* q_loc; const int* q_pos;
   const int* cnt;
   float* score;
-  float* xs;        // [B][Hkv][G][xs_stride] scaled logits by list index (F tiles, then Q tiles)
+  float* xs;        // [B][Hkv][G][xs_stride] logits by list index (F tiles, then Q tiles); unscaled where one token's waves ran on
+                    // the matrix cores, else scaled
   float* part_ml;   // [B][Hkv][S][2][G]  (m, l) of each split (= workgroup)
   float* part_o;    // [B][Hkv][S][G][D]
   int S;            // workgroups per (sequence, kv head) of this launch
