@@ -19,8 +19,9 @@
 //                 logits go to a scratch array.  16-bit rows of 256 bytes under four and more heads: the same launch with
 //                 its waves on the matrix cores, as in attn_step.
 //   attn_step   : a whole decode step's layers (or a single call over many pairs), one workgroup per (layer, sequence, kv
-//                 head) pair, on the matrix cores: the logits stay in the LDS, the workgroup writes its output itself and
-//                 one float per row (the weights summed over the group) for step_scores / call_scores.
+//                 head) pair, on the matrix cores (one or two heads a group over short lists: on the vector ALUs): the
+//                 logits stay in the LDS, the workgroup writes its output itself and one float per row (the weights summed
+//                 over the group) for step_scores / call_scores.
 //   attn_finish : grid (64-entry tiles + Hq, B).  Every workgroup first merges the (m, l) of all splits of its sequence
 //                 into the global (m, 1/l) of every query head.  Tile workgroups then turn the stored logits
 //                 into softmax weights, summed over all query heads in a fixed order, into score[b, pos]; the
@@ -526,8 +527,8 @@ __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t& rs, char* lds,
 //   slot list of tile t+2 | K scales of t+1 | per K batch of t: the V pieces of t on its bytes |
 //   V scales of t+1 | per V step of t: the K pieces of t+1 on its bytes
 // Accumulates into o, m_run, l_lane (per-lane partial sums of the softmax denominator, relative to m_run); leaves the
-// scaled logits in xs.
-template <int D, int G, Mode M, int KT, int TR>
+// scaled logits in xs (WHOLE, k_attn_step: unscaled ones in the LDS, which has room for all).
+template <int D, int G, Mode M, int KT, int TR, bool WHOLE = false>
 __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, int b, int jq, int kvh, int lane,
                                           int tile0, int tstride, int n_list, const int* loc_list, int col0,
                                           float (&o)[G][Geo<D, M>::EV], float (&m_run)[G], float (&l_lane)[G]) {
@@ -784,7 +785,12 @@ __device__ __forceinline__ void attn_wave(const AttnArgs& a, const WaveLds& w, i
         x[h] = valid ? xt[h] * a.softmax_scale : -INFINITY;
         xm[h] = x[h];
       }
-      if (valid) {
+      if constexpr (WHOLE) {
+        if (valid) {
+#pragma unroll
+          for (int h = 0; h < G; ++h) lds_wr32(w.lga + (uint32_t)(h * w.lcap + col) * 4u, __builtin_bit_cast(uint32_t, xt[h]));
+        }
+      } else if (valid) {
         const size_t xbase = xs_at(a, b * a.n_q + jq, kvh * G, col);
 #pragma unroll
         for (int h = 0; h < G; ++h) a.xs[xbase + (size_t)h * a.xs_stride] = x[h];
@@ -1669,6 +1675,26 @@ __device__ __forceinline__ void park_one(const f32x4 (&om)[D / 16], float m, flo
     }
 }
 
+// The same of a wave on the vector ALUs: the row groups are summed, and the per-lane denominators
+template <int D, int G, int EV, int LPRV>
+__device__ __forceinline__ void park_rows(const float (&o)[G][EV], int lane, float* my_o) {
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    float t[RowSum<EV, LPRV>::N];
+    row_sum<EV, LPRV>(o[h], lane, t);
+#pragma unroll
+    for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t[k];
+  }
+}
+template <int G>
+__device__ __forceinline__ void park_stats(const float (&m_run)[G], const float (&l_lane)[G], int lane, float* ml) {
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float ls = wave_sum(l_lane[h]);
+    if (lane == 0) { ml[h] = m_run[h]; ml[8 + h] = ls; }
+  }
+}
+
 // Whether a wave's outputs are all finite, in every lane (the padding columns' are those of the last head)
 template <int D>
 __device__ __forceinline__ bool finite_one(const f32x4 (&om)[D / 16]) {
@@ -1878,32 +1904,13 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
           for (int e = 0; e < 8; ++e) o8[h][e] = 0.f;
         if (a.t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
         else attn_wave<D, G, Q_INT4, KT, TR>(a, w, bl, jq, kvh, lane, u - nwf, nwq, nQ, a.q_loc + (size_t)b * a.Nmax, colq, o8, m_run, l_lane);
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-          constexpr int L8 = D / 8;
-          float t8[RowSum<8, L8>::N];
-          row_sum<8, L8>(o8[h], lane, t8);
-#pragma unroll
-          for (int k = 0; k < RowSum<8, L8>::N; ++k) my_o[h * D + row_sum_elem<8, L8>(lane, k)] = t8[k];
-        }
+        park_rows<D, G, 8, D / 8>(o8, lane, my_o);
         o_written = true;
       }
     }
     // ---- wave partial: sum the row groups and the per-lane denominators, then merge the waves through LDS
-    if (!o_written) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float t1[RowSum<EV, LPRV>::N];
-        row_sum<EV, LPRV>(o[h], lane, t1);
-#pragma unroll
-        for (int k = 0; k < RowSum<EV, LPRV>::N; ++k) my_o[h * D + row_sum_elem<EV, LPRV>(lane, k)] = t1[k];
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float ls = wave_sum(l_lane[h]);
-      if (lane == 0) { sm_ml[wave * 16 + h] = m_run[h]; sm_ml[wave * 16 + 8 + h] = ls; }
-    }
+    if (!o_written) park_rows<D, G, EV, LPRV>(o, lane, my_o);
+    park_stats<G>(m_run, l_lane, lane, sm_ml + wave * 16);
   }
   __syncthreads();
   const int bq = bl * a.n_q + jq;
@@ -1962,18 +1969,27 @@ __global__ __launch_bounds__((KernelGeo<D, G, KT>::NW * 64), (KernelGeo<D, G, KT
 // The pairs that fill the last round of the chip only in part, those of the (layer, sequence) rows from a.whole_rows on, are
 // cut into a.S parts of eight waves each (the host's rule: step_tail): a part writes its logits and a partial, as in the
 // split launch.
-template <int D, int G>
+template <int D, int G, bool VEC = false>
 struct StepGeo {
   static constexpr int NW = 8, RB = 2 * D, TR = 8192 / RB < 64 ? 8192 / RB : 64, TILE = TR * RB;
-  static constexpr int SC = (D / 64) * TR * 4, LT = 2 * TR * 4;   // per wave: K or V scales, slot lists
-  static constexpr int LDS = 163840, FIXED = NW * (TILE + 2 * SC + LT) + NW * 16 * 4 + 8 * 8 + 256;
+  static constexpr int SC = (D / 64) * TR * 4, LT = 2 * TR * 4, P = VEC ? TR * GPad<G>::v * 4 : 0;   // per wave: K or V scales, slot lists, weights
+  static constexpr int LDS = 163840, FIXED = NW * (TILE + P + 2 * SC + LT) + NW * 16 * 4 + 8 * 8 + 256;
   static constexpr int LCAP = (LDS - FIXED) / 4 / G / TR * TR;
 };
-template <int D, int G, int KT>
+// Caches whose single calls are whole-pair launches (a pair and more for every compute unit): where lists are short a wave has one
+// tile or two, and what a tile takes from its arrival on counts for each round of pairs.  With one or two heads a group the vector
+// ALUs have a 64-row tile done in half of the time that the matrix cores' wave spends on 16 columns, and keep these caches at head_dim
+// 64 up to 1024 tokens.  us a call, matrix / vector instructions: 64 sequences, 8/8 heads, 100 tokens 14.9 / 13.1, 300 19.0 / 16.5,
+// 500 20.9 / 19.4, 700 23.8 / 22.7, 1500 40.6 / 42.2, 4000 98 / 105; 4/4, 1000 18.8 / 18.5; 8/4, 300 13.2 / 12.7, 500 14.5 / 14.1; 12/4
+// (three a group), 500 14.7 / 14.5; 130 x 300, 4/2 18.4 / 17.3.  Outputs against 64 bits there: 2.0e-7 either way.  At head_dim 128 (64 x
+// 300, 4/4 14.1 / 13.7) the matrix cores' are closer, 2.3e-7 / 2.7e-7.
+constexpr int VECTOR_TOKENS = 1024;
+constexpr bool step_on_vector(int D, int G, int max_tokens) { return D == 64 && G <= 2 && max_tokens <= VECTOR_TOKENS; }
+template <int D, int G, int KT, bool VEC>
 __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
-  using SG = StepGeo<D, G>;
+  using SG = StepGeo<D, G, VEC>;
   constexpr Mode MF = KT == KT_BF16 ? F_BF16 : F_F16;
-  constexpr int NW = SG::NW, TR = SG::TR, TILE = SG::TILE, LCAP = SG::LCAP;
+  constexpr int NW = SG::NW, TR = SG::TR, TILE = SG::TILE, LCAP = SG::LCAP, EV = Geo<D, MF, TR>::EV;
   static_assert(G * D * 4 <= TILE, "a wave's output partial is parked in its tile buffer");
   __shared__ __attribute__((aligned(16))) char sm_t[NW * TILE];
   __shared__ __attribute__((aligned(16))) char sm_sc[NW * 2 * SG::SC];
@@ -1981,6 +1997,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) float sm_lg[G * LCAP];
   __shared__ float sm_ml[NW * 16];
   __shared__ float2 sm_fin[8];
+  __shared__ __attribute__((aligned(16))) char sm_p[VEC ? NW * SG::P : 16];
   const int kvh = blockIdx.x;
   int bl = blockIdx.y, part = 0;
   // What stands between a workgroup and its first request, all of the arguments asked for at once: they come over the host link,
@@ -2011,7 +2028,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
   const int nft = (nF + TR - 1) / TR, colq = nft * TR;
 
   WaveLds w;
-  w.t = sm_t + wave * TILE; w.p = nullptr; w.pa = 0;
+  w.t = sm_t + wave * TILE; w.p = sm_p + wave * SG::P; w.pa = lds_addr(w.p);
   w.sk = sm_sc + wave * 2 * SG::SC; w.sv = w.sk + SG::SC; w.lt = sm_lt + wave * SG::LT;
   w.ta = lds_addr(w.t); w.ska = lds_addr(w.sk); w.sva = lds_addr(w.sv); w.lta = lds_addr(w.lt);
   w.lga = lds_addr(sm_lg); w.lcap = LCAP;
@@ -2022,18 +2039,34 @@ __global__ __launch_bounds__(512, 2) void k_attn_step(const AttnArgs a) {
 
   const int nwf = nwv - nwq;
   const int* q_loc = q_list + (size_t)b * Nmax;
-  f32x4 om[1][D / 16];
-  float mr[1] = {-INFINITY}, lr[1] = {0.f};
+  if constexpr (VEC) {
+    static_assert(SG::LCAP >= VECTOR_TOKENS + 2 * TB && EV == 8, "all logits in the LDS");
+    float o[G][EV], m_run[G], l_lane[G];
 #pragma unroll
-  for (int db = 0; db < D / 16; ++db) om[0][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (u < nwf) attn_wave_mfma<D, KT, MF, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u, nwf, nF, nF, f_loc, 0, om, mr, lr);
-  else if (t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, q_loc, colq, om, mr, lr);
-  else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, q_loc, colq, om, mr, lr);
-  park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
-  if (!finite_one<D>(om[0])) {
-    if (u < nwf) outputs_plain<D, G, KT, MF, LOG_STEP>(a, w, bl, kvh, lane, u, nwf, nF, f_loc, 0, mr[0], my_o);
-    else if (t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, mr[0], my_o);
-    else outputs_plain<D, G, KT, Q_INT4, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, mr[0], my_o);
+    for (int h = 0; h < G; ++h) {
+      m_run[h] = -INFINITY; l_lane[h] = 0.f;
+#pragma unroll
+      for (int e = 0; e < EV; ++e) o[h][e] = 0.f;
+    }
+    if (u < nwf) attn_wave<D, G, MF, KT, TR, true>(a, w, bl, 0, kvh, lane, u, nwf, nF, f_loc, 0, o, m_run, l_lane);
+    else if (t2fmt == 0) attn_wave<D, G, Q_INT8, KT, TR, true>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, o, m_run, l_lane);
+    else attn_wave<D, G, Q_INT4, KT, TR, true>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, o, m_run, l_lane);
+    park_rows<D, G, EV, Geo<D, MF, TR>::LPRV>(o, lane, my_o);
+    park_stats<G>(m_run, l_lane, lane, sm_ml + wave * 16);
+  } else {
+    f32x4 om[1][D / 16];
+    float mr[1] = {-INFINITY}, lr[1] = {0.f};
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) om[0][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (u < nwf) attn_wave_mfma<D, KT, MF, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u, nwf, nF, nF, f_loc, 0, om, mr, lr);
+    else if (t2fmt == 0) attn_wave_mfma<D, KT, Q_INT8, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, q_loc, colq, om, mr, lr);
+    else attn_wave_mfma<D, KT, Q_INT4, 1, LOG_STEP>(a, w, bl, 0, kvh, lane, u - nwf, nwq, nQ, nQ, q_loc, colq, om, mr, lr);
+    park_one<D, G>(om[0], mr[0], lr[0], lane, my_o, sm_ml + wave * 16);
+    if (!finite_one<D>(om[0])) {
+      if (u < nwf) outputs_plain<D, G, KT, MF, LOG_STEP>(a, w, bl, kvh, lane, u, nwf, nF, f_loc, 0, mr[0], my_o);
+      else if (t2fmt == 0) outputs_plain<D, G, KT, Q_INT8, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, mr[0], my_o);
+      else outputs_plain<D, G, KT, Q_INT4, LOG_STEP>(a, w, bl, kvh, lane, u - nwf, nwq, nQ, q_loc, colq, mr[0], my_o);
+    }
   }
   // ---- merge the waves
   __syncthreads();
@@ -3187,8 +3220,15 @@ static hipError_t run_step(const AttnArgs& a, hipStream_t st, hipEvent_t ev0, hi
     return hipErrorInvalidValue;
   } else {
     const dim3 grid(a.Hkv, a.whole_rows + (a.nl * a.B - a.whole_rows) * a.S);
-    if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_step<D, G, KT>), grid, dim3(512), 0, st, ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((k_attn_step<D, G, KT>), grid, dim3(512), 0, st, a);
+    if constexpr (step_on_vector(D, G, 0)) {
+      if (a.vec) {
+        if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_step<D, G, KT, true>), grid, dim3(512), 0, st, ev0, ev1, 0, a);
+        else hipLaunchKernelGGL((k_attn_step<D, G, KT, true>), grid, dim3(512), 0, st, a);
+        return hipGetLastError();
+      }
+    }
+    if (ev0 && ev1) hipExtLaunchKernelGGL((k_attn_step<D, G, KT, false>), grid, dim3(512), 0, st, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL((k_attn_step<D, G, KT, false>), grid, dim3(512), 0, st, a);
     return hipGetLastError();
   }
 }
@@ -3305,6 +3345,7 @@ hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t
   return hipErrorInvalidValue;
 }
 
+bool attn_step_on_vector(int D, int G, int max_tokens) { return step_on_vector(D, G, max_tokens); }
 int attn_step_tile_rows(int D) { return D == 128 ? StepGeo<128, 1>::TR : StepGeo<64, 1>::TR; }
 template <int D, int G, int KT>
 static int step_cap() { return StepGeo<D, G>::LCAP; }

@@ -870,6 +870,7 @@ static tkv_status attend_one(tkv_cache* c, int32_t layer, const void* q, void* o
   if (whole) { a.sc_stride = c->sc_stride; a.xs_stride = c->spill_stride; }
   if (whole && step_launch && c->sc_step) { a.xs = c->spill_step; a.sc = c->sc_step; }
   else if (whole) { a.sc = c->xs; a.xs = c->xs + (size_t)v.B * v.Hkv * c->sc_stride; }
+  a.vec = whole && c->call_whole && attn_step_on_vector(v.D, c->G, v.Nmax);
   a.whole_rows = nl * v.B;                               // no pair in parts
   if (step_launch && c->tail_pairs > 0) {
     a.tail0 = layer * v.B * v.Hkv - (v.L * v.B * v.Hkv - c->tail_pairs);

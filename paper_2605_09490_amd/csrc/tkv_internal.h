@@ -125,6 +125,7 @@ struct AttnArgs {
   // Split pair p keeps its logits in xt [p + tail0][G][sc_stride] and the parts' partials in part_ml [p + tail0][S][2][G] and
   // part_o [p + tail0][S][G][D]; p + tail0 counts the split pairs of the whole step, however its layers are grouped.
   int whole_rows, tail0;
+  int vec;          // ... its waves on the vector ALUs
   float* xt;
   const int* f_loc_old;   // slots of list F for the layers whose bit is set in old_mask (lazy prefetch: the copies are in flight)
   uint64_t old_mask;
@@ -144,6 +145,7 @@ hipError_t launch_attn_finish(const AttnArgs& a, int D, int G, hipStream_t st, h
 // whole-pair step launch: rows per tile, entries whose logits fit the LDS, and the launch that ends it
 int attn_step_tile_rows(int D);
 int attn_step_lds_entries(int D, int G);
+bool attn_step_on_vector(int D, int G, int max_tokens);
 hipError_t launch_step_scores(const AttnArgs& a, int D, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_finish_chunk(const AttnArgs& a, int D, int G, hipStream_t st);
 // chunks of 16-bit rows (launch_attn_tiered with groups > 0; with xs_stride == 0 it is the whole call): blocks of 16 columns a

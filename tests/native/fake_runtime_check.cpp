@@ -369,6 +369,25 @@ static void chunk_splits() {
       }
 }
 
+// A cache with a pair for every compute unit, few heads a group, head_dim 64 and short lists has its whole-pair launches on the
+// vector ALUs, single calls and steps alike; others do not, nor do steps over pairs of several layers.
+static void few_heads_on_the_vector_alus() {
+  const struct { int L, B, Hq, Hkv, D, n; bool vec; } cases[] = {
+      {2, 64, 8, 8, 64, 700, true}, {1, 86, 6, 3, 64, 1024, true}, {1, 86, 6, 3, 64, 1025, false}, {1, 86, 9, 3, 64, 700, false},
+      {1, 64, 4, 4, 128, 700, false}, {70, 130, 4, 2, 64, 100, true}, {50, 2, 8, 8, 64, 700, false}};
+  for (auto& t : cases) {
+    tkv_config cfg = config(t.L, t.B, t.Hq, t.Hkv, t.D, t.n);
+    tkv_cache* c = nullptr;
+    CHECK(tkv_create(&cfg, &c) == TKV_OK);
+    fill(c, cfg, 60);
+    for (auto& l : step(c, cfg)) CHECK(l.kernel.find("k_attn_step") != std::string::npos && (l.a.vec != 0) == t.vec && (l.kernel.find("Lb1E") != std::string::npos) == t.vec);
+    g_launches.clear();
+    OK(tkv_attend_and_score(c, 0, DATA, DATA, STREAM));
+    CHECK((g_launches[0].a.vec != 0) == t.vec);
+    tkv_destroy(c);
+  }
+}
+
 // Chunks whose logits are written (up to 32 columns and 16 tokens) go in one launch pair whatever the number of heads; longer
 // ones in as many as the score launch's LDS makes of them, each with a sensible share.
 static void chunk_tokens_per_launch() {
@@ -438,6 +457,7 @@ int main(int argc, char** argv) {
   else if (what == "allocations_before_use") allocations_before_use();
   else if (what == "route_follows_from_the_shape") route_follows_from_the_shape();
   else if (what == "parts_of_pairs") parts_of_pairs();
+  else if (what == "few_heads_on_the_vector_alus") few_heads_on_the_vector_alus();
   else if (what == "long_lists_fill_the_chip") long_lists_fill_the_chip();
   else if (what == "chunk_splits") chunk_splits();
   else if (what == "chunk_tokens_per_launch") chunk_tokens_per_launch();

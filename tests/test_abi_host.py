@@ -127,7 +127,7 @@ def test_sources_compile_without_warnings():
 
 
 @pytest.mark.parametrize("scenario", ["refused_allocations", "allocations_before_use", "route_follows_from_the_shape",
-                                      "parts_of_pairs", "long_lists_fill_the_chip", "chunk_splits", "chunk_tokens_per_launch", "kernel_times"])
+                                      "parts_of_pairs", "few_heads_on_the_vector_alus", "long_lists_fill_the_chip", "chunk_splits", "chunk_tokens_per_launch", "kernel_times"])
 def test_host_code_on_a_runtime_that_launches_nothing(scenario):
     """tests/native/fake_runtime_check.cpp: the host code against a stand-in for the HIP runtime; allocations can be refused,
     and every launch is compared with the memory alive."""

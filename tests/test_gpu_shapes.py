@@ -311,7 +311,10 @@ def test_prop1_of_whole_steps(shape, monkeypatch):
 
 @pytest.mark.parametrize("shape", [
     dict(batch=64, n_q_heads=28, n_kv_heads=4, head_dim=128, context=97),
-    dict(batch=130, n_q_heads=4, n_kv_heads=2, head_dim=64, context=129, t2_format="int4_g32", kv_dtype="f16"),   # list lengths from device counters
+    dict(batch=130, n_q_heads=4, n_kv_heads=2, head_dim=64, context=129, t2_format="int4_g32", kv_dtype="f16"),   # list lengths from device counters; few heads
+    dict(batch=256, n_q_heads=1, n_kv_heads=1, head_dim=64, context=65),                                           # ... one, two tiles
+    dict(batch=86, n_q_heads=6, n_kv_heads=3, head_dim=64, context=1021, sequences=2),                             # ... two, the longest lists on the vector ALUs
+    dict(batch=86, n_q_heads=6, n_kv_heads=3, head_dim=64, context=1022, t2_format="int4_g32", sequences=2),       # ... the shortest on the matrix cores
     *CALLS_BEYOND_THE_LDS,                                                                                         # the second: the production batch's kernel
 ])
 def test_single_calls_with_a_pair_for_every_compute_unit(shape):
@@ -594,6 +597,7 @@ def _one_token_outputs(kind, cfg, k, v, k_new, v_new, q, tiers=None):
 ONE_TOKEN_LAUNCHES = [
     ("call", dict(n_layers=1, batch=256, n_q_heads=7, n_kv_heads=1, head_dim=128, context=300)),                      # one workgroup per pair
     ("call", dict(n_layers=1, batch=128, n_q_heads=16, n_kv_heads=2, head_dim=64, context=321, kv_dtype="f16")),
+    ("call", dict(n_layers=1, batch=128, n_q_heads=4, n_kv_heads=2, head_dim=64, context=333)),                       # ... vector instructions
     ("step", dict(n_layers=64, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=200, kv_dtype="f16")),      # ... of whole steps
     ("step", dict(n_layers=25, batch=2, n_q_heads=14, n_kv_heads=2, head_dim=128, context=1500)),                     # pairs in parts
     ("call", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=700)),                       # pairs split, matrix instructions
@@ -603,7 +607,7 @@ ONE_TOKEN_LAUNCHES = [
 ]
 
 
-@pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES + [("chunk", ONE_TOKEN_LAUNCHES[4][1])])
+@pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES + [("chunk", ONE_TOKEN_LAUNCHES[5][1])])
 def test_logits_that_are_no_numbers_reach_the_output(kind, shape):
     """A NaN in a key row, and an infinite key element under a query element of zero: the heads that read the row have no
     number for an output, whichever launch serves the call.  All others have the bits they have without."""
@@ -632,7 +636,7 @@ def test_logits_that_are_no_numbers_reach_the_output(kind, shape):
 @pytest.mark.parametrize("kind,shape", ONE_TOKEN_LAUNCHES + [
     ("call", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=64, context=700, kv_dtype="f32")),
     ("call", dict(n_layers=2, batch=2, n_q_heads=10, n_kv_heads=2, head_dim=128, context=900, kv_dtype="f32")),
-    ("chunk", ONE_TOKEN_LAUNCHES[4][1]),
+    ("chunk", ONE_TOKEN_LAUNCHES[5][1]),
 ])
 def test_whole_tiles_of_keys_without_weight(kind, shape):
     """Rows whose logit is -inf, whole tiles of them, a list's first and others: no weight, whatever else a wave walks."""
