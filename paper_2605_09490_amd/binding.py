@@ -88,6 +88,10 @@ SYMBOLS = {
     "tkv_tier_counts": (C.c_int, [C.POINTER(tkv_policy), C.c_int64, C.c_int64, C.POINTER(C.c_int64)]),
 }
 
+# Handle of a device's current stream.  A Stream object for every layer's call takes longer than the call's checks, so the raw handle
+# is asked for where this torch has the (private) function.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
 _lib = None
 
 
@@ -214,8 +218,7 @@ class TieredKV:
 
     @staticmethod
     def _stream(stream):
-        # (the raw handle: a Stream object for every layer's call takes longer than the call's checks)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+        return _current_raw_stream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
     def _dev_tensor(self, t, shape, dtype=None):
         assert t.is_cuda and t.dtype == (dtype or self.torch_dtype) and t.is_contiguous() and t.shape == shape, \

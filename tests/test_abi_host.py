@@ -170,6 +170,22 @@ def test_launches_that_the_gpu_tests_mean():
     assert whole > 0 and in_parts == 0 and call == 0
 
 
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """The function that gives a stream's raw handle is a private one of torch's: without it the public way is taken."""
+    import importlib.util
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=40 + device))
+    spec = importlib.util.spec_from_file_location("binding_of_its_own", binding.__file__)
+    own = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(own)
+    assert own.TieredKV._stream(None) == 43
+    assert own.TieredKV._stream(types.SimpleNamespace(cuda_stream=7)) == 7
+
+
 def test_chunk_scratch_comes_from_the_calls_own_stream(monkeypatch):
     """PyTorch's allocator keeps a pool per stream.  The scratch of a handle's first chunk is written on the stream that the
     call names, so it has to come from that stream's pool, not from the one of whatever stream is current."""
