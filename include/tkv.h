@@ -192,7 +192,7 @@ tkv_status tkv_attend_and_score(tkv_cache* c, int32_t layer, const void* q, void
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same call as tkv_attend_and_score, same arguments, same bits in out and in the scores, but the
- * call's scratch (scaled logits, split partials) lives in a fixed 16 MiB array in the library's device image instead
+ * call's scratch (logits, split partials) lives in a fixed 16 MiB array in the library's device image instead
  * of the handle's own allocations, and the call itself makes no hipMalloc / hipFree / event or stream creation and
  * issues none of the T1 copies a TKV_PREFETCH_LAZY migrate has left queued (rows still in flight are read from their
  * old HBM slots, which by Prop. 1 gives the same bits; the next ordinary call issues the copies).
@@ -211,7 +211,8 @@ tkv_status tkv_attend_and_score_noalloc(tkv_cache* c, int32_t layer, const void*
  * groups.  The cache is read once per 32 columns; beyond 32 columns or 16 tokens the K rows are read once more for the
  * scores, instead of logits being written.  The first call allocates scratch for one group of tokens from the handle's
  * allocator.  binary32 rows and TKV_PREFETCH_STREAM take the decode kernels once per token.  Outputs and scores agree
- * with single-token steps to binary32 rounding (the summation order differs), not bit for bit; T1 placement stays
+ * with single-token steps to binary32 rounding (the summation order differs), not bit for bit (where a value row has
+ * infinite elements a chunk's outputs may be NaN there, single tokens' are infinite); T1 placement stays
  * bit-invisible (Prop. 1).
  * ESTATE unless all n_q positions were appended after the last tkv_migrate (they are then in T0). */
 tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q, void* out, int32_t n_q, void* hip_stream);
@@ -222,7 +223,7 @@ tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q
  * kv_dtype; out_all [n_layers, batch, n_q_heads, head_dim] out_dtype.  Same errors as the two calls.  All capacity and
  * state checks are made before anything is enqueued; when all layers are at the same length the new rows of every
  * layer go in with one launch and the attention of consecutive layers in groups (as many layers per launch as fit the
- * step's scratch of at most 256 MiB, which tkv_create takes if it can have it), so a later failure at layer l (a HIP
+ * step's scratch of at most 256 MiB, and 64 MiB for pairs that go in parts, which tkv_create takes if it can have them), so a later failure at layer l (a HIP
  * error) leaves the step's rows appended to ALL layers and only layers < l attended: finish the step with
  * tkv_attend_and_score for layers >= l, or destroy the handle.  A step of 96 or more (layer, sequence, kv head) pairs
  * of 16-bit rows takes a launch of its own kind (not with lists beyond 20480 tokens where that would leave much of the
