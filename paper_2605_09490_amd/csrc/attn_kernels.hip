@@ -1329,7 +1329,7 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
     // first row with all of the attention but e^-24 and a value of zero outputs were 1.2e-3 off.)
     constexpr bool REL = ONE && KT == KT_F16;
     uint32_t rel = 0;                                    // REL: that power of two, as bits
-    bool wide = false;                                   // ... wave-uniform: smaller weights
+    int wide = 0;                                        // ... wave-uniform: smaller weights; 2: ones that take a second round
     float p[NCB][NRB][4];
     {
       const int e0 = tile * TR + 4 * kb;
@@ -1447,7 +1447,8 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
         if constexpr (REL) {
           // (2^-64 of the running maximum: nothing the outputs could hold)
           rel = (__builtin_bit_cast(uint32_t, fmaxf(__builtin_amdgcn_exp2f((mt - ms) * LOG2E), 0x1p-64f)) & 0x7f800000u) + 0x800000u;
-          wide = __builtin_amdgcn_ballot_w64(mt - least > 9.0f) != 0;      // (e^9 is just below 8192)
+          // (e^9 is just below 8192; e^35 below 2^51: down to there a weight's 24 bits end within the first round's 2^-62)
+          if (__builtin_amdgcn_ballot_w64(mt - least > 9.0f) != 0) wide = __builtin_amdgcn_ballot_w64(mt - least > 35.0f) != 0 ? 2 : 1;
         }
         // the output accumulators of this lane belong to columns 4*kb + j: their factors come from those columns'
         // lanes; once the maxima have settled nothing needs rescaling (x * 1.0f is exact)
@@ -1611,15 +1612,15 @@ __device__ __forceinline__ void attn_wave_mfma(const AttnArgs& a, const WaveLds&
           }
         }
         if constexpr (REL) {
-          if (wide) {
-            // what the terms leave (below 2^-24), times 2^38, and what that leaves once more: 2^-86 of the tile's largest
+          if (wide > 0) {
+            // what the terms leave (below 2^-24), times 2^38, and what that leaves once more
             constexpr int GDB = M == Q_INT4 ? 2 : NDB;   // columns of output with the same weights
 #pragma unroll
             for (int g0 = 0; g0 < NDB; g0 += GDB) {
               float f = 1.0f;
               products(tc, cb, g0 / 2, pw);
               terms(pw, pt);
-              for (int k = 0; k < 2; ++k) {
+              for (int k = 0; k < wide; ++k) {
                 f *= 0x1p-38f;
 #pragma unroll
                 for (int r2 = 0; r2 < 2; ++r2)
