@@ -211,9 +211,11 @@ tkv_status tkv_attend_and_score_noalloc(tkv_cache* c, int32_t layer, const void*
  * groups.  The cache is read once per 32 columns; beyond 32 columns or 16 tokens the K rows are read once more for the
  * scores, instead of logits being written.  The first call allocates scratch for one group of tokens from the handle's
  * allocator.  binary32 rows and TKV_PREFETCH_STREAM take the decode kernels once per token.  Outputs and scores agree
- * with single-token steps to binary32 rounding (the summation order differs), not bit for bit (where a value row has
- * infinite elements a chunk's outputs may be NaN there, single tokens' are infinite); T1 placement stays
- * bit-invisible (Prop. 1).
+ * with single-token steps to binary32 rounding (the summation order differs), not bit for bit; T1 placement stays
+ * bit-invisible (Prop. 1).  Two exceptions.  Where a value row has infinite elements a chunk's outputs may be NaN there,
+ * single tokens' are infinite.  In a binary16 cache a chunk keeps a weight (in T2 times its V scale) to 2^-38 of the
+ * largest: outputs that are made of smaller ones, beside a row with a value near zero and nearly all of the attention,
+ * are off by 1e-3 where that row's logit is 24 above the others and by 1e-1 where it is 30; single tokens' are not.
  * ESTATE unless all n_q positions were appended after the last tkv_migrate (they are then in T0). */
 tkv_status tkv_attend_and_score_chunk(tkv_cache* c, int32_t layer, const void* q, void* out, int32_t n_q, void* hip_stream);
 
